@@ -13,7 +13,7 @@ KERNELS = os.path.join(CSRC, "kernels.hip")
 # kernels.hip is compiled once per part (-DBYZ_PART=n): the single-pass kernels are large and
 # build in parallel this way
 # the slowest parts first: the pool starts them in this order
-KERNEL_PARTS = (18, 17, 16, 8, 10, 9, 11, 7, 13, 2, 4, 12, 6, 14, 15, 5, 3, 1, 0)
+KERNEL_PARTS = (18, 2, 7, 4, 22, 17, 6, 5, 23, 20, 21, 8, 10, 14, 16, 15, 9, 11, 19, 3, 1, 13, 12, 0)
 OTHER_SOURCES = [os.path.join(CSRC, "krum.hip"), os.path.join(CSRC, "host.cpp")]
 
 

@@ -43,37 +43,35 @@ int byz_internal_launch_trimmed_mean(const void *X, long long d, long long ld,
                                      const int *row_index, int f, int b, void *out,
                                      const void *gate, int gate_n, void *stream);
 
-// Trimmed mean of 49 < f <= 63 and 63 < f <= 65 rows on the 63- and 65-wire sorting networks
-// (kernels.hip, build parts 14 and 15).
-int byz_internal_launch_trimmed_mean_63(const void *X, long long d, long long ld,
-                                        const int *row_index, int f, int b, void *out,
-                                        const void *gate, int gate_n, void *stream);
-int byz_internal_launch_trimmed_mean_65(const void *X, long long d, long long ld,
-                                        const int *row_index, int f, int b, void *out,
-                                        const void *gate, int gate_n, void *stream);
-
-// Median / trimmed mean on the 169-wire network, exactly 169 rows or fewer with spare wires
-// (kernels.hip, build parts 8..11).
-int byz_internal_launch_trimmed_mean_169(const void *X, long long d, long long ld,
-                                         const int *row_index, int f, int b, void *out,
-                                         const void *gate, int gate_n, void *stream);
-int byz_internal_launch_trimmed_mean_169_padded(const void *X, long long d, long long ld,
-                                                const int *row_index, int f, int b, void *out,
-                                                const void *gate, int gate_n, void *stream);
-int byz_internal_launch_median_169(const void *X, long long d, long long ld, const int *row_index,
-                                   int f, void *out, const void *gate, int gate_n, void *stream);
-int byz_internal_launch_median_169_padded(const void *X, long long d, long long ld,
-                                          const int *row_index, int f, void *out, const void *gate,
-                                          int gate_n, void *stream);
-
+// The same on one of the larger networks: n wires and exactly n rows, or fewer rows with spare
+// wires (kernels.hip, a build part for one or two of them).
+#define BYZ_DECLARE_MEDIAN(n)                                                                   \
+    int byz_internal_launch_median_##n(const void *X, long long d, long long ld,                \
+                                       const int *row_index, int f, void *out, const void *gate, \
+                                       int gate_n, void *stream)
+BYZ_DECLARE_MEDIAN(97);
+BYZ_DECLARE_MEDIAN(109);
+BYZ_DECLARE_MEDIAN(137);
+BYZ_DECLARE_MEDIAN(153);
+BYZ_DECLARE_MEDIAN(169);
+BYZ_DECLARE_MEDIAN(169_padded);
 // ... and past 169 rows, with the rows split over two waves that sort a half each: median
-// 169 < f <= 255, trimmed mean 169 < f <= 256 (build parts 16 and 17).
-int byz_internal_launch_median_255_padded(const void *X, long long d, long long ld,
-                                          const int *row_index, int f, void *out, const void *gate,
-                                          int gate_n, void *stream);
-int byz_internal_launch_trimmed_mean_256_padded(const void *X, long long d, long long ld,
-                                                const int *row_index, int f, int b, void *out,
-                                                const void *gate, int gate_n, void *stream);
+// 169 < f <= 255, trimmed mean 169 < f <= 256
+BYZ_DECLARE_MEDIAN(255_padded);
+#define BYZ_DECLARE_TRIMMED_MEAN(n)                                                          \
+    int byz_internal_launch_trimmed_mean_##n(const void *X, long long d, long long ld,       \
+                                             const int *row_index, int f, int b, void *out,  \
+                                             const void *gate, int gate_n, void *stream)
+BYZ_DECLARE_TRIMMED_MEAN(63);
+BYZ_DECLARE_TRIMMED_MEAN(65);
+BYZ_DECLARE_TRIMMED_MEAN(97);
+BYZ_DECLARE_TRIMMED_MEAN(109);
+BYZ_DECLARE_TRIMMED_MEAN(121);
+BYZ_DECLARE_TRIMMED_MEAN(137);
+BYZ_DECLARE_TRIMMED_MEAN(153);
+BYZ_DECLARE_TRIMMED_MEAN(169);
+BYZ_DECLARE_TRIMMED_MEAN(169_padded);
+BYZ_DECLARE_TRIMMED_MEAN(256_padded);
 
 // Records the event before (which = 0) or after (1) the dominant kernel of an aggregation, if
 // byz_profile_enable has armed any.  Returns a byz_status.

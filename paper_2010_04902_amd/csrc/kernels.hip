@@ -22,15 +22,13 @@
 #include "byzshield.h"
 #include "byzshield_bench.h"
 
-// The build compiles this file once per BYZ_PART, in parallel, because the single-pass kernels
-// are large: part 0 holds every entry point, the vote and the Bulyan kernels, parts 1..4 one
-// group of single-pass instantiations each (byz_internal_launch_single_pass_<n>; the fifth
-// group is part 7, the sixth and seventh parts 14 and 15, which also hold the 63- and 65-wire
-// trimmed-mean kernels, the eighth part 18), part 5 the median kernels, part 6 the
-// trimmed-mean kernels, parts 8..11 one 169-wire network kernel each, parts 12 and 13 the 81- and
-// 121-wire second phase of Bulyan, parts 16 and 17 the two-wave median and trimmed-mean kernels for f > 169.
-// Without BYZ_PART the whole library is
-// this one translation unit.
+// The build compiles this file once per BYZ_PART, in parallel, because the kernels are large: part
+// 0 holds every entry point, the vote and the smaller Bulyan kernels, parts 1..4, 7, 14, 15 and 18 one
+// group of single-pass instantiations each (byz_internal_launch_single_pass_<n>), parts 5 and 6
+// the median and trimmed-mean kernels up to 81 wires (and the 121-wire median), parts 8..11,
+// 14, 15 and 19..23 the larger ones, parts 12 and 13 the 81- and 121-wire second phase of Bulyan,
+// parts 16 and 17 the two-wave median and trimmed-mean kernels for f > 169.
+// Without BYZ_PART the whole library is this one translation unit.
 #ifndef BYZ_PART
 #define BYZ_PART -1
 #endif
@@ -74,31 +72,47 @@ constexpr int prefetch_depth(int f, int slots) {
 // f with a generated streamed network (gen_selnet.py STREAMED_SIZES): the paper's file counts
 // l^2 (MOLS, Ramanujan Case 1; 81, 121, 169 for l = 9, 11, 13) and m*s (Ramanujan Case 2)
 constexpr bool has_streamed_network(int f) {
-    return f == 9 || f == 15 || f == 21 || f == 25 || f == 35 || f == 49 || f == 63 || f == 65 ||
-           f == 81 || f == 121 || f == 169;
+    return f == 9 || f == 15 || f == 21 || f == 25 || f == 31 || f == 35 || f == 41 || f == 49 ||
+           f == 57 || f == 63 || f == 65 || f == 73 || f == 81 || f == 97 || f == 109 || f == 121 ||
+           f == 137 || f == 153 || f == 169;
+}
+// Fewest rows the n-wire network is launched with: one more than the next smaller size holds.  Only
+// the wires from there on can be spare, so only they are looked at (a test on every wire cost 4 %).
+constexpr int least_rows(int n) {
+    int below = n - 1;
+    while (below > 0 && !has_streamed_network(below)) --below;
+    return below + 1;
 }
 // words per thread: fewer for the large networks, whose keys fill the register file
 constexpr int vec_for(int f) { return f <= 49 ? 4 : (f <= 81 ? 2 : 1); }
 // ... of the median kernels: above 49 wires they are bound by min/max issue, and one word per
 // thread (fewer registers, more waves per SIMD) measured 4-8 % faster than two at f = 63, 81
 constexpr int vec_for_median(int f) { return f <= 49 ? 4 : 1; }
-// ... of the trimmed-mean kernels: the same above 49 wires (f = 81: 5 % faster, fewer files on
-// the 81-wire network: 15 %); at f = 49 the kernel runs at the vector ALU's practical limit
-// whatever the width (0.43 ms for 11.2 M coordinates with four, two or one word per thread)
+// ... of the trimmed-mean kernels: the same above 49 wires.  With the three-wire sorters
+// (gen_selnet.py) f = 81 takes 0.57 ms for 11.2 M coordinates, 1.01 of the time its bytes take
+// at 6.5 TB/s (two-wire comparators: 0.78); f = 121 0.41 ms for 4 M (0.30 by bytes; 0.45 before).
 constexpr int vec_for_trimmed(int f) { return f <= 49 ? 4 : 1; }
 // ... and of the second phase of Bulyan, where narrower threads measured slightly slower
 constexpr int vec_for_sort(int f) { return vec_for(f); }
 // ... and of the single pass: with five or seven copies of a file in flight two words per thread
 // (more waves per SIMD, 8-byte loads) measured 1-2 % faster than four (r = 7 would not fit
-// the registers with four); with three copies four words are faster
-constexpr int vec_for_pass(int f, int r) { return (r >= 5 && f <= 49) ? 2 : vec_for(f); }
+// the registers with four); with three copies four words are faster, but for a sort of 49 keys
+// (four: 269 registers, one wave per SIMD, 409 us for 4 M coordinates; two: 377)
+constexpr int vec_for_pass(int f, int r, bool trim) {
+    return ((r >= 5 || (trim && f > 35)) && f <= 49) ? 2 : vec_for(f);
+}
 constexpr int kProbe = 256;  // sampled coordinates of the probe (512: 2x slower)
 constexpr int kProbeSplit = 4;  // the files are dealt out to this many groups of kProbe threads
 constexpr int kProbeThreads = kProbe * kProbeSplit;
 constexpr int kBlock = 256;  // threads per block of the streaming kernels (128/512/1024: slower)
 constexpr int kWide = BYZ_MAX_F_WIDE;  // largest f of the vote, the median (255) and the trimmed mean
 static_assert(kWide <= kBlock, "one thread per file in the deciding block");
-constexpr int kPinFrom = 169;  // network sizes from which the trimmed-mean kernel pins its schedule
+// Which kernels of one slot per file pin their schedule (selnet_pin_on.inc).  Trimmed mean, 4 M
+// coordinates, left alone / pinned: f = 49 143 / 198 us, 57 157 / 148, 81 226 / 206, 97 310 / 291,
+// 137 500 / 475, 169 the same.  Median: f = 97 236 / 238, 109 266 / 268, 121 307 / 300, 137 370 / 355,
+// 153 392 / 428, 169 507 / 472.
+constexpr bool pins_trimmed_mean(int f) { return f >= 57; }
+constexpr bool pins_median(int f) { return f >= 121 && f != 153; }
 constexpr int kRowStride = 8;  // slots per file in the permuted row table (>= BYZ_MAX_R)
 
 // ----------------------------------------------------------------------------- helpers
@@ -171,6 +185,22 @@ __device__ __forceinline__ uint32_t to_key(uint32_t u) {
 }
 __device__ __forceinline__ uint32_t from_key(uint32_t k) {
     return k ^ ((uint32_t)((int32_t)(~k) >> 31) | 0x80000000u);
+}
+
+__device__ __forceinline__ uint32_t min3_u32(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_min3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ uint32_t max3_u32(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_max3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
 // Bit of pair (a, b), a < b, in lexicographic numbering (0,1),(0,2),..,(1,2),..
@@ -765,6 +795,15 @@ __global__ __launch_bounds__(kBlock) void vote_pairs_tolerant_kernel(
 #define BYZ_S_CE_HI(i, j)                                                                     \
     _Pragma("unroll") for (int v_ = 0; v_ < V; ++v_)                                          \
         key[v_][j] = key[v_][i] < key[v_][j] ? key[v_][j] : key[v_][i];
+// Three wires in order with the three-operand instructions, only the outputs that are needed (the
+// compiler finds v_med3 and v_min3 in nested minima only where no intermediate value is shared)
+#define BYZ_S_SORT3(i, j, k, lo, mid, hi)                                                     \
+    _Pragma("unroll") for (int v_ = 0; v_ < V; ++v_) {                                        \
+        const uint32_t a_ = key[v_][i], b_ = key[v_][j], c_ = key[v_][k];                     \
+        if constexpr (lo) key[v_][i] = min3_u32(a_, b_, c_);                                  \
+        if constexpr (mid) key[v_][j] = med3_u32(a_, b_, c_);                                 \
+        if constexpr (hi) key[v_][k] = max3_u32(a_, b_, c_);                                  \
+    }
 #define BYZ_S_SORTED(n)  // wires 0..n-1 now hold the keys in ascending order
 #define BYZ_S_MEDIAN(w)                                                                       \
     _Pragma("unroll") for (int v_ = 0; v_ < V; ++v_) o[v_] = from_key(key[v_][w]);
@@ -791,7 +830,13 @@ __global__ __launch_bounds__(kBlock) void median_kernel(
             uint32_t flags[(F + 63) / 64] = {};
             (void)lane; (void)flags;
 #define BYZ_S_ROW_ADDR(j, k) (Xb + (uint64_t)(uint32_t)row_index[j] * (uint64_t)ld * 4u + voff)
+            if constexpr (pins_median(F)) {
+#include "selnet_pin_on.inc"
 #include "generated/selnet_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+            } else {
+#include "generated/selnet_stream_dispatch.inc"
+            }
 #undef BYZ_S_ROW_ADDR
         } else {
             const uint32_t *base = X + gt * V;
@@ -818,10 +863,11 @@ __global__ __launch_bounds__(kBlock) void median_kernel(
 }
 
 // Coordinate-wise median by the streamed program of the generated network on F wires with V = vec_for_median(F)
-// words per thread: the large networks (F = 81, 121: MOLS over F_9 and F_11) and, with PAD,
-// any odd f < F on the next generated size -- the F - f spare wires reload row_index[0] and
-// are tied half to the smallest and half to the largest key, which leaves the median where
-// it was.  Thread t owns the words starting at min(V*t, d - V): the last vector overlaps its
+// words per thread: the large networks and, with PAD, any odd least_rows(F) <= f <= F --
+// the F - f spare wires reload row_index[0] and are tied half to the smallest and half to the
+// largest key, which leaves the median where it was.  Bound by HBM up to F = 109 (4 M coordinates
+// at 6.5 TB/s and measured: f = 81 202 and 196 us, 109 271 and 266), by min/max issue above (153
+// 379 and 392, 169 419 and 472; with two-wire comparators and fewer sizes 655 and 577).  Thread t owns the words starting at min(V*t, d - V): the last vector overlaps its
 // neighbour (both write the same values).  Needs d >= V.
 template <int F, int V, bool PAD>
 __global__ __launch_bounds__(kBlock) void median_large_kernel(
@@ -847,10 +893,16 @@ __global__ __launch_bounds__(kBlock) void median_large_kernel(
     (void)lane; (void)flags;
 #undef BYZ_S_KEY
 #define BYZ_S_KEY(j, x) \
-    (!PAD || (j) < f ? to_key(x) : ((j) < pad_low_end ? 0u : 0xFFFFFFFFu))
+    (!PAD || (j) < least_rows(F) || (j) < f ? to_key(x) : ((j) < pad_low_end ? 0u : 0xFFFFFFFFu))
 #define BYZ_S_ROW_ADDR(j, k) \
-    (Xb + (uint64_t)(uint32_t)row_index[!PAD || (j) < f ? (j) : 0] * (uint64_t)ld * 4u + voff)
+    (Xb + (uint64_t)(uint32_t)row_index[!PAD || (j) < least_rows(F) || (j) < f ? (j) : 0] * (uint64_t)ld * 4u + voff)
+    if constexpr (pins_median(F)) {
+#include "selnet_pin_on.inc"
 #include "generated/selnet_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+    } else {
+#include "generated/selnet_stream_dispatch.inc"
+    }
 #undef BYZ_S_ROW_ADDR
 #undef BYZ_S_KEY
 #define BYZ_S_KEY(j, x) to_key(x)
@@ -1013,12 +1065,10 @@ __global__ __launch_bounds__(kBlock) void trimmed_mean_kernel(
     // PAD: f < F rows on the next generated size; the spare wires reload row_index[0] and carry
     // the largest key, so wires 0..f-1 end up holding the f values in ascending order
 #undef BYZ_S_KEY
-#define BYZ_S_KEY(j, x) (!PAD || (j) < f ? to_key(x) : 0xFFFFFFFFu)
+#define BYZ_S_KEY(j, x) (!PAD || (j) < least_rows(F) || (j) < f ? to_key(x) : 0xFFFFFFFFu)
 #define BYZ_S_ROW_ADDR(j, k) \
-    (Xb + (uint64_t)(uint32_t)row_index[!PAD || (j) < f ? (j) : 0] * (uint64_t)ld * 4u + voff)
-    // the widest sorting networks run with their schedule pinned (F = 169: 2.2 instead of 2.8 ms
-    // for 11.2 M coordinates; the smaller ones and the median networks are faster left alone)
-    if constexpr (F >= kPinFrom) {
+    (Xb + (uint64_t)(uint32_t)row_index[!PAD || (j) < least_rows(F) || (j) < f ? (j) : 0] * (uint64_t)ld * 4u + voff)
+    if constexpr (pins_trimmed_mean(F)) {
 #include "selnet_pin_on.inc"
 #include "generated/selnet_sort_stream_dispatch.inc"
 #include "selnet_pin_off.inc"
@@ -1029,7 +1079,7 @@ __global__ __launch_bounds__(kBlock) void trimmed_mean_kernel(
 #undef BYZ_S_KEY
 #define BYZ_S_KEY(j, x) to_key(x)
     uint32_t o[V];
-    trimmed_mean_of_sorted<F, V, (F >= kPinFrom)>(key, PAD ? f : F, b, o);
+    trimmed_mean_of_sorted<F, V, pins_trimmed_mean(F)>(key, PAD ? f : F, b, o);
     store_vec<V>(out + c0, o);
 }
 
@@ -1513,7 +1563,11 @@ __device__ __forceinline__ void fused_body(const uint32_t *__restrict__ X, int64
 }
 
 template <int F, int R, bool TRIM, int V>
-__global__ __launch_bounds__(kBlock) void fused_kernel(
+__global__ __launch_bounds__(kBlock)
+// (the 169-wire sort takes 263 registers if left alone, one wave per SIMD: 1.01 instead of 0.74 ms
+// for 2 M coordinates)
+__attribute__((amdgpu_waves_per_eu(F == 169 && TRIM ? 2 : 1)))
+void fused_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const uint64_t *__restrict__ perm_off,
     const uint32_t *__restrict__ slots_per_file, AggWorkspace *ws, int trim_b,
     uint32_t *__restrict__ out) {
@@ -1592,7 +1646,7 @@ int launch_median_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
 
 #endif  // part 5
 
-#if BYZ_IN_PART(5) || BYZ_IN_PART(9) || BYZ_IN_PART(11) || BYZ_IN_PART(16)
+#if BYZ_IN_PART(5) || BYZ_IN_PART(9) || BYZ_IN_PART(11) || BYZ_IN_PART(19) || BYZ_IN_PART(20)
 template <int F, bool PAD>
 int launch_median_large(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
                         uint32_t *out, const uint32_t *gate, int gate_n, hipStream_t s) {
@@ -1603,7 +1657,7 @@ int launch_median_large(const uint32_t *X, int64_t d, int64_t ld, const int32_t 
     return BYZ_OK;
 }
 
-#endif  // parts 5, 9, 11, 16
+#endif  // parts 5, 9, 11, 19, 20
 
 #if BYZ_IN_PART(5)
 int launch_median(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
@@ -1628,21 +1682,26 @@ int launch_median(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_i
         BYZ_HIP(hipGetLastError());
         return BYZ_OK;
     }
-    // any other odd f: the next generated size with spare wires, if d allows its vector width
+    // any other odd f: the next generated size with spare wires
     if (f <= 15) return launch_median_large<15, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 21) return launch_median_large<21, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 25) return launch_median_large<25, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 31) return launch_median_large<31, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 35) return launch_median_large<35, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 41) return launch_median_large<41, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 49) return launch_median_large<49, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
-    if ((f == 63 || f == 65) && d >= vec_for_median(81))  // Ramanujan Case 2 shapes (63,7), (65,5)
-        return f == 63 ? launch_median_large<63, false>(X, d, ld, row_index, f, out, gate, gate_n, s)
-                       : launch_median_large<65, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
-    if (f == 81 && d >= vec_for_median(81))
-        return launch_median_large<81, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
-    if (f <= 81 && d >= vec_for_median(81))
-        return launch_median_large<81, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 57) return launch_median_large<57, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 63) return launch_median_large<63, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 65) return launch_median_large<65, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 73) return launch_median_large<73, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f == 81) return launch_median_large<81, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 81) return launch_median_large<81, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 97) return byz_internal_launch_median_97(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 109) return byz_internal_launch_median_109(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f == 121) return launch_median_large<121, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 121) return launch_median_large<121, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 137) return byz_internal_launch_median_137(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f <= 153) return byz_internal_launch_median_153(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f == 169) return byz_internal_launch_median_169(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 169) return byz_internal_launch_median_169_padded(X, d, ld, row_index, f, out, gate, gate_n, s);
     return byz_internal_launch_median_255_padded(X, d, ld, row_index, f, out, gate, gate_n, s);
@@ -1660,21 +1719,23 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     BYZ_HIP(hipGetLastError());
     int rc = byz_internal_profile_mark(0, s);
     if (rc != BYZ_OK) return rc;
-    constexpr int V = vec_for_pass(F, R);
-    const unsigned g = blocks_for((d + V - 1) / V);
     if (trim_b < 0) {
-        if constexpr (WITH_MEDIAN)
-            fused_kernel<F, R, false, V><<<g, kBlock, 0, s>>>(
+        if constexpr (WITH_MEDIAN) {
+            constexpr int V = vec_for_pass(F, R, false);
+            fused_kernel<F, R, false, V><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
                 X, d, ld, ws->perm_off, &ws->slots_per_file, ws, 0, out);
+        }
     } else if constexpr (WITH_TRIM) {
-        fused_kernel<F, R, true, V><<<g, kBlock, 0, s>>>(
+        constexpr int V = vec_for_pass(F, R, true);
+        fused_kernel<F, R, true, V><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
             X, d, ld, ws->perm_off, &ws->slots_per_file, ws, trim_b, out);
     }
     BYZ_HIP(hipGetLastError());
     return byz_internal_profile_mark(1, s);
 }
 
-#if BYZ_IN_PART(6) || BYZ_IN_PART(8) || BYZ_IN_PART(10) || BYZ_IN_PART(14) || BYZ_IN_PART(15) || BYZ_IN_PART(17)
+#if BYZ_IN_PART(6) || BYZ_IN_PART(8) || BYZ_IN_PART(10) || BYZ_IN_PART(14) || BYZ_IN_PART(15) || \
+    BYZ_IN_PART(21) || BYZ_IN_PART(22) || BYZ_IN_PART(23)
 template <int F, bool PAD>
 int launch_trimmed_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
                        int b, uint32_t *O, const uint32_t *gate, int gate_n, hipStream_t s) {
@@ -1685,7 +1746,7 @@ int launch_trimmed_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *
     return BYZ_OK;
 }
 
-#endif  // parts 6, 8, 10, 14, 15, 17
+#endif  // parts 6, 8, 10, 14, 15, 21..23
 
 #if BYZ_IN_PART(6)
 int launch_trimmed_mean(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
@@ -1712,17 +1773,22 @@ int launch_trimmed_mean(const uint32_t *X, int64_t d, int64_t ld, const int32_t 
         if (f <= 15) return launch_trimmed_net<15, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
         if (f <= 21) return launch_trimmed_net<21, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
         if (f <= 25) return launch_trimmed_net<25, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+        if (f <= 31) return launch_trimmed_net<31, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
         if (f <= 35) return launch_trimmed_net<35, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+        if (f <= 41) return launch_trimmed_net<41, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
         if (f <= 49) return launch_trimmed_net<49, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     }
+    if (f <= 57) return launch_trimmed_net<57, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     if (f <= 63) return byz_internal_launch_trimmed_mean_63(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     if (f <= 65) return byz_internal_launch_trimmed_mean_65(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-    if (f == 81 && d >= vec_for_trimmed(81))
-        return launch_trimmed_net<81, false>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-    if (f <= 81 && d >= vec_for_trimmed(81))
-        return launch_trimmed_net<81, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-    if (f == 121) return launch_trimmed_net<121, false>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-    if (f <= 121) return launch_trimmed_net<121, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 73) return launch_trimmed_net<73, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f == 81) return launch_trimmed_net<81, false>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 81) return launch_trimmed_net<81, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 97) return byz_internal_launch_trimmed_mean_97(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 109) return byz_internal_launch_trimmed_mean_109(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 121) return byz_internal_launch_trimmed_mean_121(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 137) return byz_internal_launch_trimmed_mean_137(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 153) return byz_internal_launch_trimmed_mean_153(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     if (f == 169) return byz_internal_launch_trimmed_mean_169(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     if (f <= 169)
         return byz_internal_launch_trimmed_mean_169_padded(X, d, ld, row_index, f, b, O, gate, gate_n, s);
@@ -1803,72 +1869,62 @@ int byz_internal_launch_bulyan_mean_121(const void *X, long long d, long long ld
 }
 #endif
 
-// the 63- and 65-wire sorting networks (Ramanujan Case 2 with (m, s) = (9, 7) and (13, 5), and
-// padded the f between 49 and 65), in the build parts of those shapes' single-pass kernels
-#if BYZ_IN_PART(14)
-int byz_internal_launch_trimmed_mean_63(const void *X, long long d, long long ld,
-                                        const int *row_index, int f, int b, void *out,
-                                        const void *gate, int gate_n, void *stream) {
-    const uint32_t *x = static_cast<const uint32_t *>(X), *g = static_cast<const uint32_t *>(gate);
-    if (f == 63)
-        return launch_trimmed_net<63, false>(x, d, ld, row_index, f, b, static_cast<uint32_t *>(out),
-                                             g, gate_n, (hipStream_t)stream);
-    return launch_trimmed_net<63, true>(x, d, ld, row_index, f, b, static_cast<uint32_t *>(out), g,
-                                        gate_n, (hipStream_t)stream);
-}
-#endif
-#if BYZ_IN_PART(15)
-int byz_internal_launch_trimmed_mean_65(const void *X, long long d, long long ld,
-                                        const int *row_index, int f, int b, void *out,
-                                        const void *gate, int gate_n, void *stream) {
-    const uint32_t *x = static_cast<const uint32_t *>(X), *g = static_cast<const uint32_t *>(gate);
-    if (f == 65)
-        return launch_trimmed_net<65, false>(x, d, ld, row_index, f, b, static_cast<uint32_t *>(out),
-                                             g, gate_n, (hipStream_t)stream);
-    return launch_trimmed_net<65, true>(x, d, ld, row_index, f, b, static_cast<uint32_t *>(out), g,
-                                        gate_n, (hipStream_t)stream);
-}
-#endif
-
-// the 169-wire networks (MOLS over F_13 and, padded, 121 < f < 169), a build part each
+// the larger networks, one or two to a build part: byz_internal_launch_median_<n> and
+// byz_internal_launch_trimmed_mean_<n> run the n-wire network on n rows or, padded, on fewer
+#define BYZ_DEFINE_MEDIAN(name, wires, pad)                                                      \
+    int byz_internal_launch_median_##name(const void *X, long long d, long long ld,              \
+                                          const int *row_index, int f, void *out,                \
+                                          const void *gate, int gate_n, void *stream) {          \
+        return launch_median_large<wires, pad>(static_cast<const uint32_t *>(X), d, ld,          \
+                                               row_index, f, static_cast<uint32_t *>(out),       \
+                                               static_cast<const uint32_t *>(gate), gate_n,      \
+                                               (hipStream_t)stream);                             \
+    }
+#define BYZ_DEFINE_TRIMMED_MEAN(name, wires, pad)                                                \
+    int byz_internal_launch_trimmed_mean_##name(const void *X, long long d, long long ld,        \
+                                                const int *row_index, int f, int b, void *out,   \
+                                                const void *gate, int gate_n, void *stream) {    \
+        return launch_trimmed_net<wires, pad>(static_cast<const uint32_t *>(X), d, ld,           \
+                                              row_index, f, b, static_cast<uint32_t *>(out),     \
+                                              static_cast<const uint32_t *>(gate), gate_n,       \
+                                              (hipStream_t)stream);                              \
+    }
 #if BYZ_IN_PART(8)
-int byz_internal_launch_trimmed_mean_169(const void *X, long long d, long long ld,
-                                         const int *row_index, int f, int b, void *out,
-                                         const void *gate, int gate_n, void *stream) {
-    return launch_trimmed_net<169, false>(static_cast<const uint32_t *>(X), d, ld, row_index, f, b,
-                                          static_cast<uint32_t *>(out),
-                                          static_cast<const uint32_t *>(gate), gate_n,
-                                          (hipStream_t)stream);
-}
-#endif
-#if BYZ_IN_PART(10)
-int byz_internal_launch_trimmed_mean_169_padded(const void *X, long long d, long long ld,
-                                                const int *row_index, int f, int b, void *out,
-                                                const void *gate, int gate_n, void *stream) {
-    return launch_trimmed_net<169, true>(static_cast<const uint32_t *>(X), d, ld, row_index, f, b,
-                                         static_cast<uint32_t *>(out),
-                                         static_cast<const uint32_t *>(gate), gate_n,
-                                         (hipStream_t)stream);
-}
+BYZ_DEFINE_TRIMMED_MEAN(169, 169, false)
 #endif
 #if BYZ_IN_PART(9)
-int byz_internal_launch_median_169(const void *X, long long d, long long ld, const int *row_index,
-                                   int f, void *out, const void *gate, int gate_n, void *stream) {
-    return launch_median_large<169, false>(static_cast<const uint32_t *>(X), d, ld, row_index, f,
-                                           static_cast<uint32_t *>(out),
-                                           static_cast<const uint32_t *>(gate), gate_n,
-                                           (hipStream_t)stream);
-}
+BYZ_DEFINE_MEDIAN(169, 169, false)
+#endif
+#if BYZ_IN_PART(10)
+BYZ_DEFINE_TRIMMED_MEAN(169_padded, 169, true)
 #endif
 #if BYZ_IN_PART(11)
-int byz_internal_launch_median_169_padded(const void *X, long long d, long long ld,
-                                          const int *row_index, int f, void *out, const void *gate,
-                                          int gate_n, void *stream) {
-    return launch_median_large<169, true>(static_cast<const uint32_t *>(X), d, ld, row_index, f,
-                                          static_cast<uint32_t *>(out),
-                                          static_cast<const uint32_t *>(gate), gate_n,
-                                          (hipStream_t)stream);
-}
+BYZ_DEFINE_MEDIAN(169_padded, 169, true)
+#endif
+#if BYZ_IN_PART(14)
+BYZ_DEFINE_TRIMMED_MEAN(63, 63, true)
+#endif
+#if BYZ_IN_PART(15)
+BYZ_DEFINE_TRIMMED_MEAN(65, 65, true)
+#endif
+#if BYZ_IN_PART(19)
+BYZ_DEFINE_MEDIAN(97, 97, true)
+BYZ_DEFINE_MEDIAN(109, 109, true)
+#endif
+#if BYZ_IN_PART(20)
+BYZ_DEFINE_MEDIAN(137, 137, true)
+BYZ_DEFINE_MEDIAN(153, 153, true)
+#endif
+#if BYZ_IN_PART(21)
+BYZ_DEFINE_TRIMMED_MEAN(97, 97, true)
+BYZ_DEFINE_TRIMMED_MEAN(109, 109, true)
+#endif
+#if BYZ_IN_PART(22)
+BYZ_DEFINE_TRIMMED_MEAN(121, 121, true)
+BYZ_DEFINE_TRIMMED_MEAN(137, 137, true)
+#endif
+#if BYZ_IN_PART(23)
+BYZ_DEFINE_TRIMMED_MEAN(153, 153, true)
 #endif
 
 // more than 169 rows: the two-wave kernels, median for 169 < f <= 255, trimmed mean for

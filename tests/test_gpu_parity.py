@@ -653,6 +653,30 @@ def test_more_than_169_rows_random_sizes():
             _trimmed_mean_check(X, idx, d, b, (case, f, d, ld, b))
 
 
+NETWORKS = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)
+
+
+@pytest.mark.parametrize("below,wires", list(zip((0,) + NETWORKS, NETWORKS)))
+def test_networks_with_most_and_least_spare_wires(below, wires):
+    # every generated network at the ends of its range of f (no spare wire, most of them): median
+    # and trimmed mean on raw bit patterns with ties, NaNs and signed zeros and on normal data, d
+    # from one coordinate to more than a block with a ragged tail, odd row pitch
+    rng = np.random.default_rng(wires)
+    for f in sorted({below + 1, below + 2, wires}):
+        for d in (1, 5, 63, 1027):
+            U = rng.integers(0, 2**32, size=(f + 3, d + 3), dtype=np.uint64).astype(np.uint32)
+            U[:, : d // 3] &= np.uint32(0x80000007)
+            U[:, 2 * d // 3 :] = rng.standard_normal((f + 3, d + 3 - 2 * d // 3)).astype(np.float32).view(np.uint32)
+            X = torch.tensor(U.view(np.int32), device=DEV).view(torch.float32)
+            idx = rng.integers(0, f + 3, size=f).astype(np.int32)
+            if f % 2 == 1:
+                out = B.byz_median(X, d, torch.tensor(idx, device=DEV))
+                torch.cuda.synchronize()
+                assert np.array_equal(W.bits(out), W.bits(C.median(U, idx, d))), (f, d)
+            for b in sorted({0, f // 3, (f - 1) // 2}):
+                _trimmed_mean_check(X, idx, d, b, (f, d, b))
+
+
 def test_mean_around_median_alone():
     # byz_mean_around_median = the second phase of Bulyan on rows of the caller's choice: every
     # network size of that kernel and the sizes between (spare wires), d below and above the

@@ -8,6 +8,8 @@ kernels use.  The single pass's rule for the copy that feeds the median, and the
 under which its output stands, are modelled on small vectors.
 """
 import itertools
+import os
+import sys
 
 import numpy as np
 import pytest
@@ -131,3 +133,38 @@ def test_wave_local_choice_feeds_the_winner_or_says_so(r):
         if 2 * count > r:
             assert not differs[winner]
     assert stood > 0 and redone > 0
+
+
+# ------------------------------------------------------------------- three-way merge
+
+sys.path.insert(0, os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                                "paper_2010_04902_amd", "csrc"))
+import gen_selnet  # noqa: E402
+
+
+@pytest.mark.parametrize("sizes", [(1, 1, 1), (2, 1, 1), (3, 3, 3), (4, 3, 2), (5, 5, 1), (7, 6, 6),
+                                   (9, 9, 7), (9, 9, 9), (13, 4, 2), (27, 11, 11), (27, 27, 27)])
+def test_three_way_merge_all_zero_one_inputs(sizes):
+    # a merge is right iff it is right on sorted 0/1 lists, i.e. for every number of zeros in each;
+    # every block order too, because the merge numbers its lists by length
+    for order in sorted(set(itertools.permutations(sizes))):
+        starts = [sum(order[:k]) for k in range(3)]
+        sorters = []
+        out = gen_selnet.merge_three(sorters, *[list(range(s, s + m)) for s, m in zip(starts, order)])
+        assert out == list(range(sum(sizes)))
+        zeros = np.array(list(itertools.product(*[range(m + 1) for m in order])))
+        v = np.concatenate([(np.arange(m)[None, :] >= zeros[:, k:k + 1]) for k, m in enumerate(order)],
+                           axis=1).astype(np.uint8)
+        for wires in sorters:
+            v[:, list(wires)] = np.sort(v[:, list(wires)], axis=1)
+        assert np.array_equal(v, np.sort(v, axis=1)), order
+
+
+def test_sorters_and_their_comparators_agree():
+    # the comparators of a three-wire sorter give the outputs that are needed, for every subset
+    for mask in range(1, 8):
+        outputs = (bool(mask & 1), bool(mask & 2), bool(mask & 4))
+        for values in itertools.product(range(3), repeat=3):
+            got = gen_selnet.apply_network(gen_selnet.comparators((0, 1, 2), outputs), values)
+            for w in range(3):
+                assert not outputs[w] or got[w] == sorted(values)[w], (outputs, values)
