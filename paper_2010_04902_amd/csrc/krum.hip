@@ -6,13 +6,10 @@
 // other vectors; the m vectors of lowest score are averaged.
 //
 // The pairwise squared distances come from the Gram matrix G = W W^T of the f x d matrix of
-// winners: the one dense contraction of the whole path, done with fp32 MFMA tiles
-// (v_mfma_f32_16x16x4f32; only the tiles on and above the diagonal of the symmetric matrix,
-// so f = 25 costs 3 tiles of 16x16 instead of one padded 32x32).  A block stages a
-// 256-coordinate chunk of all f rows in LDS (global loads stay 1 KiB-contiguous per wave), each
-// of its four waves multiplies 64 of those coordinates, and the blocks walk the chunks
-// grid-stride.  Per-block partial tiles are added in fp64 in block order, so the result does
-// not depend on scheduling.
+// winners: the one dense contraction of the whole path, done with 16x16 MFMA tiles, only those on
+// and above the diagonal of the symmetric matrix (f = 25 costs 3 tiles of 16x16 instead of one
+// padded 32x32).  The waves walk the coordinates grid-stride.  Per-block partial tiles are added
+// in fp64 in block order, so the result does not depend on scheduling.
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
@@ -33,25 +30,22 @@ namespace {
     } while (0)
 
 constexpr int kBlock = 256;            // 4 waves
-constexpr int kChunk = 256;            // coordinates staged per block and step
-constexpr int kStride = kChunk + 4;    // row pitch in LDS: rows stay 16-byte aligned (one 16-byte
-                                       // staging write per lane); see the column swizzle below
 constexpr int kGramBlocks = 512;       // partial Gram tiles (2 blocks per CU; 1024: 4 % faster, reduction 3 us slower)
 constexpr int kTile = 16 * 16;         // outputs of one MFMA tile
 constexpr int kMaxKrum = BYZ_MAX_F_KRUM;  // most vectors Multi-Krum takes (Bulyan: BYZ_MAX_F)
 constexpr int kMaxNT = kMaxKrum / 16;  // row tiles of the largest matrix
 constexpr int kMaxPairs = kMaxNT * (kMaxNT + 1) / 2;  // tiles on and above the diagonal
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// Row tiles of 16 the Gram matrix of f vectors is computed with (the compiled kernels have
-// 1, 2, 3, 4, 6 or 8); the tiles on and above the diagonal are stored.
-__host__ __device__ constexpr int row_tiles(int f) {
-    return f <= 64 ? (f + 15) / 16 : (f <= 96 ? 6 : 8);
-}
+// Row tiles of 16 the Gram matrix of f vectors is computed with; the tiles on and above the
+// diagonal are stored.
+__host__ __device__ constexpr int row_tiles(int f) { return (f + 15) / 16; }
 
 // Tile (ti, tj), ti <= tj < nt, of the upper triangle, numbered row by row.
 __host__ __device__ constexpr int tile_pair(int nt, int ti, int tj) {
@@ -61,136 +55,252 @@ __host__ __device__ constexpr int tile_pair(int nt, int ti, int tj) {
 // The 16x16 MFMA result: accumulator register v of lane l holds row 4*(l/16) + v, column l%16
 // (gram_at below inverts this).
 
-// Partial Gram tiles of the rows row_index[0..f-1] over this block's chunks.
-// NT = ceil(f / 16) row tiles; RW = rows a wave stages per chunk (rows wave, wave+4, ...):
-// ceil(f / 4) rounded up to a compiled value.  partial: [gridDim.x][pairs][256] floats,
-// position v*64 + lane, pairs = NT(NT+1)/2.
-// Per chunk: the rows' 16-byte loads for the NEXT chunk are issued, then the current chunk
-// (already in registers) goes to LDS, is multiplied, and the loop turns: global latency hides
-// behind the matrix instructions.
-template <int NT, int RW>
-__global__ __launch_bounds__(kBlock) void gram_partial_kernel(const float *__restrict__ X, int64_t d,
-                                                              int64_t ld,
-                                                              const int32_t *__restrict__ row_index,
-                                                              int f, float *__restrict__ partial) {
-    extern __shared__ float T[];  // [16*NT][kStride]; rows >= f stay zero
-    constexpr int NP = NT * (NT + 1) / 2;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    for (int i = tid; i < (16 * NT - f) * kStride; i += kBlock) T[f * kStride + i] = 0.0f;
-    f32x4 acc[NP];
-#pragma unroll
-    for (int p = 0; p < NP; ++p) acc[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int64_t n_chunks = (d + kChunk - 1) / kChunk;
+// A float as the sum of three bf16 values, exactly: h is x rounded to 8 significant bits, m the
+// rest rounded again, l what is left (8 bits at most).  Two floats at a time.
+__device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
+}
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+    h = pack_bf16(x0, x1);
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xFFFF0000u);
+    m = pack_bf16(r0, r1);
+    l = pack_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xFFFF0000u));
+}
 
-    // this wave's rows; slots past f repeat the last row (loaded, never stored).  The widest
-    // shapes keep row numbers instead of pointers: half the registers, one multiply per load.
-    constexpr bool kRowNumbers = RW > 24;
-    const float *rowp[kRowNumbers ? 1 : RW];
-    int32_t rown[kRowNumbers ? RW : 1];
+// Waves per block, and steps of 32 coordinates a wave has in flight: enough waves to keep about
+// 100 KB per CU in flight as far as registers allow (f = 16: 16 waves x 2 steps 139 us a call, 4 x 8
+// 145; f = 33: 4 x 1 272 us, 8 x 1 280, 4 x 2 274)
+constexpr int gram_waves(int nt) { return nt <= 1 ? 16 : (nt <= 2 ? 8 : 4); }
+constexpr int gram_steps(int nt) { return nt <= 1 ? 2 : 1; }
+constexpr int kStep = 32;  // coordinates a matrix instruction contracts
+
+// Compile-time fence: what the wave's lanes have written to LDS is read by other lanes of the same
+// wave (LDS serves a wave's accesses in order, so the hardware needs no wait).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// fn(ti, tj, number of the tile) for the tiles on and above the diagonal
+template <int NT, typename FN>
+__device__ __forceinline__ void for_tiles(FN fn) {
 #pragma unroll
-    for (int t = 0; t < RW; ++t) {
-        const int j = wave + 4 * t;
-        const int32_t row = row_index[j < f ? j : f - 1];
-        if constexpr (kRowNumbers)
-            rown[t] = row;
-        else
-            rowp[t] = X + (int64_t)row * ld + 4 * lane;
-    }
-    auto row_ptr = [&](int t) -> const float * {
-        if constexpr (kRowNumbers)
-            return X + (int64_t)rown[t] * ld + 4 * lane;
-        else
-            return rowp[t];
-    };
-    float reg[RW][4];
-    auto fetch = [&](int64_t chunk) {
-        const int64_t c0 = chunk * kChunk + 4 * lane;
-        if ((chunk + 1) * kChunk <= d) {  // whole chunk inside the row: branch-free loads
+    for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
-            for (int t = 0; t < RW; ++t) {
-                const f32x4u v = __builtin_nontemporal_load(
-                    reinterpret_cast<const f32x4u *>(row_ptr(t) + chunk * kChunk));
-                reg[t][0] = v[0]; reg[t][1] = v[1]; reg[t][2] = v[2]; reg[t][3] = v[3];
-            }
-        } else {  // the ragged last chunk: missing coordinates count as zero
+        for (int tj = ti; tj < NT; ++tj) fn(ti, tj, tile_pair(NT, ti, tj));
+}
+
+// Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16.
+// A wave takes whole stretches of 32*SF coordinates of every row, so every word is loaded and
+// split once and no barrier stands between the loads and the matrix instructions.  Consecutive
+// lanes load consecutive words of a row (non-temporal: 2-5 % faster here); a pass through the
+// wave's own piece of LDS gives lane l the 8 coordinates 8*(l/16).. of row l%16 that an operand
+// takes (16-byte pieces, piece p of row r in place p ^ (r%8): neither side has bank conflicts).
+// SPLIT: the products are taken on the bf16 matrix units; x = h + m + l exactly, and
+//     x y = hh + (hm + mh) + (hl + mm + lh) + terms below 2^-26 |x y|,
+// six instructions of 32 coordinates in place of eight fp32 ones of 4: 0.4 of their time.  The unit
+// drops low bits of products that are small against the sum they are added to, so every step's
+// hh and mm start from zero and the steps are added in fp32 by the vector ALU.  The sums of h with
+// m and l are small themselves and stay on the unit; which row gives the h matters to their
+// rounding, so both kinds have their own and are added at the end: G(i, j) and G(j, i) are the
+// same bits, and equal rows tie exactly.  No further from the exact sums than the fp32 instructions
+// (f = 25, d = 11.2 M: 4e-9 against 2e-7 of the distances' norm; 25 x 100003: 2e-9 either way).
+// f = 49, d = 11.2 M: 0.37 ms (fp32 instructions on a tile in LDS shared by the block: 0.50; reading
+// the rows once at 6.9 TB/s: 0.32); multi-krum of 128 x 3 M 0.55 ms (0.83), of 80 x 4 M 0.35 (0.57).  Vector ALU 0.6 and
+// matrix units 0.4 busy at f = 49; up to f = 32 HBM-bound as before (0.18 ms at f = 25).
+template <int NT, int SF, bool SPLIT>
+__device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int64_t d, int64_t ld,
+                                                const int32_t *__restrict__ row_index, int f,
+                                                float *stage, f32x4 (&acc)[NT * (NT + 1) / 2]) {
+    constexpr int NP = NT * (NT + 1) / 2, kSpan = kStep * SF;
+    constexpr int kPieces = kSpan / 4, kRows = 64 / kPieces, kLoads = 16 * NT / kRows;
+    const int lane = threadIdx.x & 63;
+    const int64_t n_spans = (d + kSpan - 1) / kSpan;
+    const int64_t stride = (int64_t)gridDim.x * gram_waves(NT);
+    int64_t span = (int64_t)blockIdx.x * gram_waves(NT) + (threadIdx.x >> 6);
+    // load n: rows n*kRows .. + kRows - 1, one after the other; rows past f in a load that has others
+    // repeat row f-1 (nothing reads their results), loads without a row are left out
+    auto row_of = [&](int n) { return n * kRows + lane / kPieces; };
+    auto piece_of = [&](int n) { return (lane % kPieces) ^ (row_of(n) & 7); };
+    auto used = [&](int n) { return n * kRows <= 16 * (NT - 1) || n * kRows < f; };
+    const float *rowp[kLoads];
 #pragma unroll
-            for (int t = 0; t < RW; ++t)
+    for (int n = 0; n < kLoads; ++n)
+        rowp[n] = X + (int64_t)row_index[row_of(n) < f ? row_of(n) : f - 1] * ld + 4 * piece_of(n);
+    f32x4 *slots = reinterpret_cast<f32x4 *>(stage);  // [16*NT rows][kPieces]
+#pragma unroll
+    for (int n = 0; n < kLoads; ++n)
+        if (!used(n)) slots[64 * n + lane] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 raw[kLoads];
+    auto fetch = [&](int64_t at) {
+        const int64_t c0 = at * kSpan;
+        if (c0 + kSpan <= d) {
+#pragma unroll
+            for (int n = 0; n < kLoads; ++n)
+                if (used(n)) raw[n] = __builtin_nontemporal_load(
+                                 reinterpret_cast<const f32x4u *>(rowp[n] + c0));
+        } else {  // the ragged end: missing coordinates count as zero
+#pragma unroll
+            for (int n = 0; n < kLoads; ++n)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    reg[t][e] = c0 + e < d ? row_ptr(t)[chunk * kChunk + e] : 0.0f;
+                    raw[n][e] = c0 + 4 * piece_of(n) + e < d ? rowp[n][c0 + e] : 0.0f;
         }
     };
-
-    int64_t chunk = blockIdx.x;
-    if (chunk < n_chunks) fetch(chunk);
-    for (; chunk < n_chunks; chunk += gridDim.x) {
 #pragma unroll
-        for (int t = 0; t < RW; ++t) {
-            const int j = wave + 4 * t;
-            if (j < f) {
-                // column c of row j lives at c ^ 2 if bit 3 of j is set: with pitch 260 the 32
-                // lanes an operand read serves per cycle (rows 0..15, k = 0,1 or 2,3) then hit
-                // bank 4*(row % 8) + (k ^ 2*(row / 8)), all different
-                f32x4 *dst = reinterpret_cast<f32x4 *>(T + j * kStride + 4 * lane);
-                const bool swz = (j & 8) != 0;
-                f32x4 v;
-                v[0] = swz ? reg[t][2] : reg[t][0];
-                v[1] = swz ? reg[t][3] : reg[t][1];
-                v[2] = swz ? reg[t][0] : reg[t][2];
-                v[3] = swz ? reg[t][1] : reg[t][3];
-                *dst = v;
+    for (int p = 0; p < NP; ++p) acc[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // products of one row's h with the other's m and l, and the other way round
+    // kept over all steps where registers allow (NT = 4 would lose a wave per SIMD: 788 instead of
+    // 759 us a call of Bulyan on 49 x 11.2 M), added every step otherwise
+    constexpr bool kKeep = SPLIT && NT <= 6 && NT != 4;
+    constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 cross_up[kKeep ? NP : 1], cross_down[kKeep ? NP : 1];
+#pragma unroll
+    for (int p = 0; p < (kKeep ? NP : 1); ++p) cross_up[p] = cross_down[p] = zero;
+    if (span < n_spans) fetch(span);
+    for (; span < n_spans; span += stride) {
+        wave_fence();
+#pragma unroll
+        for (int n = 0; n < kLoads; ++n)
+            if (used(n)) slots[64 * n + lane] = raw[n];
+        wave_fence();
+        if (span + stride < n_spans) fetch(span + stride);
+#pragma unroll
+        for (int s = 0; s < SF; ++s) {
+            const int row = lane & 15, first = 8 * s + 2 * (lane >> 4);
+            if constexpr (SPLIT) {
+                u32x4 part[NT][3];  // h, m, l of 8 coordinates each
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const f32x4 x = slots[(16 * t + row) * kPieces + ((first + u) ^ (row & 7))];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            uint32_t h, m, l;
+                            split_pair(x[2 * e], x[2 * e + 1], h, m, l);
+                            part[t][0][2 * u + e] = h;
+                            part[t][1][2 * u + e] = m;
+                            part[t][2][2 * u + e] = l;
+                        }
+                    }
+                // a few tiles at a time: consecutive instructions go to different sums
+                constexpr int kGroups = (NP + 5) / 6, kGroup = (NP + kGroups - 1) / kGroups;
+                auto mul = [&](int ti, int ka, int tj, int kb, f32x4 c) {
+                    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, part[ti][ka]),
+                                                                   __builtin_bit_cast(bf16x8, part[tj][kb]),
+                                                                   c, 0, 0, 0);
+                };
+#pragma unroll
+                for (int p0 = 0; p0 < NP; p0 += kGroup) {
+                    f32x4 sum[kGroup], up[kGroup], down[kGroup];
+                    for_tiles<NT>([&](int ti, int tj, int p) {
+                        if (p < p0 || p >= p0 + kGroup) return;
+                        up[p - p0] = mul(ti, 0, tj, 2, kKeep ? cross_up[p] : zero);
+                        down[p - p0] = mul(ti, 2, tj, 0, kKeep ? cross_down[p] : zero);
+                    });
+                    for_tiles<NT>([&](int ti, int tj, int p) {
+                        if (p < p0 || p >= p0 + kGroup) return;
+                        up[p - p0] = mul(ti, 0, tj, 1, up[p - p0]);
+                        down[p - p0] = mul(ti, 1, tj, 0, down[p - p0]);
+                        if (kKeep) cross_up[p] = up[p - p0];
+                        if (kKeep) cross_down[p] = down[p - p0];
+                    });
+                    for_tiles<NT>([&](int ti, int tj, int p) {
+                        if (p < p0 || p >= p0 + kGroup) return;
+                        sum[p - p0] = mul(ti, 1, tj, 1, kKeep ? zero : up[p - p0] + down[p - p0]);
+                    });
+                    for_tiles<NT>([&](int ti, int tj, int p) {
+                        if (p < p0 || p >= p0 + kGroup) return;
+                        sum[p - p0] = mul(ti, 0, tj, 0, sum[p - p0]);
+                    });
+                    for_tiles<NT>([&](int ti, int tj, int p) {
+                        if (p < p0 || p >= p0 + kGroup) return;
+                        acc[p] += sum[p - p0];
+                    });
+                }
+            } else {
+                // (rare) word e of the lane's pieces: coordinates that all rows share, four at a time
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    f32x4 x[NT];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) x[t] = slots[(16 * t + row) * kPieces + ((first + u) ^ (row & 7))];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                            for (int tj = ti; tj < NT; ++tj) {
+                                f32x4 &a = acc[tile_pair(NT, ti, tj)];
+                                a = __builtin_amdgcn_mfma_f32_16x16x4f32(x[ti][e], x[tj][e], a, 0, 0, 0);
+                            }
+                }
             }
         }
-        __syncthreads();
-        if (chunk + gridDim.x < n_chunks) fetch(chunk + gridDim.x);
-        // wave w multiplies coordinates [64w, 64w+64) of the chunk, four per MFMA: lane l holds
-        // A[row = l%16][k = l/16], which is also B[k][col = l%16] of the transposed operand
-        const float *t0 = T + (lane & 15) * kStride + wave * 64 + ((lane >> 4) ^ ((lane & 8) >> 2));
-        constexpr int SB = NT > 6 ? 2 : (NT > 4 ? 4 : 8);  // steps whose operands are read ahead of their MFMAs
-#pragma unroll
-        for (int s0 = 0; s0 < 16; s0 += SB) {
-            float x[NT][SB];
-#pragma unroll
-            for (int s = 0; s < SB; ++s)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) x[t][s] = t0[16 * t * kStride + 4 * (s0 + s)];
-#pragma unroll
-            for (int s = 0; s < SB; ++s)
-#pragma unroll
-                for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-                    for (int tj = ti; tj < NT; ++tj)
-                        acc[tile_pair(NT, ti, tj)] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                            x[ti][s], x[tj][s], acc[tile_pair(NT, ti, tj)], 0, 0, 0);
-        }
-        __syncthreads();
     }
-    // add the four waves' tiles through LDS (the staging tile is free now), then store:
-    // ((wave 0 + wave 1) + wave 2) + wave 3 either way
-    float *red = T;
+    if constexpr (kKeep) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) acc[p] += cross_up[p] + cross_down[p];
+    }
+}
+
+// Partial Gram tiles of the rows row_index[0..f-1] over this block's coordinates.  partial:
+// [gridDim.x][pairs][256] floats, position v*64 + lane, pairs = NT(NT+1)/2.  A block that ends with
+// an infinity or NaN in a tile -- inputs that are not finite, or so large that h or a product
+// overflows -- starts over with the fp32 instructions, which decide what such inputs give.
+template <int NT, int SF>
+__global__ __launch_bounds__(64 * gram_waves(NT))
+__attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2 : 1)))
+void gram_partial_kernel(
+    const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
+    float *__restrict__ partial) {
+    constexpr int NP = NT * (NT + 1) / 2, kWaves = gram_waves(NT);
+    constexpr int kStage = 16 * NT * kStep * SF;  // floats of one wave's stage
+    constexpr bool kAllWaves = kWaves * NP * kTile <= 16 * 1024;  // room for the waves' tiles at a time
+    constexpr int kRed = (kAllWaves ? kWaves : 1) * NP * kTile;
+    __shared__ __align__(16) float lds[kRed > kWaves * kStage ? kRed : kWaves * kStage];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    f32x4 acc[NP];
+    gram_accumulate<NT, SF, true>(X, d, ld, row_index, f, lds + wave * kStage, acc);
+    bool finite = true;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) finite = finite && fabsf(acc[p][v]) <= __FLT_MAX__;
+    if (__syncthreads_or(finite ? 0 : 1) != 0) {
+        gram_accumulate<NT, SF, false>(X, d, ld, row_index, f, lds + wave * kStage, acc);
+        __syncthreads();  // the stages are read before the tiles below replace them
+    }
+    // the waves' tiles are added in wave order either way
     float *dst = partial + (int64_t)blockIdx.x * NP * kTile;
-    if constexpr (4 * NP * kTile <= 16 * NT * kStride) {  // [4][NP][256] floats fit the tile
+    if constexpr (kAllWaves) {
 #pragma unroll
         for (int p = 0; p < NP; ++p)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) red[(wave * NP + p) * kTile + v * 64 + lane] = acc[p][v];
+            for (int v = 0; v < 4; ++v) lds[(wave * NP + p) * kTile + v * 64 + lane] = acc[p][v];
         __syncthreads();
-        for (int i = tid; i < NP * kTile; i += kBlock)
-            dst[i] = ((red[i] + red[NP * kTile + i]) + red[2 * NP * kTile + i]) + red[3 * NP * kTile + i];
+        for (int i = tid; i < NP * kTile; i += 64 * kWaves) {
+            double total = lds[i];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) total += (double)lds[w * NP * kTile + i];
+            dst[i] = (float)total;
+        }
     } else {  // one [NP][256] array, the waves add their tiles in turn
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             if (wave == w) {
 #pragma unroll
                 for (int p = 0; p < NP; ++p)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        float *cell = red + p * kTile + v * 64 + lane;
+                        float *cell = lds + p * kTile + v * 64 + lane;
                         *cell = w == 0 ? acc[p][v] : *cell + acc[p][v];
                     }
             }
             __syncthreads();
         }
-        for (int i = tid; i < NP * kTile; i += kBlock) dst[i] = red[i];
+        for (int i = tid; i < NP * kTile; i += 64 * kWaves) dst[i] = lds[i];
     }
 }
 
@@ -635,40 +745,50 @@ struct KrumWorkspace {
 inline int stored_tiles(int f) { return row_tiles(f) * (row_tiles(f) + 1) / 2; }
 
 inline size_t krum_workspace_bytes(int f) {
+    // (callers know this size: beyond 64 vectors it has room for 6 or 8 row tiles, whatever is used)
+    const int nt = f <= 64 ? row_tiles(f) : (f <= 96 ? 6 : 8);
     return offsetof(KrumWorkspace, partial) +
-           sizeof(float) * (size_t)kGramBlocks * stored_tiles(f) * kTile;
+           sizeof(float) * (size_t)kGramBlocks * (nt * (nt + 1) / 2) * kTile;
 }
 
-// Gram matrix of the f rows into ws->gram (partial tiles, then the fp64 reduction).
-template <int NT, int RW>
-int launch_gram_shape(int grid, const float *rows_base, int64_t d, int64_t ld,
-                      const int32_t *row_index_dev, int f, float *partial, hipStream_t s) {
-    const size_t lds = (size_t)16 * NT * kStride * sizeof(float);
-    if (lds > 64 * 1024)  // more than a kernel may use without asking
-        BYZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&gram_partial_kernel<NT, RW>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    gram_partial_kernel<NT, RW><<<grid, kBlock, lds, s>>>(rows_base, d, ld, row_index_dev, f, partial);
+template <int NT, int SF>
+void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
+                       int f, float *partial, int *grid, hipStream_t s) {
+    constexpr int64_t kSpan = kStep * SF * gram_waves(NT);  // coordinates a block takes at a time
+    const int64_t n = (d + kSpan - 1) / kSpan;
+    *grid = n < 1 ? 1 : (n < kGramBlocks ? (int)n : kGramBlocks);  // d == 0: one block writes zero tiles
+    gram_partial_kernel<NT, SF><<<*grid, 64 * gram_waves(NT), 0, s>>>(rows_base, d, ld, row_index_dev,
+                                                                      f, partial);
+}
+
+template <int NT>
+int launch_gram_shape(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
+                      int f, float *partial, int *grid, hipStream_t s) {
+    constexpr int SF = gram_steps(NT);
+    // short rows, four steps per wave or fewer: one step at a time spreads them over more waves
+    // (and partial sums)
+    if (d <= (int64_t)kGramBlocks * 4 * kStep * gram_waves(NT))
+        launch_gram_spans<NT, 1>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+    else
+        launch_gram_spans<NT, SF>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
 
+// Gram matrix of the f rows into ws->gram (partial tiles, then the fp64 reduction).
 int launch_gram(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev, int f,
                 KrumWorkspace *ws, hipStream_t s) {
-    int64_t n_chunks = (d + kChunk - 1) / kChunk;
-    if (n_chunks < 1) n_chunks = 1;  // d == 0: one block writes zero tiles
-    const int grid = n_chunks < kGramBlocks ? (int)n_chunks : kGramBlocks;
-    // (row tiles, rows a wave stages per chunk = ceil(f / 4) rounded up to a compiled value)
-    int rc;
-    if (f <= 16) rc = launch_gram_shape<1, 4>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 28) rc = launch_gram_shape<2, 7>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 32) rc = launch_gram_shape<2, 8>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 36) rc = launch_gram_shape<3, 9>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 48) rc = launch_gram_shape<3, 12>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 52) rc = launch_gram_shape<4, 13>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 64) rc = launch_gram_shape<4, 16>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 84) rc = launch_gram_shape<6, 21>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else if (f <= 96) rc = launch_gram_shape<6, 24>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
-    else rc = launch_gram_shape<8, 32>(grid, rows_base, d, ld, row_index_dev, f, ws->partial, s);
+    int rc, grid = 0;
+    switch (row_tiles(f)) {
+        case 1: rc = launch_gram_shape<1>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+        case 2: rc = launch_gram_shape<2>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+        case 3: rc = launch_gram_shape<3>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+        case 4: rc = launch_gram_shape<4>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+        case 5: rc = launch_gram_shape<5>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+        case 6: rc = launch_gram_shape<6>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+        case 7: rc = launch_gram_shape<7>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+        default: rc = launch_gram_shape<8>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+    }
     if (rc != BYZ_OK) return rc;
     const int ntiles = stored_tiles(f);
     gram_reduce_kernel<<<ntiles * kTile / 32, kBlock, 0, s>>>(ws->partial, grid, ntiles, ws->gram);

@@ -653,6 +653,52 @@ def test_more_than_169_rows_random_sizes():
             _trimmed_mean_check(X, idx, d, b, (case, f, d, ld, b))
 
 
+@pytest.mark.parametrize("f", [3, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 128])
+def test_gram_distances_at_tile_edges_and_for_inputs_that_are_not_finite(f):
+    # every number of row tiles, one row more or less; d around the 32 coordinates of a matrix
+    # instruction, the span of a wave and of a block, and above the length from which a wave takes
+    # several steps at a time.  Distances against fp64: products are exact to 2^-26 and at most
+    # 8 + 32 fp32 additions on top of each other at these d, so |err| <= 64 * 2^-24 * (G_ii + G_jj).
+    rng = np.random.default_rng(f)
+    idx = torch.tensor(rng.permutation(f).astype(np.int32), device=DEV)
+    order = idx.cpu().numpy()
+    for d in (1, 31, 33, 129, 1026, 20011):
+        Xh = np.ascontiguousarray((rng.standard_normal((f, d + 1)) * rng.uniform(0.01, 3, (f, 1))).astype(np.float32))
+        X = torch.tensor(Xh, device=DEV)
+        _, _, _, dist = B.byz_multi_krum(X, d, idx, 0, 1)
+        torch.cuda.synchronize()
+        V = Xh[order, :d].astype(np.float64)
+        G = V @ V.T
+        n = np.diag(G)
+        want = np.maximum(n[:, None] + n[None, :] - 2 * G, 0)
+        np.fill_diagonal(want, 0)
+        assert (np.abs(dist.cpu().numpy() - want) <= 64 * 2.0 ** -24 * (n[:, None] + n[None, :])).all(), (f, d)
+    # infinities, NaNs and a value whose rounding to 8 bits overflows: same kinds as fp64 products
+    # of fp32 range (the huge value's square is infinite in fp32, its products with 0 are 0)
+    for what in (np.inf, -np.inf, np.nan, np.float32(3.4e38)):
+        Y = Xh.copy()
+        Y[:, 777] = 0.0
+        Y[order[1], 777] = what
+        _, _, _, dist = B.byz_multi_krum(torch.tensor(Y, device=DEV), d, idx, 0, 1)
+        torch.cuda.synchronize()
+        got = dist.cpu().numpy()
+        W64 = Y[order, :d].astype(np.float64)
+        with np.errstate(all="ignore"):
+            P = np.array([[np.float32(np.float32(W64[i, 777]) * np.float32(W64[j, 777])) for j in range(f)]
+                          for i in range(f)]).astype(np.float64)
+            W64[:, 777] = 0
+            G = W64 @ W64.T + P
+            n = np.diag(G)
+            want = n[:, None] + n[None, :] - 2 * G
+            want[want < 0] = 0
+        np.fill_diagonal(want, 0)
+        assert np.array_equal(np.isnan(got), np.isnan(want)), (f, what)
+        assert np.array_equal(np.isinf(got), np.isinf(want)), (f, what)
+        scale = (n[:, None] + n[None, :])
+        ok = np.isfinite(scale)  # the diagonal of the row itself is 0 whatever it holds
+        assert (np.abs(got - want)[ok] <= 64 * 2.0 ** -24 * scale[ok]).all(), (f, what)
+
+
 NETWORKS = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)
 
 
