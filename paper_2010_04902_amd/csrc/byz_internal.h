@@ -10,11 +10,11 @@ void byz_internal_set_hip_error(int code);
 int byz_internal_launch_bulyan_mean(const float *rows_base, long long d, long long ld,
                                     const int *selected_rows_dev, int f, int theta, int beta,
                                     float *out, void *stream);
-// The same on the 81- and the 121-wire network (kernels.hip, build parts 12 and 13), d >= 4.
+// The same for 49 < theta <= 81 and 81 < theta <= 128 (kernels.hip, build parts 12 and 13).
 int byz_internal_launch_bulyan_mean_81(const void *X, long long d, long long ld,
                                        const int *selected_rows, int theta, int beta, void *out,
                                        void *stream);
-int byz_internal_launch_bulyan_mean_121(const void *X, long long d, long long ld,
+int byz_internal_launch_bulyan_mean_137(const void *X, long long d, long long ld,
                                         const int *selected_rows, int theta, int beta, void *out,
                                         void *stream);
 

@@ -37,7 +37,7 @@ import functools
 import os
 import sys
 
-DEPTHS = (1, 2, 3, 4, 5, 20)  # prefetch distances the streamed programs carry load steps for
+DEPTHS = (1, 2, 3, 4, 5, 8, 20)  # prefetch distances the streamed programs carry load steps for
 
 
 def _merge(wires):
@@ -380,7 +380,7 @@ def emit_streamed(f, path, full_sort=False):
     return last_share
 
 
-SIZES = (3, 5, 7, 9, 15, 21, 25, 35, 49)
+SIZES = (3, 5, 7)  # medians of fewer rows than the streamed programs start at
 # sizes with a median program: the paper's file counts (l^2 for MOLS and Ramanujan Case 1, m*s for
 # Case 2) and sizes between them, so that any other f has at most a fifth of spare wires
 STREAMED_SIZES = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)

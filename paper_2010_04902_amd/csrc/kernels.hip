@@ -83,24 +83,24 @@ constexpr int least_rows(int n) {
     while (below > 0 && !has_streamed_network(below)) --below;
     return below + 1;
 }
-// words per thread: fewer for the large networks, whose keys fill the register file
+// Words per thread of the single pass: fewer for the large networks, whose keys fill the register
+// file.  The kernels with one slot per file run one word per thread at every size: the sorting
+// ones by far (fewer registers, more waves; 2.9 M coordinates, four words / one, us: f = 49 108 /
+// 96, f = 35 75 / 67), the medians by 1-3 % (f = 49 92.4 / 89.7, f = 9 17.9 / 17.1).
 constexpr int vec_for(int f) { return f <= 49 ? 4 : (f <= 81 ? 2 : 1); }
-// ... of the median kernels: above 49 wires they are bound by min/max issue, and one word per
-// thread (fewer registers, more waves per SIMD) measured 4-8 % faster than two at f = 63, 81
-constexpr int vec_for_median(int f) { return f <= 49 ? 4 : 1; }
-// ... of the trimmed-mean kernels: the same above 49 wires.  With the three-wire sorters
-// (gen_selnet.py) f = 81 takes 0.57 ms for 11.2 M coordinates, 1.01 of the time its bytes take
-// at 6.5 TB/s (two-wire comparators: 0.78); f = 121 0.41 ms for 4 M (0.30 by bytes; 0.45 before).
-constexpr int vec_for_trimmed(int f) { return f <= 49 ? 4 : 1; }
-// ... and of the second phase of Bulyan, where narrower threads measured slightly slower
-constexpr int vec_for_sort(int f) { return vec_for(f); }
-// ... and of the single pass: with five or seven copies of a file in flight two words per thread
+// With five or seven copies of a file in flight two words per thread
 // (more waves per SIMD, 8-byte loads) measured 1-2 % faster than four (r = 7 would not fit
 // the registers with four); with three copies four words are faster, but for a sort of 49 keys
 // (four: 269 registers, one wave per SIMD, 409 us for 4 M coordinates; two: 377)
 constexpr int vec_for_pass(int f, int r, bool trim) {
     return ((r >= 5 || (trim && f > 35)) && f <= 49) ? 2 : vec_for(f);
 }
+// Rows up to which the single pass runs one word per thread whatever the network, with more files
+// in flight (8 ahead for three copies, 5 for five or seven): with fewer threads than fill the chip
+// the walk over the files is bound by the latency of its loads.  us a call, four or two words and
+// one: (25,3) d = 100003 21.6 / 18.4, 262000 23.5 / 28.0; (49,3) 131072 32.4 / 27.8; (49,7) 131072
+// 51.2 / 46.0; (25,5) 20000 25.8 / 23.5, 131072 25.5 / 26.6.
+[[maybe_unused]] constexpr int64_t short_row(int f, int r) { return f <= 25 && r == 5 ? 65536 : 131072; }
 constexpr int kProbe = 256;  // sampled coordinates of the probe (512: 2x slower)
 constexpr int kProbeSplit = 4;  // the files are dealt out to this many groups of kProbe threads
 constexpr int kProbeThreads = kProbe * kProbeSplit;
@@ -365,48 +365,6 @@ template <> struct SelNet<7> {
         return result;
     }
 };
-template <> struct SelNet<9> {
-    static __device__ __forceinline__ uint32_t median(uint32_t (&k)[9]) {
-        uint32_t result;
-#include "generated/selnet_9.inc"
-        return result;
-    }
-};
-template <> struct SelNet<15> {
-    static __device__ __forceinline__ uint32_t median(uint32_t (&k)[15]) {
-        uint32_t result;
-#include "generated/selnet_15.inc"
-        return result;
-    }
-};
-template <> struct SelNet<21> {
-    static __device__ __forceinline__ uint32_t median(uint32_t (&k)[21]) {
-        uint32_t result;
-#include "generated/selnet_21.inc"
-        return result;
-    }
-};
-template <> struct SelNet<35> {
-    static __device__ __forceinline__ uint32_t median(uint32_t (&k)[35]) {
-        uint32_t result;
-#include "generated/selnet_35.inc"
-        return result;
-    }
-};
-template <> struct SelNet<25> {
-    static __device__ __forceinline__ uint32_t median(uint32_t (&k)[25]) {
-        uint32_t result;
-#include "generated/selnet_25.inc"
-        return result;
-    }
-};
-template <> struct SelNet<49> {
-    static __device__ __forceinline__ uint32_t median(uint32_t (&k)[49]) {
-        uint32_t result;
-#include "generated/selnet_49.inc"
-        return result;
-    }
-};
 
 // --------------------------------------------------------------------- device workspace
 
@@ -613,18 +571,20 @@ __global__ void revote_decide_kernel(AggWorkspace *ws, const int32_t *__restrict
 template <int R, int V>
 __global__ __launch_bounds__(kBlock) void vote_pairs_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
-    int f, uint32_t *pair_neq, const uint32_t *__restrict__ gate, int gate_n,
+    int f, int files_per_block, uint32_t *pair_neq, const uint32_t *__restrict__ gate, int gate_n,
     const uint32_t *__restrict__ only_files) {
     if (gate != nullptr && !any_word_set(gate, gate_n)) return;
     const int lane = threadIdx.x & 63;
     const int64_t n_vec = d / V;
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int j_begin = blockIdx.y * files_per_block;
+    const int j_end = j_begin + files_per_block < f ? j_begin + files_per_block : f;
     if (n_vec > 0) {
         // threads past the end redo the last vector: no branches around loads and ballots
         const uint32_t *base = X + (gt < n_vec ? gt : n_vec - 1) * V;
         // files in groups of 64: lane j - j0 collects the bits of file j
-        for (int j0 = 0; j0 < f; j0 += 64) {
-            const int j1 = j0 + 64 < f ? j0 + 64 : f;
+        for (int j0 = j_begin; j0 < j_end; j0 += 64) {
+            const int j1 = j0 + 64 < j_end ? j0 + 64 : j_end;
             uint32_t flags = 0;
             for (int j = j0; j < j1; ++j) {
                 if (only_files != nullptr && only_files[j] == 0) continue;  // the same for every thread
@@ -646,7 +606,7 @@ __global__ __launch_bounds__(kBlock) void vote_pairs_kernel(
     const int tail = (int)(d - n_vec * V);
     if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x < tail) {
         const int64_t c = n_vec * V + threadIdx.x;
-        for (int j = 0; j < f; ++j) {
+        for (int j = j_begin; j < j_end; ++j) {
             if (only_files != nullptr && only_files[j] == 0) continue;
             uint32_t x[R];
 #pragma unroll
@@ -685,14 +645,16 @@ __device__ __forceinline__ uint32_t far_apart(const uint32_t (&a)[V], const uint
 template <int R, int V>
 __global__ __launch_bounds__(kBlock) void vote_pairs_tolerant_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
-    int f, float atol, float rtol, uint32_t *pair_far) {
+    int f, int files_per_block, float atol, float rtol, uint32_t *pair_far) {
     const int lane = threadIdx.x & 63;
     const int64_t n_vec = d / V;
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int j_begin = blockIdx.y * files_per_block;
+    const int j_end = j_begin + files_per_block < f ? j_begin + files_per_block : f;
     if (n_vec > 0) {
         const uint32_t *base = X + (gt < n_vec ? gt : n_vec - 1) * V;
-        for (int j0 = 0; j0 < f; j0 += 64) {
-            const int j1 = j0 + 64 < f ? j0 + 64 : f;
+        for (int j0 = j_begin; j0 < j_end; j0 += 64) {
+            const int j1 = j0 + 64 < j_end ? j0 + 64 : j_end;
             uint32_t flags = 0;
             for (int j = j0; j < j1; ++j) {
                 uint32_t x[R][V];
@@ -713,7 +675,7 @@ __global__ __launch_bounds__(kBlock) void vote_pairs_tolerant_kernel(
     const int tail = (int)(d - n_vec * V);
     if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x < tail) {
         const int64_t c = n_vec * V + threadIdx.x;
-        for (int j = 0; j < f; ++j) {
+        for (int j = j_begin; j < j_end; ++j) {
             uint32_t x[R][1];
 #pragma unroll
             for (int k = 0; k < R; ++k) x[k][0] = X[(int64_t)file_rows[j * R + k] * ld + c];
@@ -752,6 +714,7 @@ __global__ __launch_bounds__(kBlock) void vote_pairs_tolerant_kernel(
 #define BYZ_S_LOAD3(j) if constexpr (kAhead == 3) { BYZ_S_LOAD_(j) }
 #define BYZ_S_LOAD4(j) if constexpr (kAhead == 4) { BYZ_S_LOAD_(j) }
 #define BYZ_S_LOAD5(j) if constexpr (kAhead == 5) { BYZ_S_LOAD_(j) }
+#define BYZ_S_LOAD8(j) if constexpr (kAhead == 8) { BYZ_S_LOAD_(j) }
 #define BYZ_S_LOAD20(j) if constexpr (kAhead == 20) { BYZ_S_LOAD_(j) }
 #define BYZ_S_USE(j)                                                                          \
     {                                                                                         \
@@ -808,7 +771,8 @@ __global__ __launch_bounds__(kBlock) void vote_pairs_tolerant_kernel(
 #define BYZ_S_MEDIAN(w)                                                                       \
     _Pragma("unroll") for (int v_ = 0; v_ < V; ++v_) o[v_] = from_key(key[v_][w]);
 
-// Coordinate-wise median of F rows by a register selection network.
+// Coordinate-wise median of F rows (fewer than the streamed networks start at) by a register
+// selection network, V words per thread.
 template <int F, int V>
 __global__ __launch_bounds__(kBlock) void median_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
@@ -819,37 +783,16 @@ __global__ __launch_bounds__(kBlock) void median_kernel(
     if (gt < n_vec) {
         uint32_t key[V][F];
         uint32_t o[V];
-        if constexpr (has_streamed_network(F)) {
-            // same streamed program as the single-pass kernel, one slot per file, no compares
-            constexpr int NS = 1;
-            constexpr int kAhead = prefetch_depth(F, NS);
-            const uint32_t voff = (uint32_t)(gt * (V * 4));
-            const char *Xb = reinterpret_cast<const char *>(X);
-            uint32_t stage[kAhead + 1][NS][V];
-            const int lane = 0;
-            uint32_t flags[(F + 63) / 64] = {};
-            (void)lane; (void)flags;
-#define BYZ_S_ROW_ADDR(j, k) (Xb + (uint64_t)(uint32_t)row_index[j] * (uint64_t)ld * 4u + voff)
-            if constexpr (pins_median(F)) {
-#include "selnet_pin_on.inc"
-#include "generated/selnet_stream_dispatch.inc"
-#include "selnet_pin_off.inc"
-            } else {
-#include "generated/selnet_stream_dispatch.inc"
-            }
-#undef BYZ_S_ROW_ADDR
-        } else {
-            const uint32_t *base = X + gt * V;
+        const uint32_t *base = X + gt * V;
 #pragma unroll
-            for (int j = 0; j < F; ++j) {
-                uint32_t x[V];
-                load_vec<V>(base + (int64_t)row_index[j] * ld, x);
+        for (int j = 0; j < F; ++j) {
+            uint32_t x[V];
+            load_vec<V>(base + (int64_t)row_index[j] * ld, x);
 #pragma unroll
-                for (int v = 0; v < V; ++v) key[v][j] = to_key(x[v]);
-            }
-#pragma unroll
-            for (int v = 0; v < V; ++v) o[v] = from_key(SelNet<F>::median(key[v]));
+            for (int v = 0; v < V; ++v) key[v][j] = to_key(x[v]);
         }
+#pragma unroll
+        for (int v = 0; v < V; ++v) o[v] = from_key(SelNet<F>::median(key[v]));
         store_vec<V>(out + gt * V, o);
     }
     const int tail = (int)(d - n_vec * V);
@@ -862,13 +805,13 @@ __global__ __launch_bounds__(kBlock) void median_kernel(
     }
 }
 
-// Coordinate-wise median by the streamed program of the generated network on F wires with V = vec_for_median(F)
-// words per thread: the large networks and, with PAD, any odd least_rows(F) <= f <= F --
+// Coordinate-wise median by the streamed program of the generated network on F wires, one word per
+// thread: exactly F rows or, with PAD, any odd least_rows(F) <= f <= F --
 // the F - f spare wires reload row_index[0] and are tied half to the smallest and half to the
 // largest key, which leaves the median where it was.  Bound by HBM up to F = 109 (4 M coordinates
 // at 6.5 TB/s and measured: f = 81 202 and 196 us, 109 271 and 266), by min/max issue above (153
-// 379 and 392, 169 419 and 472; with two-wire comparators and fewer sizes 655 and 577).  Thread t owns the words starting at min(V*t, d - V): the last vector overlaps its
-// neighbour (both write the same values).  Needs d >= V.
+// 379 and 392, 169 419 and 472; with two-wire comparators and fewer sizes 655 and 577).
+// (V = 4: thread t owns the words from min(4t, d - 4), the last vector overlaps its neighbour; d >= 4)
 template <int F, int V, bool PAD>
 __global__ __launch_bounds__(kBlock) void median_large_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
@@ -876,15 +819,13 @@ __global__ __launch_bounds__(kBlock) void median_large_kernel(
     if (gate != nullptr && !any_word_set(gate, gate_n)) return;
     const int pad_low_end = f + (F - f) / 2;  // wires [f, pad_low_end) smallest key, rest largest
     (void)pad_low_end;
-    const int64_t n_thr = (d + V - 1) / V;
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (gt >= n_thr) return;
-    const int64_t c0 = gt * V < d - V ? gt * V : d - V;
+    if (gt >= (d + V - 1) / V) return;
+    const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
+    // one word per thread: twenty files ahead (as measured best at F = 121)
+    constexpr int NS = 1, kAhead = V == 1 ? 20 : prefetch_depth(F, NS);
     uint32_t key[V][F];
     uint32_t o[V];
-    constexpr int NS = 1;
-    // one word per thread: 4-byte loads, twenty files ahead (as measured best at F = 121)
-    constexpr int kAhead = V == 1 ? 20 : prefetch_depth(F, NS);
     const uint32_t voff = (uint32_t)(c0 * 4);
     const char *Xb = reinterpret_cast<const char *>(X);
     uint32_t stage[kAhead + 1][NS][V];
@@ -969,26 +910,6 @@ void median_halves_kernel(
     }
 }
 
-// Coordinate-wise median for d below the vector width of the network kernels (f <= 64): rank
-// counting, one coordinate a thread.
-__global__ __launch_bounds__(kBlock) void median_generic_kernel(
-    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
-    int f, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
-    if (gate != nullptr && !any_word_set(gate, gate_n)) return;
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (c >= d) return;
-    uint32_t key[BYZ_MAX_F];
-    for (int j = 0; j < f; ++j) key[j] = to_key(X[(int64_t)row_index[j] * ld + c]);
-    const int mid = (f - 1) / 2;
-    uint32_t result = key[0];
-    for (int i = 0; i < f; ++i) {
-        int rank = 0;
-        for (int t = 0; t < f; ++t) rank += (key[t] < key[i] || (key[t] == key[i] && t < i)) ? 1 : 0;
-        if (rank == mid) result = key[i];
-    }
-    out[c] = from_key(result);
-}
-
 // Rounding contract of the trimmed mean: fp32, the kept values (ranks b .. F-b-1 of the sorted
 // keys) are added one by one in ascending order starting from +0, then one IEEE division.
 template <int F, int V, bool RUNS = false>
@@ -1041,21 +962,19 @@ __device__ __forceinline__ void trimmed_mean_of_sorted(const uint32_t (&key)[V][
 // Coordinate-wise trimmed mean of F rows: the F values of a coordinate are sorted (total order
 // of the keys), the b smallest and the b largest are dropped and the remaining F - 2b are
 // averaged.  Rounding contract: fp32, the kept values are added one by one in ascending order
-// starting from +0, then divided by float(F - 2b) (IEEE division).  Thread t owns the four
-// words starting at min(4t, d - 4): the last vector overlaps its neighbour instead of a scalar
-// tail (both write the same values).  Needs d >= 4.
+// starting from +0, then divided by float(F - 2b) (IEEE division).  One word per thread: f = 81
+// takes 0.57 ms for 11.2 M coordinates, 1.01 of the time its bytes take at 6.5 TB/s (0.78 with
+// two-wire comparators), f = 121 0.41 ms for 4 M (0.30 by bytes; 0.45 before): min/max issue.
 template <int F, int V, bool PAD>
 __global__ __launch_bounds__(kBlock) void trimmed_mean_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
     int f, int b, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
     if (gate != nullptr && !any_word_set(gate, gate_n)) return;
-    const int64_t n_thr = (d + V - 1) / V;
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (gt >= n_thr) return;
+    if (gt >= (d + V - 1) / V) return;
     const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
+    constexpr int NS = 1, kAhead = V == 1 ? 20 : prefetch_depth(F, NS);  // as the median kernels
     uint32_t key[V][F];
-    constexpr int NS = 1;
-    constexpr int kAhead = V == 1 ? 20 : prefetch_depth(F, NS);  // as the one-word median kernels
     const uint32_t voff = (uint32_t)(c0 * 4);
     const char *Xb = reinterpret_cast<const char *>(X);
     uint32_t stage[kAhead + 1][NS][V];
@@ -1216,26 +1135,6 @@ void trimmed_halves_kernel(
     }
 }
 
-// Trimmed mean for d below the vector width of the network kernels (f <= 64): insertion sort
-// in per-thread memory, one coordinate a thread; same rounding contract as trimmed_mean_kernel.
-__global__ __launch_bounds__(kBlock) void trimmed_mean_generic_kernel(
-    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
-    int f, int b, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
-    if (gate != nullptr && !any_word_set(gate, gate_n)) return;
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (c >= d) return;
-    uint32_t key[BYZ_MAX_F];
-    for (int j = 0; j < f; ++j) {
-        const uint32_t x = to_key(X[(int64_t)row_index[j] * ld + c]);
-        int t = j - 1;
-        while (t >= 0 && key[t] > x) { key[t + 1] = key[t]; --t; }
-        key[t + 1] = x;
-    }
-    float acc = 0.0f;
-    for (int i = b; i < f - b; ++i) acc += __uint_as_float(from_key(key[i]));
-    out[c] = __float_as_uint(acc / (float)(f - 2 * b));
-}
-
 // Mean around the median (second phase of Bulyan) for one coordinate whose theta values sit
 // in ascending order in col[0], col[stride], ..: the beta values closest to the middle one
 // (the median), added in ascending order from +0 in fp32 and divided by float(beta).
@@ -1291,18 +1190,15 @@ __device__ __forceinline__ float mean_around_median(const float *col, int stride
 // run-time indices.  Thread t owns the words from min(V*t, d - V); needs d >= V.
 // Dynamic LDS: N*BLOCK*4 bytes; the widest networks run one wave a block, so that several
 // blocks' columns fit a CU and the number of waves is again what the registers allow.
-template <int F, int V, int BLOCK>
+template <int F, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void bulyan_mean_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld,
     const int32_t *__restrict__ selected_rows, int theta, int beta, uint32_t *__restrict__ out) {
     extern __shared__ float s_bulyan_col[];
-    const int64_t n_thr = (d + V - 1) / V;
-    const int64_t gt = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (gt >= n_thr) return;
-    const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
+    const int64_t c0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+    if (c0 >= d) return;
+    constexpr int V = 1, NS = 1, kAhead = 20;
     uint32_t key[V][F];
-    constexpr int NS = 1;
-    constexpr int kAhead = prefetch_depth(F, NS);
     const uint32_t voff = (uint32_t)(c0 * 4);
     const char *Xb = reinterpret_cast<const char *>(X);
     uint32_t stage[kAhead + 1][NS][V];
@@ -1310,44 +1206,24 @@ __global__ __launch_bounds__(BLOCK) void bulyan_mean_kernel(
     uint32_t flags[(F + 63) / 64] = {};
     (void)lane; (void)flags;
 #undef BYZ_S_KEY
-#define BYZ_S_KEY(j, x) ((j) < theta ? to_key(x) : 0xFFFFFFFFu)
+#define BYZ_S_KEY(j, x) ((j) < least_rows(F) || (j) < theta ? to_key(x) : 0xFFFFFFFFu)
 #define BYZ_S_ROW_ADDR(j, k) \
-    (Xb + (uint64_t)(uint32_t)selected_rows[(j) < theta ? (j) : 0] * (uint64_t)ld * 4u + voff)
+    (Xb + (uint64_t)(uint32_t)selected_rows[(j) < least_rows(F) || (j) < theta ? (j) : 0] * (uint64_t)ld * 4u + voff)
+    if constexpr (pins_trimmed_mean(F)) {
+#include "selnet_pin_on.inc"
 #include "generated/selnet_sort_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+    } else {
+#include "generated/selnet_sort_stream_dispatch.inc"
+    }
 #undef BYZ_S_ROW_ADDR
 #undef BYZ_S_KEY
 #define BYZ_S_KEY(j, x) to_key(x)
     float *col = s_bulyan_col + threadIdx.x;
-    uint32_t o[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-#pragma unroll
-        for (int i = 0; i < F; ++i) col[i * BLOCK] = __uint_as_float(from_key(key[v][i]));
-        o[v] = __float_as_uint(mean_around_median(col, BLOCK, theta, beta));
-    }
-    store_vec<V>(out + c0, o);
-}
-
-// Second phase of Bulyan for theta > 121 and for d < 4: one coordinate a thread, the chosen
-// values insertion-sorted in the thread's LDS column.  Dynamic LDS: theta*kBlock*4 bytes.
-__global__ __launch_bounds__(kBlock) void bulyan_mean_generic_kernel(
-    const uint32_t *__restrict__ X, int64_t d, int64_t ld,
-    const int32_t *__restrict__ selected_rows, int theta, int beta, uint32_t *__restrict__ out) {
-    extern __shared__ float s_bulyan_col[];
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (c >= d) return;
-    uint32_t *kcol = reinterpret_cast<uint32_t *>(s_bulyan_col) + threadIdx.x;
-    for (int j = 0; j < theta; ++j) {
-        const uint32_t x = to_key(X[(int64_t)selected_rows[j] * ld + c]);
-        int t = j - 1;
-        while (t >= 0 && kcol[t * kBlock] > x) {
-            kcol[(t + 1) * kBlock] = kcol[t * kBlock];
-            --t;
-        }
-        kcol[(t + 1) * kBlock] = x;
-    }
-    for (int j = 0; j < theta; ++j) kcol[j * kBlock] = from_key(kcol[j * kBlock]);
-    out[c] = __float_as_uint(mean_around_median(s_bulyan_col + threadIdx.x, kBlock, theta, beta));
+    for (int i = 0; i < F; ++i) col[i * BLOCK] = __uint_as_float(from_key(key[0][i]));
+    const uint32_t o[1] = {__float_as_uint(mean_around_median(col, BLOCK, theta, beta))};
+    store_vec<1>(out + c0, o);
 }
 
 // First kernel of a single-pass call: clears the state the later kernels accumulate into and
@@ -1534,7 +1410,7 @@ __device__ __forceinline__ void fused_body(const uint32_t *__restrict__ X, int64
     const char *Xb = reinterpret_cast<const char *>(X);
     uint32_t key[V][F];       // wire j of the network = file j
     // files prefetched ahead of the one being consumed
-    constexpr int kAhead = prefetch_depth(F, NS);
+    constexpr int kAhead = V < vec_for_pass(F, R, TRIM) ? (NS <= 3 ? 8 : 5) : prefetch_depth(F, NS);
     uint32_t stage[kAhead + 1][NS][V];  // copies of the file in use and of those in flight
     uint32_t o[V];
     // The generated program walks the files in order: the loads of file j+kAhead are issued
@@ -1588,15 +1464,34 @@ inline unsigned blocks_for(int64_t n_vec) {
     return (unsigned)(b > 0 ? b : 1);
 }
 
+// Behind the single pass the median or trimmed-mean kernel nearly always returns at once, and its
+// cost is that of launching its blocks (1800 a microsecond: 24 us of a 540 us call with one word
+// per thread at d = 11.2 M).  There, on rows longer than this, the networks of up to 49 wires run
+// four words per thread.
+[[maybe_unused]] constexpr int64_t kManyBlocks = 131072;
+constexpr int gated_vec(int f) { return f <= 49 ? 4 : 1; }
+
 [[maybe_unused]] constexpr int64_t kMaxCoords = (int64_t)1 << 30;  // byte offsets inside a row fit 32 bits
 
 #if BYZ_IN_PART(0)
+// Blocks of a vote: every block walks over its files one after the other, so where the rows alone
+// do not give 1024 blocks the files are dealt out too, two or more to a block ((255,3) whole call,
+// d = 1003 206 -> 23 us, 100000 234 -> 89, 500000 381 -> 345; 512 or 2048 blocks: up to 20 % slower).
+inline dim3 vote_grid(int64_t d, int f) {
+    const unsigned x = blocks_for(d / kVec);
+    const unsigned want = 1024u / x, most = ((unsigned)f + 1) / 2;
+    const unsigned y = want < 1 ? 1 : (want < most ? want : most);
+    const unsigned per = ((unsigned)f + y - 1) / y;
+    return dim3(x, ((unsigned)f + per - 1) / per);
+}
+
 template <int R>
 int launch_vote_pairs(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, int f,
                       uint32_t *neq, const uint32_t *gate, int gate_n, const uint32_t *only_files,
                       hipStream_t s) {
-    vote_pairs_kernel<R, kVec><<<blocks_for(d / kVec), kBlock, 0, s>>>(X, d, ld, rows, f, neq, gate,
-                                                                      gate_n, only_files);
+    const dim3 grid = vote_grid(d, f);
+    vote_pairs_kernel<R, kVec><<<grid, kBlock, 0, s>>>(X, d, ld, rows, f, (f + grid.y - 1) / grid.y, neq,
+                                                       gate, gate_n, only_files);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
@@ -1615,16 +1510,17 @@ int launch_vote_pairs_r(int r, const uint32_t *X, int64_t d, int64_t ld, const i
 int launch_vote_pairs_tolerant(int r, const uint32_t *X, int64_t d, int64_t ld,
                                const int32_t *rows, int f, float atol, float rtol, uint32_t *far,
                                hipStream_t s) {
-    const unsigned g = blocks_for(d / kVec);
+    const dim3 g = vote_grid(d, f);
+    const int per = (f + (int)g.y - 1) / (int)g.y;
     switch (r) {
         case 3:
-            vote_pairs_tolerant_kernel<3, kVec><<<g, kBlock, 0, s>>>(X, d, ld, rows, f, atol, rtol, far);
+            vote_pairs_tolerant_kernel<3, kVec><<<g, kBlock, 0, s>>>(X, d, ld, rows, f, per, atol, rtol, far);
             break;
         case 5:
-            vote_pairs_tolerant_kernel<5, kVec><<<g, kBlock, 0, s>>>(X, d, ld, rows, f, atol, rtol, far);
+            vote_pairs_tolerant_kernel<5, kVec><<<g, kBlock, 0, s>>>(X, d, ld, rows, f, per, atol, rtol, far);
             break;
         case 7:
-            vote_pairs_tolerant_kernel<7, kVec><<<g, kBlock, 0, s>>>(X, d, ld, rows, f, atol, rtol, far);
+            vote_pairs_tolerant_kernel<7, kVec><<<g, kBlock, 0, s>>>(X, d, ld, rows, f, per, atol, rtol, far);
             break;
         default: return BYZ_EINVAL;
     }
@@ -1650,9 +1546,17 @@ int launch_median_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
 template <int F, bool PAD>
 int launch_median_large(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
                         uint32_t *out, const uint32_t *gate, int gate_n, hipStream_t s) {
-    constexpr int V = vec_for_median(F);
-    median_large_kernel<F, V, PAD><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
-        X, d, ld, row_index, f, out, gate, gate_n);
+    if constexpr (gated_vec(F) > 1 && !PAD) {
+        if (gate != nullptr && d > kManyBlocks) {
+            constexpr int V = gated_vec(F);
+            median_large_kernel<F, V, PAD><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
+                X, d, ld, row_index, f, out, gate, gate_n);
+            BYZ_HIP(hipGetLastError());
+            return BYZ_OK;
+        }
+    }
+    median_large_kernel<F, 1, PAD><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, out, gate,
+                                                                    gate_n);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
@@ -1668,21 +1572,15 @@ int launch_median(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_i
         case 3: return launch_median_net<3>(X, d, ld, row_index, out, gate, gate_n, s);
         case 5: return launch_median_net<5>(X, d, ld, row_index, out, gate, gate_n, s);
         case 7: return launch_median_net<7>(X, d, ld, row_index, out, gate, gate_n, s);
-        case 9: return launch_median_net<9>(X, d, ld, row_index, out, gate, gate_n, s);
-        case 15: return launch_median_net<15>(X, d, ld, row_index, out, gate, gate_n, s);
-        case 21: return launch_median_net<21>(X, d, ld, row_index, out, gate, gate_n, s);
-        case 25: return launch_median_net<25>(X, d, ld, row_index, out, gate, gate_n, s);
-        case 35: return launch_median_net<35>(X, d, ld, row_index, out, gate, gate_n, s);
-        case 49: return launch_median_net<49>(X, d, ld, row_index, out, gate, gate_n, s);
         default: break;
     }
-    if (d < kVec && f <= BYZ_MAX_F) {  // too short for the vector kernels: cost is irrelevant
-        median_generic_kernel<<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, out, gate,
-                                                               gate_n);
-        BYZ_HIP(hipGetLastError());
-        return BYZ_OK;
-    }
-    // any other odd f: the next generated size with spare wires
+    // the paper's file counts exactly, any other odd f on the next generated size with spare wires
+    if (f == 9) return launch_median_large<9, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f == 15) return launch_median_large<15, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f == 21) return launch_median_large<21, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f == 25) return launch_median_large<25, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f == 35) return launch_median_large<35, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
+    if (f == 49) return launch_median_large<49, false>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 15) return launch_median_large<15, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 21) return launch_median_large<21, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
     if (f <= 25) return launch_median_large<25, true>(X, d, ld, row_index, f, out, gate, gate_n, s);
@@ -1719,7 +1617,17 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     BYZ_HIP(hipGetLastError());
     int rc = byz_internal_profile_mark(0, s);
     if (rc != BYZ_OK) return rc;
-    if (trim_b < 0) {
+    constexpr bool kShortToo = vec_for_pass(F, R, false) > 1;  // or the only width is one word already
+    if (kShortToo && d <= short_row(F, R)) {
+        if constexpr (kShortToo) {
+            if (trim_b < 0)
+                fused_kernel<F, R, false, 1><<<blocks_for(d), kBlock, 0, s>>>(
+                    X, d, ld, ws->perm_off, &ws->slots_per_file, ws, 0, out);
+            else
+                fused_kernel<F, R, true, 1><<<blocks_for(d), kBlock, 0, s>>>(
+                    X, d, ld, ws->perm_off, &ws->slots_per_file, ws, trim_b, out);
+        }
+    } else if (trim_b < 0) {
         if constexpr (WITH_MEDIAN) {
             constexpr int V = vec_for_pass(F, R, false);
             fused_kernel<F, R, false, V><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
@@ -1739,9 +1647,17 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
 template <int F, bool PAD>
 int launch_trimmed_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
                        int b, uint32_t *O, const uint32_t *gate, int gate_n, hipStream_t s) {
-    constexpr int V = vec_for_trimmed(F);
-    trimmed_mean_kernel<F, V, PAD><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
-        X, d, ld, row_index, f, b, O, gate, gate_n);
+    if constexpr (gated_vec(F) > 1 && !PAD) {
+        if (gate != nullptr && d > kManyBlocks) {
+            constexpr int V = gated_vec(F);
+            trimmed_mean_kernel<F, V, PAD><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
+                X, d, ld, row_index, f, b, O, gate, gate_n);
+            BYZ_HIP(hipGetLastError());
+            return BYZ_OK;
+        }
+    }
+    trimmed_mean_kernel<F, 1, PAD><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, b, O, gate,
+                                                                    gate_n);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
@@ -1752,12 +1668,6 @@ int launch_trimmed_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *
 int launch_trimmed_mean(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
                         int b, uint32_t *O, const uint32_t *gate, int gate_n, hipStream_t s) {
     if (d == 0) return BYZ_OK;
-    if (d < kVec && f <= BYZ_MAX_F) {  // too short for the vector kernels: cost is irrelevant
-        trimmed_mean_generic_kernel<<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, b, O,
-                                                                     gate, gate_n);
-        BYZ_HIP(hipGetLastError());
-        return BYZ_OK;
-    }
     // the generated full-sort network of size f, else the next size with spare wires
     switch (f) {
         case 9: return launch_trimmed_net<9, false>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
@@ -1768,16 +1678,14 @@ int launch_trimmed_mean(const uint32_t *X, int64_t d, int64_t ld, const int32_t 
         case 49: return launch_trimmed_net<49, false>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
         default: break;
     }
-    if (d >= kVec) {
-        if (f <= 9) return launch_trimmed_net<9, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-        if (f <= 15) return launch_trimmed_net<15, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-        if (f <= 21) return launch_trimmed_net<21, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-        if (f <= 25) return launch_trimmed_net<25, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-        if (f <= 31) return launch_trimmed_net<31, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-        if (f <= 35) return launch_trimmed_net<35, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-        if (f <= 41) return launch_trimmed_net<41, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-        if (f <= 49) return launch_trimmed_net<49, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
-    }
+    if (f <= 9) return launch_trimmed_net<9, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 15) return launch_trimmed_net<15, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 21) return launch_trimmed_net<21, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 25) return launch_trimmed_net<25, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 31) return launch_trimmed_net<31, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 35) return launch_trimmed_net<35, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 41) return launch_trimmed_net<41, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
+    if (f <= 49) return launch_trimmed_net<49, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     if (f <= 57) return launch_trimmed_net<57, true>(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     if (f <= 63) return byz_internal_launch_trimmed_mean_63(X, d, ld, row_index, f, b, O, gate, gate_n, s);
     if (f <= 65) return byz_internal_launch_trimmed_mean_65(X, d, ld, row_index, f, b, O, gate, gate_n, s);
@@ -1801,12 +1709,10 @@ int launch_trimmed_mean(const uint32_t *X, int64_t d, int64_t ld, const int32_t 
 template <int F>
 int launch_bulyan_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *selected_rows,
                       int theta, int beta, uint32_t *O, hipStream_t s) {
-    constexpr int V = vec_for_sort(F);
     constexpr int BLOCK = F > 49 ? 64 : kBlock;
     constexpr size_t lds = (size_t)F * BLOCK * 4;
     static_assert(lds <= 64 * 1024, "more than a kernel may use without asking");
-    const int64_t n_thr = (d + V - 1) / V;
-    bulyan_mean_kernel<F, V, BLOCK><<<(unsigned)((n_thr + BLOCK - 1) / BLOCK), BLOCK, lds, s>>>(
+    bulyan_mean_kernel<F, BLOCK><<<(unsigned)((d + BLOCK - 1) / BLOCK), BLOCK, lds, s>>>(
         X, d, ld, selected_rows, theta, beta, O);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
@@ -1851,21 +1757,32 @@ int byz_internal_launch_median(const void *X, long long d, long long ld, const i
 }
 #endif
 
-// second phase of Bulyan on the 81- and 121-wire networks, a build part each
+// second phase of Bulyan on the larger networks: 49 < theta <= 81 and 81 < theta <= 128
 #if BYZ_IN_PART(12)
 int byz_internal_launch_bulyan_mean_81(const void *X, long long d, long long ld,
                                        const int *selected_rows, int theta, int beta, void *out,
                                        void *stream) {
-    return launch_bulyan_net<81>(static_cast<const uint32_t *>(X), d, ld, selected_rows, theta, beta,
-                                 static_cast<uint32_t *>(out), (hipStream_t)stream);
+    const uint32_t *x = static_cast<const uint32_t *>(X);
+    uint32_t *o = static_cast<uint32_t *>(out);
+    hipStream_t s = (hipStream_t)stream;
+    if (theta <= 57) return launch_bulyan_net<57>(x, d, ld, selected_rows, theta, beta, o, s);
+    if (theta <= 63) return launch_bulyan_net<63>(x, d, ld, selected_rows, theta, beta, o, s);
+    if (theta <= 65) return launch_bulyan_net<65>(x, d, ld, selected_rows, theta, beta, o, s);
+    if (theta <= 73) return launch_bulyan_net<73>(x, d, ld, selected_rows, theta, beta, o, s);
+    return launch_bulyan_net<81>(x, d, ld, selected_rows, theta, beta, o, s);
 }
 #endif
 #if BYZ_IN_PART(13)
-int byz_internal_launch_bulyan_mean_121(const void *X, long long d, long long ld,
+int byz_internal_launch_bulyan_mean_137(const void *X, long long d, long long ld,
                                         const int *selected_rows, int theta, int beta, void *out,
                                         void *stream) {
-    return launch_bulyan_net<121>(static_cast<const uint32_t *>(X), d, ld, selected_rows, theta, beta,
-                                  static_cast<uint32_t *>(out), (hipStream_t)stream);
+    const uint32_t *x = static_cast<const uint32_t *>(X);
+    uint32_t *o = static_cast<uint32_t *>(out);
+    hipStream_t s = (hipStream_t)stream;
+    if (theta <= 97) return launch_bulyan_net<97>(x, d, ld, selected_rows, theta, beta, o, s);
+    if (theta <= 109) return launch_bulyan_net<109>(x, d, ld, selected_rows, theta, beta, o, s);
+    if (theta <= 121) return launch_bulyan_net<121>(x, d, ld, selected_rows, theta, beta, o, s);
+    return launch_bulyan_net<137>(x, d, ld, selected_rows, theta, beta, o, s);
 }
 #endif
 
@@ -2116,27 +2033,18 @@ int byz_internal_launch_bulyan_mean(const float *rows_base, long long d, long lo
     hipStream_t s = (hipStream_t)stream;
     const uint32_t *X = reinterpret_cast<const uint32_t *>(rows_base);
     uint32_t *O = reinterpret_cast<uint32_t *>(out);
-    if (d >= kVec) {
-        // the smallest generated network that holds the theta chosen rows
-        if (theta <= 9) return launch_bulyan_net<9>(X, d, ld, selected_rows_dev, theta, beta, O, s);
-        if (theta <= 15) return launch_bulyan_net<15>(X, d, ld, selected_rows_dev, theta, beta, O, s);
-        if (theta <= 21) return launch_bulyan_net<21>(X, d, ld, selected_rows_dev, theta, beta, O, s);
-        if (theta <= 25) return launch_bulyan_net<25>(X, d, ld, selected_rows_dev, theta, beta, O, s);
-        if (theta <= 35) return launch_bulyan_net<35>(X, d, ld, selected_rows_dev, theta, beta, O, s);
-        if (theta <= 49) return launch_bulyan_net<49>(X, d, ld, selected_rows_dev, theta, beta, O, s);
-        if (theta <= 81)
-            return byz_internal_launch_bulyan_mean_81(X, d, ld, selected_rows_dev, theta, beta, O, s);
-        if (theta <= 121)
-            return byz_internal_launch_bulyan_mean_121(X, d, ld, selected_rows_dev, theta, beta, O, s);
-    }
-    const size_t lds = (size_t)theta * kBlock * 4;
-    if (lds > 64 * 1024)
-        BYZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&bulyan_mean_generic_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    bulyan_mean_generic_kernel<<<blocks_for(d), kBlock, lds, s>>>(
-        X, d, ld, selected_rows_dev, theta, beta, O);
-    BYZ_HIP(hipGetLastError());
-    return BYZ_OK;
+    // the smallest generated network that holds the theta chosen rows
+    if (theta <= 9) return launch_bulyan_net<9>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 15) return launch_bulyan_net<15>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 21) return launch_bulyan_net<21>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 25) return launch_bulyan_net<25>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 31) return launch_bulyan_net<31>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 35) return launch_bulyan_net<35>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 41) return launch_bulyan_net<41>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 49) return launch_bulyan_net<49>(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    if (theta <= 81)
+        return byz_internal_launch_bulyan_mean_81(X, d, ld, selected_rows_dev, theta, beta, O, s);
+    return byz_internal_launch_bulyan_mean_137(X, d, ld, selected_rows_dev, theta, beta, O, s);
 }
 
 extern "C" int byz_last_hip_error(void) { return g_last_hip_error; }
