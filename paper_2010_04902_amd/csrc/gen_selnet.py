@@ -150,7 +150,7 @@ def best_split(n):
             last = n - a * (k - 1)
             if last >= 1:
                 candidates.add(tuple(sorted((a,) * (k - 1) + (last,), reverse=True)))
-        for sizes in sorted(candidates):
+        for sizes in sorted(candidates, reverse=True):  # of equals, the smallest last block
             cost = sum(best_split(m)[0] for m in sizes) + merge_cost(sizes)
             if best is None or cost < best[0]:
                 best = (cost, sizes)
