@@ -6,10 +6,11 @@
 // other vectors; the m vectors of lowest score are averaged.
 //
 // The pairwise squared distances come from the Gram matrix G = W W^T of the f x d matrix of
-// winners: the one dense contraction of the whole path, done with 16x16 MFMA tiles, only those on
-// and above the diagonal of the symmetric matrix (f = 25 costs 3 tiles of 16x16 instead of one
-// padded 32x32).  The waves walk the coordinates grid-stride.  Per-block partial tiles are added
-// in fp64 in block order, so the result does not depend on scheduling.
+// winners: the one dense contraction of the whole path, done with fp32 MFMA tiles
+// (v_mfma_f32_16x16x4f32), only those on and above the diagonal of the symmetric matrix (f = 25
+// costs 3 tiles of 16x16 instead of one padded 32x32).  The waves walk the coordinates
+// grid-stride.  Per-block partial tiles are added in fp64 in block order, so the result does not
+// depend on scheduling.
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
@@ -36,12 +37,8 @@ constexpr int kMaxKrum = BYZ_MAX_F_KRUM;  // most vectors Multi-Krum takes (Buly
 constexpr int kMaxNT = kMaxKrum / 16;  // row tiles of the largest matrix
 constexpr int kMaxPairs = kMaxNT * (kMaxNT + 1) / 2;  // tiles on and above the diagonal
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // Row tiles of 16 the Gram matrix of f vectors is computed with; the tiles on and above the
 // diagonal are stored.
@@ -55,24 +52,12 @@ __host__ __device__ constexpr int tile_pair(int nt, int ti, int tj) {
 // The 16x16 MFMA result: accumulator register v of lane l holds row 4*(l/16) + v, column l%16
 // (gram_at below inverts this).
 
-// A float as the sum of three bf16 values, exactly: h is x rounded to 8 significant bits, m the
-// rest rounded again, l what is left (8 bits at most).  Two floats at a time.
-__device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
-}
-__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
-    h = pack_bf16(x0, x1);
-    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xFFFF0000u);
-    m = pack_bf16(r0, r1);
-    l = pack_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xFFFF0000u));
-}
-
 // Waves per block, and steps of 32 coordinates a wave has in flight: enough waves to keep about
 // 100 KB per CU in flight as far as registers allow (f = 16: 16 waves x 2 steps 139 us a call, 4 x 8
 // 145; f = 33: 4 x 1 272 us, 8 x 1 280, 4 x 2 274)
 constexpr int gram_waves(int nt) { return nt <= 1 ? 16 : (nt <= 2 ? 8 : 4); }
 constexpr int gram_steps(int nt) { return nt <= 1 ? 2 : 1; }
-constexpr int kStep = 32;  // coordinates a matrix instruction contracts
+constexpr int kStep = 32;  // coordinates a wave multiplies between two visits to its stage
 
 // Compile-time fence: what the wave's lanes have written to LDS is read by other lanes of the same
 // wave (LDS serves a wave's accesses in order, so the hardware needs no wait).
@@ -82,34 +67,19 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// fn(ti, tj, number of the tile) for the tiles on and above the diagonal
-template <int NT, typename FN>
-__device__ __forceinline__ void for_tiles(FN fn) {
-#pragma unroll
-    for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-        for (int tj = ti; tj < NT; ++tj) fn(ti, tj, tile_pair(NT, ti, tj));
-}
-
 // Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16.
-// A wave takes whole stretches of 32*SF coordinates of every row, so every word is loaded and
-// split once and no barrier stands between the loads and the matrix instructions.  Consecutive
-// lanes load consecutive words of a row (non-temporal: 2-5 % faster here); a pass through the
-// wave's own piece of LDS gives lane l the 8 coordinates 8*(l/16).. of row l%16 that an operand
-// takes (16-byte pieces, piece p of row r in place p ^ (r%8): neither side has bank conflicts).
-// SPLIT: the products are taken on the bf16 matrix units; x = h + m + l exactly, and
-//     x y = hh + (hm + mh) + (hl + mm + lh) + terms below 2^-26 |x y|,
-// six instructions of 32 coordinates in place of eight fp32 ones of 4: 0.4 of their time.  The unit
-// drops low bits of products that are small against the sum they are added to, so every step's
-// hh and mm start from zero and the steps are added in fp32 by the vector ALU.  The sums of h with
-// m and l are small themselves and stay on the unit; which row gives the h matters to their
-// rounding, so both kinds have their own and are added at the end: G(i, j) and G(j, i) are the
-// same bits, and equal rows tie exactly.  No further from the exact sums than the fp32 instructions
-// (f = 25, d = 11.2 M: 4e-9 against 2e-7 of the distances' norm; 25 x 100003: 2e-9 either way).
-// f = 49, d = 11.2 M: 0.37 ms (fp32 instructions on a tile in LDS shared by the block: 0.50; reading
-// the rows once at 6.9 TB/s: 0.32); multi-krum of 128 x 3 M 0.55 ms (0.83), of 80 x 4 M 0.35 (0.57).  Vector ALU 0.6 and
-// matrix units 0.4 busy at f = 49; up to f = 32 HBM-bound as before (0.18 ms at f = 25).
-template <int NT, int SF, bool SPLIT>
+// A wave takes whole stretches of 32*SF coordinates of every row, so every word is loaded once
+// and no barrier stands between the loads and the matrix instructions.  Consecutive lanes load
+// consecutive words of a row (non-temporal: 2-5 % faster here); a pass through the wave's own
+// piece of LDS gives lane l four coordinates of row l%16 at a time, the k of its quarter of the
+// wave for four instructions (16-byte pieces, piece p of row r in place p ^ (r%8): neither side
+// has bank conflicts).  Products and sums are the fp32 instruction's, one rounding each; G(i, j)
+// and G(j, i) are the same bits, and equal rows tie exactly.
+// Calls of Multi-Krum with rows on cache lines, us, and with a tile in LDS shared by the block, two
+// barriers a chunk and row tiles rounded up to 6 or 8 above 64 rows: 49 x 11.2 M 629 (698), 80 x 3 M
+// 288 (441), 128 x 3 M 606 (837); to f = 32, HBM-bound, the same (32 x 11.2 M 353 and 351).  Matrix
+// instructions bound it from f = 33 up: ten tiles at f = 49 are 365 us at the fp32 rate.
+template <int NT, int SF>
 __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int64_t d, int64_t ld,
                                                 const int32_t *__restrict__ row_index, int f,
                                                 float *stage, f32x4 (&acc)[NT * (NT + 1) / 2]) {
@@ -150,14 +120,6 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
     };
 #pragma unroll
     for (int p = 0; p < NP; ++p) acc[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    // products of one row's h with the other's m and l, and the other way round
-    // kept over all steps where registers allow (NT = 4 would lose a wave per SIMD: 788 instead of
-    // 759 us a call of Bulyan on 49 x 11.2 M), added every step otherwise
-    constexpr bool kKeep = SPLIT && NT <= 6 && NT != 4;
-    constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 cross_up[kKeep ? NP : 1], cross_down[kKeep ? NP : 1];
-#pragma unroll
-    for (int p = 0; p < (kKeep ? NP : 1); ++p) cross_up[p] = cross_down[p] = zero;
     if (span < n_spans) fetch(span);
     for (; span < n_spans; span += stride) {
         wave_fence();
@@ -166,93 +128,38 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
             if (used(n)) slots[64 * n + lane] = raw[n];
         wave_fence();
         if (span + stride < n_spans) fetch(span + stride);
+        const int row = lane & 15;
 #pragma unroll
-        for (int s = 0; s < SF; ++s) {
-            const int row = lane & 15, first = 8 * s + 2 * (lane >> 4);
-            if constexpr (SPLIT) {
-                u32x4 part[NT][3];  // h, m, l of 8 coordinates each
+        for (int s = 0; s < SF; ++s)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int piece = 8 * s + 2 * (lane >> 4) + u;
+                f32x4 x[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
+                    x[t] = slots[(16 * t + row) * kPieces + (piece ^ (row & 7))];
+                // lane l holds A[row = l%16][k = l/16], which is also B[k][col = l%16] of the
+                // transposed operand
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const f32x4 x = slots[(16 * t + row) * kPieces + ((first + u) ^ (row & 7))];
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            uint32_t h, m, l;
-                            split_pair(x[2 * e], x[2 * e + 1], h, m, l);
-                            part[t][0][2 * u + e] = h;
-                            part[t][1][2 * u + e] = m;
-                            part[t][2][2 * u + e] = l;
+                    for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                        for (int tj = ti; tj < NT; ++tj) {
+                            f32x4 &a = acc[tile_pair(NT, ti, tj)];
+                            a = __builtin_amdgcn_mfma_f32_16x16x4f32(x[ti][e], x[tj][e], a, 0, 0, 0);
                         }
-                    }
-                // a few tiles at a time: consecutive instructions go to different sums
-                constexpr int kGroups = (NP + 5) / 6, kGroup = (NP + kGroups - 1) / kGroups;
-                auto mul = [&](int ti, int ka, int tj, int kb, f32x4 c) {
-                    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, part[ti][ka]),
-                                                                   __builtin_bit_cast(bf16x8, part[tj][kb]),
-                                                                   c, 0, 0, 0);
-                };
-#pragma unroll
-                for (int p0 = 0; p0 < NP; p0 += kGroup) {
-                    f32x4 sum[kGroup], up[kGroup], down[kGroup];
-                    for_tiles<NT>([&](int ti, int tj, int p) {
-                        if (p < p0 || p >= p0 + kGroup) return;
-                        up[p - p0] = mul(ti, 0, tj, 2, kKeep ? cross_up[p] : zero);
-                        down[p - p0] = mul(ti, 2, tj, 0, kKeep ? cross_down[p] : zero);
-                    });
-                    for_tiles<NT>([&](int ti, int tj, int p) {
-                        if (p < p0 || p >= p0 + kGroup) return;
-                        up[p - p0] = mul(ti, 0, tj, 1, up[p - p0]);
-                        down[p - p0] = mul(ti, 1, tj, 0, down[p - p0]);
-                        if (kKeep) cross_up[p] = up[p - p0];
-                        if (kKeep) cross_down[p] = down[p - p0];
-                    });
-                    for_tiles<NT>([&](int ti, int tj, int p) {
-                        if (p < p0 || p >= p0 + kGroup) return;
-                        sum[p - p0] = mul(ti, 1, tj, 1, kKeep ? zero : up[p - p0] + down[p - p0]);
-                    });
-                    for_tiles<NT>([&](int ti, int tj, int p) {
-                        if (p < p0 || p >= p0 + kGroup) return;
-                        sum[p - p0] = mul(ti, 0, tj, 0, sum[p - p0]);
-                    });
-                    for_tiles<NT>([&](int ti, int tj, int p) {
-                        if (p < p0 || p >= p0 + kGroup) return;
-                        acc[p] += sum[p - p0];
-                    });
-                }
-            } else {
-                // (rare) word e of the lane's pieces: coordinates that all rows share, four at a time
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    f32x4 x[NT];
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) x[t] = slots[(16 * t + row) * kPieces + ((first + u) ^ (row & 7))];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-                            for (int tj = ti; tj < NT; ++tj) {
-                                f32x4 &a = acc[tile_pair(NT, ti, tj)];
-                                a = __builtin_amdgcn_mfma_f32_16x16x4f32(x[ti][e], x[tj][e], a, 0, 0, 0);
-                            }
-                }
             }
-        }
-    }
-    if constexpr (kKeep) {
-#pragma unroll
-        for (int p = 0; p < NP; ++p) acc[p] += cross_up[p] + cross_down[p];
     }
 }
 
 // Partial Gram tiles of the rows row_index[0..f-1] over this block's coordinates.  partial:
-// [gridDim.x][pairs][256] floats, position v*64 + lane, pairs = NT(NT+1)/2.  A block that ends with
-// an infinity or NaN in a tile -- inputs that are not finite, or so large that h or a product
-// overflows -- starts over with the fp32 instructions, which decide what such inputs give.
+// [gridDim.x][pairs][256] floats, position v*64 + lane, pairs = NT(NT+1)/2.
 template <int NT, int SF>
 __global__ __launch_bounds__(64 * gram_waves(NT))
-__attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2 : 1)))
+// (keeps the accumulators out of the accumulation registers: f = 112 on 11.2 M 1808 -> 1757 us;
+// eight row tiles would spill)
+__attribute__((amdgpu_waves_per_eu(NT <= 7 ? 2 : 1)))
 void gram_partial_kernel(
     const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
     float *__restrict__ partial) {
@@ -263,16 +170,8 @@ void gram_partial_kernel(
     __shared__ __align__(16) float lds[kRed > kWaves * kStage ? kRed : kWaves * kStage];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     f32x4 acc[NP];
-    gram_accumulate<NT, SF, true>(X, d, ld, row_index, f, lds + wave * kStage, acc);
-    bool finite = true;
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) finite = finite && fabsf(acc[p][v]) <= __FLT_MAX__;
-    if (__syncthreads_or(finite ? 0 : 1) != 0) {
-        gram_accumulate<NT, SF, false>(X, d, ld, row_index, f, lds + wave * kStage, acc);
-        __syncthreads();  // the stages are read before the tiles below replace them
-    }
+    gram_accumulate<NT, SF>(X, d, ld, row_index, f, lds + wave * kStage, acc);
+    __syncthreads();  // the stages are read before the tiles below replace them
     // the waves' tiles are added in wave order either way
     float *dst = partial + (int64_t)blockIdx.x * NP * kTile;
     if constexpr (kAllWaves) {

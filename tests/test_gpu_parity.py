@@ -655,10 +655,10 @@ def test_more_than_169_rows_random_sizes():
 
 @pytest.mark.parametrize("f", [3, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 128])
 def test_gram_distances_at_tile_edges_and_for_inputs_that_are_not_finite(f):
-    # every number of row tiles, one row more or less; d around the 32 coordinates of a matrix
-    # instruction, the span of a wave and of a block, and above the length from which a wave takes
-    # several steps at a time.  Distances against fp64: products are exact to 2^-26 and at most
-    # 8 + 32 fp32 additions on top of each other at these d, so |err| <= 64 * 2^-24 * (G_ii + G_jj).
+    # every number of row tiles, one row more or less; d around the 32 coordinates a wave multiplies
+    # at a time, the span of a wave and of a block, all within one step of a wave.  Distances
+    # against fp64: at most 32 rounded sums of a wave and the waves of a block on top of each other,
+    # far from adding up (three times the largest error seen is 40): |err| <= 64 * 2^-24 * (G_ii + G_jj).
     rng = np.random.default_rng(f)
     idx = torch.tensor(rng.permutation(f).astype(np.int32), device=DEV)
     order = idx.cpu().numpy()
@@ -673,8 +673,8 @@ def test_gram_distances_at_tile_edges_and_for_inputs_that_are_not_finite(f):
         want = np.maximum(n[:, None] + n[None, :] - 2 * G, 0)
         np.fill_diagonal(want, 0)
         assert (np.abs(dist.cpu().numpy() - want) <= 64 * 2.0 ** -24 * (n[:, None] + n[None, :])).all(), (f, d)
-    # infinities, NaNs and a value whose rounding to 8 bits overflows: same kinds as fp64 products
-    # of fp32 range (the huge value's square is infinite in fp32, its products with 0 are 0)
+    # infinities, NaNs and a value whose square overflows: same kinds as fp64 products of fp32
+    # range (the huge value's square is infinite in fp32, its products with 0 are 0)
     for what in (np.inf, -np.inf, np.nan, np.float32(3.4e38)):
         Y = Xh.copy()
         Y[:, 777] = 0.0
@@ -697,6 +697,56 @@ def test_gram_distances_at_tile_edges_and_for_inputs_that_are_not_finite(f):
         scale = (n[:, None] + n[None, :])
         ok = np.isfinite(scale)  # the diagonal of the row itself is 0 whatever it holds
         assert (np.abs(got - want)[ok] <= 64 * 2.0 ** -24 * scale[ok]).all(), (f, what)
+
+
+def _krum_distances(Xh, d, order):
+    X = torch.tensor(Xh, device=DEV)
+    _, _, _, dist = B.byz_multi_krum(X, d, torch.tensor(order, device=DEV), 0, 1)
+    torch.cuda.synchronize()
+    return dist.cpu().numpy()
+
+
+@pytest.mark.parametrize("f", [3, 16, 17, 33, 49, 65, 81, 97, 113, 128])
+def test_gram_products_are_rounded_once(f):
+    # one coordinate, one row of zeros: the distance from it to row i is the fp32 rounding of the
+    # square of row i's value, to the bit, whatever the size of the square (down to subnormal ones)
+    rng = np.random.default_rng(f)
+    for scale in (1.0, 1e15, 1e-18, 1e-20):
+        Xh = ((1 + rng.random((f, 1))) * scale).astype(np.float32)
+        Xh[f // 2] = 0.0
+        got = _krum_distances(Xh, 1, np.arange(f, dtype=np.int32))[f // 2]
+        assert np.array_equal(got, (Xh[:, 0] * Xh[:, 0]).astype(np.float64)), (f, scale)
+
+
+@pytest.mark.parametrize("f,d", [(9, 300007), (16, 1048601), (3, 1600013), (25, 300007), (33, 140011), (49, 140011),
+                                 (65, 140011), (81, 140011), (100, 140011), (128, 140011)])
+def test_gram_of_long_rows(f, d):
+    # every number of row tiles with two or three steps of a wave one after the other, f <= 16 also
+    # with two stretches of 32 coordinates a step, and a ragged end; rows far apart in size, one
+    # around 1e-18, row pitch that is no multiple of a cache line and rows on cache lines.  Each sum of a wave is
+    # rounded at most 32 times a stretch, at most eight of them, then come the waves of a block:
+    # |err| <= 2 (32 * 8 + 16) 2^-24 (G_ii + G_jj); a stretch left out is 32 / d of that sum and more.
+    rng = np.random.default_rng(f * 1000003 + d)
+    order = rng.permutation(f).astype(np.int32)
+    for ld in (d + 2, (d + 31) // 32 * 32):
+        Xh = rng.standard_normal((f, ld), dtype=np.float32)
+        Xh *= rng.uniform(0.01, 3, (f, 1)).astype(np.float32)
+        Xh[order[0]] *= np.float32(1e-18)
+        got = _krum_distances(Xh, d, order)
+        V = torch.tensor(Xh, device=DEV)[torch.tensor(order, device=DEV).long(), :d].double()
+        G = (V @ V.T.contiguous()).cpu().numpy()
+        n = np.diag(G)
+        want = np.maximum(n[:, None] + n[None, :] - 2 * G, 0)
+        np.fill_diagonal(want, 0)
+        assert (np.abs(got - want) <= 2 * (32 * 8 + 16) * 2.0 ** -24 * (n[:, None] + n[None, :])).all(), (f, d, ld)
+    # an infinity (times the others' zeros a NaN) and a NaN in the last step of a wave
+    for what in (np.inf, np.nan):
+        Xh[:, d - 5] = 0.0
+        Xh[order[1], d - 5] = what
+        got = _krum_distances(Xh, d, order)
+        assert np.isnan(got[1, [0] + list(range(2, f))]).all(), (f, what)
+        rest = np.ix_([0] + list(range(2, f)), [0] + list(range(2, f)))
+        assert np.isfinite(got[rest]).all(), (f, what)
 
 
 NETWORKS = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)
