@@ -52,12 +52,22 @@ __host__ __device__ constexpr int tile_pair(int nt, int ti, int tj) {
 // The 16x16 MFMA result: accumulator register v of lane l holds row 4*(l/16) + v, column l%16
 // (gram_at below inverts this).
 
-// Waves per block, and steps of 32 coordinates a wave has in flight: enough waves to keep about
-// 100 KB per CU in flight as far as registers allow (f = 16: 16 waves x 2 steps 139 us a call, 4 x 8
-// 145; f = 33: 4 x 1 272 us, 8 x 1 280, 4 x 2 274)
-constexpr int gram_waves(int nt) { return nt <= 1 ? 16 : (nt <= 2 ? 8 : 4); }
-constexpr int gram_steps(int nt) { return nt <= 1 ? 2 : 1; }
+// Waves per block, for sf steps of 32 coordinates a wave has in flight: enough waves to keep about
+// 100 KB per CU in flight as far as registers allow (f = 16 on 4 M coordinates: 16 waves x 2 steps
+// 139 us a call, 4 x 8 145; f = 25 on 11.2 M: 4 x 2 279, 8 x 1 282; f = 49: 4 x 1 629, 8 x 1 664,
+// 4 x 2 644)
+constexpr int gram_waves(int nt, int sf) { return nt <= 1 ? 16 : (nt <= 2 && sf == 1 ? 8 : 4); }
 constexpr int kStep = 32;  // coordinates a wave multiplies between two visits to its stage
+
+// Rows that do not start on cache lines (LINES false): the pieces of two neighbouring waves share a
+// line.  Ordinary loads leave it in the L2, and groups of eight blocks' neighbours go to one of the
+// eight L2s (blocks go to the XCDs round-robin), 4 KB of a row together.  us a call, non-temporal
+// loads in plain order / this: 25 x 3 M 108 / 92, 48 x 3 M 195 / 166, 64 x 3 M 277 / 231; on cache
+// lines ordinary loads are slower (48 x 3 M 151 / 160).
+__device__ __forceinline__ unsigned neighbours_together(unsigned b, unsigned n_blocks, unsigned group) {
+    const unsigned r = b % (8 * group);
+    return b - r + 8 * group <= n_blocks ? b - r + (r % 8) * group + r / 8 : b;
+}
 
 // Compile-time fence: what the wave's lanes have written to LDS is read by other lanes of the same
 // wave (LDS serves a wave's accesses in order, so the hardware needs no wait).
@@ -70,7 +80,7 @@ __device__ __forceinline__ void wave_fence() {
 // Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16.
 // A wave takes whole stretches of 32*SF coordinates of every row, so every word is loaded once
 // and no barrier stands between the loads and the matrix instructions.  Consecutive lanes load
-// consecutive words of a row (non-temporal: 2-5 % faster here); a pass through the wave's own
+// consecutive words of a row; a pass through the wave's own
 // piece of LDS gives lane l four coordinates of row l%16 at a time, the k of its quarter of the
 // wave for four instructions (16-byte pieces, piece p of row r in place p ^ (r%8): neither side
 // has bank conflicts).  Products and sums are the fp32 instruction's, one rounding each; G(i, j)
@@ -79,7 +89,7 @@ __device__ __forceinline__ void wave_fence() {
 // barriers a chunk and row tiles rounded up to 6 or 8 above 64 rows: 49 x 11.2 M 629 (698), 80 x 3 M
 // 288 (441), 128 x 3 M 606 (837); to f = 32, HBM-bound, the same (32 x 11.2 M 353 and 351).  Matrix
 // instructions bound it from f = 33 up: ten tiles at f = 49 are 365 us at the fp32 rate.
-template <int NT, int SF>
+template <int NT, int SF, bool LINES>
 __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int64_t d, int64_t ld,
                                                 const int32_t *__restrict__ row_index, int f,
                                                 float *stage, f32x4 (&acc)[NT * (NT + 1) / 2]) {
@@ -87,8 +97,11 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
     constexpr int kPieces = kSpan / 4, kRows = 64 / kPieces, kLoads = 16 * NT / kRows;
     const int lane = threadIdx.x & 63;
     const int64_t n_spans = (d + kSpan - 1) / kSpan;
-    const int64_t stride = (int64_t)gridDim.x * gram_waves(NT);
-    int64_t span = (int64_t)blockIdx.x * gram_waves(NT) + (threadIdx.x >> 6);
+    constexpr int kWaves = gram_waves(NT, SF);
+    const int64_t stride = (int64_t)gridDim.x * kWaves;
+    constexpr unsigned kGroup = NT <= 1 ? 1 : (NT == 2 ? 4 : 8);
+    const unsigned block = LINES ? blockIdx.x : neighbours_together(blockIdx.x, gridDim.x, kGroup);
+    int64_t span = (int64_t)block * kWaves + (threadIdx.x >> 6);
     // load n: rows n*kRows .. + kRows - 1, one after the other; rows past f in a load that has others
     // repeat row f-1 (nothing reads their results), loads without a row are left out
     auto row_of = [&](int n) { return n * kRows + lane / kPieces; };
@@ -108,8 +121,10 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
         if (c0 + kSpan <= d) {
 #pragma unroll
             for (int n = 0; n < kLoads; ++n)
-                if (used(n)) raw[n] = __builtin_nontemporal_load(
-                                 reinterpret_cast<const f32x4u *>(rowp[n] + c0));
+                if (used(n)) {
+                    const f32x4u *p = reinterpret_cast<const f32x4u *>(rowp[n] + c0);
+                    raw[n] = LINES ? __builtin_nontemporal_load(p) : *p;
+                }
         } else {  // the ragged end: missing coordinates count as zero
 #pragma unroll
             for (int n = 0; n < kLoads; ++n)
@@ -155,22 +170,22 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
 
 // Partial Gram tiles of the rows row_index[0..f-1] over this block's coordinates.  partial:
 // [gridDim.x][pairs][256] floats, position v*64 + lane, pairs = NT(NT+1)/2.
-template <int NT, int SF>
-__global__ __launch_bounds__(64 * gram_waves(NT))
-// (keeps the accumulators out of the accumulation registers: f = 112 on 11.2 M 1808 -> 1757 us;
-// eight row tiles would spill)
-__attribute__((amdgpu_waves_per_eu(NT <= 7 ? 2 : 1)))
+template <int NT, int SF, bool LINES>
+__global__ __launch_bounds__(64 * gram_waves(NT, SF))
+// (2: accumulators in ordinary registers.  112 x 11.2 M 1757 us, 1808 with 1; 80 x 3 M 306 and 288, 96 x
+// 3 M the same; eight row tiles would spill)
+__attribute__((amdgpu_waves_per_eu(NT <= 4 || NT == 7 ? 2 : 1)))
 void gram_partial_kernel(
     const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
     float *__restrict__ partial) {
-    constexpr int NP = NT * (NT + 1) / 2, kWaves = gram_waves(NT);
+    constexpr int NP = NT * (NT + 1) / 2, kWaves = gram_waves(NT, SF);
     constexpr int kStage = 16 * NT * kStep * SF;  // floats of one wave's stage
     constexpr bool kAllWaves = kWaves * NP * kTile <= 16 * 1024;  // room for the waves' tiles at a time
     constexpr int kRed = (kAllWaves ? kWaves : 1) * NP * kTile;
     __shared__ __align__(16) float lds[kRed > kWaves * kStage ? kRed : kWaves * kStage];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     f32x4 acc[NP];
-    gram_accumulate<NT, SF>(X, d, ld, row_index, f, lds + wave * kStage, acc);
+    gram_accumulate<NT, SF, LINES>(X, d, ld, row_index, f, lds + wave * kStage, acc);
     __syncthreads();  // the stages are read before the tiles below replace them
     // the waves' tiles are added in wave order either way
     float *dst = partial + (int64_t)blockIdx.x * NP * kTile;
@@ -650,26 +665,39 @@ inline size_t krum_workspace_bytes(int f) {
            sizeof(float) * (size_t)kGramBlocks * (nt * (nt + 1) / 2) * kTile;
 }
 
-template <int NT, int SF>
+template <int NT, int SF, bool LINES>
 void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
                        int f, float *partial, int *grid, hipStream_t s) {
-    constexpr int64_t kSpan = kStep * SF * gram_waves(NT);  // coordinates a block takes at a time
+    constexpr int kWaves = gram_waves(NT, SF);
+    constexpr int64_t kSpan = kStep * SF * kWaves;  // coordinates a block takes at a time
     const int64_t n = (d + kSpan - 1) / kSpan;
     *grid = n < 1 ? 1 : (n < kGramBlocks ? (int)n : kGramBlocks);  // d == 0: one block writes zero tiles
-    gram_partial_kernel<NT, SF><<<*grid, 64 * gram_waves(NT), 0, s>>>(rows_base, d, ld, row_index_dev,
-                                                                      f, partial);
+    gram_partial_kernel<NT, SF, LINES><<<*grid, 64 * kWaves, 0, s>>>(rows_base, d, ld, row_index_dev, f,
+                                                                    partial);
+}
+
+template <int NT, bool LINES>
+void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
+                      int f, float *partial, int *grid, hipStream_t s) {
+    // Long rows: two steps at a time up to 32 vectors (four steps per wave or fewer: one at a time
+    // spreads them over more waves and partial sums).  Above, more registers and fewer waves cost more
+    // than longer pieces of a row give, but for rows off the cache lines that are far larger than the
+    // last-level cache (48 x 11.2 M 596 -> 584 us, 64 x 11.2 M 857 -> 804; 64 x 3 M 231 -> 232).
+    constexpr int SF = NT <= 2 || (NT <= 4 && !LINES) ? 2 : 1;
+    const int64_t one_at_a_time = NT <= 2 ? (int64_t)kGramBlocks * 4 * kStep * gram_waves(NT, 1) : (int64_t)1 << 22;
+    if (SF > 1 && d > one_at_a_time)
+        launch_gram_spans<NT, SF, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+    else
+        launch_gram_spans<NT, 1, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
 }
 
 template <int NT>
 int launch_gram_shape(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
                       int f, float *partial, int *grid, hipStream_t s) {
-    constexpr int SF = gram_steps(NT);
-    // short rows, four steps per wave or fewer: one step at a time spreads them over more waves
-    // (and partial sums)
-    if (d <= (int64_t)kGramBlocks * 4 * kStep * gram_waves(NT))
-        launch_gram_spans<NT, 1>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+    if (((uintptr_t)rows_base & 127u) == 0 && ld % 32 == 0)
+        launch_gram_rows<NT, true>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     else
-        launch_gram_spans<NT, SF>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_rows<NT, false>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }

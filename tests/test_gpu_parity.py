@@ -749,6 +749,37 @@ def test_gram_of_long_rows(f, d):
         assert np.isfinite(got[rest]).all(), (f, what)
 
 
+@pytest.mark.parametrize("f,d", [(3, 31), (16, 4001), (16, 1048601), (25, 140011), (32, 262177), (25, 262177), (33, 50021),
+                                 (48, 140011), (49, 50021), (64, 140011), (80, 50021), (96, 140011), (112, 50021),
+                                 (128, 50021), (128, 140011), (33, 4194337), (49, 4194337)])
+def test_gram_of_whole_numbers_is_exact(f, d):
+    # entries -1, 0 and 1: every product and every sum is a whole number below 2^24, so the distances
+    # are exact in whatever order they are added, and one coordinate left out or taken twice shows.
+    # Rows on cache lines and off them (ordinary loads, blocks in another order, longer stretches a
+    # step above 4 M coordinates), the table in reverse order, guard words behind the rows
+    order = np.arange(f, dtype=np.int32)[::-1].copy()
+    g = torch.Generator(device=DEV).manual_seed(f * 7 + d)
+    for ld in ((d + 31) // 32 * 32, (d + 31) // 32 * 32 + 7, (d + 31) // 32 * 32 + 16):
+        X = torch.randint(-1, 2, (f, ld), generator=g, device=DEV, dtype=torch.int8).float()
+        X[:, d:] = 3.0
+        G = torch.zeros((f, f), dtype=torch.float64, device=DEV)
+        for c in range(0, d, 1 << 19):
+            V = X[:, c:min(d, c + (1 << 19))].flip(0).double()
+            G += V @ V.T.contiguous()
+        n = G.diagonal()
+        want = n[:, None] + n[None, :] - 2 * G
+        _, _, _, dist = B.byz_multi_krum(X, d, torch.tensor(order, device=DEV), 0, 1)
+        torch.cuda.synchronize()
+        assert torch.equal(dist, want), (f, d, ld)
+        # a matrix that starts off a cache line
+        if d < 300000:
+            Y = torch.zeros(f * ld + 1, device=DEV)
+            Y[1:] = X.reshape(-1)
+            _, _, _, dist = B.byz_multi_krum(Y[1:].reshape(f, ld), d, torch.tensor(order, device=DEV), 0, 1)
+            torch.cuda.synchronize()
+            assert torch.equal(dist, want), (f, d, ld)
+
+
 NETWORKS = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)
 
 
