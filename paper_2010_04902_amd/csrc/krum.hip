@@ -55,8 +55,10 @@ __host__ __device__ constexpr int tile_pair(int nt, int ti, int tj) {
 // Waves per block, for sf steps of 32 coordinates a wave has in flight: enough waves to keep about
 // 100 KB per CU in flight as far as registers allow (f = 16 on 4 M coordinates: 16 waves x 2 steps
 // 139 us a call, 4 x 8 145; f = 25 on 11.2 M: 4 x 2 279, 8 x 1 282; f = 49: 4 x 1 629, 8 x 1 664,
-// 4 x 2 644)
-constexpr int gram_waves(int nt, int sf) { return nt <= 1 ? 16 : (nt <= 2 && sf == 1 ? 8 : 4); }
+// 4 x 2 644).  Short rows of up to 16 vectors: 8 waves (f = 16, d = 20011 16.8, 16 waves 17.7, 4 17.7).
+constexpr int gram_waves(int nt, int sf) {
+    return sf == 1 ? (nt <= 2 ? 8 : 4) : (nt <= 1 ? 16 : 4);
+}
 constexpr int kStep = 32;  // coordinates a wave multiplies between two visits to its stage
 
 // Rows that do not start on cache lines (LINES false): the pieces of two neighbouring waves share a
@@ -670,7 +672,11 @@ void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int3
                        int f, float *partial, int *grid, hipStream_t s) {
     constexpr int kWaves = gram_waves(NT, SF);
     constexpr int64_t kSpan = kStep * SF * kWaves;  // coordinates a block takes at a time
-    const int64_t n = (d + kSpan - 1) / kSpan;
+    // up to a block per CU each takes one step, then up to the full grid each takes two: a block more is
+    // a partial matrix more to write and add (128 x 50001 62.9 us, one step each 73.9; 96 x 50001 48.7
+    // and 51.3)
+    int64_t n = (d + kSpan - 1) / kSpan;
+    if (n > kGramBlocks / 2) n = n / 2 > kGramBlocks / 2 ? n / 2 : kGramBlocks / 2;
     *grid = n < 1 ? 1 : (n < kGramBlocks ? (int)n : kGramBlocks);  // d == 0: one block writes zero tiles
     gram_partial_kernel<NT, SF, LINES><<<*grid, 64 * kWaves, 0, s>>>(rows_base, d, ld, row_index_dev, f,
                                                                     partial);
@@ -684,7 +690,7 @@ void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32
     // than longer pieces of a row give, but for rows off the cache lines that are far larger than the
     // last-level cache (48 x 11.2 M 596 -> 584 us, 64 x 11.2 M 857 -> 804; 64 x 3 M 231 -> 232).
     constexpr int SF = NT <= 2 || (NT <= 4 && !LINES) ? 2 : 1;
-    const int64_t one_at_a_time = NT <= 2 ? (int64_t)kGramBlocks * 4 * kStep * gram_waves(NT, 1) : (int64_t)1 << 22;
+    const int64_t one_at_a_time = (int64_t)1 << (NT <= 1 ? 20 : (NT <= 2 ? 19 : 22));
     if (SF > 1 && d > one_at_a_time)
         launch_gram_spans<NT, SF, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     else
