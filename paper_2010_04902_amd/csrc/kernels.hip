@@ -771,6 +771,14 @@ __global__ __launch_bounds__(kBlock) void vote_pairs_tolerant_kernel(
 #define BYZ_S_MEDIAN(w)                                                                       \
     _Pragma("unroll") for (int v_ = 0; v_ < V; ++v_) o[v_] = from_key(key[v_][w]);
 
+// Order of the blocks for rows that do not start on cache lines: neighbouring blocks share a line of
+// every row, and blocks go to the eight XCDs round-robin, so each XCD gets `group` neighbours at a
+// time.
+__device__ __forceinline__ unsigned neighbours_together(unsigned b, unsigned n_blocks, unsigned group) {
+    const unsigned r = b % (8 * group);
+    return b - r + 8 * group <= n_blocks ? b - r + (r % 8) * group + r / 8 : b;
+}
+
 // Coordinate-wise median of F rows (fewer than the streamed networks start at) by a register
 // selection network, V words per thread.
 template <int F, int V>
@@ -812,14 +820,16 @@ __global__ __launch_bounds__(kBlock) void median_kernel(
 // at 6.5 TB/s and measured: f = 81 202 and 196 us, 109 271 and 266), by min/max issue above (153
 // 379 and 392, 169 419 and 472; with two-wire comparators and fewer sizes 655 and 577).
 // (V = 4: thread t owns the words from min(4t, d - 4), the last vector overlaps its neighbour; d >= 4)
+// group: see neighbours_together; 0 = plain order.
 template <int F, int V, bool PAD>
 __global__ __launch_bounds__(kBlock) void median_large_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
-    int f, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
+    int f, unsigned group, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
     if (gate != nullptr && !any_word_set(gate, gate_n)) return;
     const int pad_low_end = f + (F - f) / 2;  // wires [f, pad_low_end) smallest key, rest largest
     (void)pad_low_end;
-    const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const unsigned tile = group != 0 ? neighbours_together(blockIdx.x, gridDim.x, group) : blockIdx.x;
+    const int64_t gt = (int64_t)tile * kBlock + threadIdx.x;
     if (gt >= (d + V - 1) / V) return;
     const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
     // one word per thread: twenty files ahead (as measured best at F = 121)
@@ -1471,6 +1481,17 @@ inline unsigned blocks_for(int64_t n_vec) {
 [[maybe_unused]] constexpr int64_t kManyBlocks = 131072;
 constexpr int gated_vec(int f) { return f <= 49 ? 4 : 1; }
 
+// Rows that do not start on cache lines: with one word per thread a block of the median reads nine
+// lines for eight of every row (f = 49, 2 M coordinates: 77 us, 68 with four words; on lines 63
+// and 67).  So networks that HBM bounds alone run four words per thread there, up to 35 wires
+// from kManyBlocks coordinates on (f = 25, 0.4 / 2 M: 7.7 / 34.4 us, one word 8.5 / 38.2), up to 49 from
+// 1 M on (f = 49, 0.7 M: 27.4, one word 25.6), and otherwise up to 81 wires neighbouring blocks go
+// to one XCD, sixteen at a time (f = 65, 2 M: 99.9 -> 95.4; above 81 wires nothing is gained).
+[[maybe_unused]] inline bool rows_on_lines(const void *X, int64_t ld) {
+    return ((uintptr_t)X & 127u) == 0 && ld % 32 == 0;
+}
+[[maybe_unused]] constexpr int64_t four_words_from(int f) { return f <= 35 ? kManyBlocks : (int64_t)1 << 20; }
+
 [[maybe_unused]] constexpr int64_t kMaxCoords = (int64_t)1 << 30;  // byte offsets inside a row fit 32 bits
 
 #if BYZ_IN_PART(0)
@@ -1546,17 +1567,19 @@ int launch_median_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
 template <int F, bool PAD>
 int launch_median_large(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
                         uint32_t *out, const uint32_t *gate, int gate_n, hipStream_t s) {
-    if constexpr (gated_vec(F) > 1 && !PAD) {
-        if (gate != nullptr && d > kManyBlocks) {
+    const bool lines = rows_on_lines(X, ld);
+    if constexpr (gated_vec(F) > 1) {
+        if ((gate != nullptr && d > kManyBlocks) || (!lines && d > four_words_from(F))) {
             constexpr int V = gated_vec(F);
             median_large_kernel<F, V, PAD><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
-                X, d, ld, row_index, f, out, gate, gate_n);
+                X, d, ld, row_index, f, 0, out, gate, gate_n);
             BYZ_HIP(hipGetLastError());
             return BYZ_OK;
         }
     }
-    median_large_kernel<F, 1, PAD><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, out, gate,
-                                                                    gate_n);
+    const unsigned group = !lines && F <= 81 && d > kManyBlocks ? 16 : 0;
+    median_large_kernel<F, 1, PAD><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, group, out,
+                                                                    gate, gate_n);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }

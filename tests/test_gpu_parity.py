@@ -804,6 +804,26 @@ def test_networks_with_most_and_least_spare_wires(below, wires):
                 _trimmed_mean_check(X, idx, d, b, (f, d, b))
 
 
+@pytest.mark.parametrize("below,wires", [p for p in zip((0,) + NETWORKS, NETWORKS) if p[1] <= 97])
+def test_median_of_long_rows_on_and_off_cache_lines(below, wires):
+    # above 131072 coordinates rows that do not start on cache lines take four words per thread (from
+    # 2^20 on above 35 wires) or another order of the blocks; the last vector overlaps its neighbour
+    # and the last group of blocks is not whole.  Pitch off the lines, matrix off the lines, both on
+    rng = np.random.default_rng(wires)
+    for f, d in [(below + 1, 131077), (wires, 131074), (wires, 262147)] + ([(wires, 1048583)] if wires in (41, 49) else []):
+        f += 1 - f % 2
+        X = torch.empty(f * ((d + 31) // 32 * 32 + 33) + 1, device=DEV).normal_(generator=torch.Generator(device=DEV).manual_seed(f))
+        idx = rng.permutation(f).astype(np.int32)
+        idx_dev = torch.tensor(idx, device=DEV)
+        for start, ld in ((0, (d + 31) // 32 * 32), (0, (d + 31) // 32 * 32 + 33), (1, (d + 31) // 32 * 32)):
+            M = X[start:start + f * ld].reshape(f, ld)
+            out = torch.full((d + 8,), 7.0, device=DEV)
+            B.byz_median(M, d, idx_dev, out=out)
+            torch.cuda.synchronize()
+            want = M[:, :d].sort(dim=0).values[(f - 1) // 2]
+            assert torch.equal(out[:d], want) and bool((out[d:] == 7.0).all()), (f, d, start, ld)
+
+
 def test_mean_around_median_alone():
     # byz_mean_around_median = the second phase of Bulyan on rows of the caller's choice: every
     # network size of that kernel and the sizes between (spare wires), d below and above the
