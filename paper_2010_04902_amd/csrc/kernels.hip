@@ -1670,8 +1670,11 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
 template <int F, bool PAD>
 int launch_trimmed_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_index, int f,
                        int b, uint32_t *O, const uint32_t *gate, int gate_n, hipStream_t s) {
-    if constexpr (gated_vec(F) > 1 && !PAD) {
-        if (gate != nullptr && d > kManyBlocks) {
+    // fewer than nine rows are bound by the launch of their blocks too (f = 3, 0.4 / 2 M coordinates: 3.7 /
+    // 9.6 us, one word per thread 4.2 / 12.0; f = 7, 131073: 3.5 and 2.8)
+    constexpr bool few_rows = F == 9 && PAD;
+    if constexpr (gated_vec(F) > 1 && (few_rows || !PAD)) {
+        if (few_rows ? d > 2 * kManyBlocks : gate != nullptr && d > kManyBlocks) {
             constexpr int V = gated_vec(F);
             trimmed_mean_kernel<F, V, PAD><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
                 X, d, ld, row_index, f, b, O, gate, gate_n);

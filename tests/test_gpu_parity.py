@@ -824,6 +824,20 @@ def test_median_of_long_rows_on_and_off_cache_lines(below, wires):
             assert torch.equal(out[:d], want) and bool((out[d:] == 7.0).all()), (f, d, start, ld)
 
 
+def test_trimmed_mean_of_few_long_rows():
+    # fewer than nine rows on the nine-wire network: four words per thread above 262144 coordinates,
+    # the last vector overlaps its neighbour; raw bit patterns with ties, odd pitch
+    rng = np.random.default_rng(8)
+    for f in range(1, 9):
+        for d in (262144, 262145, 262150, 300003):
+            U = rng.integers(0, 2**32, size=(f + 1, d + 3), dtype=np.uint64).astype(np.uint32)
+            U[:, : d // 3] &= np.uint32(0x80000007)
+            U[:, d // 2 :] = rng.standard_normal((f + 1, d + 3 - d // 2)).astype(np.float32).view(np.uint32)
+            X = torch.tensor(U.view(np.int32), device=DEV).view(torch.float32)
+            for b in sorted({0, (f - 1) // 2}):
+                _trimmed_mean_check(X, rng.permutation(f + 1)[:f].astype(np.int32), d, b, (f, d, b))
+
+
 def test_mean_around_median_alone():
     # byz_mean_around_median = the second phase of Bulyan on rows of the caller's choice: every
     # network size of that kernel and the sizes between (spare wires), d below and above the
