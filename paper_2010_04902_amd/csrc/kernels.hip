@@ -1498,9 +1498,12 @@ constexpr int gated_vec(int f) { return f <= 49 ? 4 : 1; }
 // Blocks of a vote: every block walks over its files one after the other, so where the rows alone
 // do not give 1024 blocks the files are dealt out too, two or more to a block ((255,3) whole call,
 // d = 1003 206 -> 23 us, 100000 234 -> 89, 500000 381 -> 345; 512 or 2048 blocks: up to 20 % slower).
-inline dim3 vote_grid(int64_t d, int f) {
+// `even`: nearly two blocks a CU are left as they are, which suits the exact vote of five or seven copies
+// (rows of 500032 words: (49,5) 77.5 -> 72.7 us, (49,7) 113 -> 102; of 400001 dealt out 70.6 and 104,
+// left 80.3 and 116) and neither three copies (500032: 45.7 dealt out, 50.0 left) nor the tolerant vote.
+inline dim3 vote_grid(int64_t d, int f, bool even) {
     const unsigned x = blocks_for(d / kVec);
-    const unsigned want = 1024u / x, most = ((unsigned)f + 1) / 2;
+    const unsigned want = even && x > 450 ? 1 : 1024u / x, most = ((unsigned)f + 1) / 2;
     const unsigned y = want < 1 ? 1 : (want < most ? want : most);
     const unsigned per = ((unsigned)f + y - 1) / y;
     return dim3(x, ((unsigned)f + per - 1) / per);
@@ -1510,7 +1513,7 @@ template <int R>
 int launch_vote_pairs(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, int f,
                       uint32_t *neq, const uint32_t *gate, int gate_n, const uint32_t *only_files,
                       hipStream_t s) {
-    const dim3 grid = vote_grid(d, f);
+    const dim3 grid = vote_grid(d, f, R >= 5);
     vote_pairs_kernel<R, kVec><<<grid, kBlock, 0, s>>>(X, d, ld, rows, f, (f + grid.y - 1) / grid.y, neq,
                                                        gate, gate_n, only_files);
     BYZ_HIP(hipGetLastError());
@@ -1531,7 +1534,7 @@ int launch_vote_pairs_r(int r, const uint32_t *X, int64_t d, int64_t ld, const i
 int launch_vote_pairs_tolerant(int r, const uint32_t *X, int64_t d, int64_t ld,
                                const int32_t *rows, int f, float atol, float rtol, uint32_t *far,
                                hipStream_t s) {
-    const dim3 g = vote_grid(d, f);
+    const dim3 g = vote_grid(d, f, false);
     const int per = (f + (int)g.y - 1) / (int)g.y;
     switch (r) {
         case 3:

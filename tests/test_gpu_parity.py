@@ -3,6 +3,8 @@
 Vote and odd-count median are pure selection, so the bar is exact equality of every output
 word (winner indices, pair bits, median bit patterns).
 """
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -836,6 +838,25 @@ def test_trimmed_mean_of_few_long_rows():
             X = torch.tensor(U.view(np.int32), device=DEV).view(torch.float32)
             for b in sorted({0, (f - 1) // 2}):
                 _trimmed_mean_check(X, rng.permutation(f + 1)[:f].astype(np.int32), d, b, (f, d, b))
+
+
+@pytest.mark.parametrize("f,r", [(49, 5), (9, 7)])
+def test_vote_where_the_files_are_no_longer_dealt_out(f, r):
+    # 449 to 452 blocks of rows: around the number from which five and seven copies are left to whole
+    # blocks; one word of one copy differs, in the first, the last whole and the ragged vector
+    for d in (449 * 1024 + 3, 450 * 1024, 450 * 1024 + 5, 452 * 1024 + 1):
+        g = torch.Generator(device=DEV).manual_seed(d)
+        X = torch.randn(f, 1, d, device=DEV, generator=g).expand(f, r, d).reshape(f * r, d).contiguous()
+        rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
+        want = np.zeros(f, dtype=np.int64)
+        for j, k, c in ((0, 0, 0), (f // 2, r - 1, d // 1024 * 1024 - 1), (f - 1, 1, d - 1)):
+            X[j * r + k, c] += 1
+            want[j] = sum(1 << i for i, p in enumerate(itertools.combinations(range(r), 2)) if k in p)
+        wrep, wrow, neq = B.byz_vote(X, d, rows, f, r)
+        torch.cuda.synchronize()
+        assert np.array_equal(neq.cpu().numpy(), want), d
+        best = [1 if j == 0 else 0 for j in range(f)]
+        assert wrep.cpu().tolist() == best and wrow.cpu().tolist() == [j * r + best[j] for j in range(f)], d
 
 
 def test_mean_around_median_alone():
