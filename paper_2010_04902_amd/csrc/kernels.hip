@@ -100,6 +100,9 @@ constexpr int vec_for_pass(int f, int r, bool trim) {
 // the walk over the files is bound by the latency of its loads.  us a call, four or two words and
 // one: (25,3) d = 100003 21.6 / 18.4, 262000 23.5 / 28.0; (49,3) 131072 32.4 / 27.8; (49,7) 131072
 // 51.2 / 46.0; (25,5) 20000 25.8 / 23.5, 131072 25.5 / 26.6.
+// Rows that one block holds with the wider form, but not with one word per thread, keep the wider form:
+// a block merges its bits with no other ((25,3) d = 1003, us of GPU time, median 14.4, one word 15.2,
+// early-majority 16.0 and 18.3; (25,5) 500 17.4 and 20.5).
 [[maybe_unused]] constexpr int64_t short_row(int f, int r) { return f <= 25 && r == 5 ? 65536 : 131072; }
 constexpr int kProbe = 256;  // sampled coordinates of the probe (512: 2x slower)
 constexpr int kProbeSplit = 4;  // the files are dealt out to this many groups of kProbe threads
@@ -1644,7 +1647,8 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     int rc = byz_internal_profile_mark(0, s);
     if (rc != BYZ_OK) return rc;
     constexpr bool kShortToo = vec_for_pass(F, R, false) > 1;  // or the only width is one word already
-    if (kShortToo && d <= short_row(F, R)) {
+    const int64_t one_block = (int64_t)kBlock * vec_for_pass(F, R, trim_b >= 0);
+    if (kShortToo && d <= short_row(F, R) && (d <= kBlock || d > one_block)) {
         if constexpr (kShortToo) {
             if (trim_b < 0)
                 fused_kernel<F, R, false, 1><<<blocks_for(d), kBlock, 0, s>>>(

@@ -1186,6 +1186,60 @@ def test_hip_graph_capture_of_the_other_entry_points(l):
             assert torch.equal(got.view(torch.int32), want.view(torch.int32))
 
 
+SINGLE_PASS_SHAPES = ((9, 3), (15, 3), (21, 3), (25, 3), (25, 5), (35, 5), (49, 3), (49, 5), (49, 7), (63, 7),
+                      (65, 5), (81, 3), (121, 3), (169, 3))
+
+
+def _median_and_trimmed_mean(winners, b):
+    """Of distinct finite values: the middle row of the sorted ones; the kept ones added in order."""
+    v = winners.sort(dim=0).values
+    f = v.shape[0]
+    total = torch.zeros(v.shape[1], device=v.device)
+    for i in range(b, f - b):
+        total += v[i]
+    trimmed = total.cpu().numpy() / np.float32(f - 2 * b)
+    return W.bits(v[(f - 1) // 2].contiguous()), trimmed.view(np.uint32)
+
+
+@pytest.mark.parametrize("f,r", SINGLE_PASS_SHAPES)
+def test_single_pass_around_every_change_of_width(f, r):
+    # every single-pass shape, median and trimmed mean, with and without the early majority, where the
+    # number of words per thread changes: one block of 256 threads, one block of the wide form, the
+    # longest row that runs one word per thread; above 131072 coordinates the median and the trimmed
+    # mean behind the decision run four words too.  First with tampered copies that are outvoted,
+    # then with a file without a majority whose winner every stretch around one word outnumbers, so
+    # that the kernels behind the decision write the output
+    assert B.byz_aggregate_has_single_pass(f, r)
+    wide = (2 if r >= 5 else 4) if f <= 49 else (2 if f <= 81 else 1)
+    short = 65536 if f <= 25 and r == 5 else 131072
+    rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
+    b = max(1, f // 8)
+    for d in sorted({255, 256, 257, 256 * wide, 256 * wide + 1, short, short + 1, 131072, 131079}):
+        g = torch.Generator(device=DEV).manual_seed(f * 10 + r + d)
+        X = torch.randn(f, 1, d + 3, device=DEV, generator=g).expand(f, r, d + 3).reshape(f * r, d + 3).contiguous()
+        X[0] += 1.0                        # file 0: the first copy differs everywhere
+        X[r + r - 1, d - 1] -= 2.0         # file 1: the last copy differs in the last word
+        winner = [1] + [0] * (f - 1)
+        for majority in (True, False):
+            if not majority:               # the middle file: every copy differs from every other in a word of its own
+                j = f // 2
+                for k in range(r):
+                    X[j * r + k, d // 2 + k] = 9.0 + k
+                X[j * r, d - 2] = -9.0
+            won = torch.stack([X[q * r + winner[q], :d] for q in range(f)])
+            want = _median_and_trimmed_mean(won, b)
+            for flags in (0, B.BYZ_AGG_TRIM(b), B.BYZ_AGG_EARLY_MAJORITY, B.BYZ_AGG_TRIM(b) | B.BYZ_AGG_EARLY_MAJORITY):
+                out = torch.full((d + 8,), 7.0, device=DEV)
+                _, wrep, ws = B.byz_aggregate_opts(X, d, rows, f, r, flags, out=out)
+                torch.cuda.synchronize()
+                tag = (f, r, d, majority, flags)
+                assert wrep.cpu().tolist() == winner, tag
+                assert np.array_equal(W.bits(out[:d].contiguous()), want[1 if flags & B.BYZ_AGG_TRIMMED_MEAN else 0]), tag
+                assert bool((out[d:] == 7.0).all()), tag
+                if flags & B.BYZ_AGG_EARLY_MAJORITY == 0:
+                    assert B.byz_aggregate_path(ws) == (SINGLE if majority else REDONE), tag
+
+
 def test_hidden_equality_patterns_of_wide_files():
     # r = 3 ... 13: random equality patterns among the copies of random files, the classes one
     # changed word apart at random coordinates (the comparison over all of d is what finds
