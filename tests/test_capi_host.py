@@ -436,3 +436,27 @@ def test_binding_refuses_row_tables_that_point_outside_the_matrix():
     t[3] = 1000
     with pytest.raises(ValueError, match="names rows"):
         B.byz_median(X, 64, t[:25])
+
+
+def test_binding_stream_argument():
+    # a Stream object, a raw handle or None; text and bytes, which ctypes would take for a pointer, and
+    # anything else are refused before a launch
+    import types
+    from paper_2010_04902_amd import binding
+    assert binding._stream_ptr(0x1230).value == 0x1230
+    assert binding._stream_ptr(types.SimpleNamespace(cuda_stream=0x4560)).value == 0x4560
+    for bad in ("0x1230", b"1230", 1.5, object()):
+        with pytest.raises(TypeError):
+            binding._stream_ptr(bad)
+
+
+def test_binding_finds_the_current_stream_without_the_private_name(monkeypatch):
+    import types
+    from paper_2010_04902_amd import binding
+    cuda = types.SimpleNamespace(current_device=lambda: 3,
+                                 current_stream=lambda: types.SimpleNamespace(cuda_stream=0x7890))
+    torch = types.SimpleNamespace(cuda=cuda, _C=types.SimpleNamespace())
+    monkeypatch.setattr(binding, "_torch", lambda: torch)
+    assert binding._stream_ptr(None).value == 0x7890
+    torch._C._cuda_getCurrentRawStream = lambda device: 0x1000 + device
+    assert binding._stream_ptr(None) == 0x1003
