@@ -676,7 +676,7 @@ void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int3
     // a partial matrix more to write and add (128 x 50001 62.9 us, one step each 73.9; 96 x 50001 48.7
     // and 51.3)
     int64_t n = (d + kSpan - 1) / kSpan;
-    if (n > kGramBlocks / 2) n = n / 2 > kGramBlocks / 2 ? n / 2 : kGramBlocks / 2;
+    if (n > kGramBlocks / 2) n = n > kGramBlocks ? (n + 1) / 2 : kGramBlocks / 2;
     *grid = n < 1 ? 1 : (n < kGramBlocks ? (int)n : kGramBlocks);  // d == 0: one block writes zero tiles
     gram_partial_kernel<NT, SF, LINES><<<*grid, 64 * kWaves, 0, s>>>(rows_base, d, ld, row_index_dev, f,
                                                                     partial);
