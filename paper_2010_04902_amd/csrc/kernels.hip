@@ -4,7 +4,8 @@
 // Bulyan, plus the C-ABI entry points that launch them.
 //
 // Work decomposition shared by all streaming kernels: one thread owns V consecutive
-// coordinates (4; 2 or 1 for the largest networks) and walks over all files, so every global
+// coordinates (4 in the vote; in the single pass 4, or 2 or 1 for the largest networks and short
+// rows; 1 in most kernels with one slot per file) and walks over all files, so every global
 // load of a wave is one contiguous segment of one row (1 KiB with 16-byte loads; gfx950 global
 // loads only need dword alignment).  Threads past the end of the grid redo the last vector, so
 // loads and wave ballots sit in straight-line code; trailing words are done by a few threads
@@ -26,8 +27,8 @@
 // 0 holds every entry point, the vote and the smaller Bulyan kernels, parts 1..4, 7, 14, 15 and 18 one
 // group of single-pass instantiations each (byz_internal_launch_single_pass_<n>), parts 5 and 6
 // the median and trimmed-mean kernels up to 81 wires (and the 121-wire median), parts 8..11,
-// 14, 15 and 19..23 the larger ones, parts 12 and 13 the 81- and 121-wire second phase of Bulyan,
-// parts 16 and 17 the two-wave median and trimmed-mean kernels for f > 169.
+// 14, 15 and 19..23 the larger ones, parts 12 and 13 the second phase of Bulyan on 57 to 81 and on 97
+// to 137 wires, parts 16 and 17 the two-wave median and trimmed-mean kernels for f > 169.
 // Without BYZ_PART the whole library is this one translation unit.
 #ifndef BYZ_PART
 #define BYZ_PART -1
@@ -58,13 +59,13 @@ struct ProfileState {
 thread_local ProfileState g_prof;
 #endif
 
-// Files the single-pass kernel prefetches ahead of the one it consumes, from the number of
-// 16-byte loads per thread it should keep in flight.  Measured on MI355X: about 6 for f = 25
+// Files a kernel of several words per thread prefetches ahead of the one it consumes, from the number
+// of 16-byte loads per thread it should keep in flight.  Measured on MI355X: about 6 for f = 25
 // (3-4 waves per SIMD), about 12 for f = 49 (2 waves per SIMD); more is slower.  f = 121 runs
-// one word per thread (4-byte loads) and, with one slot per file, gains up to 20 files ahead;
-// f = 81 (two words per thread, 253 registers) has no room for more than 5.
+// one word per thread (4-byte loads); f = 81 (two words per thread, 253 registers) has no room for
+// more than 5.  The kernels with one slot per file run one word per thread, twenty files ahead.
 constexpr int prefetch_depth(int f, int slots) {
-    if (f > 81) return slots == 1 ? 20 : 5;
+    if (f > 81) return 5;
     const int target = f >= 49 ? 12 : 6;
     const int a = (target + slots - 1) / slots - 1;
     return a < 1 ? 1 : (a > 5 ? 5 : a);
@@ -99,7 +100,9 @@ constexpr int vec_for_pass(int f, int r, bool trim) {
 // in flight (8 ahead for three copies, 5 for five or seven): with fewer threads than fill the chip
 // the walk over the files is bound by the latency of its loads.  us a call, four or two words and
 // one: (25,3) d = 100003 21.6 / 18.4, 262000 23.5 / 28.0; (49,3) 131072 32.4 / 27.8; (49,7) 131072
-// 51.2 / 46.0; (25,5) 20000 25.8 / 23.5, 131072 25.5 / 26.6.
+// 51.2 / 46.0; (25,5) 20000 25.8 / 23.5, 131072 25.5 / 26.6.  Depths, us of GPU time, 4 and 3 ahead / 5 and
+// 2 / 8 and 5 / 20 and 8: (25,3) d = 100003 16.6 / 16.3 / 16.1 / 15.2, (49,3) 27.1 / 26.9 / 26.7 / 25.9, (49,5)
+// 34.1 / 34.4 / 34.1 / 34.2, (49,7) 42.4 / 42.6 / 42.7 / 43.2 (20 for three copies would be the better one).
 // Rows that one block holds with the wider form, but not with one word per thread, keep the wider form:
 // a block merges its bits with no other ((25,3) d = 1003, us of GPU time, median 14.4, one word 15.2,
 // early-majority 16.0 and 18.3; (25,5) 500 17.4 and 20.5).
@@ -819,9 +822,10 @@ __global__ __launch_bounds__(kBlock) void median_kernel(
 // Coordinate-wise median by the streamed program of the generated network on F wires, one word per
 // thread: exactly F rows or, with PAD, any odd least_rows(F) <= f <= F --
 // the F - f spare wires reload row_index[0] and are tied half to the smallest and half to the
-// largest key, which leaves the median where it was.  Bound by HBM up to F = 109 (4 M coordinates
-// at 6.5 TB/s and measured: f = 81 202 and 196 us, 109 271 and 266), by min/max issue above (153
-// 379 and 392, 169 419 and 472; with two-wire comparators and fewer sizes 655 and 577).
+// largest key, which leaves the median where it was.  Within 4 % of the time its bytes take up to
+// F = 153 (4 M coordinates at 6.5 TB/s and measured, us: f = 81 202 and 196, 109 271 and 266, 137 340 and
+// 355, 153 379 and 392), bound by min/max issue at 169 (419 and 472; with two-wire comparators and
+// fewer sizes 153 took 655 and 169 577).
 // (V = 4: thread t owns the words from min(4t, d - 4), the last vector overlaps its neighbour; d >= 4)
 // group: see neighbours_together; 0 = plain order.
 template <int F, int V, bool PAD>
@@ -1196,11 +1200,10 @@ __device__ __forceinline__ float mean_around_median(const float *col, int stride
 
 // Second phase of Bulyan: the theta rows selected_rows[0..theta-1] are sorted per coordinate
 // by the streamed full-sort network on N >= theta wires (N the next generated size); the
-// N - theta spare wires reload the first row and are tied to the largest
-// key, so wires 0..theta-1
-// end up holding the chosen values in ascending order.  They go to an LDS column of the thread
-// (word i*BLOCK + thread: conflict-free), where the window around the median is found with
-// run-time indices.  Thread t owns the words from min(V*t, d - V); needs d >= V.
+// N - theta spare wires reload the first row and are tied to the largest key, so wires
+// 0..theta-1 end up holding the chosen values in ascending order.  They go to an LDS column of the
+// thread (word i*BLOCK + thread: conflict-free), where the window around the median is found with
+// run-time indices.  One word per thread.
 // Dynamic LDS: N*BLOCK*4 bytes; the widest networks run one wave a block, so that several
 // blocks' columns fit a CU and the number of waves is again what the registers allow.
 template <int F, int BLOCK>
