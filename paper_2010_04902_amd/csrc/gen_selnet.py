@@ -211,29 +211,38 @@ def most_live(f, sorters):
 BLOCKS = (3, 5, 7, 9, 11, 13, 15, 17, 18, 19, 21, 25, 27, 30, 33, 36, 39, 43, 45, 51, 54, 57, 63, 81)
 
 
+def _median_part(f, sizes):
+    return _needed_part(_sort_blocks(f, sizes), [(f - 1) // 2])
+
+
+@functools.lru_cache(None)
+def median_blocks(f):
+    """Sizes of the blocks the median of f wires merges last, decided by what is left after
+    dropping, an instruction counting as much as half a live wire: fewer live wires are fewer
+    registers (25 files in the single pass: 9 + 9 + 7 needs 23 keys at a time, 9 + 8 + 8 all 25,
+    which costs a quarter of the resident waves)."""
+    candidates = {best_split(f)[1]}
+    if f >= 4:
+        for a in BLOCKS:
+            for b in BLOCKS:
+                if b <= a and a < f <= 3 * a and 0 <= f - a - b <= b:
+                    candidates.add(tuple(m for m in (a, b, f - a - b) if m))
+    best = None
+    for sizes in sorted(candidates):
+        sorters = _median_part(f, sizes)
+        score = op_count(sorters) + 2 * most_live(f, sorters)
+        if best is None or score < best[0]:
+            best = (score, sizes)
+    return best[1]
+
+
 @functools.lru_cache(None)
 def sorters_for(f, full_sort=False):
     """The network on wires 0..f-1 as sorters (wires ascending, which outputs are needed): after
-    it wire i holds the element of rank i, or (full_sort false) wire (f-1)/2 the median.
-    Which blocks a median merges last is decided by what is left after dropping, an instruction
-    counting as much as half a live wire: fewer live wires are fewer registers (25 files in the
-    single pass: 9 + 9 + 7 needs 23 keys at a time, 9 + 8 + 8 all 25, which costs a quarter of
-    the resident waves)."""
-    sizes = best_split(f)[1]
-    if full_sort or f < 4:
-        return _needed_part(_sort_blocks(f, sizes), range(f) if full_sort else [(f - 1) // 2])
-    candidates = {sizes}
-    for a in BLOCKS:
-        for b in BLOCKS:
-            if b <= a and a < f <= 3 * a and 0 <= f - a - b <= b:
-                candidates.add(tuple(m for m in (a, b, f - a - b) if m))
-    best = None
-    for sizes in sorted(candidates):
-        sorters = _needed_part(_sort_blocks(f, sizes), [(f - 1) // 2])
-        score = op_count(sorters) + 2 * most_live(f, sorters)
-        if best is None or score < best[0]:
-            best = (score, sorters)
-    return best[1]
+    it wire i holds the element of rank i, or (full_sort false) wire (f-1)/2 the median."""
+    if full_sort:
+        return _needed_part(_sort_blocks(f, best_split(f)[1]), range(f))
+    return _median_part(f, median_blocks(f))
 
 
 def comparators(wires, outputs):

@@ -217,7 +217,7 @@ def test_selection_network_zero_one_exhaustive(f):
     assert np.array_equal(v[wire], (pop > f // 2).astype(np.uint8))
 
 
-@pytest.mark.parametrize("f", [35, 49, 63, 65, 81, 121, 169])
+@pytest.mark.parametrize("f", [f for f in gen_selnet.STREAMED_SIZES if f > 25])
 def test_selection_network_near_balanced_inputs(f):
     ops, wire = gen_selnet.best_network(f)
     rng = np.random.default_rng(f)
@@ -250,7 +250,7 @@ def _run_network_columns(ops, cols):
     return cols
 
 
-@pytest.mark.parametrize("f", [49, 63, 65, 81, 121])
+@pytest.mark.parametrize("f", [f for f in gen_selnet.STREAMED_SIZES if 25 < f <= 153])
 def test_pruned_median_network_equals_the_unpruned_sort_on_tie_heavy_data(f):
     # a second check that shares nothing with the pruning: Batcher's sort on the next power of
     # two, every comparator kept, spare wires holding the largest value, must leave on wire

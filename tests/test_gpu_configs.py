@@ -243,7 +243,7 @@ def test_trimmed_mean_full_size(idx):
 
 def test_multi_krum_full_size():
     # Multi-Krum over the vote winners of workload 2 (c = c_max = 5, m = f - c = 20) at full
-    # size: 11,173,962 coordinates = 43,649 chunks, 86 per block
+    # size: 11,173,962 coordinates, 86 steps of 64 for a wave
     from tests.test_gpu_parity import _multi_krum_check
     cfg = synth.CONFIGS[1]
     w = W.from_config(cfg, DEV, ld=synth.padded_ld(cfg.d, 64))
@@ -256,7 +256,7 @@ def test_multi_krum_full_size():
 def test_multi_krum_81_files():
     # Multi-Krum over the 81 vote winners of the F_9 cluster (six row tiles in the Gram kernel,
     # two distances per lane in the row sort), c = c_max = 8, m = f - c = 73; 3,000,001
-    # coordinates (24 chunks per block and a ragged last one) keep the fp64 oracle to seconds
+    # coordinates (46 steps of 32 for a wave, the last one ragged) keep the fp64 oracle to seconds
     from tests.test_gpu_parity import _multi_krum_check
     cfg = synth.CONFIGS[7]
     d = 3000001

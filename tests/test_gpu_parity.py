@@ -861,8 +861,8 @@ def test_vote_where_the_files_are_no_longer_dealt_out(f, r):
 
 def test_mean_around_median_alone():
     # byz_mean_around_median = the second phase of Bulyan on rows of the caller's choice: every
-    # network size of that kernel and the sizes between (spare wires), d below and above the
-    # vector width, beta = 1 (the median, bit for bit), a random beta, beta = f (plain mean);
+    # network size of that kernel and the sizes between (spare wires), d from one word to many
+    # blocks, beta = 1 (the median, bit for bit), a random beta, beta = f (plain mean);
     # normal data and small integers (ties in the window rule)
     rng = np.random.default_rng(183)
     for f in (1, 3, 9, 13, 15, 25, 27, 49, 51, 63, 81, 99, 121, 127):
@@ -891,12 +891,19 @@ def test_mean_around_median_alone():
         assert e.value.code == code, (n, beta)
 
 
+def _gram_additions(d):
+    """Most fp32 additions behind one entry of a partial Gram matrix: a wave adds the products of its
+    coordinates, 32 at a time or 64 (at least four waves in each of 512 blocks; short rows up to two
+    times 32), then at most sixteen waves are added."""
+    return max(64, 64 * -(-d // (512 * 4 * 64)), 32 * -(-d // (512 * 4 * 32))) + 16
+
+
 def _multi_krum_check(X, idx_np, d, c, m, tag):
     """GPU Multi-Krum against the fp64 oracle.
 
-    Tolerances from the arithmetic: a Gram entry is accumulated in fp32 over at most L products
-    per block (L = coordinates a block handles) plus a few adds, then in fp64, so
-    |dG_ij| <= (L + 8) * 2^-24 * (G_ii + G_jj) / 2 and |dD_ij| <= 2 * (L + 8) * 2^-24 * (G_ii + G_jj).
+    Tolerances from the arithmetic: a Gram entry is accumulated in fp32 with at most L additions
+    (_gram_additions), then in fp64, so
+    |dG_ij| <= L * 2^-24 * (G_ii + G_jj) / 2 and |dD_ij| <= 2 * L * 2^-24 * (G_ii + G_jj).
     A score adds at most f distances.  The selection is compared where the oracle's scores are
     further from the cut than twice that; the mean is checked against the oracle's mean
     (fp32 sequential sum: m * 2^-24 * max|x|)."""
@@ -906,10 +913,9 @@ def _multi_krum_check(X, idx_np, d, c, m, tag):
     Xh = X.detach().cpu().numpy()
     mean_o, sel_o, scores_o, dist_o = O.multi_krum(Xh, idx_np, d, c, m)
     f = len(idx_np)
-    n_chunks = max(1, -(-d // 256))
-    L = -(-n_chunks // min(n_chunks, 512)) * 256
+    L = _gram_additions(d)
     norms = np.diag(dist_o * 0) + np.array([float(np.dot(Xh[j, :d].astype(np.float64), Xh[j, :d].astype(np.float64))) for j in idx_np])
-    tol_d = 2.0 * (L + 8) * 2.0 ** -24 * (norms[:, None] + norms[None, :]) + 1e-300
+    tol_d = 2.0 * L * 2.0 ** -24 * (norms[:, None] + norms[None, :]) + 1e-300
     dist_g = dist.cpu().numpy()
     assert (np.abs(dist_g - dist_o) <= tol_d).all(), tag
     assert (np.diag(dist_g) == 0).all() and np.array_equal(dist_g, dist_g.T), tag
@@ -956,7 +962,7 @@ def test_multi_krum_on_the_vote_winners(scheme, a, b, q, attack):
 def _bulyan_check(X, idx_np, d, c, tag, big=False, exact_order=False):
     """GPU Bulyan against the fp64 oracle.
 
-    Distances: tolerance of the Multi-Krum check (fp32 Gram over L products per block).  Phase 1
+    Distances: tolerance of the Multi-Krum check (L fp32 additions behind a Gram entry).  Phase 1
     is a chain of argmin decisions on fp64 scores computed from those distances: the order
     chosen must equal the oracle's whenever, in every round, the oracle's best score is further
     than twice the score tolerance from its second best; in any case each GPU pick must be
@@ -974,10 +980,9 @@ def _bulyan_check(X, idx_np, d, c, tag, big=False, exact_order=False):
     f = len(idx_np)
     theta, beta = f - 2 * c, f - 4 * c
     out_o, chosen_o, dist_o = (C.bulyan if big else O.bulyan)(Xh, idx_np, d, c)
-    n_chunks = max(1, -(-d // 256))
-    L = -(-n_chunks // min(n_chunks, 512)) * 256
+    L = _gram_additions(d)
     norms = np.array([float(np.dot(Xh[j, :d].astype(np.float64), Xh[j, :d].astype(np.float64))) for j in idx_np])
-    tol_d = 2.0 * (L + 8) * 2.0 ** -24 * (norms[:, None] + norms[None, :]) + 1e-300
+    tol_d = 2.0 * L * 2.0 ** -24 * (norms[:, None] + norms[None, :]) + 1e-300
     dist_g = dist.cpu().numpy()
     assert (np.abs(dist_g - dist_o) <= tol_d).all(), tag
     tol_s = f * tol_d.max()
@@ -1142,8 +1147,8 @@ def test_tolerant_vote_special_values_and_errors():
 @pytest.mark.parametrize("l", [5, 7, 9])
 def test_hip_graph_capture_of_the_other_entry_points(l):
     # vote (exact and tolerant), trimmed mean, Multi-Krum and Bulyan also enqueue kernels only;
-    # f = 49 uses the Gram kernel that asks for more than 64 KiB of LDS, f = 81 the wide
-    # selection kernels and the 81-wire second phase of Bulyan, which do so too
+    # f = 49 has four row tiles in the Gram kernel, f = 81 six, the wide selection kernel, which asks for
+    # more than 64 KiB of LDS, and the 81-wire second phase of Bulyan
     w = W.make(MOLS, l, 3, 3, 50_001, dict(REVERSED, file_scales=True), seed=14, device=DEV)
     rows_dev = torch.tensor(w.file_rows.reshape(-1), dtype=torch.int32, device=DEV)
     c = 2
@@ -1300,6 +1305,10 @@ def test_repeated_calls_on_one_workspace_never_change():
             path0 = B.byz_aggregate_path(ws)
             seen_paths.add(path0)
             out0, wrep0 = out0.clone(), wrep0.clone()
+            if flags & B.BYZ_AGG_TRIMMED_MEAN == 0:
+                out_o, wrep_o, _ = C.aggregate(X.cpu().numpy(), w.file_rows, d)
+                assert np.array_equal(W.bits(out0), W.bits(out_o)), flags
+                assert np.array_equal(wrep0.cpu().numpy(), wrep_o), flags
             out, wrep = torch.empty_like(out0), torch.empty_like(wrep0)
             for it in range(40):
                 B.byz_aggregate_opts(X, d, rows_dev, w.f, w.r, flags, out=out, winner_replica=wrep,
@@ -1357,8 +1366,8 @@ def test_random_shapes_sizes_and_layouts():
 def test_multi_krum_and_bulyan_for_every_f():
     # every f from 3 to 64 and a spread of the wider ones (all tile counts and staging shapes of
     # the Gram kernel, one and two distances per lane in the row sort, Bulyan's rounds in
-    # registers and in LDS, every network size of its second phase incl. the spare-wire cases
-    # and the sorted-column kernel past 121), random d, row pitch, c and m; per-row scales keep
+    # registers and in LDS, every network size of its second phase incl. the spare-wire cases),
+    # random d, row pitch, c and m; per-row scales keep
     # the scores apart, so selections are compared exactly
     rng = np.random.default_rng(64)
     compared = []

@@ -160,6 +160,44 @@ def test_three_way_merge_all_zero_one_inputs(sizes):
         assert np.array_equal(v, np.sort(v, axis=1)), order
 
 
+def _merges_in_use():
+    """Sizes of the blocks of every merge that the generated networks are made of."""
+    merges = set()
+
+    def descend(sizes):
+        if len(sizes) > 1 and tuple(sizes) not in merges:
+            merges.add(tuple(sizes))
+            for m in sizes:
+                descend(gen_selnet.best_split(m)[1])
+
+    for f in set(gen_selnet.SIZES) | set(gen_selnet.STREAMED_SIZES):
+        descend(gen_selnet.median_blocks(f))
+    for f in gen_selnet.SORT_SIZES:
+        descend(gen_selnet.best_split(f)[1])
+    return sorted(merges, key=lambda m: (sum(m), m))
+
+
+@pytest.mark.parametrize("sizes", _merges_in_use(), ids=str)
+def test_every_merge_of_the_generated_networks_on_all_zero_one_inputs(sizes):
+    # with sorted blocks merged rightly at every level the whole network sorts
+    starts = [sum(sizes[:k]) for k in range(len(sizes))]
+    sorters = []
+    out = gen_selnet.merge_blocks(sorters, [list(range(s, s + m)) for s, m in zip(starts, sizes)])
+    assert out == list(range(sum(sizes)))
+    zeros = np.array(list(itertools.product(*[range(m + 1) for m in sizes])))
+    v = [(i >= zeros[:, k]).astype(np.uint8) for k, m in enumerate(sizes) for i in range(m)]
+    for wires in sorters:
+        if len(wires) == 2:
+            (a, b), x = wires, [v[w] for w in wires]
+            v[a], v[b] = x[0] & x[1], x[0] | x[1]
+        else:
+            (a, b, c), x = wires, [v[w] for w in wires]
+            v[a], v[b], v[c] = x[0] & x[1] & x[2], (x[0] & x[1]) | (x[2] & (x[0] | x[1])), x[0] | x[1] | x[2]
+    total = sum(sizes) - zeros.sum(axis=1)  # ones
+    for i in range(sum(sizes)):
+        assert np.array_equal(v[i], (i >= sum(sizes) - total).astype(np.uint8)), i
+
+
 def test_sorters_and_their_comparators_agree():
     # the comparators of a three-wire sorter give the outputs that are needed, for every subset
     for mask in range(1, 8):
