@@ -85,13 +85,20 @@ __device__ __forceinline__ void wave_fence() {
 // consecutive words of a row; a pass through the wave's own
 // piece of LDS gives lane l four coordinates of row l%16 at a time, the k of its quarter of the
 // wave for four instructions (16-byte pieces, piece p of row r in place p ^ (r%8): neither side
-// has bank conflicts).  Products and sums are the fp32 instruction's, one rounding each; G(i, j)
+// has bank conflicts).  Products are the fp32 instruction's, rounded once each into their sum; G(i, j)
 // and G(j, i) are the same bits, and equal rows tie exactly.
-// Calls of Multi-Krum with rows on cache lines, us, and with a tile in LDS shared by the block, two
-// barriers a chunk and row tiles rounded up to 6 or 8 above 64 rows: 49 x 11.2 M 629 (698), 80 x 3 M
-// 288 (441), 128 x 3 M 606 (837); to f = 32, HBM-bound, the same (32 x 11.2 M 353 and 351).  Matrix
-// instructions bound it from f = 33 up: ten tiles at f = 49 are 365 us at the fp32 rate.
-template <int NT, int SF, bool LINES>
+// A long running sum is off by its roundings and, one-sidedly, by about 1.3e-11 of itself per
+// product (25 x 11.2 M, 5456 products: 2e-7 of the norms).  So a run ends after three steps of 32
+// coordinates (two of 64) and is added to the totals by the vector ALU; SHORT, one to four steps a
+// wave, ends it after 16 coordinates, where the sums are few.  Distances' error over G_ii + G_jj,
+// rms, 1e-9, f = 49, d = 2048 / 20011 / 140001 / 1.1 M: 5.0 / 2.5 / 1.1 / 1.7; one running sum 8.7 / 3.4 / 2.3 /
+// 8.9; bf16 matrix units on rows split in three parts 7.9 / 2.9 / 2.1 / 2.0.
+// Calls of Multi-Krum with rows on cache lines, us, in brackets with one running sum, a tile in LDS
+// shared by the block, two barriers a chunk and row tiles rounded up to 6 or 8 above 64 rows: 49 x
+// 11.2 M 660 (705), 80 x 3 M 308 (442), 128 x 3 M 697 (843); to f = 32, HBM-bound, the same (32 x 11.2 M
+// 355 and 352).  Matrix instructions bound it from f = 33 up: ten tiles at f = 49 are 365 us at the fp32
+// rate; the runs cost 3 % there (15 % with eight row tiles, where the sums fill the registers).
+template <int NT, int SF, bool LINES, bool SHORT>
 __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int64_t d, int64_t ld,
                                                 const int32_t *__restrict__ row_index, int f,
                                                 float *stage, f32x4 (&acc)[NT * (NT + 1) / 2]) {
@@ -135,95 +142,108 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
                     raw[n][e] = c0 + 4 * piece_of(n) + e < d ? rowp[n][c0 + e] : 0.0f;
         }
     };
+    constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int kRun = SF == 1 ? 3 : 2;           // stretches of a run
+    constexpr int kRuns = SHORT ? (NP < 6 ? NP : 6) : NP;  // tiles whose runs are open at a time
+    f32x4 run[kRuns];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) acc[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int p = 0; p < NP; ++p) acc[p] = zero;
+    const int row = lane & 15;
     if (span < n_spans) fetch(span);
-    for (; span < n_spans; span += stride) {
-        wave_fence();
+    while (span < n_spans) {
+        if constexpr (!SHORT)
 #pragma unroll
-        for (int n = 0; n < kLoads; ++n)
-            if (used(n)) slots[64 * n + lane] = raw[n];
-        wave_fence();
-        if (span + stride < n_spans) fetch(span + stride);
-        const int row = lane & 15;
+            for (int p = 0; p < NP; ++p) run[p] = zero;
+        for (int k = 0; k < kRun && span < n_spans; ++k, span += stride) {
+            wave_fence();
 #pragma unroll
-        for (int s = 0; s < SF; ++s)
+            for (int n = 0; n < kLoads; ++n)
+                if (used(n)) slots[64 * n + lane] = raw[n];
+            wave_fence();
+            if (span + stride < n_spans) fetch(span + stride);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int piece = 8 * s + 2 * (lane >> 4) + u;
+            for (int h = 0; h < 2 * SF; ++h) {  // 16 coordinates
+                const int piece = 8 * (h / 2) + 2 * (lane >> 4) + h % 2;
                 f32x4 x[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     x[t] = slots[(16 * t + row) * kPieces + (piece ^ (row & 7))];
                 // lane l holds A[row = l%16][k = l/16], which is also B[k][col = l%16] of the
-                // transposed operand
+                // transposed operand; tiles p0 .. p0 + kRuns - 1
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int p0 = 0; p0 < NP; p0 += kRuns) {
 #pragma unroll
-                    for (int ti = 0; ti < NT; ++ti)
+                    for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int tj = ti; tj < NT; ++tj) {
-                            f32x4 &a = acc[tile_pair(NT, ti, tj)];
-                            a = __builtin_amdgcn_mfma_f32_16x16x4f32(x[ti][e], x[tj][e], a, 0, 0, 0);
-                        }
+                        for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                            for (int tj = ti; tj < NT; ++tj) {
+                                const int p = tile_pair(NT, ti, tj) - p0;
+                                if (p < 0 || p >= kRuns) continue;
+                                run[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                    x[ti][e], x[tj][e], SHORT && e == 0 ? zero : run[p], 0, 0, 0);
+                            }
+                    if constexpr (SHORT)
+#pragma unroll
+                        for (int p = 0; p < kRuns && p0 + p < NP; ++p) acc[p0 + p] += run[p];
+                }
             }
+        }
+        if constexpr (!SHORT)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) acc[p] += run[p];
     }
 }
 
 // Partial Gram tiles of the rows row_index[0..f-1] over this block's coordinates.  partial:
-// [gridDim.x][pairs][256] floats, position v*64 + lane, pairs = NT(NT+1)/2.
-template <int NT, int SF, bool LINES>
+// [gridDim.x][pairs][256] values, position v*64 + lane, pairs = NT(NT+1)/2, fp32 or, where a few
+// blocks would leave their last roundings visible, fp64 (d = 2048: 8.9e-9 -> 4.9e-9 at f = 100).
+template <int NT, int SF, bool LINES, bool SHORT>
 __global__ __launch_bounds__(64 * gram_waves(NT, SF))
-// (2: accumulators in ordinary registers.  112 x 11.2 M 1757 us, 1808 with 1; 80 x 3 M 306 and 288, 96 x
-// 3 M the same; eight row tiles would spill)
-__attribute__((amdgpu_waves_per_eu(NT <= 4 || NT == 7 ? 2 : 1)))
+// (2: accumulators in ordinary registers; more row tiles would spill: 96 x 11.2 M 1502 us, 1362 with 1,
+// 80 x 11.2 M 998 and 1060)
+__attribute__((amdgpu_waves_per_eu(NT <= 5 || (NT == 6 && SHORT) ? 2 : 1)))
 void gram_partial_kernel(
     const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
-    float *__restrict__ partial) {
+    float *__restrict__ partial, int in_fp64) {
     constexpr int NP = NT * (NT + 1) / 2, kWaves = gram_waves(NT, SF);
     constexpr int kStage = 16 * NT * kStep * SF;  // floats of one wave's stage
-    constexpr bool kAllWaves = kWaves * NP * kTile <= 16 * 1024;  // room for the waves' tiles at a time
-    constexpr int kRed = (kAllWaves ? kWaves : 1) * NP * kTile;
+    constexpr int kRoom = 16 * 1024 / (kWaves * kTile);  // tiles of every wave that 64 KB hold
+    constexpr int kAtOnce = NP < kRoom ? NP : kRoom;
+    constexpr int kRed = kWaves * kAtOnce * kTile;
     __shared__ __align__(16) float lds[kRed > kWaves * kStage ? kRed : kWaves * kStage];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     f32x4 acc[NP];
-    gram_accumulate<NT, SF, LINES>(X, d, ld, row_index, f, lds + wave * kStage, acc);
-    __syncthreads();  // the stages are read before the tiles below replace them
-    // the waves' tiles are added in wave order either way
-    float *dst = partial + (int64_t)blockIdx.x * NP * kTile;
-    if constexpr (kAllWaves) {
+    gram_accumulate<NT, SF, LINES, SHORT>(X, d, ld, row_index, f, lds + wave * kStage, acc);
+    // the waves' tiles are added in wave order in fp64, as many tiles at a time as fit
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
+    for (int p0 = 0; p0 < NP; p0 += kAtOnce) {
+        __syncthreads();  // the stages, or the tiles before these, are read before these replace them
 #pragma unroll
-            for (int v = 0; v < 4; ++v) lds[(wave * NP + p) * kTile + v * 64 + lane] = acc[p][v];
+        for (int p = p0; p < p0 + kAtOnce && p < NP; ++p)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                lds[(wave * kAtOnce + p - p0) * kTile + v * 64 + lane] = acc[p][v];
         __syncthreads();
-        for (int i = tid; i < NP * kTile; i += 64 * kWaves) {
+        const int count = (NP - p0 < kAtOnce ? NP - p0 : kAtOnce) * kTile;
+        for (int i = tid; i < count; i += 64 * kWaves) {
             double total = lds[i];
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) total += (double)lds[w * NP * kTile + i];
-            dst[i] = (float)total;
+            for (int w = 1; w < kWaves; ++w) total += (double)lds[w * kAtOnce * kTile + i];
+            const int64_t at = ((int64_t)blockIdx.x * NP + p0) * kTile + i;
+            if (in_fp64 != 0)
+                reinterpret_cast<double *>(partial)[at] = total;
+            else
+                partial[at] = (float)total;
         }
-    } else {  // one [NP][256] array, the waves add their tiles in turn
-        for (int w = 0; w < kWaves; ++w) {
-            if (wave == w) {
-#pragma unroll
-                for (int p = 0; p < NP; ++p)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        float *cell = lds + p * kTile + v * 64 + lane;
-                        *cell = w == 0 ? acc[p][v] : *cell + acc[p][v];
-                    }
-            }
-            __syncthreads();
-        }
-        for (int i = tid; i < NP * kTile; i += 64 * kWaves) dst[i] = lds[i];
     }
 }
 
 // gram[t][pos] = sum over blocks of partial[block][t][pos] in fp64, in a fixed order: thread
 // (pos, g) adds the blocks g, g+8, g+16, ... one by one, then the eight group sums are added
 // in order.  Block = 32 positions x 8 groups.
-__global__ __launch_bounds__(kBlock) void gram_reduce_kernel(const float *__restrict__ partial,
+template <typename T>
+__global__ __launch_bounds__(kBlock) void gram_reduce_kernel(const T *__restrict__ partial,
                                                              int n_partial, int ntiles,
                                                              double *__restrict__ gram) {
     __shared__ double s_sum[8][32];
@@ -657,8 +677,12 @@ struct KrumWorkspace {
     int32_t pad[63];
     float partial[1];  // [kGramBlocks][tiles of f][256], sized by krum_workspace_bytes
 };
+static_assert(offsetof(KrumWorkspace, partial) % sizeof(double) == 0, "partial tiles may be fp64");
 
 inline int stored_tiles(int f) { return row_tiles(f) * (row_tiles(f) + 1) / 2; }
+
+// Blocks up to which partial tiles are fp64: a quarter of the grid they have room for in fp32.
+inline bool partials_in_fp64(int grid) { return grid <= kGramBlocks / 4; }
 
 inline size_t krum_workspace_bytes(int f) {
     // (callers know this size: beyond 64 vectors it has room for 6 or 8 row tiles, whatever is used)
@@ -675,11 +699,18 @@ void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int3
     // up to a block per CU each takes one step, then up to the full grid each takes two: a block more is
     // a partial matrix more to write and add (128 x 50001 62.9 us, one step each 73.9; 96 x 50001 48.7
     // and 51.3)
-    int64_t n = (d + kSpan - 1) / kSpan;
+    const int64_t steps = (d + kSpan - 1) / kSpan;
+    int64_t n = steps;
     if (n > kGramBlocks / 2) n = n > kGramBlocks ? (n + 1) / 2 : kGramBlocks / 2;
     *grid = n < 1 ? 1 : (n < kGramBlocks ? (int)n : kGramBlocks);  // d == 0: one block writes zero tiles
-    gram_partial_kernel<NT, SF, LINES><<<*grid, 64 * kWaves, 0, s>>>(rows_base, d, ld, row_index_dev, f,
-                                                                    partial);
+    const int in_fp64 = partials_in_fp64(*grid) ? 1 : 0;
+    // up to four steps a wave; two steps of 32 at a time are taken on longer rows only
+    if (SF == 1 && steps <= 4 * (int64_t)*grid)
+        gram_partial_kernel<NT, 1, LINES, SF == 1><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
+            rows_base, d, ld, row_index_dev, f, partial, in_fp64);
+    else
+        gram_partial_kernel<NT, SF, LINES, false><<<*grid, 64 * kWaves, 0, s>>>(
+            rows_base, d, ld, row_index_dev, f, partial, in_fp64);
 }
 
 template <int NT, bool LINES>
@@ -724,7 +755,11 @@ int launch_gram(const float *rows_base, int64_t d, int64_t ld, const int32_t *ro
     }
     if (rc != BYZ_OK) return rc;
     const int ntiles = stored_tiles(f);
-    gram_reduce_kernel<<<ntiles * kTile / 32, kBlock, 0, s>>>(ws->partial, grid, ntiles, ws->gram);
+    if (partials_in_fp64(grid))
+        gram_reduce_kernel<<<ntiles * kTile / 32, kBlock, 0, s>>>(
+            reinterpret_cast<const double *>(ws->partial), grid, ntiles, ws->gram);
+    else
+        gram_reduce_kernel<<<ntiles * kTile / 32, kBlock, 0, s>>>(ws->partial, grid, ntiles, ws->gram);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }

@@ -4,6 +4,7 @@ Vote and odd-count median are pure selection, so the bar is exact equality of ev
 word (winner indices, pair bits, median bit patterns).
 """
 import itertools
+import math
 
 import numpy as np
 import pytest
@@ -725,9 +726,8 @@ def test_gram_products_are_rounded_once(f):
 def test_gram_of_long_rows(f, d):
     # every number of row tiles with two or three steps of a wave one after the other, f <= 16 also
     # with two stretches of 32 coordinates a step, and a ragged end; rows far apart in size, one
-    # around 1e-18, row pitch that is no multiple of a cache line and rows on cache lines.  Each sum of a wave is
-    # rounded at most 32 times a stretch, at most eight of them, then come the waves of a block:
-    # |err| <= 2 (32 * 8 + 16) 2^-24 (G_ii + G_jj); a stretch left out is 32 / d of that sum and more.
+    # around 1e-18, row pitch that is no multiple of a cache line and rows on cache lines.
+    # |err| <= 2 L 2^-24 (G_ii + G_jj), L = _gram_additions; a stretch left out is 32 / d of that and more.
     rng = np.random.default_rng(f * 1000003 + d)
     order = rng.permutation(f).astype(np.int32)
     for ld in (d + 2, (d + 31) // 32 * 32):
@@ -740,7 +740,7 @@ def test_gram_of_long_rows(f, d):
         n = np.diag(G)
         want = np.maximum(n[:, None] + n[None, :] - 2 * G, 0)
         np.fill_diagonal(want, 0)
-        assert (np.abs(got - want) <= 2 * (32 * 8 + 16) * 2.0 ** -24 * (n[:, None] + n[None, :])).all(), (f, d, ld)
+        assert (np.abs(got - want) <= 2 * _gram_additions(d) * 2.0 ** -24 * (n[:, None] + n[None, :])).all(), (f, d, ld)
     # an infinity (times the others' zeros a NaN) and a NaN in the last step of a wave
     for what in (np.inf, np.nan):
         Xh[:, d - 5] = 0.0
@@ -749,6 +749,26 @@ def test_gram_of_long_rows(f, d):
         assert np.isnan(got[1, [0] + list(range(2, f))]).all(), (f, what)
         rest = np.ix_([0] + list(range(2, f)), [0] + list(range(2, f)))
         assert np.isfinite(got[rest]).all(), (f, what)
+
+
+@pytest.mark.parametrize("f,d,ld", [(9, 6000001, 6000032), (25, 6000001, 6000032), (33, 6000001, 6000032),
+                                    (33, 6000001, 6000001), (65, 3000001, 3000032), (97, 3000001, 3000001)])
+def test_gram_of_long_rows_does_not_drift(f, d, ld):
+    # the distance from a row of zeros to a row of values between 1 and 2 is that row's sum of squares.
+    # Runs of at most 128 products whose roundings go either way: at most 2^-24 sqrt(128) of a run, over
+    # sqrt(runs) of them together and as many blocks rounded once, four times that for 2 f rows; one
+    # running sum per wave is 1.5 to 4e-8 too low
+    X = torch.rand((f, ld), generator=torch.Generator(device=DEV).manual_seed(f), device=DEV) + 1
+    X[f // 2] = 0.0
+    want = np.array([float((X[j, :d].double() ** 2).sum()) for j in range(f)])
+    _, _, _, dist = B.byz_multi_krum(X, d, torch.arange(f, dtype=torch.int32, device=DEV), 0, 1)
+    torch.cuda.synchronize()
+    got = dist[f // 2].cpu().numpy()
+    runs = d / 128
+    bound = 4 * 2.0 ** -24 * (math.sqrt(128 / runs) + 1 / math.sqrt(512))
+    with np.errstate(invalid="ignore"):
+        off = np.delete(np.abs(got / want - 1), f // 2)
+    assert off.max() <= bound, (f, d, off.max(), bound)
 
 
 @pytest.mark.parametrize("f,d", [(3, 31), (16, 4001), (16, 1048601), (25, 140011), (32, 262177), (25, 262177), (33, 50021),
@@ -892,10 +912,10 @@ def test_mean_around_median_alone():
 
 
 def _gram_additions(d):
-    """Most fp32 additions behind one entry of a partial Gram matrix: a wave adds the products of its
-    coordinates, 32 at a time or 64 (at least four waves in each of 512 blocks; short rows up to two
-    times 32), then at most sixteen waves are added."""
-    return max(64, 64 * -(-d // (512 * 4 * 64)), 32 * -(-d // (512 * 4 * 32))) + 16
+    """Most fp32 additions behind one entry of a partial Gram matrix: a run of at most 128 products, the
+    runs of a wave (at least four waves in each of 512 blocks, 96 products or more each), then one
+    rounding of the block's sum."""
+    return 129 + -(-d // (512 * 4 * 96))
 
 
 def _multi_krum_check(X, idx_np, d, c, m, tag):
