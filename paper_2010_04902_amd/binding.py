@@ -168,24 +168,24 @@ def byz_gamma_bound(asg, q):
 
 
 _torch_module = None
+_raw_current_stream = None  # torch's device -> stream handle, where it has it (not a public name)
 
 
 def _torch():
-    global _torch_module
+    global _torch_module, _raw_current_stream
     if _torch_module is None:
         import torch
+        _raw_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         _torch_module = torch
     return _torch_module
 
 
 def _stream_ptr(stream):
     if stream is None:
-        # the current stream's handle without building a Stream object (1.5 us a call less) where
-        # torch offers it (not a public name)
+        # the current stream's handle without building a Stream object (1.5 us a call less)
         torch = _torch()
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is not None:
-            return raw(torch.cuda.current_device())
+        if _raw_current_stream is not None:
+            return _raw_current_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     # refuses what is neither a stream nor a handle; as an argument ctypes would take text and bytes
     return ctypes.c_void_p(getattr(stream, "cuda_stream", stream))

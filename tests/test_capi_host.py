@@ -455,8 +455,8 @@ def test_binding_finds_the_current_stream_without_the_private_name(monkeypatch):
     from paper_2010_04902_amd import binding
     cuda = types.SimpleNamespace(current_device=lambda: 3,
                                  current_stream=lambda: types.SimpleNamespace(cuda_stream=0x7890))
-    torch = types.SimpleNamespace(cuda=cuda, _C=types.SimpleNamespace())
-    monkeypatch.setattr(binding, "_torch", lambda: torch)
+    monkeypatch.setattr(binding, "_torch", lambda: types.SimpleNamespace(cuda=cuda))
+    monkeypatch.setattr(binding, "_raw_current_stream", None)
     assert binding._stream_ptr(None).value == 0x7890
-    torch._C._cuda_getCurrentRawStream = lambda device: 0x1000 + device
+    monkeypatch.setattr(binding, "_raw_current_stream", lambda device: 0x1000 + device)
     assert binding._stream_ptr(None) == 0x1003
