@@ -1455,11 +1455,7 @@ __device__ __forceinline__ void fused_body(const uint32_t *__restrict__ X, int64
 }
 
 template <int F, int R, bool TRIM, int V>
-__global__ __launch_bounds__(kBlock)
-// (the 169-wire sort takes 263 registers if left alone, one wave per SIMD: 1.01 instead of 0.74 ms
-// for 2 M coordinates)
-__attribute__((amdgpu_waves_per_eu(F == 169 && TRIM ? 2 : 1)))
-void fused_kernel(
+__global__ __launch_bounds__(kBlock) void fused_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const uint64_t *__restrict__ perm_off,
     const uint32_t *__restrict__ slots_per_file, AggWorkspace *ws, int trim_b,
     uint32_t *__restrict__ out) {

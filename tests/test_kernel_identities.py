@@ -206,3 +206,27 @@ def test_sorters_and_their_comparators_agree():
             got = gen_selnet.apply_network(gen_selnet.comparators((0, 1, 2), outputs), values)
             for w in range(3):
                 assert not outputs[w] or got[w] == sorted(values)[w], (outputs, values)
+
+
+@pytest.mark.parametrize("full_sort,sizes", [(False, gen_selnet.STREAMED_SIZES),
+                                             (True, gen_selnet.SORT_SIZES)])
+def test_every_changed_wire_is_pinned_before_the_next_file(full_sort, sizes):
+    for f in sizes:
+        most = gen_selnet.SORTERS_BETWEEN_PINS.get(f) if full_sort else None
+        changed, run, longest, total = set(), 0, 0, 0
+        for step in gen_selnet.streamed_sorters(f, full_sort):
+            if step[0] == "sort":
+                run += 1
+                total += 1
+                longest = max(longest, run)
+                changed |= {w for w, needed in zip(step[1], step[2]) if needed}
+            elif step[0] == "pin":
+                assert step[1] in changed, (f, step)
+                changed.remove(step[1])
+                if not changed:
+                    run = 0
+            else:  # the next file's share, or the end
+                assert not changed, (f, step, changed)
+                run = 0
+        assert total == len(gen_selnet.sorters_for(f, full_sort)), f
+        assert longest == most if most else longest > 0, (f, longest)
