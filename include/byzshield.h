@@ -219,10 +219,12 @@ int byz_trimmed_mean(const float *rows_base, int64_t d, int64_t ld, const int32_
  *              other vectors,
  *   the m vectors of lowest score are selected (equal scores: lower index first), 1 <= m <= f - c
  *   (m = 1 is Krum, m = f - c the usual Multi-Krum), and out = their coordinate-wise mean.
- * Arithmetic: the Gram matrix of the f rows is accumulated by fp32 matrix instructions over
- * 512 fixed coordinate slices and the slices are added in fp64 in a fixed order (results are
- * reproducible); distances d(i,j) = G_ii + G_jj - 2 G_ij, scores and ranking in fp64; the mean
- * is fp32, selected rows added one by one in ascending index from +0, one IEEE division by m.
+ * Arithmetic: the products of the Gram matrix of the f rows are taken and added by fp32 matrix
+ * instructions in runs of at most 128 coordinates, the runs of a wave are added in fp32, waves and
+ * up to 512 coordinate slices in fp64 (a slice is rounded to fp32 in between when there are more than
+ * 128), all in an order that f, d, ld and the rows' alignment fix (results are reproducible);
+ * distances d(i,j) = G_ii + G_jj - 2 G_ij, scores and ranking in fp64; the mean is fp32, selected
+ * rows added one by one in ascending index from +0, one IEEE division by m.
  *   rows_base / row_index_dev  as byz_median (f rows gathered through the index table)
  *   out           device [d] fp32
  *   selected_out  device [f] int32 out: 1 for the selected rows, else 0
@@ -250,8 +252,8 @@ int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld, const int32_t 
  *            the window grows one neighbour at a time, the lower one when
  *            (median - lower) <= (upper - median), both differences in fp32, or when no upper
  *            neighbour is left.
- * Arithmetic: distances as in byz_multi_krum (fp32 matrix instructions, fp64 reduction in a
- * fixed order), scores in fp64 added in ascending order; the mean is fp32, window values added
+ * Arithmetic: distances as in byz_multi_krum (fp32 matrix instructions, waves and slices added in
+ * fp64 in a fixed order), scores in fp64 added in ascending order; the mean is fp32, window values added
  * one by one in ascending order from +0, one IEEE division by float(beta).  Inputs with
  * non-finite values give NaN distances, for which phase 1 is not specified.
  *   selected_out  device [f] int32 out: 1 for the theta chosen rows, else 0
