@@ -8,7 +8,8 @@
 // The pairwise squared distances come from the Gram matrix G = W W^T of the f x d matrix of
 // winners: the one dense contraction of the whole path, done with fp32 MFMA tiles
 // (v_mfma_f32_16x16x4f32), only those on and above the diagonal of the symmetric matrix (f = 25
-// costs 3 tiles of 16x16 instead of one padded 32x32).  The waves walk the coordinates
+// costs 3 tiles of 16x16 instead of one padded 32x32), and v_mfma_f32_4x4x1f32 for a few rows behind
+// the last full tile.  The waves walk the coordinates
 // grid-stride.  Per-block partial tiles are added in fp64 in block order, so the result does not
 // depend on scheduling.
 #include <hip/hip_runtime.h>
@@ -40,9 +41,27 @@ constexpr int kMaxPairs = kMaxNT * (kMaxNT + 1) / 2;  // tiles on and above the 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// Row tiles of 16 the Gram matrix of f vectors is computed with; the tiles on and above the
-// diagonal are stored.
-__host__ __device__ constexpr int row_tiles(int f) { return (f + 15) / 16; }
+// How the Gram matrix of f vectors is cut: nt row tiles of 16, of which the 16x16 tiles on and above
+// the diagonal are computed, and `groups` groups of four rows behind them.  A group is multiplied with
+// all rows by 4x4x1 matrix instructions, four rows against 64 a time, a quarter of the cycles of a tile
+// for one coordinate of four: it costs one tile up to 64 rows and two above, a row tile with a few rows
+// in it costs nt + 1.  Two tiles saved or more pay; with seven row tiles (f = 105..108) one does, as the
+// kernel of seven spills.  Five and two groups (f = 85..88) would leave one wave per SIMD, up to 32 rows HBM
+// bounds the kernel.  Calls of Multi-Krum on 3 M coordinates, us, without / with groups: f = 33 131 / 112,
+// 49 190 / 165, 53 196 / 182, 65 275 / 245, 81 384 / 343, 97 494 / 431, 108 511 / 495, 113 659 / 537,
+// 120 259 / 220 (1 M); of 140 k, f = 49 34.6 / 32.2, 97 76.5 / 71.6.  (40 rows, two groups for three tiles: 60.3 /
+// 62.2 on 1 M; 60 rows, three for four: 208.6 / 203.7, short rows the same.)  The vector ALU instead of the
+// small matrix instructions costs the same a row and more from two rows on: the two do not overlap.
+__host__ __device__ constexpr int row_groups(int f) {
+    const int nt = f / 16, groups = (f % 16 + 3) / 4, saved = nt + 1 - groups * (f <= 64 ? 1 : 2);
+    return nt >= 2 && groups <= 3 && (saved >= 2 || (nt == 6 && saved >= 1)) && !(nt == 5 && groups == 2)
+               ? groups : 0;
+}
+__host__ __device__ constexpr int row_tiles(int f) { return row_groups(f) != 0 ? f / 16 : (f + 15) / 16; }
+// stored tiles of 256 values: the 16x16 ones, then every group's 4x64 ones
+__host__ __device__ constexpr int stored_tiles(int nt, int groups) {
+    return nt * (nt + 1) / 2 + groups * (nt < 4 ? 1 : 2);
+}
 
 // Tile (ti, tj), ti <= tj < nt, of the upper triangle, numbered row by row.
 __host__ __device__ constexpr int tile_pair(int nt, int ti, int tj) {
@@ -79,7 +98,34 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16.
+// Rows of a wave's stage: whole loads of 64 pieces of 16 bytes.
+__host__ __device__ constexpr int staged_rows(int nt, int groups, int sf) {
+    const int per_load = 64 / (kStep * sf / 4);
+    return (16 * nt + 4 * groups + per_load - 1) / per_load * per_load;
+}
+
+// Element e of the sixteen coordinates in y: run[g * kParts + c] (four rows of group g against the rows
+// 64c + lane) takes the products of the four quarters in ascending order, one rounding each.
+template <int NT, int NG, int kParts, int N>
+__device__ __forceinline__ void group_products(const f32x4 (&y)[kParts > 0 ? kParts : 1][4], int e, bool fresh,
+                                               f32x4 (&run)[N]) {
+    constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    // (cbsz 4 and abid name the block of four lanes that is A for all sixteen blocks; constants)
+#define BYZ_GROUP(g)                                                                                  \
+    if constexpr (NG > (g))                                                                           \
+        _Pragma("unroll") for (int q = 0; q < 4; ++q)                                                 \
+        _Pragma("unroll") for (int c = 0; c < kParts; ++c)                                            \
+            run[(g) * kParts + c] = __builtin_amdgcn_mfma_f32_4x4x1f32(                               \
+                y[kParts - 1][q][e], y[c][q][e], fresh && q == 0 ? zero : run[(g) * kParts + c], 4,   \
+                (4 * NT + (g)) % 16, 0);
+    BYZ_GROUP(0)
+    BYZ_GROUP(1)
+    BYZ_GROUP(2)
+#undef BYZ_GROUP
+}
+
+// Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16, NG =
+// groups of four rows behind them (row_groups).
 // A wave takes whole stretches of 32*SF coordinates of every row, so every word is loaded once
 // and no barrier stands between the loads and the matrix instructions.  Consecutive lanes load
 // consecutive words of a row; a pass through the wave's own
@@ -95,15 +141,19 @@ __device__ __forceinline__ void wave_fence() {
 // 8.9; bf16 matrix units on rows split in three parts 7.9 / 2.9 / 2.1 / 2.0.
 // Calls of Multi-Krum with rows on cache lines, us, in brackets with one running sum, a tile in LDS
 // shared by the block, two barriers a chunk and row tiles rounded up to 6 or 8 above 64 rows: 49 x
-// 11.2 M 660 (705), 80 x 3 M 308 (442), 128 x 3 M 697 (843); to f = 32, HBM-bound, the same (32 x 11.2 M
-// 355 and 352).  Matrix instructions bound it from f = 33 up: ten tiles at f = 49 are 365 us at the fp32
-// rate; the runs cost 3 % there (15 % with eight row tiles, where the sums fill the registers).
-template <int NT, int SF, bool LINES, bool SHORT>
+// 11.2 M 660 (705; with a group instead of a row tile 577), 80 x 3 M 308 (442), 128 x 3 M 697 (843); to
+// f = 32, HBM-bound, the same (32 x 11.2 M 355 and 352).  From f = 49 up matrix instructions and what little
+// the vector ALU does bound it together, as they share one datapath (six tiles and a group at f = 49: the
+// kernel takes 390 us, 344 with its loads left out, 322 with its products left out; more waves, longer
+// stretches or loads two steps ahead changed nothing); the runs cost 3 % there (15 % with eight row
+// tiles, where the sums fill the registers).
+template <int NT, int NG, int SF, bool LINES, bool SHORT>
 __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int64_t d, int64_t ld,
                                                 const int32_t *__restrict__ row_index, int f,
-                                                float *stage, f32x4 (&acc)[NT * (NT + 1) / 2]) {
-    constexpr int NP = NT * (NT + 1) / 2, kSpan = kStep * SF;
-    constexpr int kPieces = kSpan / 4, kRows = 64 / kPieces, kLoads = 16 * NT / kRows;
+                                                float *stage, f32x4 (&acc)[stored_tiles(NT, NG)]) {
+    constexpr int NP = NT * (NT + 1) / 2, NALL = stored_tiles(NT, NG), kSpan = kStep * SF;
+    constexpr int kPieces = kSpan / 4, kRows = 64 / kPieces, kLoads = staged_rows(NT, NG, SF) / kRows;
+    constexpr int kParts = NG == 0 ? 0 : (NALL - NP) / NG;  // stretches of 64 rows a group meets
     const int lane = threadIdx.x & 63;
     const int64_t n_spans = (d + kSpan - 1) / kSpan;
     constexpr int kWaves = gram_waves(NT, SF);
@@ -115,7 +165,7 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
     // repeat row f-1 (nothing reads their results), loads without a row are left out
     auto row_of = [&](int n) { return n * kRows + lane / kPieces; };
     auto piece_of = [&](int n) { return (lane % kPieces) ^ (row_of(n) & 7); };
-    auto used = [&](int n) { return n * kRows <= 16 * (NT - 1) || n * kRows < f; };
+    auto used = [&](int n) { return NG > 0 || n * kRows <= 16 * (NT - 1) || n * kRows < f; };
     const float *rowp[kLoads];
 #pragma unroll
     for (int n = 0; n < kLoads; ++n)
@@ -145,15 +195,19 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
     constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     constexpr int kRun = SF == 1 ? 3 : 2;           // stretches of a run
     constexpr int kRuns = SHORT ? (NP < 6 ? NP : 6) : NP;  // tiles whose runs are open at a time
-    f32x4 run[kRuns];
+    constexpr int kGroupRuns = NG > 0 ? NALL - NP : 1;
+    f32x4 run[kRuns], grun[kGroupRuns];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) acc[p] = zero;
+    for (int p = 0; p < NALL; ++p) acc[p] = zero;
     const int row = lane & 15;
     if (span < n_spans) fetch(span);
     while (span < n_spans) {
-        if constexpr (!SHORT)
+        if constexpr (!SHORT) {
 #pragma unroll
             for (int p = 0; p < NP; ++p) run[p] = zero;
+#pragma unroll
+            for (int p = 0; p < kGroupRuns; ++p) grun[p] = zero;
+        }
         for (int k = 0; k < kRun && span < n_spans; ++k, span += stride) {
             wave_fence();
 #pragma unroll
@@ -168,12 +222,27 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     x[t] = slots[(16 * t + row) * kPieces + (piece ^ (row & 7))];
+                // the groups' operand, both sides of it: lane l holds row l (and 64 + l); the
+                // instruction takes the four lanes of one group as A and all as B.  The order of
+                // the products is that of the 16x16 instruction, which multiplies the four
+                // quarters of the wave one after the other.
+                f32x4 y[NG > 0 ? kParts : 1][4];
+                if constexpr (NG > 0)
+#pragma unroll
+                    for (int c = 0; c < kParts; ++c)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int r = 64 * c + lane < 16 * NT + 4 * NG ? 64 * c + lane : 16 * NT;
+                            y[c][q] = slots[r * kPieces + ((8 * (h / 2) + 2 * q + h % 2) ^ (r & 7))];
+                        }
                 // lane l holds A[row = l%16][k = l/16], which is also B[k][col = l%16] of the
                 // transposed operand; tiles p0 .. p0 + kRuns - 1
 #pragma unroll
                 for (int p0 = 0; p0 < NP; p0 += kRuns) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (NG > 0)
+                            if (p0 == 0) group_products<NT, NG, kParts>(y, e, SHORT && e == 0, grun);
 #pragma unroll
                         for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
@@ -183,38 +252,45 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
                                 run[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(
                                     x[ti][e], x[tj][e], SHORT && e == 0 ? zero : run[p], 0, 0, 0);
                             }
+                    }
                     if constexpr (SHORT)
 #pragma unroll
                         for (int p = 0; p < kRuns && p0 + p < NP; ++p) acc[p0 + p] += run[p];
                 }
+                if constexpr (SHORT)
+#pragma unroll
+                    for (int p = NP; p < NALL; ++p) acc[p] += grun[p - NP];
             }
         }
-        if constexpr (!SHORT)
+        if constexpr (!SHORT) {
 #pragma unroll
             for (int p = 0; p < NP; ++p) acc[p] += run[p];
+#pragma unroll
+            for (int p = NP; p < NALL; ++p) acc[p] += grun[p - NP];
+        }
     }
 }
 
 // Partial Gram tiles of the rows row_index[0..f-1] over this block's coordinates.  partial:
-// [gridDim.x][pairs][256] values, position v*64 + lane, pairs = NT(NT+1)/2, fp32 or, where a few
+// [gridDim.x][tiles][256] values, position v*64 + lane, tiles = stored_tiles(NT, NG), fp32 or, where a few
 // blocks would leave their last roundings visible, fp64 (d = 2048: 8.9e-9 -> 4.9e-9 at f = 100).
-template <int NT, int SF, bool LINES, bool SHORT>
+template <int NT, int NG, int SF, bool LINES, bool SHORT>
 __global__ __launch_bounds__(64 * gram_waves(NT, SF))
 // (2: accumulators in ordinary registers; more row tiles would spill: 96 x 11.2 M 1502 us, 1362 with 1,
-// 80 x 11.2 M 998 and 1060)
-__attribute__((amdgpu_waves_per_eu(NT <= 5 || (NT == 6 && SHORT) ? 2 : 1)))
+// 80 x 11.2 M 998 and 1060; the same with groups, (5, 1) on long rows 41 registers)
+__attribute__((amdgpu_waves_per_eu(NG > 0 ? (NT <= 4 || (NT == 5 && SHORT) ? 2 : 1) : (NT <= 5 || (NT == 6 && SHORT) ? 2 : 1))))
 void gram_partial_kernel(
     const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
     float *__restrict__ partial, int in_fp64) {
-    constexpr int NP = NT * (NT + 1) / 2, kWaves = gram_waves(NT, SF);
-    constexpr int kStage = 16 * NT * kStep * SF;  // floats of one wave's stage
+    constexpr int NP = stored_tiles(NT, NG), kWaves = gram_waves(NT, SF);
+    constexpr int kStage = staged_rows(NT, NG, SF) * kStep * SF;  // floats of one wave's stage
     constexpr int kRoom = 16 * 1024 / (kWaves * kTile);  // tiles of every wave that 64 KB hold
     constexpr int kAtOnce = NP < kRoom ? NP : kRoom;
     constexpr int kRed = kWaves * kAtOnce * kTile;
     __shared__ __align__(16) float lds[kRed > kWaves * kStage ? kRed : kWaves * kStage];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     f32x4 acc[NP];
-    gram_accumulate<NT, SF, LINES, SHORT>(X, d, ld, row_index, f, lds + wave * kStage, acc);
+    gram_accumulate<NT, NG, SF, LINES, SHORT>(X, d, ld, row_index, f, lds + wave * kStage, acc);
     // the waves' tiles are added in wave order in fp64, as many tiles at a time as fit
 #pragma unroll
     for (int p0 = 0; p0 < NP; p0 += kAtOnce) {
@@ -264,7 +340,9 @@ __global__ __launch_bounds__(kBlock) void gram_reduce_kernel(const T *__restrict
 __device__ inline double gram_at(const double *gram, int f, int i, int j) {
     // entry (i, j) of the symmetric matrix from the stored upper-triangle tiles
     if (i > j) { const int t = i; i = j; j = t; }
-    const int nt = row_tiles(f);
+    const int nt = row_tiles(f), g = (j - 16 * nt) / 4;
+    if (j >= 16 * nt)  // row j of group g, column i
+        return gram[(nt * (nt + 1) / 2 + g * (nt < 4 ? 1 : 2) + i / 64) * kTile + j % 4 * 64 + i % 64];
     const int r = i % 16, c = j % 16;
     // row r = 4*(l/16) + v, column c = l%16  =>
     const int v = r % 4, l = c + 16 * (r / 4);
@@ -679,19 +757,19 @@ struct KrumWorkspace {
 };
 static_assert(offsetof(KrumWorkspace, partial) % sizeof(double) == 0, "partial tiles may be fp64");
 
-inline int stored_tiles(int f) { return row_tiles(f) * (row_tiles(f) + 1) / 2; }
+inline int stored_tiles(int f) { return stored_tiles(row_tiles(f), row_groups(f)); }
 
 // Blocks up to which partial tiles are fp64: a quarter of the grid they have room for in fp32.
 inline bool partials_in_fp64(int grid) { return grid <= kGramBlocks / 4; }
 
 inline size_t krum_workspace_bytes(int f) {
     // (callers know this size: beyond 64 vectors it has room for 6 or 8 row tiles, whatever is used)
-    const int nt = f <= 64 ? row_tiles(f) : (f <= 96 ? 6 : 8);
+    const int nt = f <= 64 ? (f + 15) / 16 : (f <= 96 ? 6 : 8);
     return offsetof(KrumWorkspace, partial) +
            sizeof(float) * (size_t)kGramBlocks * (nt * (nt + 1) / 2) * kTile;
 }
 
-template <int NT, int SF, bool LINES>
+template <int NT, int NG, int SF, bool LINES>
 void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
                        int f, float *partial, int *grid, hipStream_t s) {
     constexpr int kWaves = gram_waves(NT, SF);
@@ -706,35 +784,35 @@ void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int3
     const int in_fp64 = partials_in_fp64(*grid) ? 1 : 0;
     // up to four steps a wave; two steps of 32 at a time are taken on longer rows only
     if (SF == 1 && steps <= 4 * (int64_t)*grid)
-        gram_partial_kernel<NT, 1, LINES, SF == 1><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
+        gram_partial_kernel<NT, NG, 1, LINES, SF == 1><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
             rows_base, d, ld, row_index_dev, f, partial, in_fp64);
     else
-        gram_partial_kernel<NT, SF, LINES, false><<<*grid, 64 * kWaves, 0, s>>>(
+        gram_partial_kernel<NT, NG, SF, LINES, false><<<*grid, 64 * kWaves, 0, s>>>(
             rows_base, d, ld, row_index_dev, f, partial, in_fp64);
 }
 
-template <int NT, bool LINES>
+template <int NT, int NG, bool LINES>
 void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
                       int f, float *partial, int *grid, hipStream_t s) {
     // Long rows: two steps at a time up to 32 vectors (four steps per wave or fewer: one at a time
     // spreads them over more waves and partial sums).  Above, more registers and fewer waves cost more
     // than longer pieces of a row give, but for rows off the cache lines that are far larger than the
     // last-level cache (48 x 11.2 M 596 -> 584 us, 64 x 11.2 M 857 -> 804; 64 x 3 M 231 -> 232).
-    constexpr int SF = NT <= 2 || (NT <= 4 && !LINES) ? 2 : 1;
+    constexpr int SF = NT <= 2 || (NT + (NG > 0 ? 1 : 0) <= 4 && !LINES) ? 2 : 1;
     const int64_t one_at_a_time = (int64_t)1 << (NT <= 1 ? 20 : (NT <= 2 ? 19 : 22));
     if (SF > 1 && d > one_at_a_time)
-        launch_gram_spans<NT, SF, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_spans<NT, NG, SF, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     else
-        launch_gram_spans<NT, 1, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_spans<NT, NG, 1, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
 }
 
-template <int NT>
+template <int NT, int NG>
 int launch_gram_shape(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
                       int f, float *partial, int *grid, hipStream_t s) {
     if (((uintptr_t)rows_base & 127u) == 0 && ld % 32 == 0)
-        launch_gram_rows<NT, true>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_rows<NT, NG, true>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     else
-        launch_gram_rows<NT, false>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_rows<NT, NG, false>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
@@ -743,15 +821,18 @@ int launch_gram_shape(const float *rows_base, int64_t d, int64_t ld, const int32
 int launch_gram(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev, int f,
                 KrumWorkspace *ws, hipStream_t s) {
     int rc, grid = 0;
-    switch (row_tiles(f)) {
-        case 1: rc = launch_gram_shape<1>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
-        case 2: rc = launch_gram_shape<2>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
-        case 3: rc = launch_gram_shape<3>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
-        case 4: rc = launch_gram_shape<4>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
-        case 5: rc = launch_gram_shape<5>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
-        case 6: rc = launch_gram_shape<6>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
-        case 7: rc = launch_gram_shape<7>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
-        default: rc = launch_gram_shape<8>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s); break;
+    switch (4 * row_tiles(f) + row_groups(f)) {
+#define BYZ_GRAM_SHAPE(nt, ng)                                                                       \
+    case 4 * (nt) + (ng):                                                                            \
+        rc = launch_gram_shape<nt, ng>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s);   \
+        break;
+        BYZ_GRAM_SHAPE(1, 0) BYZ_GRAM_SHAPE(2, 0) BYZ_GRAM_SHAPE(3, 0) BYZ_GRAM_SHAPE(4, 0)
+        BYZ_GRAM_SHAPE(5, 0) BYZ_GRAM_SHAPE(6, 0) BYZ_GRAM_SHAPE(7, 0) BYZ_GRAM_SHAPE(8, 0)
+        BYZ_GRAM_SHAPE(2, 1) BYZ_GRAM_SHAPE(3, 1) BYZ_GRAM_SHAPE(3, 2) BYZ_GRAM_SHAPE(4, 1) BYZ_GRAM_SHAPE(5, 1)
+        BYZ_GRAM_SHAPE(6, 1) BYZ_GRAM_SHAPE(6, 2) BYZ_GRAM_SHAPE(6, 3)
+        BYZ_GRAM_SHAPE(7, 1) BYZ_GRAM_SHAPE(7, 2) BYZ_GRAM_SHAPE(7, 3)
+#undef BYZ_GRAM_SHAPE
+        default: return BYZ_EINTERNAL;
     }
     if (rc != BYZ_OK) return rc;
     const int ntiles = stored_tiles(f);

@@ -802,6 +802,28 @@ def test_gram_of_whole_numbers_is_exact(f, d):
             assert torch.equal(dist, want), (f, d, ld)
 
 
+@pytest.mark.parametrize("f", [33, 36, 37, 50, 52, 53, 56, 57, 68, 69, 84, 85, 100, 104, 105, 108, 109, 116, 120, 121, 124, 125])
+def test_gram_of_rows_in_groups_of_four(f):
+    # every number of groups behind the row tiles, full and with one row, and the first f without: whole
+    # numbers are exact, and a row of the last four that repeats row 1, 17 or its neighbour has the
+    # repeated row's distances to the bit (the groups' matrix instructions add in the tiles' order)
+    rng = np.random.default_rng(f)
+    order = np.arange(f, dtype=np.int32)
+    for d, ld in ((1, 3), (35, 64), (1027, 1056), (20011, 20011), (150011, 150016)):
+        Xh = rng.integers(-1, 2, size=(f, ld)).astype(np.float32)
+        got = _krum_distances(Xh, d, order)
+        G = Xh[:, :d] @ Xh[:, :d].T
+        n = np.diag(G)
+        assert np.array_equal(got, (n[:, None] + n[None, :] - 2 * G).astype(np.float64)), (f, d)
+        Xh = rng.standard_normal((f, ld)).astype(np.float32)
+        last, same = f - 1 - int(rng.integers(0, 3)), int(rng.choice([1, 17, f - 5]))
+        Xh[last] = Xh[same]
+        got = _krum_distances(Xh, d, order)
+        assert got[last, same] == 0 and np.array_equal(got, got.T), (f, d)
+        rest = np.delete(order, [last, same])
+        assert np.array_equal(got[last, rest], got[same, rest]), (f, d, last, same)
+
+
 NETWORKS = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)
 
 
