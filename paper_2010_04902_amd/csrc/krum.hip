@@ -502,186 +502,158 @@ __device__ __forceinline__ void argmin_exchange(double &score, int &best) {
     }
 }
 
+// quad_perm [1,0,3,2]: lane ^ 1; quad_perm [2,3,0,1]: lane ^ 2; row_half_mirror: the other quad of the
+// 8; row_mirror: the other half of the 16
+constexpr int kDppPairs[4] = {0xB1, 0x4E, 0x141, 0x140};
+
+// The smallest of the wave's 64 values, in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+    auto lower = [](uint32_t a, int b) { return a < (uint32_t)b ? a : (uint32_t)b; };
+    v = lower(v, __builtin_amdgcn_update_dpp(0, (int)v, kDppPairs[0], 0xF, 0xF, false));
+    v = lower(v, __builtin_amdgcn_update_dpp(0, (int)v, kDppPairs[1], 0xF, 0xF, false));
+    v = lower(v, __builtin_amdgcn_update_dpp(0, (int)v, kDppPairs[2], 0xF, 0xF, false));
+    v = lower(v, __builtin_amdgcn_update_dpp(0, (int)v, kDppPairs[3], 0xF, 0xF, false));
+    uint32_t least = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
+#pragma unroll
+    for (int row = 1; row < 4; ++row) least = lower(least, __builtin_amdgcn_readlane((int)v, 16 * row));
+    return least;
+}
+
+// Lowest (score, lane) of the wave.  Scores are sums of distances from +0, never negative, so
+// without NaNs their bit patterns are in the order of the values: the lowest upper half, the lowest lower
+// half that comes with it, the first lane that has both.  With a NaN anywhere: comparisons as they
+// fall, four exchanges inside each row of 16 lanes, then the four rows from their first lanes.
+__device__ __forceinline__ void wave_argmin(double score, int i, double &w_score, int &w_best) {
+    if (__builtin_amdgcn_ballot_w64(score != score) == 0) {
+        const uint32_t hi = (uint32_t)__double2hiint(score), lo = (uint32_t)__double2loint(score);
+        const uint32_t least_hi = wave_min(hi);
+        const uint32_t least_lo = wave_min(hi == least_hi ? lo : 0xFFFFFFFFu);
+        const uint64_t here = __builtin_amdgcn_ballot_w64(hi == least_hi && lo == least_lo);
+        w_score = __hiloint2double((int)least_hi, (int)least_lo);
+        w_best = __builtin_amdgcn_readfirstlane(i) + (int)__builtin_ctzll(here);
+        return;
+    }
+    int best = i;
+    argmin_exchange<kDppPairs[0]>(score, best);
+    argmin_exchange<kDppPairs[1]>(score, best);
+    argmin_exchange<kDppPairs[2]>(score, best);
+    argmin_exchange<kDppPairs[3]>(score, best);
+    w_score = lane_value(score, 0);
+    w_best = __builtin_amdgcn_readlane(best, 0);
+#pragma unroll
+    for (int row = 1; row < 4; ++row) {
+        const double r_score = lane_value(score, 16 * row);
+        const int r_best = __builtin_amdgcn_readlane(best, 16 * row);
+        if (r_score < w_score || (r_score == w_score && r_best < w_best)) {
+            w_score = r_score;
+            w_best = r_best;
+        }
+    }
+}
+
 // First phase of Bulyan: Krum applied again and again to the vectors not yet chosen, until
 // theta = f - 2c are chosen.  Round with n' vectors left: score(i) = the n' - c - 2 smallest
 // distances from i to the other vectors left, added one by one in ascending order (no terms
 // when that count is <= 0); lowest score wins, lowest index among equal scores.
-// One wave with lane i = vector i, on the sorted rows distance_rows_kernel left.  The lane keeps
-// its sorted row in registers and, as a 64-bit mask over the positions of that row, the terms
-// of its next score.  A vector left has n' - 1 others left and takes n' - c - 2 of them, so the
-// terms are the others left without the c + 1 farthest; choosing a vector removes it from
-// every row: where it was a term the mask just loses it, elsewhere it was one of the c + 1
-// farthest and the farthest term takes its place there.  A score is then one walk over the
-// mask, and the winner is the lowest (score, index) of the wave.
-__global__ __launch_bounds__(64) void bulyan_select_kernel(const double *__restrict__ sorted_dist,
-                                                           const uint8_t *__restrict__ sorted_nbr,
-                                                           int f, int c, int32_t *selected_out,
-                                                           int32_t *order_out,
-                                                           int32_t *selected_list,
-                                                           int32_t *n_selected,
-                                                           const int32_t *__restrict__ row_index,
-                                                           int32_t *selected_rows) {
-    __shared__ uint8_t s_pos[BYZ_MAX_F * 64];  // [j*64 + i]: where vector j stands in i's row
-    const int i = threadIdx.x;
-    if (i < f) selected_out[i] = 0;
-    const int theta = f - 2 * c;
-    const int32_t my_row = row_index[i < f ? i : 0];  // a round then needs no load from memory
-    int32_t first_row = my_row;
-    // entries the set-up did not write are loaded and set aside
-    constexpr int kMaxOthers = BYZ_MAX_F - 1;
-    double rdist[kMaxOthers];
-#pragma unroll
-    for (int t = 0; t < kMaxOthers; ++t) {
-        const bool have = i < f && t < f - 1;
-        const double dv = sorted_dist[t * kRowStride + i];
-        const uint32_t nv = sorted_nbr[t * kRowStride + i];
-        rdist[t] = have ? dv : 0.0;
-        if (have) s_pos[nv * 64 + i] = (uint8_t)t;
-    }
-    __syncthreads();
-    bool left = i < f;  // not chosen yet
-    uint64_t terms = left ? ((1ull << (f - c - 2)) - 1ull) : 0ull;  // f - c - 2 <= 62
-    for (int round = 0; round < theta; ++round) {
-        double score = left ? 0.0 : __builtin_huge_val();
-        bool done = __builtin_amdgcn_ballot_w64(terms != 0) == 0;
-#pragma unroll
-        for (int t0 = 0; t0 < kMaxOthers; t0 += 8) {
-            if (!done && t0 < f - 1) {
-#pragma unroll
-                for (int t = t0; t < t0 + 8 && t < kMaxOthers; ++t)
-                    score += ((terms >> t) & 1ull) != 0 ? rdist[t] : 0.0;
-                if (t0 + 8 < 64) done = __builtin_amdgcn_ballot_w64((terms >> (t0 + 8)) != 0) == 0;
-            }
-        }
-        // lowest (score, index) of the wave: four exchanges inside each row of 16 lanes, then
-        // the four rows are compared from their first lanes
-        int best = i;
-        argmin_exchange<0xB1>(score, best);   // quad_perm [1,0,3,2]: lane ^ 1
-        argmin_exchange<0x4E>(score, best);   // quad_perm [2,3,0,1]: lane ^ 2
-        argmin_exchange<0x141>(score, best);  // row_half_mirror: the other quad of the 8
-        argmin_exchange<0x140>(score, best);  // row_mirror: the other half of the 16
-        {
-            double w_score = lane_value(score, 0);
-            int w_best = __builtin_amdgcn_readlane(best, 0);
-#pragma unroll
-            for (int row = 1; row < 4; ++row) {
-                const double r_score = lane_value(score, 16 * row);
-                const int r_best = __builtin_amdgcn_readlane(best, 16 * row);
-                if (r_score < w_score || (r_score == w_score && r_best < w_best)) {
-                    w_score = r_score;
-                    w_best = r_best;
-                }
-            }
-            best = w_best;
-        }
-        const int32_t best_row = __shfl(my_row, best, 64);
-        if (round == 0) first_row = best_row;
-        if (i == 0) {
-            selected_list[round] = best;
-            selected_rows[round] = best_row;
-            selected_out[best] = 1;
-            if (order_out != nullptr) order_out[round] = best;
-        }
-        if (i == best) {
-            left = false;
-            terms = 0;
-        } else if (left) {
-            const uint64_t bit = 1ull << s_pos[best * 64 + i];
-            if ((terms & bit) != 0)
-                terms &= ~bit;
-            else if (terms != 0)
-                terms &= ~(1ull << (63 - __builtin_clzll(terms)));
-        }
-    }
-    // rows of the chosen vectors for the second phase; the spare entries of the whole table
-    // (the second phase's network may have more wires than this kernel has lanes) repeat the
-    // first one
-    for (int e = i; e < kMaxKrum; e += 64)
-        if (e >= theta) selected_rows[e] = first_row;
-    if (i == 0) *n_selected = theta;
-}
+// One thread per vector, WAVES = 1 up to 64 vectors and 2 up to 128, on the sorted rows
+// distance_rows_kernel left.  A vector left has n' - 1 others left and takes n' - c - 2 of them, so its
+// terms are the others left without the c + 1 farthest; choosing a vector removes it from every row:
+// where it was a term the row loses it, elsewhere it was one of the c + 1 farthest and the farthest
+// term takes its place there.  So only the first f - c - 2 of a row are ever terms.  They sit in LDS, a
+// column per vector, and a term that goes is overwritten with zero: a score is a walk of plain
+// additions over the column, as x + 0 is x, with no test per position.  Which positions are still
+// terms is a mask of 64 * WAVES bits, for the farthest one and for the end of the walk.
+// Bound by latencies: per round the walk's chain of additions, the search, and the look where the
+// chosen vector stands in each row.  Calls of Bulyan on 10 k coordinates,
+// us, with a test per position on rows in registers (f <= 64) or in LDS / this: f = 25 42.7 / 30.8, 49 67.8 /
+// 46.9, 63 87 / 60, 65 175 / 78, 101 327 / 119, 127 503 / 164.
+// The other waves of the block only help to fill LDS.
+// Dynamic LDS: select_terms(f, c) * 64 * WAVES doubles, pairs of positions next to each other, then f * 64 *
+// WAVES bytes.
+constexpr int kSelectThreads = 512;
+__host__ __device__ constexpr int select_terms(int f, int c) { return (f - c - 2 + 15) / 16 * 16; }
 
-// The same rounds for 64 < f <= kMaxKrum: one block of kMaxKrum threads, thread i = vector i.
-// The sorted rows do not fit registers and stay in LDS ([t*kRowStride + i], read once per
-// position of a walk), a vector's terms are a 128-bit mask, and the winner is the lower of the
-// two waves' winners.  Dynamic LDS: (f-1)*kRowStride doubles, then kMaxKrum*kRowStride bytes.
-__global__ __launch_bounds__(kMaxKrum) void bulyan_select_wide_kernel(
+template <int WAVES>
+__global__ __launch_bounds__(kSelectThreads) void bulyan_select_kernel(
     const double *__restrict__ sorted_dist, const uint8_t *__restrict__ sorted_nbr, int f, int c,
     int32_t *selected_out, int32_t *order_out, int32_t *selected_list, int32_t *n_selected,
     const int32_t *__restrict__ row_index, int32_t *selected_rows) {
-    extern __shared__ double s_rows[];
-    uint8_t *s_pos = reinterpret_cast<uint8_t *>(s_rows + (f - 1) * kRowStride);  // [j*kRowStride + i]
-    __shared__ double s_wave_score[kMaxKrum / 64];
-    __shared__ int s_wave_best[kMaxKrum / 64];
-    __shared__ int32_t s_row_of[kMaxKrum];
-    const int i = threadIdx.x;
-    const int theta = f - 2 * c;
-    if (i < f) selected_out[i] = 0;
-    s_row_of[i] = row_index[i < f ? i : 0];
-    for (int t = 0; t < f - 1; ++t) {
-        if (i < f) {
-            s_rows[t * kRowStride + i] = sorted_dist[t * kRowStride + i];
-            s_pos[sorted_nbr[t * kRowStride + i] * kRowStride + i] = (uint8_t)t;
-        }
+    constexpr int S = 64 * WAVES, kFillers = kSelectThreads / S;
+    typedef double f64x2 __attribute__((ext_vector_type(2)));
+    extern __shared__ __align__(16) double s_rows[];
+    __shared__ double s_wave_score[2][WAVES];
+    __shared__ int s_wave_best[2][WAVES];
+    __shared__ int32_t s_row_of[S];
+    const int i = threadIdx.x % S, filler = threadIdx.x / S;
+    const int theta = f - 2 * c, n_terms = f - c - 2, walk = select_terms(f, c);
+    uint8_t *s_pos = reinterpret_cast<uint8_t *>(s_rows + walk * S);  // [j*S + i]: where vector j stands in i's row
+    auto place = [&](int t) { return (t / 2 * S + i) * 2 + t % 2; };
+#pragma unroll 8
+    for (int t = filler; t < walk; t += kFillers)
+        s_rows[place(t)] = t < n_terms && i < f ? sorted_dist[t * kRowStride + i] : 0.0;
+#pragma unroll 8
+    for (int t = filler; t < f - 1; t += kFillers)
+        if (i < f) s_pos[sorted_nbr[t * kRowStride + i] * S + i] = (uint8_t)t;
+    if (filler == 0) {
+        s_row_of[i] = row_index[i < f ? i : 0];
+        if (i < f) selected_out[i] = 0;
     }
     __syncthreads();
+    if (filler != 0) return;  // whole waves
     bool left = i < f;  // not chosen yet
-    // the f - c - 2 <= 125 nearest: bits 0..63 in lo, 64.. in hi
-    const int k0 = f - c - 2;
-    uint64_t lo = !left ? 0ull : (k0 >= 64 ? ~0ull : ((1ull << k0) - 1ull));
-    uint64_t hi = !left || k0 <= 64 ? 0ull : ((1ull << (k0 - 64)) - 1ull);
+    uint64_t lo = !left ? 0ull : (n_terms >= 64 ? ~0ull : (1ull << n_terms) - 1ull);  // positions 0..63
+    uint64_t hi = !left || n_terms <= 64 ? 0ull : (1ull << (n_terms - 64)) - 1ull;    // 64..
     int32_t first_row = 0;
+    const f64x2 *column = reinterpret_cast<const f64x2 *>(s_rows) + i;
     for (int round = 0; round < theta; ++round) {
-        double score = left ? 0.0 : __builtin_huge_val();
-        for (int t0 = 0; t0 < f - 1; t0 += 8) {
-            const uint64_t rest = t0 < 64 ? ((lo >> t0) | hi) : (hi >> (t0 - 64));
-            if (__builtin_amdgcn_ballot_w64(rest != 0) == 0) break;  // this wave has its terms
+        double score = 0.0;
+        f64x2 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = column[u * S];
+        for (int t0 = 0;; t0 += 16) {
+            // has any vector of this wave terms further on?
+            const int on = t0 + 16;
+            const uint64_t rest = on < 64 ? ((lo >> on) | hi) : (on < 128 ? hi >> (on - 64) : 0ull);
+            const bool more = __builtin_amdgcn_ballot_w64(rest != 0) != 0;
+            f64x2 y[8];
+            if (more) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) y[u] = column[(on / 2 + u) * S];
+            }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int t = t0 + u;  // the same for the whole block
-                if (t < f - 1) {
-                    const uint64_t word = t < 64 ? lo : hi;
-                    const double x = s_rows[t * kRowStride + i];
-                    score += ((word >> (t & 63)) & 1ull) != 0 ? x : 0.0;
-                }
+                score += x[u][0];
+                score += x[u][1];
             }
-        }
-        int best = i;
-        argmin_exchange<0xB1>(score, best);   // quad_perm [1,0,3,2]: lane ^ 1
-        argmin_exchange<0x4E>(score, best);   // quad_perm [2,3,0,1]: lane ^ 2
-        argmin_exchange<0x141>(score, best);  // row_half_mirror: the other quad of the 8
-        argmin_exchange<0x140>(score, best);  // row_mirror: the other half of the 16
-        double w_score = lane_value(score, 0);
-        int w_best = __builtin_amdgcn_readlane(best, 0);
+            if (!more) break;
 #pragma unroll
-        for (int row = 1; row < 4; ++row) {
-            const double r_score = lane_value(score, 16 * row);
-            const int r_best = __builtin_amdgcn_readlane(best, 16 * row);
-            if (r_score < w_score || (r_score == w_score && r_best < w_best)) {
-                w_score = r_score;
-                w_best = r_best;
+            for (int u = 0; u < 8; ++u) x[u] = y[u];
+        }
+        if (!left) score = __builtin_huge_val();
+        double w_score;
+        int best;
+        wave_argmin(score, i, w_score, best);
+        if constexpr (WAVES > 1) {
+            const int side = round & 1;  // a round's winners are read while the next one's are written
+            if ((i & 63) == 0) {
+                s_wave_score[side][i >> 6] = w_score;
+                s_wave_best[side][i >> 6] = best;
             }
-        }
-        if ((i & 63) == 0) {
-            s_wave_score[i >> 6] = w_score;
-            s_wave_best[i >> 6] = w_best;
-        }
-        __syncthreads();
-        best = s_wave_best[0];
-        {
-            double b_score = s_wave_score[0];
+            __syncthreads();
+            double b_score = s_wave_score[side][0];
+            best = s_wave_best[side][0];
 #pragma unroll
-            for (int w = 1; w < kMaxKrum / 64; ++w) {
-                const double o_score = s_wave_score[w];
-                const int o_best = s_wave_best[w];
+            for (int w = 1; w < WAVES; ++w) {
+                const double o_score = s_wave_score[side][w];
+                const int o_best = s_wave_best[side][w];
                 if (o_score < b_score || (o_score == b_score && o_best < best)) {
                     b_score = o_score;
                     best = o_best;
                 }
             }
         }
+        const int p = s_pos[best * S + i];
         const int32_t best_row = s_row_of[best];
-        __syncthreads();  // the waves' winners are read before the next round replaces them
         if (round == 0) first_row = best_row;
         if (i == 0) {
             selected_list[round] = best;
@@ -693,20 +665,19 @@ __global__ __launch_bounds__(kMaxKrum) void bulyan_select_wide_kernel(
             left = false;
             lo = 0;
             hi = 0;
-        } else if (left) {
-            const int p = s_pos[best * kRowStride + i];
-            const uint64_t bit = 1ull << (p & 63);
-            uint64_t &word = p < 64 ? lo : hi;
-            if ((word & bit) != 0)
-                word &= ~bit;
-            else if (hi != 0)
-                hi &= ~(1ull << (63 - __builtin_clzll(hi)));
-            else if (lo != 0)
-                lo &= ~(1ull << (63 - __builtin_clzll(lo)));
+        } else if (left && (lo | hi) != 0) {
+            const bool is_term = ((p < 64 ? lo >> p : hi >> (p - 64)) & 1ull) != 0;
+            const int gone = is_term ? p : (hi != 0 ? 127 - __builtin_clzll(hi) : 63 - __builtin_clzll(lo));
+            const uint64_t bit = 1ull << (gone & 63);
+            lo &= gone < 64 ? ~bit : ~0ull;
+            hi &= gone < 64 ? ~0ull : ~bit;
+            s_rows[place(gone)] = 0.0;
         }
     }
-    // rows of the chosen vectors for the second phase; the spare entries repeat the first one
-    if (i >= theta) selected_rows[i] = first_row;
+    // rows of the chosen vectors for the second phase; the spare entries of the whole table
+    // (the second phase's network may have more wires than there are vectors) repeat the first one
+    for (int e = i; e < kMaxKrum; e += S)
+        if (e >= theta) selected_rows[e] = first_row;
     if (i == 0) *n_selected = theta;
 }
 
@@ -919,14 +890,15 @@ extern "C" int byz_bulyan(const float *rows_base, int64_t d, int64_t ld,
     rc = launch_distance_rows(f, -1, dist_out, nullptr, ws, s);
     if (rc != BYZ_OK) return rc;
     if (f <= BYZ_MAX_F) {
-        bulyan_select_kernel<<<1, 64, 0, s>>>(ws->sorted_dist, ws->sorted_nbr, f, c, selected_out,
-                                              order_out, ws->selected_list, &ws->n_selected,
-                                              row_index_dev, ws->selected_rows);
+        const size_t lds = (size_t)select_terms(f, c) * 64 * sizeof(double) + (size_t)f * 64;
+        bulyan_select_kernel<1><<<1, kSelectThreads, lds, s>>>(
+            ws->sorted_dist, ws->sorted_nbr, f, c, selected_out, order_out, ws->selected_list,
+            &ws->n_selected, row_index_dev, ws->selected_rows);
     } else {
-        const size_t lds = (size_t)(f - 1) * kRowStride * sizeof(double) + (size_t)kMaxKrum * kRowStride;
-        BYZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&bulyan_select_wide_kernel),
+        const size_t lds = (size_t)select_terms(f, c) * 128 * sizeof(double) + (size_t)f * 128;
+        BYZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&bulyan_select_kernel<2>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        bulyan_select_wide_kernel<<<1, kMaxKrum, lds, s>>>(
+        bulyan_select_kernel<2><<<1, kSelectThreads, lds, s>>>(
             ws->sorted_dist, ws->sorted_nbr, f, c, selected_out, order_out, ws->selected_list,
             &ws->n_selected, row_index_dev, ws->selected_rows);
     }

@@ -824,6 +824,42 @@ def test_gram_of_rows_in_groups_of_four(f):
         assert np.array_equal(got[last, rest], got[same, rest]), (f, d, last, same)
 
 
+def _bulyan_order(dist, c):
+    """Bulyan's first phase on given distances: terms added one by one in ascending order, lowest index on ties."""
+    f = len(dist)
+    left, order = list(range(f)), []
+    for _ in range(f - 2 * c):
+        scores = []
+        for i in left:
+            near = sorted(dist[i, j] for j in left if j != i)[:max(0, len(left) - c - 2)]
+            total = 0.0
+            for v in near:
+                total += v
+            scores.append((total, i))
+        best = min(scores)[1]
+        order.append(best)
+        left.remove(best)
+    return order
+
+
+@pytest.mark.parametrize("f,c", [(3, 0), (7, 1), (18 + 1, 1), (19, 0), (35, 1), (35, 2), (51, 1), (63, 0), (63, 13), (65, 1),
+                                 (67, 1), (67, 0), (69, 1), (83, 1), (127, 0), (127, 1), (127, 31)])
+def test_bulyan_selection_on_the_returned_distances(f, c):
+    # f - c - 2 terms around whole stretches of sixteen, 64 and the widest; whole numbers, so that equal
+    # distances and equal scores abound, and ordinary rows; an infinite row comes last
+    rng = np.random.default_rng(f * 100 + c)
+    for kind in range(3):
+        Xh = rng.integers(-1, 2, size=(f, 40)).astype(np.float32) if kind == 0 else \
+            rng.standard_normal((f, 40)).astype(np.float32)
+        if kind == 2:
+            Xh[f // 2, 3] = 3e30  # its distances are infinite
+        out, sel, order, dist = B.byz_bulyan(torch.tensor(Xh, device=DEV), 40, torch.arange(f, dtype=torch.int32, device=DEV), c)
+        torch.cuda.synchronize()
+        want = _bulyan_order(dist.cpu().numpy(), c)
+        assert order.cpu().tolist() == want, (f, c, kind)
+        assert sorted(np.nonzero(sel.cpu().numpy())[0].tolist()) == sorted(want), (f, c, kind)
+
+
 NETWORKS = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)
 
 
