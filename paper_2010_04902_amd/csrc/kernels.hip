@@ -97,7 +97,8 @@ constexpr int vec_for_pass(int f, int r, bool trim) {
     return ((r >= 5 || (trim && f > 35)) && f <= 49) ? 2 : vec_for(f);
 }
 // Rows up to which the single pass runs one word per thread whatever the network, with more files
-// in flight (8 ahead for three copies, 5 for five or seven): with fewer threads than fill the chip
+// in flight (8 ahead for three copies, 5 for five or seven) where launch_short has no room for it or
+// early-majority mode rules it out: with fewer threads than fill the chip
 // the walk over the files is bound by the latency of its loads.  us a call, four or two words and
 // one: (25,3) d = 100003 21.6 / 18.4, 262000 23.5 / 28.0; (49,3) 131072 32.4 / 27.8; (49,7) 131072
 // 51.2 / 46.0; (25,5) 20000 25.8 / 23.5, 131072 25.5 / 26.6.  Depths, us of GPU time, 4 and 3 ahead / 5 and
@@ -107,6 +108,9 @@ constexpr int vec_for_pass(int f, int r, bool trim) {
 // a block merges its bits with no other ((25,3) d = 1003, us of GPU time, median 14.4, one word 15.2,
 // early-majority 16.0 and 18.3; (25,5) 500 17.4 and 20.5).
 [[maybe_unused]] constexpr int64_t short_row(int f, int r) { return f <= 25 && r == 5 ? 65536 : 131072; }
+// Files ahead of the one in use in the first kernel of short calls: the depths measured above, as far as
+// registers allow.
+constexpr int short_pass_ahead(int f, int r) { return r == 3 ? (f <= 81 ? 20 : 8) : 5; }
 constexpr int kProbe = 256;  // sampled coordinates of the probe (512: 2x slower)
 constexpr int kProbeSplit = 4;  // the files are dealt out to this many groups of kProbe threads
 constexpr int kProbeThreads = kProbe * kProbeSplit;
@@ -381,7 +385,8 @@ struct AggWorkspace {
     // network from a slot that differed from slot p on that wave's coordinates
     uint32_t pneq[kWide];
     uint32_t pair_neq[kWide];        // two-step path and re-vote: all pair bits, replica numbering
-    // byte offsets row*ld*4 of a file's rows, probable winner's class first
+    // byte offsets row*ld*4 of a file's rows, probable winner's class first; in a call on short rows the
+    // blocks' slots instead (short_pass_kernel)
     uint64_t perm_off[kWide * kRowStride];
     // bits 3p..3p+2: replica in slot p; bits 24..27: slots of the file that hold a copy of their
     // own (r, or r' for a file read in early-majority mode; the other slots repeat slot 0)
@@ -1466,6 +1471,139 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(
         fused_body<F, R, R, TRIM, V>(X, d, ld, perm_off, ws, trim_b, out);
 }
 
+// The call on short rows in two kernels that need nothing cleared before them: instead of merging their bits
+// into shared words by atomics, the blocks of the first write them to a slot each, and every block of the
+// second adds the slots up and decides for itself.  Four kernels one after the other (clear and lay
+// out, pass, decide, gated median) cost 14 us of launches and waits whatever d is; the figures of both
+// forms stand at launch_short.
+// Slots sit where the long form keeps its row offsets: one to four bytes per file, whole 16-byte pieces.
+constexpr int slot_bits(int r) { return r == 3 ? 8 : (r == 5 ? 16 : 32); }  // of the r(r-1)/2 + r used
+constexpr int slot_words(int f, int r) { return (f * slot_bits(r) + 127) / 128 * 4; }
+constexpr int most_slots(int f, int r) {
+    return (int)(sizeof(AggWorkspace::perm_off) / 4) / slot_words(f, r);
+}
+
+// First kernel: fused_body's walk over every copy.
+template <int F, int R, bool TRIM, int V, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void short_pass_kernel(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
+    uint32_t *__restrict__ slots, int trim_b, uint32_t *__restrict__ out) {
+    constexpr int NS = R, kBits = slot_bits(R), kWords = slot_words(F, R);
+    __shared__ uint32_t s_bits[kWords];
+    for (int t = threadIdx.x; t < kWords; t += BLOCK) s_bits[t] = 0;
+    const int lane = threadIdx.x & 63;
+    const int64_t n_thr = (d + V - 1) / V;
+    const int64_t gt = (int64_t)tile_of_block(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
+    const int64_t c0 = (gt + 1) * V <= d ? gt * V : d - V;  // as in fused_body
+    const uint32_t voff = (uint32_t)(c0 * 4);
+    uint32_t flags[(F + 63) / 64] = {};
+    const char *Xb = reinterpret_cast<const char *>(X);
+    uint32_t key[V][F];
+    constexpr int kAhead = V == 1 ? short_pass_ahead(F, R) : prefetch_depth(F, NS);
+    uint32_t stage[kAhead + 1][NS][V];
+    uint32_t o[V];
+#define BYZ_S_ROW_ADDR(j, k) \
+    (Xb + (uint64_t)(uint32_t)file_rows[(j) * R + (k)] * (uint64_t)ld * 4u + voff)
+    if constexpr (!TRIM) {
+#include "selnet_pin_on.inc"
+#include "generated/selnet_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+    } else {
+#include "selnet_pin_on.inc"
+#include "generated/selnet_sort_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+        trimmed_mean_of_sorted<F, V, true>(key, F, trim_b, o);
+    }
+#undef BYZ_S_ROW_ADDR
+    if (gt < n_thr) store_vec<V>(out + c0, o);
+    __syncthreads();  // s_bits is clear
+#pragma unroll
+    for (int w = 0; w < (F + 63) / 64; ++w) {
+        const int bit = (64 * w + lane) * kBits;
+        if (64 * w + lane < F && flags[w] != 0) atomicOr(&s_bits[bit / 32], flags[w] << (bit % 32));
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < kWords; t += BLOCK) slots[(int64_t)blockIdx.x * kWords + t] = s_bits[t];
+}
+
+// Second kernel: the decision of single_pass_decide_kernel in every block, then, where it
+// asks for it, the median or trimmed mean of the winners' rows again.  Block 0 writes what the caller gets.
+template <int F, int R, bool TRIM, int V>
+__global__ __launch_bounds__(kBlock) void short_decide_kernel(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
+    AggWorkspace *ws, int n_slots, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out) {
+    constexpr int kBits = slot_bits(R), kWords = slot_words(F, R), kPieces = kWords / 4;
+    static_assert(R * (R - 1) / 2 + R <= kBits && kPieces <= kBlock && F <= kBlock, "a file's bits, a thread a piece and a file");
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __shared__ uint32_t s_bits[kWords];
+    __shared__ uint32_t s_redo;
+    __shared__ int32_t s_row[F];
+    for (int t = threadIdx.x; t < kWords; t += kBlock) s_bits[t] = 0;
+    if (threadIdx.x == 0) s_redo = 0;
+    const u32x4 *pieces = reinterpret_cast<const u32x4 *>(ws->perm_off);
+    constexpr int kStride = kBlock / kPieces * kPieces;  // a thread's pieces are the same files' every time
+    u32x4 mine = {0, 0, 0, 0};
+    if ((int)threadIdx.x < kStride) {
+#pragma unroll 4
+        for (int t = threadIdx.x; t < n_slots * kPieces; t += kStride) mine |= pieces[t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (mine[e] != 0) atomicOr(&s_bits[(int)threadIdx.x % kPieces * 4 + e], mine[e]);
+    __syncthreads();
+    if (const int j = threadIdx.x; j < F) {
+        const uint32_t field = s_bits[j * kBits / 32] >> (j * kBits % 32);
+        const int w = decide_winner(field, R);
+        if ((field & fed_differs_bit(R, w)) != 0) s_redo = 1;
+        s_row[j] = file_rows[j * R + w];
+        if (blockIdx.x == 0) {
+            if (winner_replica != nullptr) winner_replica[j] = w;
+            ws->winner_row[j] = s_row[j];
+        }
+    }
+    __syncthreads();
+    const bool redo = s_redo != 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        ws->path = redo ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : (uint32_t)BYZ_PATH_SINGLE_PASS;
+    if (!redo) return;
+    const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (gt >= (d + V - 1) / V) return;
+    const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
+    constexpr int NS = 1, kAhead = V == 1 ? 20 : prefetch_depth(F, NS);
+    uint32_t key[V][F];
+    uint32_t o[V];
+    const uint32_t voff = (uint32_t)(c0 * 4);
+    const char *Xb = reinterpret_cast<const char *>(X);
+    uint32_t stage[kAhead + 1][NS][V];
+    const int lane = 0;
+    uint32_t flags[(F + 63) / 64] = {};
+    (void)lane; (void)flags;
+    // (the winners' rows from LDS as scalars)
+#define BYZ_S_ROW_ADDR(j, k) \
+    (Xb + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(s_row[j]) * (uint64_t)ld * 4u + voff)
+    if constexpr (!TRIM) {
+        if constexpr (pins_median(F)) {
+#include "selnet_pin_on.inc"
+#include "generated/selnet_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+        } else {
+#include "generated/selnet_stream_dispatch.inc"
+        }
+    } else {
+        if constexpr (pins_trimmed_mean(F)) {
+#include "selnet_pin_on.inc"
+#include "generated/selnet_sort_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+        } else {
+#include "generated/selnet_sort_stream_dispatch.inc"
+        }
+        trimmed_mean_of_sorted<F, V, pins_trimmed_mean(F)>(key, F, trim_b, o);
+    }
+#undef BYZ_S_ROW_ADDR
+    store_vec<V>(out + c0, o);
+}
+
 // ---------------------------------------------------------------------------- launchers
 
 [[maybe_unused]] constexpr int kVec = 4;  // words per thread and load; rows only need dword alignment
@@ -1635,12 +1773,68 @@ int launch_median(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_i
 
 #endif  // part 5
 
+// The two kernels of a short call; *done stays false where the blocks have no room for their slots.
+template <int F, int R, bool TRIM, int V, int BLOCK, int DV>
+int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
+                      uint32_t *out, int trim_b, int32_t *winner_replica, bool *done, hipStream_t s) {
+    const int64_t blocks = (d + (int64_t)V * BLOCK - 1) / ((int64_t)V * BLOCK);
+    if (blocks > most_slots(F, R)) return BYZ_OK;
+    int rc = byz_internal_profile_mark(0, s);
+    if (rc != BYZ_OK) return rc;
+    short_pass_kernel<F, R, TRIM, V, BLOCK><<<(unsigned)blocks, BLOCK, 0, s>>>(
+        X, d, ld, rows, reinterpret_cast<uint32_t *>(ws->perm_off), trim_b, out);
+    BYZ_HIP(hipGetLastError());
+    rc = byz_internal_profile_mark(1, s);
+    if (rc != BYZ_OK) return rc;
+    short_decide_kernel<F, R, TRIM, DV><<<blocks_for((d + DV - 1) / DV), kBlock, 0, s>>>(
+        X, d, ld, rows, ws, (int)blocks, trim_b, winner_replica, out);
+    BYZ_HIP(hipGetLastError());
+    *done = true;
+    return BYZ_OK;
+}
+
+// Which block of the first kernel: the smallest whose slots fit, one word per thread while that is the faster
+// form.  us a call, four kernels / two: 256 threads (25,3) d = 1003 15.3 / 9.1, 100003 18.3 / 12.1, (49,5) 20000
+// 37.1 / 23.2, (169,3) 20000 65.8 / 37.1; 512 threads (49,3) 100000 24.7 / 16.8, (81,3) 86000 40.8 / 22.3, (49,7)
+// 30000 45.1 / 38.5, (169,3) 46000 64.0 / 40.7.  Then up to 49 files: the long form's words per thread and 512
+// threads for five and seven copies ((49,5) 145000 40.2 / 33.4, (25,5) 260000 33.7 / 24.5) and for the median of up
+// to 25 files of three (1 M 55.9 / 50.8, 400000 25.9 / 22.7), two words for their trimmed mean (500000 31.1 /
+// 27.5; four 41.0), 1024 threads of one word for 49 files of three (250000 37.4 / 29.0; 512 of two 50.4).  More
+// files and two words per thread: (81,3) 140000 44.4 / 65.6, (63,7) 50000 54.2 / 56.8.  Fewer than 21 files of
+// longer rows keep the four kernels: (15,3) 500000 20.7 / 39.3, (9,3) 17.6 / 22.9.
+template <int F, int R, bool TRIM>
+int launch_short(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
+                 uint32_t *out, int trim_b, int32_t *winner_replica, bool *done, hipStream_t s) {
+    if (F < 21 && d > kManyBlocks) return BYZ_OK;
+    int rc = launch_short_pair<F, R, TRIM, 1, kBlock, 1>(X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
+    if (rc != BYZ_OK || *done) return rc;
+    rc = launch_short_pair<F, R, TRIM, 1, 512, 1>(X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
+    if (rc != BYZ_OK || *done) return rc;
+    if constexpr (F >= 21 && F <= 49) {
+        constexpr bool one_word = R == 3 && F > 25;
+        constexpr int V = one_word ? 1 : (R == 3 && TRIM ? 2 : vec_for_pass(F, R, TRIM));
+        rc = launch_short_pair<F, R, TRIM, V, one_word ? 1024 : 512, gated_vec(F)>(
+            X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
+    }
+    return rc;
+}
+
 // WITH_TRIM = false / WITH_MEDIAN = false leave that variant of the kernel out (a shape whose two
 // variants are compiled in different build parts)
 template <int F, int R, bool WITH_TRIM = true, bool WITH_MEDIAN = true>
 int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
-                 uint32_t *out, int probe_opts, int trim_b, hipStream_t s) {
+                 uint32_t *out, int probe_opts, int trim_b, int32_t *winner_replica, bool *done,
+                 hipStream_t s) {
     if ((!WITH_TRIM && trim_b >= 0) || (!WITH_MEDIAN && trim_b < 0)) return BYZ_EINTERNAL;
+    if ((probe_opts & 1) == 0) {
+        int rc;
+        if (trim_b < 0) {
+            if constexpr (WITH_MEDIAN) rc = launch_short<F, R, false>(X, d, ld, rows, ws, out, 0, winner_replica, done, s);
+        } else if constexpr (WITH_TRIM) {
+            rc = launch_short<F, R, true>(X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
+        }
+        if (rc != BYZ_OK || *done) return rc;
+    }
     probe_kernel<F, R><<<1, kProbeThreads, 0, s>>>(X, d, ld, rows, ws, probe_opts);
     BYZ_HIP(hipGetLastError());
     int rc = byz_internal_profile_mark(0, s);
@@ -1936,17 +2130,17 @@ int byz_internal_launch_trimmed_mean(const void *X, long long d, long long ld,
 #if BYZ_IN_PART(1)
 int byz_internal_launch_single_pass_1(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     const uint32_t *x = static_cast<const uint32_t *>(X);
     AggWorkspace *w = static_cast<AggWorkspace *>(ws);
     uint32_t *o = static_cast<uint32_t *>(out);
     hipStream_t s = (hipStream_t)stream;
-    if (f == 9 && r == 3) return launch_fused<9, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
-    if (f == 15 && r == 3) return launch_fused<15, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
-    if (f == 21 && r == 3) return launch_fused<21, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
-    if (f == 25 && r == 3) return launch_fused<25, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
-    if (f == 25 && r == 5) return launch_fused<25, 5>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
-    if (f == 35 && r == 5) return launch_fused<35, 5>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
+    if (f == 9 && r == 3) return launch_fused<9, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
+    if (f == 15 && r == 3) return launch_fused<15, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
+    if (f == 21 && r == 3) return launch_fused<21, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
+    if (f == 25 && r == 3) return launch_fused<25, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
+    if (f == 25 && r == 5) return launch_fused<25, 5>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
+    if (f == 35 && r == 5) return launch_fused<35, 5>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -1954,14 +2148,14 @@ int byz_internal_launch_single_pass_1(int f, int r, const void *X, long long d, 
 #if BYZ_IN_PART(2)
 int byz_internal_launch_single_pass_2(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     const uint32_t *x = static_cast<const uint32_t *>(X);
     AggWorkspace *w = static_cast<AggWorkspace *>(ws);
     uint32_t *o = static_cast<uint32_t *>(out);
     hipStream_t s = (hipStream_t)stream;
-    if (f == 49 && r == 3) return launch_fused<49, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
-    if (f == 49 && r == 5) return launch_fused<49, 5>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
-    if (f == 49 && r == 7) return launch_fused<49, 7>(x, d, ld, rows, w, o, probe_opts, trim_b, s);
+    if (f == 49 && r == 3) return launch_fused<49, 3>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
+    if (f == 49 && r == 5) return launch_fused<49, 5>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
+    if (f == 49 && r == 7) return launch_fused<49, 7>(x, d, ld, rows, w, o, probe_opts, trim_b, winner_replica, done, s);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -1969,11 +2163,11 @@ int byz_internal_launch_single_pass_2(int f, int r, const void *X, long long d, 
 #if BYZ_IN_PART(3)
 int byz_internal_launch_single_pass_3(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     if (f == 81 && r == 3)
         return launch_fused<81, 3>(static_cast<const uint32_t *>(X), d, ld, rows,
                                    static_cast<AggWorkspace *>(ws), static_cast<uint32_t *>(out),
-                                   probe_opts, trim_b, (hipStream_t)stream);
+                                   probe_opts, trim_b, winner_replica, done, (hipStream_t)stream);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -1981,11 +2175,11 @@ int byz_internal_launch_single_pass_3(int f, int r, const void *X, long long d, 
 #if BYZ_IN_PART(4)
 int byz_internal_launch_single_pass_4(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     if (f == 121 && r == 3)
         return launch_fused<121, 3>(static_cast<const uint32_t *>(X), d, ld, rows,
                                     static_cast<AggWorkspace *>(ws), static_cast<uint32_t *>(out),
-                                    probe_opts, trim_b, (hipStream_t)stream);
+                                    probe_opts, trim_b, winner_replica, done, (hipStream_t)stream);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -1993,11 +2187,11 @@ int byz_internal_launch_single_pass_4(int f, int r, const void *X, long long d, 
 #if BYZ_IN_PART(7)
 int byz_internal_launch_single_pass_5(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     if (f == 169 && r == 3)
         return launch_fused<169, 3, false>(static_cast<const uint32_t *>(X), d, ld, rows,
                                     static_cast<AggWorkspace *>(ws), static_cast<uint32_t *>(out),
-                                    probe_opts, trim_b, (hipStream_t)stream);
+                                    probe_opts, trim_b, winner_replica, done, (hipStream_t)stream);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -2006,11 +2200,11 @@ int byz_internal_launch_single_pass_5(int f, int r, const void *X, long long d, 
 // (169, 3) with the trimmed mean: the widest sorting network in the single pass, a part of its own
 int byz_internal_launch_single_pass_8(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     if (f == 169 && r == 3)
         return launch_fused<169, 3, true, false>(static_cast<const uint32_t *>(X), d, ld, rows,
                                     static_cast<AggWorkspace *>(ws), static_cast<uint32_t *>(out),
-                                    probe_opts, trim_b, (hipStream_t)stream);
+                                    probe_opts, trim_b, winner_replica, done, (hipStream_t)stream);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -2018,11 +2212,11 @@ int byz_internal_launch_single_pass_8(int f, int r, const void *X, long long d, 
 #if BYZ_IN_PART(14)
 int byz_internal_launch_single_pass_6(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     if (f == 63 && r == 7)
         return launch_fused<63, 7>(static_cast<const uint32_t *>(X), d, ld, rows,
                                     static_cast<AggWorkspace *>(ws), static_cast<uint32_t *>(out),
-                                    probe_opts, trim_b, (hipStream_t)stream);
+                                    probe_opts, trim_b, winner_replica, done, (hipStream_t)stream);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -2030,11 +2224,11 @@ int byz_internal_launch_single_pass_6(int f, int r, const void *X, long long d, 
 #if BYZ_IN_PART(15)
 int byz_internal_launch_single_pass_7(int f, int r, const void *X, long long d, long long ld,
                                       const int *rows, void *ws, void *out, int probe_opts, int trim_b,
-                                      void *stream) {
+                                      int *winner_replica, bool *done, void *stream) {
     if (f == 65 && r == 5)
         return launch_fused<65, 5>(static_cast<const uint32_t *>(X), d, ld, rows,
                                     static_cast<AggWorkspace *>(ws), static_cast<uint32_t *>(out),
-                                    probe_opts, trim_b, (hipStream_t)stream);
+                                    probe_opts, trim_b, winner_replica, done, (hipStream_t)stream);
     return BYZ_EINTERNAL;
 }
 #endif
@@ -2202,23 +2396,33 @@ static int aggregate_on_workspace(const float *copies, int64_t d, int64_t ld,
     // probe -> single pass -> decision (one block) -> median, which returns at once unless the
     // decision found a file whose slot 0 did not hold its winner.  Early-majority mode adds the
     // gated vote kernel and its decision between the two, for the files whose r' copies differ.
+    // Short rows take two kernels instead of all that.
+    bool done = false;
     if (f == 169 && trim_b >= 0)
-        rc = byz_internal_launch_single_pass_8(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
+        rc = byz_internal_launch_single_pass_8(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
     else if (f == 169)
-        rc = byz_internal_launch_single_pass_5(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
+        rc = byz_internal_launch_single_pass_5(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
     else if (f == 121)
-        rc = byz_internal_launch_single_pass_4(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
+        rc = byz_internal_launch_single_pass_4(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
     else if (f == 81)
-        rc = byz_internal_launch_single_pass_3(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
+        rc = byz_internal_launch_single_pass_3(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
     else if (f == 63)
-        rc = byz_internal_launch_single_pass_6(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
+        rc = byz_internal_launch_single_pass_6(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
     else if (f == 65)
-        rc = byz_internal_launch_single_pass_7(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
+        rc = byz_internal_launch_single_pass_7(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
     else if (f == 49)
-        rc = byz_internal_launch_single_pass_2(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
+        rc = byz_internal_launch_single_pass_2(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
     else
-        rc = byz_internal_launch_single_pass_1(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b, s);
-    if (rc != BYZ_OK) return rc;
+        rc = byz_internal_launch_single_pass_1(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
+                                                 winner_replica, &done, s);
+    if (rc != BYZ_OK || done) return rc;
     single_pass_decide_kernel<<<1, kWide, 0, s>>>(ws, file_rows_dev, f, r, winner_replica);
     BYZ_HIP(hipGetLastError());
     if ((flags & BYZ_AGG_EARLY_MAJORITY) != 0) {

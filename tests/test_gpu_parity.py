@@ -1323,6 +1323,41 @@ def test_single_pass_around_every_change_of_width(f, r):
                     assert B.byz_aggregate_path(ws) == (SINGLE if majority else REDONE), tag
 
 
+@pytest.mark.parametrize("f,r", SINGLE_PASS_SHAPES)
+def test_short_rows_where_the_blocks_or_the_kernels_change(f, r):
+    # the longest row of every form of the two-kernel call and the shortest of the next one: blocks of 256 and
+    # 512 threads of one word, the wider blocks of up to 49 files, the four kernels; a tampered copy that
+    # is outvoted, told by the last word, then a file without a majority
+    slots = 4096 // ((f * {3: 8, 5: 16, 7: 32}[r] + 127) // 128 * 4)
+    sizes = [slots * 256, slots * 512] if f >= 21 else [131072]
+    if 21 <= f <= 49:
+        sizes += [slots * 1024] + ([slots * 2048] if r == 3 and f <= 25 else [])
+    rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
+    b = max(1, f // 8)
+    for d in sorted({1003} | {n + e for n in sizes for e in (0, 1)}):
+        g = torch.Generator(device=DEV).manual_seed(f * 10 + r + d)
+        X = torch.randn(f, 1, d + 2, device=DEV, generator=g).expand(f, r, d + 2).reshape(f * r, d + 2).contiguous()
+        X[0, d - 1] += 1.0
+        X[r * f - 1, 0] -= 2.0
+        winner = [1] + [0] * (f - 1)
+        for majority in (True, False):
+            if not majority:
+                for k in range(r):
+                    X[f // 2 * r + k, d // 2 + k] = 9.0 + k
+                X[f // 2 * r, d - 2] = -9.0
+            want = _median_and_trimmed_mean(torch.stack([X[q * r + winner[q], :d] for q in range(f)]), b)
+            for trim in (0, 1):
+                out = torch.full((d + 8,), 7.0, device=DEV)
+                ws = torch.randint(0, 256, (B.byz_aggregate_workspace_bytes(f, r),), dtype=torch.uint8, device=DEV)
+                _, wrep, _ = B.byz_aggregate_opts(X, d, rows, f, r, B.BYZ_AGG_TRIM(b) if trim else 0, out=out, workspace=ws)
+                torch.cuda.synchronize()
+                tag = (f, r, d, majority, trim)
+                assert B.byz_aggregate_path(ws) == (SINGLE if majority else REDONE), tag
+                assert wrep.cpu().tolist() == winner, tag
+                assert np.array_equal(W.bits(out[:d].contiguous()), want[trim]), tag
+                assert bool((out[d:] == 7.0).all()), tag
+
+
 def test_hidden_equality_patterns_of_wide_files():
     # r = 3 ... 13: random equality patterns among the copies of random files, the classes one
     # changed word apart at random coordinates (the comparison over all of d is what finds
