@@ -312,7 +312,8 @@ size_t byz_aggregate_workspace_bytes(int f, int r);
  * (49,3), (49,5), (49,7), (63,7), (65,5), (81,3), (121,3), (169,3)
  * (byz_aggregate_has_single_pass; with and without BYZ_AGG_TRIM); for
  * every other valid (f, r), and for d < 4, the call runs byz_vote's kernels and then
- * byz_median's (or byz_trimmed_mean's), reading the winners a second time.
+ * byz_median's (or byz_trimmed_mean's), reading the winners a second time; for r = 3 and
+ * 169 < f <= 255, d >= 2^18, the two are one kernel that reads every copy once.
  * Errors: as byz_vote / byz_median, plus BYZ_ENOMEM (workspace too small).
  */
 int byz_aggregate(const float *copies, int64_t d, int64_t ld, const int32_t *file_rows_dev,
@@ -389,8 +390,9 @@ typedef enum byz_path {
     BYZ_PATH_REVOTED = 2,       /* early-majority mode only: the r' copies read of some files
                                    differed and all copies of those files were compared (bit 1;
                                    with bit 0 if the median was redone as well: 3)               */
-    BYZ_PATH_TWO_STEP = 4       /* no single pass for this (f, r) or d < 4: byz_vote's and
-                                   byz_median's kernels one after the other                      */
+    BYZ_PATH_TWO_STEP = 4       /* (f, r) not among byz_aggregate_has_single_pass' shapes or d < 4:
+                                   byz_vote's and byz_median's kernels one after the other, or,
+                                   for r = 3 and 169 < f <= 255, long rows, in one                */
 } byz_path;
 int byz_aggregate_path(const void *workspace, int *path, void *stream);
 

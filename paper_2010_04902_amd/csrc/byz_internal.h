@@ -36,6 +36,15 @@ BYZ_DECLARE_SINGLE_PASS(6);
 BYZ_DECLARE_SINGLE_PASS(7);
 BYZ_DECLARE_SINGLE_PASS(8);  // (169, 3) with the trimmed mean only
 
+// Layout + single pass of a call on 169 < f <= 255 files of three copies (kernels.hip, parts 24 and 25), for the
+// decision and the gated kernels behind it.  Returns a byz_status.
+#define BYZ_DECLARE_HALVES_PASS(name)                                                            \
+    int byz_internal_launch_##name##_halves_pass(const void *X, long long d, long long ld,       \
+                                                 const int *rows, int f, void *ws, void *out,    \
+                                                 int trim_b, void *stream)
+BYZ_DECLARE_HALVES_PASS(median);
+BYZ_DECLARE_HALVES_PASS(trimmed);
+
 // Coordinate-wise median / trimmed mean of the rows row_index[0..f-1] (kernels.hip, parts 5 and
 // 6): picks the network kernel for f; gate != NULL makes the kernels return at once unless one
 // of gate[0..gate_n-1] is nonzero.  Device pointers.  Returns a byz_status.

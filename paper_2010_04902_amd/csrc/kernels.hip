@@ -28,7 +28,7 @@
 // group of single-pass instantiations each (byz_internal_launch_single_pass_<n>), parts 5 and 6
 // the median and trimmed-mean kernels up to 81 wires (and the 121-wire median), parts 8..11,
 // 14, 15 and 19..23 the larger ones, parts 12 and 13 the second phase of Bulyan on 57 to 81 and on 97
-// to 137 wires, parts 16 and 17 the two-wave median and trimmed-mean kernels for f > 169.
+// to 137 wires, parts 16 and 17 the two-wave median and trimmed-mean kernels for f > 169, 24 and 25 the pass over their files.
 // Without BYZ_PART the whole library is this one translation unit.
 #ifndef BYZ_PART
 #define BYZ_PART -1
@@ -499,8 +499,9 @@ __device__ __forceinline__ uint32_t fed_differs_bit(int ns, int p) { return 1u <
 // A file read in early-majority mode has only r' slots of its own: if they are identical they
 // are the majority (Sec. 2) and any of them is the winner; if not, nothing is known about the
 // copies that were skipped and need_revote sends the call through the gated vote kernel.
+// two_step: the call counts as a two-step one, whatever came out.
 __global__ void single_pass_decide_kernel(AggWorkspace *ws, const int32_t *__restrict__ file_rows,
-                                          int f, int r, int32_t *winner_replica) {
+                                          int f, int r, int32_t *winner_replica, int two_step) {
     __shared__ uint32_t s_median, s_revote;
     if (threadIdx.x == 0) { s_median = 0; s_revote = 0; }
     __syncthreads();
@@ -539,8 +540,9 @@ __global__ void single_pass_decide_kernel(AggWorkspace *ws, const int32_t *__res
     if (threadIdx.x == 0) {
         ws->need_median = s_median;
         ws->need_revote = s_revote;
-        ws->path = (s_median != 0 ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : 0u) |
-                   (s_revote != 0 ? (uint32_t)BYZ_PATH_REVOTED : 0u);
+        ws->path = two_step != 0 ? (uint32_t)BYZ_PATH_TWO_STEP
+                                 : (s_median != 0 ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : 0u) |
+                                       (s_revote != 0 ? (uint32_t)BYZ_PATH_REVOTED : 0u);
     }
 }
 
@@ -872,6 +874,28 @@ __global__ __launch_bounds__(kBlock) void median_large_kernel(
     store_vec<V>(out + c0, o);
 }
 
+// The median of two sorted halves of F keys, the wave of wires 0..F-1 and that of F..2F-1 (see
+// median_halves_kernel): out[c] of lane ln.
+template <int F>
+__device__ __forceinline__ void median_of_halves(const uint32_t (&k)[F], uint32_t *s_half, int first, int ln,
+                                                 int64_t c, int64_t d, uint32_t *__restrict__ out) {
+    if (first != 0) {
+#pragma unroll
+        for (int m = 0; m < F; ++m) s_half[m * 64 + ln] = k[m];
+    }
+    __syncthreads();
+    if (first == 0) {
+        uint32_t best = k[F - 1] < s_half[(F - 1) * 64 + ln] ? k[F - 1] : s_half[(F - 1) * 64 + ln];
+#pragma unroll
+        for (int m = 0; m < F - 1; ++m) {
+            const uint32_t b = s_half[(F - 2 - m) * 64 + ln];
+            const uint32_t t = k[m] > b ? k[m] : b;
+            best = best < t ? best : t;
+        }
+        if (c < d) out[c] = from_key(best);
+    }
+}
+
 // Coordinate-wise median of H < f <= 2H - 1 rows (H = 96, 112, 128: up to 255 rows), two waves per
 // 64 coordinates: wave h of a block sorts wires [hH, hH + H) of its coordinates in registers
 // (H-wire sorting network, one word per thread), wave 1 hands its sorted keys over through LDS,
@@ -915,21 +939,7 @@ void median_halves_kernel(
 #undef BYZ_S_ROW_ADDR
 #undef BYZ_S_KEY
 #define BYZ_S_KEY(j, x) to_key(x)
-    if (first != 0) {
-#pragma unroll
-        for (int m = 0; m < F; ++m) s_half[m * 64 + ln] = key[0][m];
-    }
-    __syncthreads();
-    if (first == 0) {
-        uint32_t best = key[0][F - 1] < s_half[(F - 1) * 64 + ln] ? key[0][F - 1] : s_half[(F - 1) * 64 + ln];
-#pragma unroll
-        for (int m = 0; m < F - 1; ++m) {
-            const uint32_t b = s_half[(F - 2 - m) * 64 + ln];
-            const uint32_t t = key[0][m] > b ? key[0][m] : b;
-            best = best < t ? best : t;
-        }
-        if (c < d) out[c] = from_key(best);
-    }
+    median_of_halves<F>(key[0], s_half, first, ln, c, d, out);
 }
 
 // Rounding contract of the trimmed mean: fp32, the kept values (ranks b .. F-b-1 of the sorted
@@ -1077,45 +1087,11 @@ __device__ __forceinline__ float add_kept_ranks(const uint32_t (&k)[F], int rank
     return acc;
 }
 
-// Coordinate-wise trimmed mean of F < f <= 2F rows (F = 96, 112, 128), two waves per 64 coordinates, same
-// rounding contract as trimmed_mean_kernel.  Wave h sorts wires [hF, hF + F) of its coordinates
-// in registers (the 2F - f spare wires at the end carry the largest key).  With A and B the two
-// sorted halves, min(A[m], B[F-1-m]) over m holds the F smallest of the union and max(...) the
-// F largest, each as a bitonic sequence: wave 1 passes B through LDS, wave 0 keeps the minima
-// and passes the maxima back through the same words, and each wave sorts its bitonic half
-// (sort_bitonic).  Wave 0 then holds ranks 0..F-1 and
-// wave 1 ranks F..2F-1; the kept ranks are added in ascending order, wave 0's partial sum
-// going to wave 1 through LDS.  Half the registers of one 256-wire network per thread.
+// The trimmed mean of two sorted halves (see trimmed_halves_kernel): out[c] of lane ln.
 template <int F>
-__global__ __launch_bounds__(128)
-__attribute__((amdgpu_waves_per_eu(2, 2)))
-void trimmed_halves_kernel(
-    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
-    int f, int b, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
-    if (gate != nullptr && !any_word_set(gate, gate_n)) return;
-    __shared__ uint32_t s_half[F * 64];
-    __shared__ float s_sum[64];
-    const int ln = threadIdx.x & 63;
-    const int first = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * F;  // first wire of this wave
-    const int64_t c = (int64_t)blockIdx.x * 64 + ln;
-    const int64_t cc = c < d ? c : d - 1;  // lanes past the end redo the last coordinate
-    constexpr int V = 1, NS = 1, kAhead = 20;
-    uint32_t key[V][F];
-    const uint32_t voff = (uint32_t)(cc * 4);
-    const char *Xb = reinterpret_cast<const char *>(X);
-    uint32_t stage[kAhead + 1][NS][V];
-    const int lane = 0;
-    uint32_t flags[(F + 63) / 64] = {};
-    (void)lane; (void)flags;
-#undef BYZ_S_KEY
-#define BYZ_S_KEY(j, x) (first + (j) < f ? to_key(x) : 0xFFFFFFFFu)
-#define BYZ_S_ROW_ADDR(j, k) \
-    (Xb + (uint64_t)(uint32_t)row_index[first + (j) < f ? first + (j) : 0] * (uint64_t)ld * 4u + voff)
-#include "generated/selnet_sort_stream_dispatch.inc"
-#undef BYZ_S_ROW_ADDR
-#undef BYZ_S_KEY
-#define BYZ_S_KEY(j, x) to_key(x)
-    uint32_t(&k)[F] = key[0];
+__device__ __forceinline__ void trimmed_mean_of_halves(uint32_t (&k)[F], uint32_t *s_half, float *s_sum,
+                                                       int first, int ln, int64_t c, int64_t d, int f, int b,
+                                                       uint32_t *__restrict__ out) {
     if (first != 0) {
 #pragma unroll
         for (int m = 0; m < F; ++m) s_half[m * 64 + ln] = k[m];
@@ -1155,6 +1131,47 @@ void trimmed_halves_kernel(
         acc = add_kept_ranks<F>(k, F, b, f, s_sum[ln]);
         if (c < d) out[c] = __float_as_uint(acc / (float)(f - 2 * b));
     }
+}
+
+// Coordinate-wise trimmed mean of F < f <= 2F rows (F = 96, 112, 128), two waves per 64 coordinates, same
+// rounding contract as trimmed_mean_kernel.  Wave h sorts wires [hF, hF + F) of its coordinates
+// in registers (the 2F - f spare wires at the end carry the largest key).  With A and B the two
+// sorted halves, min(A[m], B[F-1-m]) over m holds the F smallest of the union and max(...) the
+// F largest, each as a bitonic sequence: wave 1 passes B through LDS, wave 0 keeps the minima
+// and passes the maxima back through the same words, and each wave sorts its bitonic half
+// (sort_bitonic).  Wave 0 then holds ranks 0..F-1 and
+// wave 1 ranks F..2F-1; the kept ranks are added in ascending order, wave 0's partial sum
+// going to wave 1 through LDS.  Half the registers of one 256-wire network per thread.
+template <int F>
+__global__ __launch_bounds__(128)
+__attribute__((amdgpu_waves_per_eu(2, 2)))
+void trimmed_halves_kernel(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
+    int f, int b, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
+    if (gate != nullptr && !any_word_set(gate, gate_n)) return;
+    __shared__ uint32_t s_half[F * 64];
+    __shared__ float s_sum[64];
+    const int ln = threadIdx.x & 63;
+    const int first = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * F;  // first wire of this wave
+    const int64_t c = (int64_t)blockIdx.x * 64 + ln;
+    const int64_t cc = c < d ? c : d - 1;  // lanes past the end redo the last coordinate
+    constexpr int V = 1, NS = 1, kAhead = 20;
+    uint32_t key[V][F];
+    const uint32_t voff = (uint32_t)(cc * 4);
+    const char *Xb = reinterpret_cast<const char *>(X);
+    uint32_t stage[kAhead + 1][NS][V];
+    const int lane = 0;
+    uint32_t flags[(F + 63) / 64] = {};
+    (void)lane; (void)flags;
+#undef BYZ_S_KEY
+#define BYZ_S_KEY(j, x) (first + (j) < f ? to_key(x) : 0xFFFFFFFFu)
+#define BYZ_S_ROW_ADDR(j, k) \
+    (Xb + (uint64_t)(uint32_t)row_index[first + (j) < f ? first + (j) : 0] * (uint64_t)ld * 4u + voff)
+#include "generated/selnet_sort_stream_dispatch.inc"
+#undef BYZ_S_ROW_ADDR
+#undef BYZ_S_KEY
+#define BYZ_S_KEY(j, x) to_key(x)
+    trimmed_mean_of_halves<F>(key[0], s_half, s_sum, first, ln, c, d, f, b, out);
 }
 
 // Mean around the median (second phase of Bulyan) for one coordinate whose theta values sit
@@ -1469,6 +1486,73 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(
         fused_body<F, R, (R + 1) / 2, TRIM, V>(X, d, ld, perm_off, ws, trim_b, out);
     else
         fused_body<F, R, R, TRIM, V>(X, d, ld, perm_off, ws, trim_b, out);
+}
+
+// First kernel of a call on more than 169 files: clears the state the later kernels accumulate into and
+// lays out the rows of each file in replica order, spare wires repeating file 0.
+__global__ __launch_bounds__(kWide) void lay_out_rows_kernel(const int32_t *__restrict__ file_rows, int f, int r,
+                                                             int64_t ld, AggWorkspace *ws) {
+    const int j = threadIdx.x;
+    ws->pneq[j] = 0;
+    uint32_t packed = (uint32_t)r << 24;
+    for (int p = 0; p < r; ++p) {
+        ws->perm_off[j * kRowStride + p] = (uint64_t)file_rows[(j < f ? j : 0) * r + p] * (uint64_t)ld * 4u;
+        packed |= (uint32_t)p << (3 * p);
+    }
+    ws->perm[j] = packed;
+    if (j == 0) {
+        ws->need_median = 0;
+        ws->need_revote = 0;
+        ws->slots_per_file = (uint32_t)r;
+    }
+}
+
+// Vote and median or trimmed mean of F < f <= 2F - 1 files of three copies in one pass, the files split over two
+// waves per 64 coordinates as the rows are in median_halves_kernel: each wave streams the copies of its F
+// files, compares them and chooses what it feeds as in fused_body.  Within 1.12 of the time its bytes take at
+// 6.5 TB/s at f = 255 (1 M coordinates 554 us a call, vote and median one after the other 709; 2 M 992 and 1374;
+// trimmed mean 647 and 833): two waves per SIMD, HBM and min/max issue together.  F = 96 leaves room for a
+// third wave (171 files, 1 M: 383 -> 338; 112 would spill).  20 files ahead: 2 % slower than 5.
+template <int F, bool TRIM>
+__global__ __launch_bounds__(128)
+__attribute__((amdgpu_waves_per_eu(!TRIM && F <= 96 ? 3 : 2, !TRIM && F <= 96 ? 3 : 2)))
+void fused_halves_kernel(const uint32_t *__restrict__ X, int64_t d, const uint64_t *__restrict__ perm_off,
+                         AggWorkspace *ws, int f, int trim_b, uint32_t *__restrict__ out) {
+    __shared__ uint32_t s_half[F * 64];
+    __shared__ float s_sum[64];
+    const int lane = threadIdx.x & 63;
+    const int first = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * F;  // first file of this wave
+    const int64_t c = (int64_t)tile_of_block(blockIdx.x, gridDim.x) * 64 + lane;
+    const int64_t cc = c < d ? c : d - 1;  // lanes past the end redo the last coordinate
+    const int pad_low_end = TRIM ? f : f + (F - 1 - (f - 1) / 2);
+    constexpr int V = 1, NS = 3, kAhead = 5;
+    uint32_t flags[(F + 63) / 64] = {}, seen[(F + 63) / 64];
+#pragma unroll
+    for (int w = 0; w < (F + 63) / 64; ++w)
+        seen[w] = 64 * w + lane < F && first + 64 * w + lane < f ? load_shared_word(&ws->pneq[first + 64 * w + lane]) : 0u;
+    const uint32_t voff = (uint32_t)(cc * 4);
+    const char *Xb = reinterpret_cast<const char *>(X);
+    uint32_t key[V][F];
+    uint32_t stage[kAhead + 1][NS][V];
+#undef BYZ_S_KEY
+#define BYZ_S_KEY(j, x) \
+    (first + (j) < f ? to_key(x) : (first + (j) < pad_low_end ? 0u : 0xFFFFFFFFu))
+#define BYZ_S_ROW_ADDR(j, k) (Xb + perm_off[(first + (j)) * kRowStride + (k)] + voff)
+#include "selnet_pin_on.inc"
+#include "generated/selnet_sort_stream_dispatch.inc"
+#include "selnet_pin_off.inc"
+#undef BYZ_S_ROW_ADDR
+#undef BYZ_S_KEY
+#define BYZ_S_KEY(j, x) to_key(x)
+#pragma unroll
+    for (int w = 0; w < (F + 63) / 64; ++w) {
+        const int here = F - 64 * w < 64 ? F - 64 * w : 64, files = f - first - 64 * w;
+        merge_flags(ws->pneq + first + 64 * w, files < here ? files : here, lane, flags[w] & ~seen[w]);
+    }
+    if constexpr (TRIM)
+        trimmed_mean_of_halves<F>(key[0], s_half, s_sum, first, lane, c, d, f, trim_b, out);
+    else
+        median_of_halves<F>(key[0], s_half, first, lane, c, d, out);
 }
 
 // The call on short rows in two kernels that need nothing cleared before them: instead of merging their bits
@@ -1960,6 +2044,14 @@ bool has_fused(int f, int r) {
 // ... whose trimmed-mean variant is compiled as well: all of them
 bool has_fused_trim(int f, int r) { return has_fused(f, r); }
 
+// More than 169 files of three copies, rows of four rounds of resident blocks or more: one pass with the files
+// split over two waves.  Shorter rows are voted on faster with the files dealt out to more blocks (f = 255,
+// us a call, vote and median / one pass: d = 10000 34 / 54, 100000 89 / 91, 140000 114 / 121, 200000 151 / 150,
+// 262145 218 / 172; f = 195 200000 121 / 129, 262145 167 / 150; f = 171 200000 100 / 101, 262145 141 / 117).
+bool takes_halves_pass(int f, int r, int64_t d) {
+    return f > 169 && f <= 255 && r == 3 && d >= ((int64_t)1 << 18);
+}
+
 int check_common(const void *copies, int64_t d, int64_t ld, const void *rows, int f, int r) {
     if (copies == nullptr || rows == nullptr) return BYZ_EINVAL;
     if (d < 0 || ld < d || d > kMaxCoords) return BYZ_EINVAL;
@@ -2113,6 +2205,42 @@ int byz_internal_launch_trimmed_mean_256_padded(const void *X, long long d, long
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
+#endif
+
+#if BYZ_IN_PART(24) || BYZ_IN_PART(25)
+namespace {
+template <bool TRIM>
+int launch_halves_pass(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, int f, AggWorkspace *ws,
+                       uint32_t *out, int trim_b, hipStream_t s) {
+    lay_out_rows_kernel<<<1, kWide, 0, s>>>(rows, f, 3, ld, ws);
+    BYZ_HIP(hipGetLastError());
+    int rc = byz_internal_profile_mark(0, s);
+    if (rc != BYZ_OK) return rc;
+    const unsigned g = (unsigned)((d + 63) / 64);
+    if (f <= 2 * 96 - 1)
+        fused_halves_kernel<96, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, out);
+    else if (f <= 2 * 112 - 1)
+        fused_halves_kernel<112, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, out);
+    else
+        fused_halves_kernel<128, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, out);
+    BYZ_HIP(hipGetLastError());
+    return byz_internal_profile_mark(1, s);
+}
+}  // namespace
+#define BYZ_DEFINE_HALVES_PASS(name, trim)                                                        \
+    int byz_internal_launch_##name##_halves_pass(const void *X, long long d, long long ld,        \
+                                                 const int *rows, int f, void *ws, void *out,     \
+                                                 int trim_b, void *stream) {                      \
+        return launch_halves_pass<trim>(static_cast<const uint32_t *>(X), d, ld, rows, f,         \
+                                        static_cast<AggWorkspace *>(ws),                          \
+                                        static_cast<uint32_t *>(out), trim_b, (hipStream_t)stream); \
+    }
+#if BYZ_IN_PART(24)
+BYZ_DEFINE_HALVES_PASS(median, false)
+#endif
+#if BYZ_IN_PART(25)
+BYZ_DEFINE_HALVES_PASS(trimmed, true)
+#endif
 #endif
 
 #if BYZ_IN_PART(6)
@@ -2372,6 +2500,18 @@ static int aggregate_on_workspace(const float *copies, int64_t d, int64_t ld,
     const uint32_t *X = reinterpret_cast<const uint32_t *>(copies);
     uint32_t *O = reinterpret_cast<uint32_t *>(out);
 
+    if (takes_halves_pass(f, r, d)) {
+        rc = trim_b >= 0
+                 ? byz_internal_launch_trimmed_halves_pass(X, d, ld, file_rows_dev, f, ws, O, trim_b, s)
+                 : byz_internal_launch_median_halves_pass(X, d, ld, file_rows_dev, f, ws, O, trim_b, s);
+        if (rc != BYZ_OK) return rc;
+        single_pass_decide_kernel<<<1, kWide, 0, s>>>(ws, file_rows_dev, f, r, winner_replica, 1);
+        BYZ_HIP(hipGetLastError());
+        if (trim_b >= 0)
+            return byz_internal_launch_trimmed_mean(X, d, ld, ws->winner_row, f, trim_b, O,
+                                                    &ws->need_median, 1, s);
+        return byz_internal_launch_median(X, d, ld, ws->winner_row, f, O, &ws->need_median, 1, s);
+    }
     if (!has_fused(f, r) || d < kVec || (trim_b >= 0 && !has_fused_trim(f, r))) {
         // two-step path, unconditionally: vote, then median over the winners
         reset_workspace_kernel<<<1, kWide, 0, s>>>(ws, (uint32_t)BYZ_PATH_TWO_STEP);
@@ -2423,7 +2563,7 @@ static int aggregate_on_workspace(const float *copies, int64_t d, int64_t ld,
         rc = byz_internal_launch_single_pass_1(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,
                                                  winner_replica, &done, s);
     if (rc != BYZ_OK || done) return rc;
-    single_pass_decide_kernel<<<1, kWide, 0, s>>>(ws, file_rows_dev, f, r, winner_replica);
+    single_pass_decide_kernel<<<1, kWide, 0, s>>>(ws, file_rows_dev, f, r, winner_replica, 0);
     BYZ_HIP(hipGetLastError());
     if ((flags & BYZ_AGG_EARLY_MAJORITY) != 0) {
         rc = launch_vote_pairs_r(r, X, d, ld, file_rows_dev, f, ws->pair_neq, &ws->need_revote, 1,

@@ -1358,6 +1358,39 @@ def test_short_rows_where_the_blocks_or_the_kernels_change(f, r):
                 assert bool((out[d:] == 7.0).all()), tag
 
 
+@pytest.mark.parametrize("f", [171, 191, 193, 223, 225, 255])
+def test_pass_over_files_split_over_two_waves(f):
+    # most and fewest spare wires of every size of the halves, the shortest rows that take it and a ragged
+    # end; files of both waves tampered with: copies that are outvoted, told by one word, then a file of each
+    # wave without a majority, whose winner the stretch around one word outnumbers
+    r, rows, b = 3, torch.arange(f * 3, dtype=torch.int32, device=DEV), f // 8
+    for d in (1 << 18, (1 << 18) + 37):
+        g = torch.Generator(device=DEV).manual_seed(f + d)
+        X = torch.randn(f, 1, d + 2, device=DEV, generator=g).expand(f, r, d + 2).reshape(f * r, d + 2).contiguous()
+        X[0] += 1.0
+        X[3 * 130, d - 1] += 1.0
+        X[3 * f - 1, 5] -= 2.0
+        winner = [0] * f
+        winner[0] = winner[130] = 1
+        for majority in (True, False):
+            if not majority:
+                for j in (7, f - 20):
+                    for k in range(r):
+                        X[3 * j + k, d // 2 + k] = 9.0 + k
+                    X[3 * j, d - 2] = -9.0
+            want = _median_and_trimmed_mean(torch.stack([X[3 * q + winner[q], :d] for q in range(f)]), b)
+            for trim in (0, 1):
+                out = torch.full((d + 8,), 7.0, device=DEV)
+                ws = torch.randint(0, 256, (B.byz_aggregate_workspace_bytes(f, r),), dtype=torch.uint8, device=DEV)
+                _, wrep, _ = B.byz_aggregate_opts(X, d, rows, f, r, B.BYZ_AGG_TRIM(b) if trim else 0, out=out, workspace=ws)
+                torch.cuda.synchronize()
+                tag = (f, d, majority, trim)
+                assert B.byz_aggregate_path(ws) == TWO_STEP, tag
+                assert wrep.cpu().tolist() == winner, tag
+                assert np.array_equal(W.bits(out[:d].contiguous()), want[trim]), tag
+                assert bool((out[d:] == 7.0).all()), tag
+
+
 def test_hidden_equality_patterns_of_wide_files():
     # r = 3 ... 13: random equality patterns among the copies of random files, the classes one
     # changed word apart at random coordinates (the comparison over all of d is what finds
