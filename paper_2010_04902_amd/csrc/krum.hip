@@ -452,17 +452,14 @@ __global__ __launch_bounds__(kBlock) void distance_rows_kernel(const double *__r
     }
 }
 
-// Multi-Krum's choice, thread i = vector i (one block of kMaxKrum threads): the m lowest
-// scores, the lower index first among equal scores.
-__global__ __launch_bounds__(kMaxKrum) void krum_select_kernel(const double *__restrict__ scores, int f,
-                                                               int m, int32_t *selected_out,
-                                                               int32_t *selected_list,
-                                                               int32_t *n_selected) {
-    __shared__ double s_score[kMaxKrum];
-    __shared__ uint64_t s_chosen[kMaxKrum / 64];
+// Multi-Krum's choice, thread i = vector i (the first kMaxKrum threads of a block): the m lowest
+// scores, the lower index first among equal scores.  Returns whether i is chosen, *before = chosen
+// vectors with a lower index, *total = how many there are.  All threads of the block call it.
+__device__ __forceinline__ bool choose_vector(const double *__restrict__ scores, int f, int m, double *s_score,
+                                              uint64_t *s_chosen, int *before, int *total) {
     const int i = threadIdx.x;
     const double mine = i < f ? scores[i] : 0.0;
-    s_score[i] = mine;
+    if (i < kMaxKrum) s_score[i] = mine;
     __syncthreads();
     int rank = 0;
 #pragma unroll 8
@@ -472,16 +469,28 @@ __global__ __launch_bounds__(kMaxKrum) void krum_select_kernel(const double *__r
     }
     const bool chosen = i < f && rank < m;
     const uint64_t mask = __builtin_amdgcn_ballot_w64(chosen);
-    if ((i & 63) == 0) s_chosen[i >> 6] = mask;
+    if (i < kMaxKrum && (i & 63) == 0) s_chosen[i >> 6] = mask;
     __syncthreads();
-    int before = __builtin_popcountll(mask & ((1ull << (i & 63)) - 1ull));
-    int total = 0;
+    *before = __builtin_popcountll(mask & ((1ull << (i & 63)) - 1ull));
+    *total = 0;
 #pragma unroll
     for (int w = 0; w < kMaxKrum / 64; ++w) {
         const int n = __builtin_popcountll(s_chosen[w]);
-        if (w < (i >> 6)) before += n;
-        total += n;
+        if (w < (i >> 6)) *before += n;
+        *total += n;
     }
+    return chosen;
+}
+
+__global__ __launch_bounds__(kMaxKrum) void krum_select_kernel(const double *__restrict__ scores, int f,
+                                                               int m, int32_t *selected_out,
+                                                               int32_t *selected_list,
+                                                               int32_t *n_selected) {
+    __shared__ double s_score[kMaxKrum];
+    __shared__ uint64_t s_chosen[kMaxKrum / 64];
+    const int i = threadIdx.x;
+    int before, total;
+    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &total);
     if (i < f) selected_out[i] = chosen ? 1 : 0;
     if (chosen) selected_list[before] = i;
     if (i == 0) *n_selected = total;
@@ -715,6 +724,37 @@ __global__ __launch_bounds__(kBlock) void selected_mean_kernel(const float *__re
     }
 }
 
+// Both on short rows, where a launch and the chain of loads count and not HBM: every block chooses for itself
+// (block 0 writes the choice) and takes one word per thread, kAheadRows rows in flight; the additions are those
+// of selected_mean_kernel.  Figures at kShortMean.
+constexpr int kAheadRows = 32;
+__global__ __launch_bounds__(kBlock) void choose_and_mean_kernel(const float *__restrict__ X, int64_t d, int64_t ld,
+                                                                 const int32_t *__restrict__ row_index,
+                                                                 const double *__restrict__ scores, int f, int m,
+                                                                 int32_t *selected_out, float *__restrict__ out) {
+    static_assert(kBlock >= kMaxKrum, "a thread per vector");
+    __shared__ double s_score[kMaxKrum];
+    __shared__ uint64_t s_chosen[kMaxKrum / 64];
+    __shared__ int64_t s_first[kMaxKrum];  // first words of the chosen rows
+    const int i = threadIdx.x;
+    int before, n;
+    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &n);
+    if (blockIdx.x == 0 && i < f) selected_out[i] = chosen ? 1 : 0;
+    if (chosen) s_first[before] = (int64_t)row_index[i] * ld;
+    __syncthreads();
+    const int64_t c = (int64_t)blockIdx.x * kBlock + i;
+    if (c >= d) return;
+    float a = 0.0f;
+    for (int t = 0; t < n; t += kAheadRows) {
+        float v[kAheadRows];
+#pragma unroll
+        for (int u = 0; u < kAheadRows; ++u) v[u] = t + u < n ? X[s_first[t + u] + c] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < kAheadRows; ++u) a = t + u < n ? a + v[u] : a;
+    }
+    out[c] = a / (float)n;
+}
+
 struct KrumWorkspace {
     double gram[kMaxPairs * kTile];
     double sorted_dist[kMaxKrum * kRowStride];  // [t*kRowStride + i]: i's t-th smallest distance
@@ -839,6 +879,11 @@ extern "C" size_t byz_multi_krum_workspace_bytes(int f) {
     return krum_workspace_bytes(f);
 }
 
+// Rows up to which the choice is made in the blocks of the mean.  us a call, two kernels / one: f = 25 d = 1003
+// 21.3 / 18.6, 131072 23.9 / 21.0, 262144 27.8 / 23.8, 400000 31.2 / 28.0, 700000 37.4 / 38.9; f = 127 1003 45.2 / 41.8,
+// 100003 87.2 / 75.0, 262144 118 / 110, 400000 150.3 / 150.1, 1 M 319 / 326.
+constexpr int64_t kShortMean = 3 << 17;
+
 extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
                               const int32_t *row_index_dev, int f, int c, int m, float *out,
                               int32_t *selected_out, double *scores_out, double *dist_out,
@@ -857,6 +902,12 @@ extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
     if (rc != BYZ_OK) return rc;
     rc = launch_distance_rows(f, f - c - 2, dist_out, scores_out, ws, s);
     if (rc != BYZ_OK) return rc;
+    if (d > 0 && d <= kShortMean) {
+        choose_and_mean_kernel<<<(unsigned)((d + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+            rows_base, d, ld, row_index_dev, ws->scores, f, m, selected_out, out);
+        BYZ_HIP(hipGetLastError());
+        return BYZ_OK;
+    }
     krum_select_kernel<<<1, kMaxKrum, 0, s>>>(ws->scores, f, m, selected_out, ws->selected_list,
                                               &ws->n_selected);
     BYZ_HIP(hipGetLastError());

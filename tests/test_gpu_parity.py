@@ -1509,6 +1509,38 @@ def test_random_shapes_sizes_and_layouts():
         _tolerant_check(X, w.file_rows, d, w.f, w.r, 1e-6, 1e-5, tag)
 
 
+@pytest.mark.parametrize("f", [3, 31, 32, 33, 64, 65, 128])
+def test_multi_krum_mean_of_short_and_long_rows(f):
+    # rows of up to 3 * 2^17 coordinates are averaged in blocks that choose for themselves: one
+    # word more and less than a block and than that limit, more chosen rows than are in flight at once and
+    # fewer, rows off the cache lines.  Choice and mean from the scores the call returned: m lowest, lower index
+    # first; fp32 additions in ascending index order.  NaN compares with nothing: every vector is chosen.
+    rng = np.random.default_rng(f)
+    limit = 3 << 17
+    for d, nan in [(1, False), (3, False), (4, False), (255, False), (257, True), (limit, False), (limit + 1, False)]:
+        ld = d + 5
+        X = torch.empty((f + 2, ld), device=DEV).normal_(generator=torch.Generator(device=DEV).manual_seed(f * 1000 + d % 997))
+        idx = rng.permutation(f + 2)[:f].astype(np.int32)
+        if nan:
+            X[int(idx[f // 2]), 7] = float("nan")
+        c = (f - 3) // 2
+        for m in {1, f - c}:
+            out = torch.full((d + 8,), 7.0, device=DEV)
+            _, sel, scores, _ = B.byz_multi_krum(X, d, torch.tensor(idx, device=DEV), c, m, out=out)
+            torch.cuda.synchronize()
+            sc = scores.cpu().numpy()
+            with np.errstate(invalid="ignore"):
+                rank = [sum((sc[k] < sc[i]) or (sc[k] == sc[i] and k < i) for k in range(f)) for i in range(f)]
+            want_sel = np.array([r < m for r in rank])
+            assert np.array_equal(sel.cpu().numpy().astype(bool), want_sel), (f, d, m)
+            acc = torch.zeros(d, device=DEV)
+            for i in np.flatnonzero(want_sel):
+                acc += X[int(idx[i]), :d]
+            want = (acc / torch.tensor(float(want_sel.sum()), device=DEV)).cpu().numpy()
+            assert np.array_equal(out[:d].cpu().numpy(), want, equal_nan=True), (f, d, m)
+            assert bool((out[d:] == 7.0).all()), (f, d, m)
+
+
 def test_multi_krum_and_bulyan_for_every_f():
     # every f from 3 to 64 and a spread of the wider ones (all tile counts and staging shapes of
     # the Gram kernel, one and two distances per lane in the row sort, Bulyan's rounds in
