@@ -239,7 +239,9 @@ def _need_rows_in_range(table, count, n_rows, what):
     if known:
         bounds = entry[2]
     else:
-        head = table.reshape(-1)[:count]
+        # one copy to the host, then the bounds there: two reductions on the device, a copy back each,
+        # took 20 us more of a call with a new table (tolerant vote, then the median of its winners)
+        head = table.reshape(-1)[:count].cpu()
         bounds = (int(head.min()), int(head.max()))
         if len(_checked_tables) >= 256:
             _checked_tables.clear()
