@@ -652,6 +652,28 @@ __device__ __forceinline__ uint32_t far_apart(const uint32_t (&a)[V], const uint
     return acc;
 }
 
+// The same for a whole wave, all lanes active: is some word of some lane far apart?  The five operations of the
+// bound are all a pair of close chunks takes: bit patterns are looked at only where a bound was missed (they
+// excuse nothing but copies that are both infinite or NaN, or a negative tolerance).
+template <int V>
+__device__ __forceinline__ uint32_t wave_far_apart(const uint32_t (&a)[V], const uint32_t (&b)[V], float atol,
+                                                   float rtol) {
+    uint64_t missed[V], any = 0;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const float x = __uint_as_float(a[v]), y = __uint_as_float(b[v]);
+        const float diff = fabsf(__fsub_rn(x, y));
+        const float bound = __fadd_rn(atol, __fmul_rn(rtol, fmaxf(fabsf(x), fabsf(y))));
+        missed[v] = __builtin_amdgcn_ballot_w64(!(diff <= bound));
+        any |= missed[v];
+    }
+    if (any == 0) return 0;
+    any = 0;
+#pragma unroll
+    for (int v = 0; v < V; ++v) any |= missed[v] & __builtin_amdgcn_ballot_w64(a[v] != b[v]);
+    return any != 0 ? 1u : 0u;
+}
+
 // Tolerant variant of the vote's comparison (Sec. 2: rounding differences between honest copies can be
 // handled by clustering the copies): for every file, which pairs of copies are not close
 // somewhere in [0, d).  Same decomposition as vote_pairs_kernel.
@@ -679,7 +701,7 @@ __global__ __launch_bounds__(kBlock) void vote_pairs_tolerant_kernel(
                 for (int a = 0; a < R; ++a)
 #pragma unroll
                     for (int b = a + 1; b < R; ++b)
-                        wb |= wave_any(far_apart<V>(x[a], x[b], atol, rtol)) << pair_bit(R, a, b);
+                        wb |= wave_far_apart<V>(x[a], x[b], atol, rtol) << pair_bit(R, a, b);
                 if (lane == j - j0) flags |= wb;
             }
             merge_flags(pair_far + j0, j1 - j0, lane, flags);
