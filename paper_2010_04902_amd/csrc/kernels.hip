@@ -107,6 +107,14 @@ constexpr int vec_for_pass(int f, int r, bool trim) {
 // Rows that one block holds with the wider form, but not with one word per thread, keep the wider form:
 // a block merges its bits with no other ((25,3) d = 1003, us of GPU time, median 14.4, one word 15.2,
 // early-majority 16.0 and 18.3; (25,5) 500 17.4 and 20.5).
+// Rows of five copies from which four words per thread are the faster form after all: always up to 25 files, and
+// off the cache lines up to 49, where two words a thread leave more lines shared by two blocks.  us a call, two
+// words / four: (25,5) 1 M 91.6 / 92.0 off lines, 2 M 177 / 164 off and 163 / 159 on, 6 M 526 / 488 and 470 / 468;
+// (35,5) off lines 0.7 M 84 / 90, 1 M 123 / 112, 6 M 697 / 650, on lines 637 / 641; (49,5) off lines 1 M 168 / 161, 6 M
+// 974 / 889, trimmed mean 977 / 913, on lines 876 / 887.
+[[maybe_unused]] constexpr bool four_words_of_five(int f, int64_t d, bool lines) {
+    return d >= (int64_t)15 << 16 && (f <= 25 || (f <= 49 && !lines));
+}
 [[maybe_unused]] constexpr int64_t short_row(int f, int r) { return f <= 25 && r == 5 ? 65536 : 131072; }
 // Files ahead of the one in use in the first kernel of short calls: the depths measured above, as far as
 // registers allow.
@@ -1429,10 +1437,15 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(const uint32_t *__
 // (block b runs on XCD b mod 8).  A launch that is over after a round or two of resident blocks
 // is dominated by its start: there every XCD gets one contiguous eighth of the tiles, so that
 // its L2 and address translation see one range of every row instead of all of it (d = 2^20,
-// 75 rows: 56 -> 52.5 us).  Long launches keep the plain order, which measured 1-3 % faster there.
+// 75 rows: 56 -> 52.5 us).  In long launches that costs 1-3 %; there each XCD gets GROUP neighbours at a time,
+// which share the cache lines where rows don't start on one.  us a call, plain order / 16 / 64 neighbours, 6 M
+// coordinates off lines: (25,3) 302 / 292 / 290, (49,3) 589 / 569 / 566, (49,7) 1377 / 1329 / 1332, (81,3) 962 /
+// 924 / 928; on lines 291 / 292 / 289, 556 / 548 / 544, 1233 / 1212 / 1218, 893 / 872 / 878.
 constexpr unsigned kShortLaunchBlocks = 2048;
+constexpr unsigned block_group(int v) { return v == 4 ? 64 : 16; }
+template <unsigned GROUP>
 __device__ __forceinline__ unsigned tile_of_block(unsigned b, unsigned n_blocks) {
-    if (n_blocks > kShortLaunchBlocks) return b;
+    if (n_blocks > kShortLaunchBlocks) return neighbours_together(b, n_blocks, GROUP);
     const unsigned q = n_blocks / 8, rem = n_blocks % 8, x = b % 8, i = b / 8;
     return x * q + (x < rem ? x : rem) + i;  // XCD x owns q tiles, one more if x < rem
 }
@@ -1456,7 +1469,7 @@ __device__ __forceinline__ void fused_body(const uint32_t *__restrict__ X, int64
     // its neighbour instead of a scalar tail, and threads past the end redo it, so there are
     // no branches around loads and ballots (d >= V is the launcher's business).
     const int64_t n_thr = (d + V - 1) / V;
-    const int64_t gt = (int64_t)tile_of_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    const int64_t gt = (int64_t)tile_of_block<block_group(V)>(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     const int64_t c0 = (gt + 1) * V <= d ? gt * V : d - V;
     uint32_t flags[(F + 63) / 64] = {};  // lane j%64 collects the pair bits of file j
     // What other waves have published so far, read now so that the wait is over long before the
@@ -1535,16 +1548,18 @@ __global__ __launch_bounds__(kWide) void lay_out_rows_kernel(const int32_t *__re
 // 6.5 TB/s at f = 255 (1 M coordinates 554 us a call, vote and median one after the other 709; 2 M 992 and 1374;
 // trimmed mean 647 and 833): two waves per SIMD, HBM and min/max issue together.  F = 96 leaves room for a
 // third wave (171 files, 1 M: 383 -> 338; 112 would spill).  20 files ahead: 2 % slower than 5.
+// A block's 64 words off the cache lines are three lines for two: there neighbours go to one XCD (f = 255, 1 M
+// 705 us in plain order, 597; 2 M 1379, 1149; on lines 188.7 and 192 for 300 k, the same for 2 M).
 template <int F, bool TRIM>
 __global__ __launch_bounds__(128)
 __attribute__((amdgpu_waves_per_eu(!TRIM && F <= 96 ? 3 : 2, !TRIM && F <= 96 ? 3 : 2)))
 void fused_halves_kernel(const uint32_t *__restrict__ X, int64_t d, const uint64_t *__restrict__ perm_off,
-                         AggWorkspace *ws, int f, int trim_b, uint32_t *__restrict__ out) {
+                         AggWorkspace *ws, int f, int trim_b, unsigned group, uint32_t *__restrict__ out) {
     __shared__ uint32_t s_half[F * 64];
     __shared__ float s_sum[64];
     const int lane = threadIdx.x & 63;
     const int first = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * F;  // first file of this wave
-    const int64_t c = (int64_t)tile_of_block(blockIdx.x, gridDim.x) * 64 + lane;
+    const int64_t c = (int64_t)(group != 0 ? neighbours_together(blockIdx.x, gridDim.x, group) : blockIdx.x) * 64 + lane;
     const int64_t cc = c < d ? c : d - 1;  // lanes past the end redo the last coordinate
     const int pad_low_end = TRIM ? f : f + (F - 1 - (f - 1) / 2);
     constexpr int V = 1, NS = 3, kAhead = 5;
@@ -1599,7 +1614,7 @@ __global__ __launch_bounds__(BLOCK) void short_pass_kernel(
     for (int t = threadIdx.x; t < kWords; t += BLOCK) s_bits[t] = 0;
     const int lane = threadIdx.x & 63;
     const int64_t n_thr = (d + V - 1) / V;
-    const int64_t gt = (int64_t)tile_of_block(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
+    const int64_t gt = (int64_t)tile_of_block<block_group(V)>(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
     const int64_t c0 = (gt + 1) * V <= d ? gt * V : d - V;  // as in fused_body
     const uint32_t voff = (uint32_t)(c0 * 4);
     uint32_t flags[(F + 63) / 64] = {};
@@ -1736,6 +1751,8 @@ constexpr int gated_vec(int f) { return f <= 49 ? 4 : 1; }
 [[maybe_unused]] inline bool rows_on_lines(const void *X, int64_t ld) {
     return ((uintptr_t)X & 127u) == 0 && ld % 32 == 0;
 }
+// Neighbouring blocks an XCD takes at a time in the two-wave kernels off the lines (64 words a block).
+[[maybe_unused]] constexpr unsigned kHalvesGroup = 64;
 [[maybe_unused]] constexpr int64_t four_words_from(int f) { return f <= 35 ? kManyBlocks : (int64_t)1 << 20; }
 
 [[maybe_unused]] constexpr int64_t kMaxCoords = (int64_t)1 << 30;  // byte offsets inside a row fit 32 bits
@@ -1947,6 +1964,7 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     if (rc != BYZ_OK) return rc;
     constexpr bool kShortToo = vec_for_pass(F, R, false) > 1;  // or the only width is one word already
     const int64_t one_block = (int64_t)kBlock * vec_for_pass(F, R, trim_b >= 0);
+    [[maybe_unused]] const bool four = four_words_of_five(F, d, rows_on_lines(X, ld));
     if (kShortToo && d <= short_row(F, R) && (d <= kBlock || d > one_block)) {
         if constexpr (kShortToo) {
             if (trim_b < 0)
@@ -1959,11 +1977,27 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     } else if (trim_b < 0) {
         if constexpr (WITH_MEDIAN) {
             constexpr int V = vec_for_pass(F, R, false);
+            if constexpr (R == 5 && F <= 49) {
+                if (four) {
+                    fused_kernel<F, R, false, 4><<<blocks_for((d + 3) / 4), kBlock, 0, s>>>(
+                        X, d, ld, ws->perm_off, &ws->slots_per_file, ws, 0, out);
+                    BYZ_HIP(hipGetLastError());
+                    return byz_internal_profile_mark(1, s);
+                }
+            }
             fused_kernel<F, R, false, V><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
                 X, d, ld, ws->perm_off, &ws->slots_per_file, ws, 0, out);
         }
     } else if constexpr (WITH_TRIM) {
         constexpr int V = vec_for_pass(F, R, true);
+        if constexpr (R == 5 && F <= 49) {
+            if (four) {
+                fused_kernel<F, R, true, 4><<<blocks_for((d + 3) / 4), kBlock, 0, s>>>(
+                    X, d, ld, ws->perm_off, &ws->slots_per_file, ws, trim_b, out);
+                BYZ_HIP(hipGetLastError());
+                return byz_internal_profile_mark(1, s);
+            }
+        }
         fused_kernel<F, R, true, V><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
             X, d, ld, ws->perm_off, &ws->slots_per_file, ws, trim_b, out);
     }
@@ -2239,12 +2273,13 @@ int launch_halves_pass(const uint32_t *X, int64_t d, int64_t ld, const int32_t *
     int rc = byz_internal_profile_mark(0, s);
     if (rc != BYZ_OK) return rc;
     const unsigned g = (unsigned)((d + 63) / 64);
+    const unsigned group = rows_on_lines(X, ld) ? 0 : kHalvesGroup;
     if (f <= 2 * 96 - 1)
-        fused_halves_kernel<96, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, out);
+        fused_halves_kernel<96, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, group, out);
     else if (f <= 2 * 112 - 1)
-        fused_halves_kernel<112, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, out);
+        fused_halves_kernel<112, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, group, out);
     else
-        fused_halves_kernel<128, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, out);
+        fused_halves_kernel<128, TRIM><<<g, 128, 0, s>>>(X, d, ws->perm_off, ws, f, trim_b, group, out);
     BYZ_HIP(hipGetLastError());
     return byz_internal_profile_mark(1, s);
 }

@@ -937,6 +937,48 @@ def test_vote_where_the_files_are_no_longer_dealt_out(f, r):
         assert wrep.cpu().tolist() == best and wrow.cpu().tolist() == [j * r + best[j] for j in range(f)], d
 
 
+def _rows_on_and_off_lines(n, d, seed):
+    # [n, d] values in rows that start on cache lines, and off them by pitch and by the matrix's start
+    ld = (d + 31) // 32 * 32
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    buf = torch.empty(n * (ld + 33) + 1, device=DEV).normal_(generator=gen)
+    for start, pitch in ((0, ld), (1, ld + 33)):
+        yield buf[start:start + n * pitch].reshape(n, pitch)
+
+
+@pytest.mark.parametrize("f,r,vec", [(25, 3, 4), (49, 3, 4), (49, 7, 2), (81, 3, 2), (121, 3, 1), (169, 3, 1),
+                                     (25, 5, 4), (35, 5, 4), (49, 5, 4)])
+def test_long_single_passes_on_and_off_cache_lines(f, r, vec):
+    # more than 2048 blocks, dealt out to the XCDs by whole groups of neighbours, the last group not
+    # whole and the last vector overlapping; five copies also around the length from which a thread takes
+    # four words.  A false copy of every third file, in its last word.
+    sizes = [2048 * 256 * vec + 1, 2048 * 256 * vec + 8 * 64 * 256 * vec + 77]
+    if r == 5:
+        sizes = [(15 << 16) - 1, 15 << 16, sizes[0]]
+    for d in sizes:
+        for X in _rows_on_and_off_lines(f * r, d, f * r + d % 911):
+            for j in range(f):
+                X[j * r + 1:(j + 1) * r] = X[j * r]
+                if j % 3 == 0:
+                    X[j * r + j % r, d - 1] += 1.0
+            rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
+            first = torch.tensor([1 if j % 3 == 0 and j % r == 0 else 0 for j in range(f)], device=DEV)
+            ranks = X.index_select(0, torch.arange(f, device=DEV) * r + first)[:, :d].sort(dim=0).values
+            for flags, b in ((0, -1), (B.BYZ_AGG_TRIM(4), 4), (B.BYZ_AGG_EARLY_MAJORITY, -1)):
+                out = torch.full((d + 8,), 7.0, device=DEV)
+                _, wrep, _ = B.byz_aggregate_opts(X, d, rows, f, r, flags, out=out)
+                torch.cuda.synchronize()
+                want = ranks[(f - 1) // 2]
+                if b >= 0:
+                    want = torch.zeros(d, device=DEV)
+                    for v in ranks[b:f - b]:
+                        want += v
+                    want /= torch.tensor(float(f - 2 * b), device=DEV)
+                assert torch.equal(out[:d], want) and bool((out[d:] == 7.0).all()), (f, r, d, X.shape[1], flags)
+                assert torch.equal(wrep.long(), first), (f, r, d, X.shape[1], flags)
+            del ranks
+
+
 def test_mean_around_median_alone():
     # byz_mean_around_median = the second phase of Bulyan on rows of the caller's choice: every
     # network size of that kernel and the sizes between (spare wires), d from one word to many
