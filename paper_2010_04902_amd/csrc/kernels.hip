@@ -662,7 +662,7 @@ __device__ __forceinline__ uint32_t far_apart(const uint32_t (&a)[V], const uint
 
 // The same for a whole wave, all lanes active: is some word of some lane far apart?  The five operations of the
 // bound are all a pair of close chunks takes: bit patterns are looked at only where a bound was missed (they
-// excuse nothing but copies that are both infinite or NaN, or a negative tolerance).
+// excuse only copies that are both infinite or NaN).
 template <int V>
 __device__ __forceinline__ uint32_t wave_far_apart(const uint32_t (&a)[V], const uint32_t (&b)[V], float atol,
                                                    float rtol) {
@@ -939,7 +939,8 @@ __device__ __forceinline__ void median_of_halves(const uint32_t (&k)[F], uint32_
 // spills; the schedule is not pinned (pinned as in the single pass it was 14 % slower).
 // The waves-per-SIMD attribute states what the registers allow anyway; without it the compiler
 // schedules the H = 128 kernel half as fast (4.7 instead of 3.0 ms on 11.2 M coordinates).
-template <int F>  // = H
+// GROUP: see neighbours_together; 0 = plain order (a constant: as an argument it costs 7-16 % on the lines).
+template <int F, unsigned GROUP>  // F = H
 __global__ __launch_bounds__(128)
 __attribute__((amdgpu_waves_per_eu(F <= 96 ? 3 : 2, F <= 96 ? 3 : 2)))
 void median_halves_kernel(
@@ -949,7 +950,11 @@ void median_halves_kernel(
     __shared__ uint32_t s_half[F * 64];
     const int ln = threadIdx.x & 63;
     const int first = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * F;  // first wire of this wave
-    const int64_t c = (int64_t)blockIdx.x * 64 + ln;
+    int64_t c;
+    if constexpr (GROUP != 0)
+        c = (int64_t)neighbours_together(blockIdx.x, gridDim.x, GROUP) * 64 + ln;
+    else
+        c = (int64_t)blockIdx.x * 64 + ln;
     const int64_t cc = c < d ? c : d - 1;  // lanes past the end redo the last coordinate
     const int pad_low_end = f + (F - 1 - (f - 1) / 2);
     constexpr int V = 1, NS = 1, kAhead = 20;
@@ -1030,9 +1035,10 @@ __device__ __forceinline__ void trimmed_mean_of_sorted(const uint32_t (&key)[V][
 template <int F, int V, bool PAD>
 __global__ __launch_bounds__(kBlock) void trimmed_mean_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
-    int f, int b, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
+    int f, int b, unsigned group, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
     if (gate != nullptr && !any_word_set(gate, gate_n)) return;
-    const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const unsigned tile = group != 0 ? neighbours_together(blockIdx.x, gridDim.x, group) : blockIdx.x;
+    const int64_t gt = (int64_t)tile * kBlock + threadIdx.x;
     if (gt >= (d + V - 1) / V) return;
     const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
     constexpr int NS = 1, kAhead = V == 1 ? 20 : prefetch_depth(F, NS);  // as the median kernels
@@ -1261,9 +1267,10 @@ __device__ __forceinline__ float mean_around_median(const float *col, int stride
 template <int F, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void bulyan_mean_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld,
-    const int32_t *__restrict__ selected_rows, int theta, int beta, uint32_t *__restrict__ out) {
+    const int32_t *__restrict__ selected_rows, int theta, int beta, unsigned group, uint32_t *__restrict__ out) {
     extern __shared__ float s_bulyan_col[];
-    const int64_t c0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+    const unsigned tile = group != 0 ? neighbours_together(blockIdx.x, gridDim.x, group) : blockIdx.x;
+    const int64_t c0 = (int64_t)tile * BLOCK + threadIdx.x;
     if (c0 >= d) return;
     constexpr int V = 1, NS = 1, kAhead = 20;
     uint32_t key[V][F];
@@ -1950,7 +1957,7 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
                  hipStream_t s) {
     if ((!WITH_TRIM && trim_b >= 0) || (!WITH_MEDIAN && trim_b < 0)) return BYZ_EINTERNAL;
     if ((probe_opts & 1) == 0) {
-        int rc;
+        int rc = BYZ_EINTERNAL;
         if (trim_b < 0) {
             if constexpr (WITH_MEDIAN) rc = launch_short<F, R, false>(X, d, ld, rows, ws, out, 0, winner_replica, done, s);
         } else if constexpr (WITH_TRIM) {
@@ -2017,13 +2024,16 @@ int launch_trimmed_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *
         if (few_rows ? d > 2 * kManyBlocks : gate != nullptr && d > kManyBlocks) {
             constexpr int V = gated_vec(F);
             trimmed_mean_kernel<F, V, PAD><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
-                X, d, ld, row_index, f, b, O, gate, gate_n);
+                X, d, ld, row_index, f, b, 0, O, gate, gate_n);
             BYZ_HIP(hipGetLastError());
             return BYZ_OK;
         }
     }
-    trimmed_mean_kernel<F, 1, PAD><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, b, O, gate,
-                                                                    gate_n);
+    // off the cache lines, as the median (4 M coordinates, us: f = 25 76.5 -> 72.3, 49 157 -> 152, 81 239 -> 232; above
+    // 81 wires nothing is gained)
+    const unsigned group = F <= 81 && d > kManyBlocks && !rows_on_lines(X, ld) ? 16 : 0;
+    trimmed_mean_kernel<F, 1, PAD><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, row_index, f, b, group, O,
+                                                                    gate, gate_n);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
@@ -2078,8 +2088,10 @@ int launch_bulyan_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *s
     constexpr int BLOCK = F > 49 ? 64 : kBlock;
     constexpr size_t lds = (size_t)F * BLOCK * 4;
     static_assert(lds <= 64 * 1024, "more than a kernel may use without asking");
+    // off the cache lines (1 M coordinates, us: f = 49 44.9 -> 44.1, 65 74.0 -> 69.5, 97 142 -> 138, 127 256 -> 250)
+    const unsigned group = d > kManyBlocks && !rows_on_lines(X, ld) ? (BLOCK == 64 ? kHalvesGroup : 16) : 0;
     bulyan_mean_kernel<F, BLOCK><<<(unsigned)((d + BLOCK - 1) / BLOCK), BLOCK, lds, s>>>(
-        X, d, ld, selected_rows, theta, beta, O);
+        X, d, ld, selected_rows, theta, beta, group, O);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
@@ -2230,13 +2242,23 @@ int byz_internal_launch_median_255_padded(const void *X, long long d, long long 
     const uint32_t *x = static_cast<const uint32_t *>(X), *gt = static_cast<const uint32_t *>(gate);
     uint32_t *o = static_cast<uint32_t *>(out);
     hipStream_t s = (hipStream_t)stream;
-    // the smallest pair of halves that holds f rows
+    // the smallest pair of halves that holds f rows; off the lines neighbours go to one XCD (1 M coordinates, us:
+    // f = 171 161 -> 136, 191 178 -> 144, 223 217 -> 190, 255 252 -> 223)
+    const bool together = d > kManyBlocks && !rows_on_lines(X, ld);
+#define BYZ_LAUNCH_HALVES(H)                                                                          \
+    do {                                                                                              \
+        if (together)                                                                                 \
+            median_halves_kernel<H, kHalvesGroup><<<g, 128, 0, s>>>(x, d, ld, row_index, f, o, gt, gate_n); \
+        else                                                                                          \
+            median_halves_kernel<H, 0><<<g, 128, 0, s>>>(x, d, ld, row_index, f, o, gt, gate_n);      \
+    } while (0)
     if (f <= 2 * 96 - 1)
-        median_halves_kernel<96><<<g, 128, 0, s>>>(x, d, ld, row_index, f, o, gt, gate_n);
+        BYZ_LAUNCH_HALVES(96);
     else if (f <= 2 * 112 - 1)
-        median_halves_kernel<112><<<g, 128, 0, s>>>(x, d, ld, row_index, f, o, gt, gate_n);
+        BYZ_LAUNCH_HALVES(112);
     else
-        median_halves_kernel<128><<<g, 128, 0, s>>>(x, d, ld, row_index, f, o, gt, gate_n);
+        BYZ_LAUNCH_HALVES(128);
+#undef BYZ_LAUNCH_HALVES
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }

@@ -979,6 +979,30 @@ def test_long_single_passes_on_and_off_cache_lines(f, r, vec):
             del ranks
 
 
+@pytest.mark.parametrize("f", [9, 49, 81, 97, 127, 171, 207, 255])
+def test_sorts_of_long_rows_on_and_off_cache_lines(f):
+    # above 131072 coordinates neighbouring blocks go to one XCD where rows don't start on cache lines:
+    # trimmed mean, median of more than 169 rows, mean around the median; a last group that is not whole
+    for d in (131073, 131072 + 8 * 64 * 64 + 77):
+        for X in _rows_on_and_off_lines(f, d, f + d):
+            idx = torch.randperm(f, generator=torch.Generator().manual_seed(f)).to(torch.int32).to(DEV)
+            ranks = X[:, :d].sort(dim=0).values
+            b = f // 4
+            want = torch.zeros(d, device=DEV)
+            for v in ranks[b:f - b]:
+                want += v
+            want /= torch.tensor(float(f - 2 * b), device=DEV)
+            calls = [(lambda o: B.byz_trimmed_mean(X, d, idx, b, out=o), want),
+                     (lambda o: B.byz_median(X, d, idx, out=o), ranks[(f - 1) // 2])]
+            if f <= 128:  # one value around the median is the median
+                calls.append((lambda o: B.byz_mean_around_median(X, d, idx, 1, out=o), ranks[(f - 1) // 2]))
+            for n, (call, expected) in enumerate(calls):
+                out = torch.full((d + 8,), 7.0, device=DEV)
+                call(out)
+                torch.cuda.synchronize()
+                assert torch.equal(out[:d], expected) and bool((out[d:] == 7.0).all()), (f, d, X.shape[1], n)
+
+
 def test_mean_around_median_alone():
     # byz_mean_around_median = the second phase of Bulyan on rows of the caller's choice: every
     # network size of that kernel and the sizes between (spare wires), d from one word to many
