@@ -1447,9 +1447,10 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(const uint32_t *__
 // 75 rows: 56 -> 52.5 us).  In long launches that costs 1-3 %; there each XCD gets GROUP neighbours at a time,
 // which share the cache lines where rows don't start on one.  us a call, plain order / 16 / 64 neighbours, 6 M
 // coordinates off lines: (25,3) 302 / 292 / 290, (49,3) 589 / 569 / 566, (49,7) 1377 / 1329 / 1332, (81,3) 962 /
-// 924 / 928; on lines 291 / 292 / 289, 556 / 548 / 544, 1233 / 1212 / 1218, 893 / 872 / 878.
+// 924 / 928; on lines 291 / 292 / 289, 556 / 548 / 544, 1233 / 1212 / 1218, 893 / 872 / 878.  One word a thread, 2.5 M:
+// (121,3) 668 / 639 / 637 off lines, 562 / 571 / 556 on, (169,3) 922 / 870 / 864 and 792 / 787 / 785.
 constexpr unsigned kShortLaunchBlocks = 2048;
-constexpr unsigned block_group(int v) { return v == 4 ? 64 : 16; }
+constexpr unsigned block_group(int v) { return v == 2 ? 16 : 64; }
 template <unsigned GROUP>
 __device__ __forceinline__ unsigned tile_of_block(unsigned b, unsigned n_blocks) {
     if (n_blocks > kShortLaunchBlocks) return neighbours_together(b, n_blocks, GROUP);
