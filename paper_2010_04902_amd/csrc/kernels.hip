@@ -91,7 +91,7 @@ constexpr int least_rows(int n) {
 constexpr int vec_for(int f) { return f <= 49 ? 4 : (f <= 81 ? 2 : 1); }
 // With five or seven copies of a file in flight two words per thread
 // (more waves per SIMD, 8-byte loads) measured 1-2 % faster than four (r = 7 would not fit
-// the registers with four); with three copies four words are faster, but for a sort of 49 keys
+// the registers with four; long rows of five copies: four_words_of_five); with three copies four words are faster, but for a sort of 49 keys
 // (four: 269 registers, one wave per SIMD, 409 us for 4 M coordinates; two: 377)
 constexpr int vec_for_pass(int f, int r, bool trim) {
     return ((r >= 5 || (trim && f > 35)) && f <= 49) ? 2 : vec_for(f);
