@@ -255,7 +255,8 @@ int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld, const int32_t 
  * Arithmetic: distances as in byz_multi_krum (fp32 matrix instructions, waves and slices added in
  * fp64 in a fixed order), scores in fp64 added in ascending order; the mean is fp32, window values added
  * one by one in ascending order from +0, one IEEE division by float(beta).  Inputs with
- * non-finite values give NaN distances, for which phase 1 is not specified.
+ * non-finite values give NaN distances, for which the order of phase 1 is not specified (a vector is
+ * chosen once all the same).
  *   selected_out  device [f] int32 out: 1 for the theta chosen rows, else 0
  *   order_out     device [theta] int32 out, may be NULL: indices (into row_index_dev) in the
  *                 order chosen

@@ -496,21 +496,6 @@ __global__ __launch_bounds__(kMaxKrum) void krum_select_kernel(const double *__r
     if (i == 0) *n_selected = total;
 }
 
-// One exchange of a wave-wide search for the lowest (score, index): every lane looks at the
-// lane the data-parallel-primitive pattern CTRL pairs it with (a pairing inside a row of 16
-// lanes that is its own inverse) and keeps the lower of the two keys.
-template <int CTRL>
-__device__ __forceinline__ void argmin_exchange(double &score, int &best) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(score), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(score), CTRL, 0xF, 0xF, false);
-    const int o_best = __builtin_amdgcn_update_dpp(0, best, CTRL, 0xF, 0xF, false);
-    const double o_score = __hiloint2double(hi, lo);
-    if (o_score < score || (o_score == score && o_best < best)) {
-        score = o_score;
-        best = o_best;
-    }
-}
-
 // quad_perm [1,0,3,2]: lane ^ 1; quad_perm [2,3,0,1]: lane ^ 2; row_half_mirror: the other quad of the
 // 8; row_mirror: the other half of the 16
 constexpr int kDppPairs[4] = {0xB1, 0x4E, 0x141, 0x140};
@@ -528,36 +513,21 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
     return least;
 }
 
-// Lowest (score, lane) of the wave.  Scores are sums of distances from +0, never negative, so
-// without NaNs their bit patterns are in the order of the values: the lowest upper half, the lowest lower
-// half that comes with it, the first lane that has both.  With a NaN anywhere: comparisons as they
-// fall, four exchanges inside each row of 16 lanes, then the four rows from their first lanes.
-__device__ __forceinline__ void wave_argmin(double score, int i, double &w_score, int &w_best) {
-    if (__builtin_amdgcn_ballot_w64(score != score) == 0) {
-        const uint32_t hi = (uint32_t)__double2hiint(score), lo = (uint32_t)__double2loint(score);
-        const uint32_t least_hi = wave_min(hi);
-        const uint32_t least_lo = wave_min(hi == least_hi ? lo : 0xFFFFFFFFu);
-        const uint64_t here = __builtin_amdgcn_ballot_w64(hi == least_hi && lo == least_lo);
-        w_score = __hiloint2double((int)least_hi, (int)least_lo);
-        w_best = __builtin_amdgcn_readfirstlane(i) + (int)__builtin_ctzll(here);
-        return;
-    }
-    int best = i;
-    argmin_exchange<kDppPairs[0]>(score, best);
-    argmin_exchange<kDppPairs[1]>(score, best);
-    argmin_exchange<kDppPairs[2]>(score, best);
-    argmin_exchange<kDppPairs[3]>(score, best);
-    w_score = lane_value(score, 0);
-    w_best = __builtin_amdgcn_readlane(best, 0);
-#pragma unroll
-    for (int row = 1; row < 4; ++row) {
-        const double r_score = lane_value(score, 16 * row);
-        const int r_best = __builtin_amdgcn_readlane(best, 16 * row);
-        if (r_score < w_score || (r_score == w_score && r_best < w_best)) {
-            w_score = r_score;
-            w_best = r_best;
-        }
-    }
+// What a vector's score is ordered by.  Scores are sums of distances from +0, never negative, so their bit
+// patterns are in the order of the values, NaNs behind infinity; a vector that is not left comes behind any score.
+__device__ __forceinline__ uint64_t score_key(double score, bool left) {
+    return left ? (uint64_t)__double_as_longlong(score) : ~0ull;
+}
+
+// Lowest (key, lane) of the wave: the lowest upper half, the lowest lower half that comes with it, the first
+// lane that has both.
+__device__ __forceinline__ void wave_argmin(uint64_t key, int i, uint64_t &w_key, int &w_best) {
+    const uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key;
+    const uint32_t least_hi = wave_min(hi);
+    const uint32_t least_lo = wave_min(hi == least_hi ? lo : 0xFFFFFFFFu);
+    const uint64_t here = __builtin_amdgcn_ballot_w64(hi == least_hi && lo == least_lo);
+    w_key = (uint64_t)least_hi << 32 | least_lo;
+    w_best = __builtin_amdgcn_readfirstlane(i) + (int)__builtin_ctzll(here);
 }
 
 // First phase of Bulyan: Krum applied again and again to the vectors not yet chosen, until
@@ -590,7 +560,7 @@ __global__ __launch_bounds__(kSelectThreads) void bulyan_select_kernel(
     constexpr int S = 64 * WAVES, kFillers = kSelectThreads / S;
     typedef double f64x2 __attribute__((ext_vector_type(2)));
     extern __shared__ __align__(16) double s_rows[];
-    __shared__ double s_wave_score[2][WAVES];
+    __shared__ uint64_t s_wave_key[2][WAVES];
     __shared__ int s_wave_best[2][WAVES];
     __shared__ int32_t s_row_of[S];
     const int i = threadIdx.x % S, filler = threadIdx.x / S;
@@ -638,25 +608,24 @@ __global__ __launch_bounds__(kSelectThreads) void bulyan_select_kernel(
 #pragma unroll
             for (int u = 0; u < 8; ++u) x[u] = y[u];
         }
-        if (!left) score = __builtin_huge_val();
-        double w_score;
+        uint64_t w_key;
         int best;
-        wave_argmin(score, i, w_score, best);
+        wave_argmin(score_key(score, left), i, w_key, best);
         if constexpr (WAVES > 1) {
             const int side = round & 1;  // a round's winners are read while the next one's are written
             if ((i & 63) == 0) {
-                s_wave_score[side][i >> 6] = w_score;
+                s_wave_key[side][i >> 6] = w_key;
                 s_wave_best[side][i >> 6] = best;
             }
             __syncthreads();
-            double b_score = s_wave_score[side][0];
+            uint64_t b_key = s_wave_key[side][0];
             best = s_wave_best[side][0];
 #pragma unroll
             for (int w = 1; w < WAVES; ++w) {
-                const double o_score = s_wave_score[side][w];
+                const uint64_t o_key = s_wave_key[side][w];
                 const int o_best = s_wave_best[side][w];
-                if (o_score < b_score || (o_score == b_score && o_best < best)) {
-                    b_score = o_score;
+                if (o_key < b_key || (o_key == b_key && o_best < best)) {
+                    b_key = o_key;
                     best = o_best;
                 }
             }

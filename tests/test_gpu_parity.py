@@ -860,6 +860,40 @@ def test_bulyan_selection_on_the_returned_distances(f, c):
         assert sorted(np.nonzero(sel.cpu().numpy())[0].tolist()) == sorted(want), (f, c, kind)
 
 
+@pytest.mark.parametrize("f,c", [(7, 0), (7, 1), (49, 8), (63, 0), (65, 1), (83, 20), (127, 0), (127, 31)])
+def test_bulyan_selection_among_infinite_scores(f, c):
+    # finite rows whose squared norm is beyond fp32: distances to them are infinite, and with more than c + 1 of
+    # them so are the scores of all vectors left in some round.  A vector is chosen once all the same; lowest
+    # index among equal scores.  c + 2 such rows, every second row and all of them
+    rng = np.random.default_rng(f * 100 + c)
+    d = 131
+    idx = torch.arange(f, dtype=torch.int32, device=DEV)
+    for far in (np.arange(c + 2) * (f // (c + 2)), np.arange(0, f, 2), np.arange(f)):
+        Xh = rng.standard_normal((f, d)).astype(np.float32)
+        Xh[far, far] = 3e30
+        out, sel, order, dist = B.byz_bulyan(torch.tensor(Xh, device=DEV), d, idx, c)
+        torch.cuda.synchronize()
+        assert not np.isnan(dist.cpu().numpy()).any()
+        want = _bulyan_order(dist.cpu().numpy(), c)
+        assert order.cpu().tolist() == want, (f, c, len(far))
+        assert np.nonzero(sel.cpu().numpy())[0].tolist() == sorted(want), (f, c, len(far))
+    # NaN distances (rows that hold a NaN; two finite rows with such a norm in one column): the order is not
+    # specified, a vector is still chosen once
+    for kind in range(3):
+        Xh = rng.standard_normal((f, d)).astype(np.float32)
+        if kind == 0:
+            Xh[0, 5] = np.nan
+        elif kind == 1:
+            Xh[:, 7] = np.nan
+        else:
+            Xh[[1, f - 1], 9] = 3e30
+        out, sel, order, dist = B.byz_bulyan(torch.tensor(Xh, device=DEV), d, idx, c)
+        torch.cuda.synchronize()
+        chosen = order.cpu().tolist()
+        assert np.isnan(dist.cpu().numpy()).any() and len(set(chosen)) == f - 2 * c, (f, c, kind, chosen)
+        assert np.nonzero(sel.cpu().numpy())[0].tolist() == sorted(chosen), (f, c, kind)
+
+
 NETWORKS = (9, 15, 21, 25, 31, 35, 41, 49, 57, 63, 65, 73, 81, 97, 109, 121, 137, 153, 169)
 
 
