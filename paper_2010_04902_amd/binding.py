@@ -214,41 +214,66 @@ def _need(t, n, what):
         raise ValueError("%s has %d elements, the call needs %d" % (what, int(t.numel()), n))
 
 
+def _other_stream(stream, device):
+    """The stream of a call as one of torch's, None where it is the current one anyway."""
+    if stream is None:
+        return None
+    torch = _torch()
+    handle = _stream_ptr(stream).value or 0
+    if handle == torch.cuda.current_stream(device).cuda_stream:
+        return None
+    if handle <= 1:  # the default stream; torch would take 0 for a new one
+        return torch.cuda.default_stream(device)
+    return stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(handle, device=device)
+
+
 _checked_tables = {}
 
 
-def _need_rows_in_range(table, count, n_rows, what):
+def _need_rows_in_range(table, count, n_rows, what, stream=None):
     """The kernels trust the row numbers they are given (they are not range-checked on the
     device): refuse, before any launch, a table whose first `count` entries do not all lie in
     [0, n_rows).  The minimum and maximum are read back once per tensor object -- remembered
     through a weak reference, with torch's modification counter -- so repeated calls with one
-    table cost nothing, and a new tensor that happens to reuse the memory is looked at afresh."""
+    table cost nothing, and a new tensor that happens to reuse the memory is looked at afresh.
+    They are read on the stream of the call, behind what that stream still has to write (a vote's
+    winners); a table that was refused is looked at again the next time."""
     if count <= 0:
         return
     _need(table, count, what)
     entry = _checked_tables.get(id(table))
-    known = (entry is not None and entry[0]() is table and
-             entry[1] == (int(table._version), int(count)))
-    if known and entry[2][0] >= 0 and entry[2][1] < n_rows:
+    key = (int(table._version), int(count))
+    if (entry is not None and entry[0]() is table and entry[1] == key and
+            entry[2][0] >= 0 and entry[2][1] < n_rows):
         return
-    if table.is_cuda and _torch().cuda.is_current_stream_capturing():
+    torch = _torch()
+    other = _other_stream(stream, table.device) if table.is_cuda else None
+    if table.is_cuda:
         # nothing can be read back while a graph is being captured, and a table a captured
         # kernel will write (winner rows of a vote in the same graph) has no contents yet:
         # there the caller vouches for the table
-        return
-    if known:
-        bounds = entry[2]
-    else:
-        # one copy to the host, then the bounds there: two reductions on the device, a copy back each,
-        # took 20 us more of a call with a new table (tolerant vote, then the median of its winners)
+        if torch.cuda.is_current_stream_capturing():
+            return
+        if other is not None:
+            with torch.cuda.stream(other):
+                if torch.cuda.is_current_stream_capturing():
+                    return
+    # one copy to the host, then the bounds there: two reductions on the device, a copy back each,
+    # took 20 us more of a call with a new table (tolerant vote, then the median of its winners)
+    if other is None:
         head = table.reshape(-1)[:count].cpu()
-        bounds = (int(head.min()), int(head.max()))
-        if len(_checked_tables) >= 256:
-            _checked_tables.clear()
-        _checked_tables[id(table)] = (weakref.ref(table), (int(table._version), int(count)), bounds)
+    else:
+        torch.cuda.current_stream(table.device).synchronize()  # a table that was made there
+        with torch.cuda.stream(other):
+            head = table.reshape(-1)[:count].cpu()
+    bounds = (int(head.min()), int(head.max()))
     if bounds[0] < 0 or bounds[1] >= n_rows:
+        _checked_tables.pop(id(table), None)
         raise ValueError("%s names rows %d..%d, the matrix has rows 0..%d"
                          % (what, bounds[0], bounds[1], n_rows - 1))
+    if len(_checked_tables) >= 256:
+        _checked_tables.clear()
+    _checked_tables[id(table)] = (weakref.ref(table), key, bounds)
 
 
 def _rows_2d(copies):
@@ -261,7 +286,7 @@ def byz_vote(copies, d, file_rows_dev, f, r, stream=None):
     """-> (winner_replica[f] int32, winner_row[f] int32, pair_neq[f] int32 bit masks), on device."""
     torch = _torch()
     ld = _rows_2d(copies)
-    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev")
+    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
     wrep = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
     wrow = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
     neq = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
@@ -278,7 +303,7 @@ def byz_vote_tolerant(copies, d, file_rows_dev, f, r, atol, rtol, stream=None):
     """-> (winner_replica[f] int32, winner_row[f] int32, pair_far[f] int32 bit masks), on device."""
     torch = _torch()
     ld = _rows_2d(copies)
-    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev")
+    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
     wrep = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
     wrow = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
     far = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
@@ -296,7 +321,7 @@ def byz_median(rows_base, d, row_index_dev, out=None, stream=None):
     torch = _torch()
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
-    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev")
+    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
         out = torch.empty(int(d), dtype=torch.float32, device=rows_base.device)
     _need(out, int(d), "out")
@@ -311,7 +336,7 @@ def byz_trimmed_mean(rows_base, d, row_index_dev, b, out=None, stream=None):
     torch = _torch()
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
-    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev")
+    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
         out = torch.empty(int(d), dtype=torch.float32, device=rows_base.device)
     _need(out, int(d), "out")
@@ -332,7 +357,7 @@ def byz_multi_krum(rows_base, d, row_index_dev, c, m, out=None, workspace=None, 
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
     dev = rows_base.device
-    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev")
+    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
         out = torch.empty(int(d), dtype=torch.float32, device=dev)
     _need(out, int(d), "out")
@@ -362,7 +387,7 @@ def byz_bulyan(rows_base, d, row_index_dev, c, out=None, workspace=None, stream=
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
     dev = rows_base.device
-    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev")
+    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
         out = torch.empty(int(d), dtype=torch.float32, device=dev)
     _need(out, int(d), "out")
@@ -387,7 +412,7 @@ def byz_mean_around_median(rows_base, d, row_index_dev, beta, out=None, stream=N
     torch = _torch()
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
-    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev")
+    _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
         out = torch.empty(int(d), dtype=torch.float32, device=rows_base.device)
     _need(out, int(d), "out")
@@ -436,7 +461,7 @@ def byz_aggregate(copies, d, file_rows_dev, f, r, out=None, winner_replica=None,
         if nbytes == 0:
             raise ByzError(-1, "byz_aggregate_workspace_bytes")
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=copies.device)
-    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev")
+    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
     _need(out, int(d), "out")
     _need(winner_replica, int(f), "winner_replica")
     args = [_dev_ptr(copies, ("float32",), "copies"), int(d), ld,
@@ -454,7 +479,7 @@ def byz_aggregate(copies, d, file_rows_dev, f, r, out=None, winner_replica=None,
 def byz_aggregate_static(copies, d, file_rows_dev, f, r, out, winner_replica, flags=0, stream=None):
     """byz_aggregate_opts on the library's own fixed scratch; the caller supplies every buffer."""
     ld = _rows_2d(copies)
-    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev")
+    _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
     _need(out, int(d), "out")
     _need(winner_replica, int(f), "winner_replica")
     _check(_load().byz_aggregate_static(_dev_ptr(copies, ("float32",), "copies"), int(d), ld,

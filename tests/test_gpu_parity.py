@@ -1565,6 +1565,49 @@ def test_repeated_calls_on_one_workspace_never_change():
     assert SINGLE in seen_paths and REDONE in seen_paths, seen_paths
 
 
+def _keep_busy(scratch, times=100):
+    for _ in range(times):  # 50 us each at least
+        scratch.mul_(1.0)
+
+
+@pytest.mark.parametrize("as_handle", [False, True])
+def test_row_tables_are_checked_on_the_stream_of_the_call(as_handle):
+    # vote and median of its winners on a busy side stream, nothing on the current one: the check of the winner
+    # table has to come behind the vote.  The memory new tables get holds rows outside the matrix.  Then a table
+    # that the current stream is still making, for a call on the side stream.
+    f, r, d = 25, 3, 4099
+    w = W.make(MOLS, 5, 3, 3, d, REVERSED, seed=3, device=DEV)
+    rows = torch.tensor(w.file_rows.reshape(-1), dtype=torch.int32, device=DEV)
+    side = torch.cuda.Stream()
+    on = side.cuda_stream if as_handle else side
+    wrep0, wrow0, neq0 = B.byz_vote(w.X, d, rows, f, r)
+    want = B.byz_median(w.X, d, wrow0)
+    scratch = torch.ones(1 << 26, device=DEV)
+    backwards = torch.arange(f * r, dtype=torch.int32, device=DEV)
+    for it in range(3):
+        junk = [torch.full((f,), -7 + 1000 * (it % 2), dtype=torch.int32, device=DEV) for _ in range(64)]
+        torch.cuda.synchronize()
+        del junk
+        with torch.cuda.stream(side):
+            _keep_busy(scratch)
+        wrep, wrow, _ = B.byz_vote(w.X, d, rows, f, r, stream=on)
+        out = B.byz_median(w.X, d, wrow, stream=on)
+        side.synchronize()
+        assert torch.equal(wrow, wrow0) and torch.equal(out.view(torch.int32), want.view(torch.int32)), it
+        _keep_busy(scratch)
+        table = (f * r - 1 - backwards)[:f]
+        out = B.byz_median(w.X, d, table, stream=on)
+        side.synchronize()
+        assert torch.equal(out.view(torch.int32), B.byz_median(w.X, d, table.clone()).view(torch.int32)), it
+    # a table that was refused is looked at again, whoever wrote it in the meantime
+    table = torch.full((f,), f * r, dtype=torch.int32, device=DEV)
+    with pytest.raises(ValueError, match="names rows"):
+        B.byz_median(w.X, d, table, stream=on)
+    B.byz_calibration_copy(torch.zeros(4 * ((f + 3) // 4), dtype=torch.int32, device=DEV)[:f // 4 * 4], table[:f // 4 * 4])
+    with pytest.raises(ValueError, match="names rows 0..%d" % (f * r)):
+        B.byz_median(w.X, d, table, stream=on)
+
+
 def test_random_shapes_sizes_and_layouts():
     # a seeded sweep over assignments (every kernel family: generated, padded and 169-wire
     # networks, single pass and two-step, more than 64 files, r = 3, 5, 7), sizes, row pitches,
