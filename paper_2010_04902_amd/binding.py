@@ -227,6 +227,21 @@ def _other_stream(stream, device):
     return stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(handle, device=device)
 
 
+def _new(shape, dtype, device, stream):
+    """A tensor a call on `stream` may write at once.  Where that is not the current stream the memory is
+    taken from that stream's share of torch's pool: work still queued on the current one does not use it,
+    and dropped while the call runs (workspaces are, on return) it goes to nobody else.  The current
+    stream, which will read the results, is noted with it."""
+    torch = _torch()
+    other = _other_stream(stream, device) if stream is not None and device.type == "cuda" else None
+    if other is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    with torch.cuda.stream(other):
+        t = torch.empty(shape, dtype=dtype, device=device)
+    t.record_stream(torch.cuda.current_stream(device))
+    return t
+
+
 _checked_tables = {}
 
 
@@ -287,9 +302,9 @@ def byz_vote(copies, d, file_rows_dev, f, r, stream=None):
     torch = _torch()
     ld = _rows_2d(copies)
     _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
-    wrep = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
-    wrow = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
-    neq = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
+    wrep = _new(max(int(f), 0), torch.int32, copies.device, stream)
+    wrow = _new(max(int(f), 0), torch.int32, copies.device, stream)
+    neq = _new(max(int(f), 0), torch.int32, copies.device, stream)
     _check(_load().byz_vote(_dev_ptr(copies, ("float32",), "copies"), int(d), ld,
                             _dev_ptr(file_rows_dev, ("int32",), "file_rows_dev"), int(f), int(r),
                             _dev_ptr(wrep, ("int32",), "winner_replica"),
@@ -304,9 +319,9 @@ def byz_vote_tolerant(copies, d, file_rows_dev, f, r, atol, rtol, stream=None):
     torch = _torch()
     ld = _rows_2d(copies)
     _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
-    wrep = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
-    wrow = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
-    far = torch.empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
+    wrep = _new(max(int(f), 0), torch.int32, copies.device, stream)
+    wrow = _new(max(int(f), 0), torch.int32, copies.device, stream)
+    far = _new(max(int(f), 0), torch.int32, copies.device, stream)
     _check(_load().byz_vote_tolerant(_dev_ptr(copies, ("float32",), "copies"), int(d), ld,
                                      _dev_ptr(file_rows_dev, ("int32",), "file_rows_dev"),
                                      int(f), int(r), float(atol), float(rtol),
@@ -323,7 +338,7 @@ def byz_median(rows_base, d, row_index_dev, out=None, stream=None):
     f = int(row_index_dev.numel())
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = torch.empty(int(d), dtype=torch.float32, device=rows_base.device)
+        out = _new(int(d), torch.float32, rows_base.device, stream)
     _need(out, int(d), "out")
     _check(_load().byz_median(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                               _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f,
@@ -338,7 +353,7 @@ def byz_trimmed_mean(rows_base, d, row_index_dev, b, out=None, stream=None):
     f = int(row_index_dev.numel())
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = torch.empty(int(d), dtype=torch.float32, device=rows_base.device)
+        out = _new(int(d), torch.float32, rows_base.device, stream)
     _need(out, int(d), "out")
     _check(_load().byz_trimmed_mean(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                                     _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f,
@@ -359,13 +374,13 @@ def byz_multi_krum(rows_base, d, row_index_dev, c, m, out=None, workspace=None, 
     dev = rows_base.device
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = torch.empty(int(d), dtype=torch.float32, device=dev)
+        out = _new(int(d), torch.float32, dev, stream)
     _need(out, int(d), "out")
     if workspace is None:
-        workspace = torch.empty(max(byz_multi_krum_workspace_bytes(f), 256), dtype=torch.uint8, device=dev)
-    selected = torch.empty(f, dtype=torch.int32, device=dev)
-    scores = torch.empty(f, dtype=torch.float64, device=dev)
-    dist = torch.empty((f, f), dtype=torch.float64, device=dev)
+        workspace = _new(max(byz_multi_krum_workspace_bytes(f), 256), torch.uint8, dev, stream)
+    selected = _new(f, torch.int32, dev, stream)
+    scores = _new(f, torch.float64, dev, stream)
+    dist = _new((f, f), torch.float64, dev, stream)
     _check(_load().byz_multi_krum(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                                   _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f, int(c),
                                   int(m), _dev_ptr(out, ("float32",), "out"),
@@ -389,13 +404,13 @@ def byz_bulyan(rows_base, d, row_index_dev, c, out=None, workspace=None, stream=
     dev = rows_base.device
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = torch.empty(int(d), dtype=torch.float32, device=dev)
+        out = _new(int(d), torch.float32, dev, stream)
     _need(out, int(d), "out")
     if workspace is None:
-        workspace = torch.empty(max(byz_bulyan_workspace_bytes(f), 256), dtype=torch.uint8, device=dev)
-    selected = torch.empty(f, dtype=torch.int32, device=dev)
-    order = torch.empty(max(f - 2 * int(c), 1), dtype=torch.int32, device=dev)
-    dist = torch.empty((f, f), dtype=torch.float64, device=dev)
+        workspace = _new(max(byz_bulyan_workspace_bytes(f), 256), torch.uint8, dev, stream)
+    selected = _new(f, torch.int32, dev, stream)
+    order = _new(max(f - 2 * int(c), 1), torch.int32, dev, stream)
+    dist = _new((f, f), torch.float64, dev, stream)
     _check(_load().byz_bulyan(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                               _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f, int(c),
                               _dev_ptr(out, ("float32",), "out"),
@@ -414,7 +429,7 @@ def byz_mean_around_median(rows_base, d, row_index_dev, beta, out=None, stream=N
     f = int(row_index_dev.numel())
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = torch.empty(int(d), dtype=torch.float32, device=rows_base.device)
+        out = _new(int(d), torch.float32, rows_base.device, stream)
     _need(out, int(d), "out")
     _check(_load().byz_mean_around_median(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                                           _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f,
@@ -453,14 +468,14 @@ def byz_aggregate(copies, d, file_rows_dev, f, r, out=None, winner_replica=None,
     torch = _torch()
     ld = _rows_2d(copies)
     if out is None:
-        out = torch.empty(int(d), dtype=torch.float32, device=copies.device)
+        out = _new(int(d), torch.float32, copies.device, stream)
     if winner_replica is None:
-        winner_replica = torch.empty(int(f), dtype=torch.int32, device=copies.device)
+        winner_replica = _new(int(f), torch.int32, copies.device, stream)
     if workspace is None:
         nbytes = byz_aggregate_workspace_bytes(f, r)
         if nbytes == 0:
             raise ByzError(-1, "byz_aggregate_workspace_bytes")
-        workspace = torch.empty(nbytes, dtype=torch.uint8, device=copies.device)
+        workspace = _new(nbytes, torch.uint8, copies.device, stream)
     _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
     _need(out, int(d), "out")
     _need(winner_replica, int(f), "winner_replica")

@@ -1608,6 +1608,60 @@ def test_row_tables_are_checked_on_the_stream_of_the_call(as_handle):
         B.byz_median(w.X, d, table, stream=on)
 
 
+def test_tensors_of_a_call_on_another_stream_share_no_memory_with_the_current_one():
+    # what a call allocates while its stream is busy is neither what work still queued on the current stream
+    # reads, nor given away when it is dropped before the call has run
+    d = 70001
+    X = torch.randn(25, d, device=DEV)
+    idx = torch.arange(25, dtype=torch.int32, device=DEV)
+    want = B.byz_median(X, d, idx)
+    scratch = torch.ones(1 << 26, device=DEV)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for on in (side, side.cuda_stream):
+        source = torch.ones(d, device=DEV)
+        _keep_busy(scratch)
+        copy, at = source + 0, source.data_ptr()
+        del source
+        out = B.byz_median(X, d, idx, stream=on)
+        assert out.data_ptr() != at
+        torch.cuda.synchronize()
+        assert bool((copy == 1.0).all()) and torch.equal(out, want)
+        with torch.cuda.stream(side):
+            _keep_busy(scratch)
+        out = B.byz_median(X, d, idx, stream=on)
+        at = out.data_ptr()
+        del out
+        assert all(torch.empty(d, device=DEV).data_ptr() != at for _ in range(2))
+        torch.cuda.synchronize()
+
+
+def test_workspaces_of_calls_on_a_busy_stream():
+    # Multi-Krum, Bulyan and the aggregation keep working in workspaces they allocated and dropped while the
+    # current stream fills everything it can get of that size
+    f, d = 25, 4099
+    X = torch.randn(f, d, device=DEV)
+    idx = torch.arange(f, dtype=torch.int32, device=DEV)
+    w = W.make(MOLS, 5, 3, 3, d, ALIE, seed=5, device=DEV)
+    rows = torch.tensor(w.file_rows.reshape(-1), dtype=torch.int32, device=DEV)
+    scratch = torch.ones(1 << 26, device=DEV)
+    side = torch.cuda.Stream()
+    calls = [(lambda s: B.byz_multi_krum(X, d, idx, 5, 15, stream=s), B.byz_multi_krum_workspace_bytes(f)),
+             (lambda s: B.byz_bulyan(X, d, idx, 5, stream=s), B.byz_bulyan_workspace_bytes(f)),
+             (lambda s: B.byz_aggregate(w.X, d, rows, w.f, w.r, stream=s)[:2], B.byz_aggregate_workspace_bytes(w.f, w.r))]
+    for call, nbytes in calls:
+        want = call(None)
+        for on in (side, side.cuda_stream):
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                _keep_busy(scratch)
+            got = call(on)
+            junk = [torch.full((nbytes,), 255, dtype=torch.uint8, device=DEV) for _ in range(4)]
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(got, want)), (nbytes, on)
+            del junk
+
+
 def test_random_shapes_sizes_and_layouts():
     # a seeded sweep over assignments (every kernel family: generated, padded and 169-wire
     # networks, single pass and two-step, more than 64 files, r = 3, 5, 7), sizes, row pitches,
