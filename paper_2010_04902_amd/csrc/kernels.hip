@@ -1449,11 +1449,20 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(const uint32_t *__
 // coordinates off lines: (25,3) 302 / 292 / 290, (49,3) 589 / 569 / 566, (49,7) 1377 / 1329 / 1332, (81,3) 962 /
 // 924 / 928; on lines 291 / 292 / 289, 556 / 548 / 544, 1233 / 1212 / 1218, 893 / 872 / 878.  One word a thread, 2.5 M:
 // (121,3) 668 / 639 / 637 off lines, 562 / 571 / 556 on, (169,3) 922 / 870 / 864 and 792 / 787 / 785.
+// Up to 15 files of which every copy is read that pays later: us a call, plain / 64 neighbours, (9,3) 2.2 M 70.0 / 74.2 on
+// the lines, 74.3 / 78.8 off, 3.5 M 89.2 / 96.5 and 96.7 / 104.2, 6 M the same, 11.2 M 242.7 / 236.4 and 263.3 /
+// 256.3; (15,3) 3.5 M 117.7 / 122.3 and 127.1 / 133.3, 6 M 194.7 / 194.6 and 208.3 / 211.3, 11.2 M the same.  (21,3)
+// 3.5 M 147.8 / 149.6, trimmed mean off the lines 156.5 / 152.5; early-majority (9,3) 2.5 M 43.6 / 43.0 and 44.6 / 43.3.
 constexpr unsigned kShortLaunchBlocks = 2048;
 constexpr unsigned block_group(int v) { return v == 2 ? 16 : 64; }
-template <unsigned GROUP>
+// Longest launch in plain order, of those that are not short.
+constexpr unsigned plain_launch_blocks(int f, bool all_copies) {
+    return f <= 15 && all_copies ? 4 * kShortLaunchBlocks : kShortLaunchBlocks;
+}
+template <unsigned GROUP, unsigned PLAIN = kShortLaunchBlocks>
 __device__ __forceinline__ unsigned tile_of_block(unsigned b, unsigned n_blocks) {
-    if (n_blocks > kShortLaunchBlocks) return neighbours_together(b, n_blocks, GROUP);
+    if (n_blocks > PLAIN) return neighbours_together(b, n_blocks, GROUP);
+    if (PLAIN > kShortLaunchBlocks && n_blocks > kShortLaunchBlocks) return b;
     const unsigned q = n_blocks / 8, rem = n_blocks % 8, x = b % 8, i = b / 8;
     return x * q + (x < rem ? x : rem) + i;  // XCD x owns q tiles, one more if x < rem
 }
@@ -1477,7 +1486,8 @@ __device__ __forceinline__ void fused_body(const uint32_t *__restrict__ X, int64
     // its neighbour instead of a scalar tail, and threads past the end redo it, so there are
     // no branches around loads and ballots (d >= V is the launcher's business).
     const int64_t n_thr = (d + V - 1) / V;
-    const int64_t gt = (int64_t)tile_of_block<block_group(V)>(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    constexpr unsigned kPlain = plain_launch_blocks(F, NS == R);
+    const int64_t gt = (int64_t)tile_of_block<block_group(V), kPlain>(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     const int64_t c0 = (gt + 1) * V <= d ? gt * V : d - V;
     uint32_t flags[(F + 63) / 64] = {};  // lane j%64 collects the pair bits of file j
     // What other waves have published so far, read now so that the wait is over long before the

@@ -1013,6 +1013,32 @@ def test_long_single_passes_on_and_off_cache_lines(f, r, vec):
             del ranks
 
 
+@pytest.mark.parametrize("f", [9, 15])
+def test_long_single_passes_of_few_files(f):
+    # up to 15 files of three copies keep the plain order of the blocks up to 8192 of them: the last such
+    # launch and the first in groups of neighbours, the group and the last vector not whole
+    r, rows, b = 3, torch.arange(f * 3, dtype=torch.int32, device=DEV), 2
+    for d in (2049 * 1024 - 1, 8192 * 1024, 8192 * 1024 + 77):
+        X = torch.randn(f, 1, d + 1, device=DEV, generator=torch.Generator(device=DEV).manual_seed(d))
+        ranks = X[:, 0, :d].sort(dim=0).values
+        X = X.expand(f, r, d + 1).reshape(f * r, d + 1).contiguous()
+        X[0, d - 1] += 1.0
+        X[r * f - 1, 1] -= 2.0
+        first = [1] + [0] * (f - 1)
+        for flags in (0, B.BYZ_AGG_TRIM(b), B.BYZ_AGG_EARLY_MAJORITY):
+            out = torch.full((d + 8,), 7.0, device=DEV)
+            _, wrep, _ = B.byz_aggregate_opts(X, d, rows, f, r, flags, out=out)
+            torch.cuda.synchronize()
+            want = ranks[(f - 1) // 2]
+            if flags == B.BYZ_AGG_TRIM(b):
+                want = torch.zeros(d, device=DEV)
+                for v in ranks[b:f - b]:
+                    want += v
+                want /= torch.tensor(float(f - 2 * b), device=DEV)
+            assert torch.equal(out[:d], want) and bool((out[d:] == 7.0).all()), (f, d, flags)
+            assert wrep.cpu().tolist() == first, (f, d, flags)
+
+
 @pytest.mark.parametrize("f", [9, 49, 81, 97, 127, 171, 207, 255])
 def test_sorts_of_long_rows_on_and_off_cache_lines(f):
     # above 131072 coordinates neighbouring blocks go to one XCD where rows don't start on cache lines:
