@@ -1949,7 +1949,11 @@ int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
 // to 25 files of three (1 M 55.9 / 50.8, 400000 25.9 / 22.7), two words for their trimmed mean (500000 31.1 /
 // 27.5; four 41.0), 1024 threads of one word for 49 files of three (250000 37.4 / 29.0; 512 of two 50.4).  More
 // files and two words per thread: (81,3) 140000 44.4 / 65.6, (63,7) 50000 54.2 / 56.8.  Fewer than 21 files of
-// longer rows keep the four kernels: (15,3) 500000 20.7 / 39.3, (9,3) 17.6 / 22.9.
+// longer rows keep the four kernels: (15,3) 500000 20.7 / 39.3, (9,3) 17.6 / 22.9.  So do medians of (25,3) whose
+// blocks are a little more than one a CU: 524288 coordinates 32.0 / 28.3, 525001 34.3 / 35.1 (off the cache lines
+// 35.9 / 37.4), 600000 37.0 / 37.6 (38.0 / 39.6), 700001 39.7 / 39.8 (39.9 / 40.8), 786432 44.5 / 41.5 (44.7 / 42.4); on
+// the far side of 2^20 there are no slots (1048581 63.5, with two kernels' 1048576 53.4).
+constexpr int64_t kOneBlockPerCu = 256;
 template <int F, int R, bool TRIM>
 int launch_short(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
                  uint32_t *out, int trim_b, int32_t *winner_replica, bool *done, hipStream_t s) {
@@ -1961,6 +1965,7 @@ int launch_short(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     if constexpr (F >= 21 && F <= 49) {
         constexpr bool one_word = R == 3 && F > 25;
         constexpr int V = one_word ? 1 : (R == 3 && TRIM ? 2 : vec_for_pass(F, R, TRIM));
+        if (F > 21 && V == 4 && d > kOneBlockPerCu * 512 * V && d <= kOneBlockPerCu * 4 / 3 * 512 * V) return BYZ_OK;
         rc = launch_short_pair<F, R, TRIM, V, one_word ? 1024 : 512, gated_vec(F)>(
             X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
     }

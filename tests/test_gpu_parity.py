@@ -1484,6 +1484,27 @@ def test_short_rows_where_the_blocks_or_the_kernels_change(f, r):
                 assert bool((out[d:] == 7.0).all()), tag
 
 
+@pytest.mark.parametrize("d", [524288, 524289, 698368, 698369])
+def test_short_rows_around_one_block_a_cu(d):
+    # the median of (25,3) takes four kernels between 256 and 341 blocks of 2048 words and two on either side
+    f, r, rows = 25, 3, torch.arange(75, dtype=torch.int32, device=DEV)
+    X = torch.randn(f, 1, d + 1, device=DEV, generator=torch.Generator(device=DEV).manual_seed(d))
+    X = X.expand(f, r, d + 1).reshape(f * r, d + 1).contiguous()
+    X[0, d - 1] += 1.0
+    for majority in (True, False):
+        if not majority:
+            for k in range(r):
+                X[r * 12 + k, d // 2 + k] = 9.0 + k
+            X[r * 12, d - 2] = -9.0
+        keep = torch.arange(f, device=DEV) * r
+        keep[0] += 1
+        want = X.index_select(0, keep)[:, :d].sort(dim=0).values[f // 2]
+        out, wrep, ws = B.byz_aggregate(X, d, rows, f, r)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and wrep.cpu().tolist() == [1] + [0] * 24, (d, majority)
+        assert B.byz_aggregate_path(ws) == (SINGLE if majority else REDONE), (d, majority)
+
+
 @pytest.mark.parametrize("f", [171, 191, 193, 223, 225, 255])
 def test_pass_over_files_split_over_two_waves(f):
     # most and fewest spare wires of every size of the halves, the shortest rows that take it and a ragged
