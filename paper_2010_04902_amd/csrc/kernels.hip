@@ -1037,7 +1037,8 @@ __global__ __launch_bounds__(kBlock) void trimmed_mean_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
     int f, int b, unsigned group, uint32_t *__restrict__ out, const uint32_t *__restrict__ gate, int gate_n) {
     if (gate != nullptr && !any_word_set(gate, gate_n)) return;
-    const unsigned tile = group != 0 ? neighbours_together(blockIdx.x, gridDim.x, group) : blockIdx.x;
+    // (only the one-word form is launched in groups; without the test for it the gated form took 0.2-0.4 us longer)
+    const unsigned tile = V == 1 && group != 0 ? neighbours_together(blockIdx.x, gridDim.x, group) : blockIdx.x;
     const int64_t gt = (int64_t)tile * kBlock + threadIdx.x;
     if (gt >= (d + V - 1) / V) return;
     const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
