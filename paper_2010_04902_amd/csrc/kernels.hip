@@ -109,11 +109,14 @@ constexpr int vec_for_pass(int f, int r, bool trim) {
 // early-majority 16.0 and 18.3; (25,5) 500 17.4 and 20.5).
 // Rows of five copies from which four words per thread are the faster form after all: always up to 25 files, and
 // off the cache lines up to 49, where two words a thread leave more lines shared by two blocks.  us a call, two
-// words / four: (25,5) 1 M 91.6 / 92.0 off lines, 2 M 177 / 164 off and 163 / 159 on, 6 M 526 / 488 and 470 / 468;
-// (35,5) off lines 0.7 M 84 / 90, 1 M 123 / 112, 6 M 697 / 650, on lines 637 / 641; (49,5) off lines 1 M 168 / 161, 6 M
-// 974 / 889, trimmed mean 977 / 913, on lines 876 / 887.
-[[maybe_unused]] constexpr bool four_words_of_five(int f, int64_t d, bool lines) {
-    return d >= (int64_t)15 << 16 && (f <= 25 || (f <= 49 && !lines));
+// words / four: (25,5) 1 M 91.6 / 92.0 off lines, 1.05 M 122 / 100 off and 118 / 94 on, 2.1 M 212 / 183 and 194 / 172,
+// 4 M 383 / 338 and 346 / 320; (35,5) off lines 0.7 M 84 / 90, 1.05 M 161 / 132, 2.1 M 277 / 239, 4 M 503 / 435, 6 M on
+// lines 637 / 641; (49,5) off lines 1.05 M 189 / 183, 4 M 661 / 618, trimmed mean 1.1 M 197 / 208, 1.2 M 217 / 211, 4 M 663 /
+// 640, 6 M on lines 876 / 887.  Early-majority mode, where three copies are read: off lines (25,5) 2.1 M 123 / 112,
+// (35,5) 161 / 159, (49,5) 1.1 M 127 / 134, 2.1 M 224 / 218, 4 M 412 / 396.  But its trimmed mean keeps two words:
+// (49,5) 1.1 M 129 / 148, 4 M 416 / 428, (35,5) 2.1 M 168 / 168, (25,5) 1.7 M 98 / 103, on lines 97 / 103.
+[[maybe_unused]] constexpr bool four_words_of_five(int f, int64_t d, bool lines, bool early_trim) {
+    return !early_trim && d >= (int64_t)15 << 16 && (f <= 25 || (f <= 49 && !lines));
 }
 [[maybe_unused]] constexpr int64_t short_row(int f, int r) { return f <= 25 && r == 5 ? 65536 : 131072; }
 // Files ahead of the one in use in the first kernel of short calls: the depths measured above, as far as
@@ -1995,7 +1998,8 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     if (rc != BYZ_OK) return rc;
     constexpr bool kShortToo = vec_for_pass(F, R, false) > 1;  // or the only width is one word already
     const int64_t one_block = (int64_t)kBlock * vec_for_pass(F, R, trim_b >= 0);
-    [[maybe_unused]] const bool four = four_words_of_five(F, d, rows_on_lines(X, ld));
+    [[maybe_unused]] const bool four =
+        four_words_of_five(F, d, rows_on_lines(X, ld), (probe_opts & 1) != 0 && trim_b >= 0);
     if (kShortToo && d <= short_row(F, R) && (d <= kBlock || d > one_block)) {
         if constexpr (kShortToo) {
             if (trim_b < 0)

@@ -1013,6 +1013,23 @@ def test_long_single_passes_on_and_off_cache_lines(f, r, vec):
             del ranks
 
 
+@pytest.mark.parametrize("f", [25, 35, 49])
+def test_early_majority_trimmed_mean_of_long_rows_of_five_copies(f):
+    # two words a thread at every length, also where other calls take four; an odd last vector
+    r, b, rows = 5, f // 8, torch.arange(f * 5, dtype=torch.int32, device=DEV)
+    for d in (15 << 16, (1 << 20) + 1):
+        X = torch.randn(f, 1, d + 1, device=DEV, generator=torch.Generator(device=DEV).manual_seed(d))
+        want = torch.zeros(d, device=DEV)
+        for v in X[:, 0, :d].sort(dim=0).values[b:f - b]:
+            want += v
+        want /= torch.tensor(float(f - 2 * b), device=DEV)
+        X = X.expand(f, r, d + 1).reshape(f * r, d + 1).contiguous()
+        X[3 * r + 4, d - 1] += 1.0
+        out, wrep, _ = B.byz_aggregate_opts(X, d, rows, f, r, B.BYZ_AGG_EARLY_MAJORITY | B.BYZ_AGG_TRIM(b))
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and wrep.cpu().tolist() == [0] * f, (f, d)
+
+
 @pytest.mark.parametrize("f", [9, 15])
 def test_long_single_passes_of_few_files(f):
     # up to 15 files of three copies keep the plain order of the blocks up to 8192 of them: the last such
