@@ -314,7 +314,8 @@ size_t byz_aggregate_workspace_bytes(int f, int r);
  * (byz_aggregate_has_single_pass; with and without BYZ_AGG_TRIM); for
  * every other valid (f, r), and for d < 4, the call runs byz_vote's kernels and then
  * byz_median's (or byz_trimmed_mean's), reading the winners a second time; for r = 3 and
- * 169 < f <= 255, d >= 2^18, the two are one kernel that reads every copy once.
+ * 169 < f <= 255, d >= 2^18, the two are one kernel that reads every copy once, and the
+ * median is redone behind it where it has to be, as behind the single pass.
  * Errors: as byz_vote / byz_median, plus BYZ_ENOMEM (workspace too small).
  */
 int byz_aggregate(const float *copies, int64_t d, int64_t ld, const int32_t *file_rows_dev,
@@ -373,9 +374,9 @@ int byz_aggregate_static(const float *copies, int64_t d, int64_t ld, const int32
                          int f, int r, float *out, int32_t *winner_replica, unsigned flags,
                          void *stream);
 
-/* 1 if byz_aggregate runs (f, r) as the single pass described above, 0 if it runs byz_vote's and
- * byz_median's kernels one after the other (shapes without a compiled single-pass kernel, or
- * invalid (f, r)). */
+/* 1 if byz_aggregate runs (f, r) as the single pass described above for every d >= 4, 0 if it runs
+ * byz_vote's and byz_median's kernels one after the other (shapes without a compiled single-pass
+ * kernel; long rows of r = 3 and 169 < f <= 255 in one kernel all the same) or refuses (f, r). */
 int byz_aggregate_has_single_pass(int f, int r);
 
 /*
@@ -393,7 +394,8 @@ typedef enum byz_path {
                                    with bit 0 if the median was redone as well: 3)               */
     BYZ_PATH_TWO_STEP = 4       /* (f, r) not among byz_aggregate_has_single_pass' shapes or d < 4:
                                    byz_vote's and byz_median's kernels one after the other, or,
-                                   for r = 3 and 169 < f <= 255, long rows, in one                */
+                                   for r = 3 and 169 < f <= 255, long rows, in one (bit 2; with
+                                   bit 0 if there the median had to be redone: 5)                 */
 } byz_path;
 int byz_aggregate_path(const void *workspace, int *path, void *stream);
 

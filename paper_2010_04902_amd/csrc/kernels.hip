@@ -510,7 +510,7 @@ __device__ __forceinline__ uint32_t fed_differs_bit(int ns, int p) { return 1u <
 // A file read in early-majority mode has only r' slots of its own: if they are identical they
 // are the majority (Sec. 2) and any of them is the winner; if not, nothing is known about the
 // copies that were skipped and need_revote sends the call through the gated vote kernel.
-// two_step: the call counts as a two-step one, whatever came out.
+// two_step: the call counts as a two-step one (BYZ_PATH_TWO_STEP is set as well).
 __global__ void single_pass_decide_kernel(AggWorkspace *ws, const int32_t *__restrict__ file_rows,
                                           int f, int r, int32_t *winner_replica, int two_step) {
     __shared__ uint32_t s_median, s_revote;
@@ -551,9 +551,9 @@ __global__ void single_pass_decide_kernel(AggWorkspace *ws, const int32_t *__res
     if (threadIdx.x == 0) {
         ws->need_median = s_median;
         ws->need_revote = s_revote;
-        ws->path = two_step != 0 ? (uint32_t)BYZ_PATH_TWO_STEP
-                                 : (s_median != 0 ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : 0u) |
-                                       (s_revote != 0 ? (uint32_t)BYZ_PATH_REVOTED : 0u);
+        ws->path = (two_step != 0 ? (uint32_t)BYZ_PATH_TWO_STEP : 0u) |
+                   (s_median != 0 ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : 0u) |
+                   (s_revote != 0 ? (uint32_t)BYZ_PATH_REVOTED : 0u);
     }
 }
 
@@ -2144,6 +2144,9 @@ bool has_fused_trim(int f, int r) { return has_fused(f, r); }
 // split over two waves.  Shorter rows are voted on faster with the files dealt out to more blocks (f = 255,
 // us a call, vote and median / one pass: d = 10000 34 / 54, 100000 89 / 91, 140000 114 / 121, 200000 151 / 150,
 // 262145 218 / 172; f = 195 200000 121 / 129, 262145 167 / 150; f = 171 200000 100 / 101, 262145 141 / 117).
+// A file without a majority that makes the pass feed a loser's values costs the median on top: f = 171 262200
+// coordinates 125 (vote and median) / 159, trimmed mean 158 / 224, 1 M 482 / 509 and 606 / 740, 2.5 M 1176 / 1149 and 1454 / 1684;
+// f = 255 188 / 245, 219 / 303, 749 / 797, 868 / 997.  As everywhere, who does that gives up the vote in those files.
 bool takes_halves_pass(int f, int r, int64_t d) {
     return f > 169 && f <= 255 && r == 3 && d >= ((int64_t)1 << 18);
 }
