@@ -1,8 +1,8 @@
 """Benchmark of the ByzShield aggregation path (majority vote + coordinate-wise median) on one MI355X.
 
-A step is one pass of the whole path (byz_aggregate: probe, single-pass vote+median kernel,
-decision, gated median) over one batch of stacked worker returns that is already resident in
-HBM.  Prints ONE JSON line.
+A step is one pass of the whole path (byz_aggregate: for the headline workload probe, single-pass
+vote+median kernel, decision, gated median) over one batch of stacked worker returns that is
+already resident in HBM.  Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 2] [--unpadded] [--no-cpu]
 """
@@ -33,7 +33,7 @@ def kernel_code_digest():
     return hashlib.sha256("\n".join(lines).encode()).hexdigest()
 
 
-def _traffic_from_profiles(workload, kernel="fused_kernel"):
+def _traffic_from_profiles(workload, kernel):
     """(HBM bytes per launch, where the figure comes from) from the committed rocprofv3 counter
     summary of this kernel and workload; (None, why) if there is none or the kernels' code has
     changed since the counters were taken.  Nothing is counted during the benchmark run."""
@@ -138,7 +138,8 @@ def main():
                              winner_replica=wrep, workspace=ws, stream=on)
 
     def timed(flags, profile=True):
-        """W warm-up steps, then K timed steps; returns (ms per step, kernel ms list, byz_path)."""
+        """W warm-up steps, then K timed steps; returns (ms per step, kernel ms list, byz_path, the
+        name of the kernel timed)."""
         for i in range(args.warmup):
             step(i, flags)
         torch.cuda.synchronize()
@@ -151,11 +152,12 @@ def main():
             step(i, flags)
         torch.cuda.synchronize()
         t1 = time.perf_counter()
-        kernel_ms = []
+        kernel_ms, kernel = [], None
         if profile:
             kernel_ms = B.byz_profile_collect(args.steps)
+            kernel = B.byz_profile_kernel()
             B.byz_profile_enable(0)
-        return (t1 - t0) * 1e3 / args.steps, kernel_ms, path
+        return (t1 - t0) * 1e3 / args.steps, kernel_ms, path, kernel
 
     if args.calibration_copy:
         # a plain copy of known size: reads 2^30 bytes and writes 2^30 bytes
@@ -172,12 +174,14 @@ def main():
     # duration comes from a second region of the same K steps with a HIP event before and after
     # that kernel in every step (byz_profile_enable); those events sit between the launches and
     # cost a few microseconds per step, so they stay out of the headline region.
-    ms_per_step, _, path = timed(0, profile=False)
-    ms_per_step_events, kernel_ms, _ = timed(0)
+    ms_per_step, _, path, _ = timed(0, profile=False)
+    ms_per_step_events, kernel_ms, _, kernel = timed(0)
     coords_per_s = d / (ms_per_step * 1e-3)
-    if single_pass:
+    # what the library itself says it ran: one kernel that reads every copy, or the vote on its own
+    one_pass = kernel != "vote_pairs_kernel"
+    if one_pass:
         alg_bytes = 4.0 * (asg.r * asg.f + 1) * d  # every copy read once, one value written
-        kernel_bytes, kernel_name = alg_bytes, "fused_kernel<%d,%d>" % (asg.f, asg.r)
+        kernel_bytes, kernel_name = alg_bytes, "%s<%d,%d>" % (kernel, asg.f, asg.r)
     else:
         # vote kernel, then median kernel over the winners: the winners are read twice
         alg_bytes = 4.0 * ((asg.r + 1) * asg.f + 1) * d
@@ -206,8 +210,7 @@ def main():
     if kernel_ms:
         avg_ms = sum(kernel_ms) / len(kernel_ms)
         achieved = kernel_bytes / (avg_ms * 1e-3) / 1e9
-        traffic, traffic_source = _traffic_from_profiles(
-            cfg.name, "fused_kernel" if single_pass else "vote_pairs_kernel")
+        traffic, traffic_source = _traffic_from_profiles(cfg.name, kernel)
         result["roofline"] = {
             "bound": "hbm", "kernel": kernel_name,
             "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
@@ -231,13 +234,13 @@ def main():
     # (b) In the files where they hold a majority of the copies, make their copies pairwise
     # different by one such word each: those files have no majority left, the waves still saw
     # the false copies as the largest class, and wherever Eq. 3's tie rule now picks another
-    # copy the median is redone from the true winners (byz_path 1).  The price is theirs: the
+    # copy the median is redone from the true winners (bit 0 of byz_path).  The price is theirs: the
     # false vector no longer wins those files.
     # `adversarial_ms_per_step` is the slowest of these; the output stays the oracle's throughout.
     byz_set = set(int(b) for b in byz)
     clean = [j for j in range(asg.f) if not any(int(w) in byz_set for w in fw[j])]
     held = [j for j in range(asg.f) if sum(int(w) in byz_set for w in fw[j]) >= (asg.r + 1) // 2]
-    if single_pass and not args.no_extra and d > 1000:
+    if one_pass and not args.no_extra and d > 1000:
         c_hidden = d // 2 + 7
         legs = []
         if clean:
@@ -254,7 +257,7 @@ def main():
             for b in bufs:
                 for row, c in words:
                     b[row, c] += 1.0
-            a_ms, _, a_path = timed(0, profile=False)
+            a_ms, _, a_path, _ = timed(0, profile=False)
             for b, vals in zip(bufs, saved):
                 for (row, c), v in zip(words, vals):
                     b[row, c] = v
@@ -264,13 +267,13 @@ def main():
             result["adversarial_ms_per_step"] = max(result[key]["ms_per_step"] for key, _, _ in legs)
             result["adversarial_note"] = (
                 "slowest of: one word of one copy changed off the probe's sample (costs nothing: "
-                "byz_path 0); the Byzantine copies of every file they hold a majority of made "
-                "pairwise different by one word each (byz_path 1 where the tie rule then picks "
+                "byz_path as before); the Byzantine copies of every file they hold a majority of made "
+                "pairwise different by one word each (bit 0 of byz_path where the tie rule then picks "
                 "another copy: single pass + median over the winners, and the false vector "
                 "loses those files)")
 
     # The same steps replayed from a HIP graph (n_buf consecutive steps captured once): what is
-    # left of the launch gaps between the four kernels of a step.
+    # left of the launch gaps between the kernels of a step.
     if not args.no_extra:
         side = torch.cuda.Stream()
         side.wait_stream(stream)
@@ -302,8 +305,8 @@ def main():
     # beside the headline, never as `value`.
     if not args.no_early and single_pass:
         rp = (asg.r + 1) // 2
-        e_ms, _, e_path = timed(B.BYZ_AGG_EARLY_MAJORITY, profile=False)
-        _, e_kernel_ms, _ = timed(B.BYZ_AGG_EARLY_MAJORITY)
+        e_ms, _, e_path, _ = timed(B.BYZ_AGG_EARLY_MAJORITY, profile=False)
+        _, e_kernel_ms, _, _ = timed(B.BYZ_AGG_EARLY_MAJORITY)
         e_bytes = 4.0 * (rp * asg.f + 1) * d
         e_avg = sum(e_kernel_ms) / len(e_kernel_ms) if e_kernel_ms else None
         result["early_majority"] = {

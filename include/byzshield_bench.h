@@ -16,17 +16,21 @@ extern "C" {
 /*
  * Timing aid for benchmarks.  byz_profile_enable(n) with n > 0 creates n HIP event pairs for
  * the calling thread; from then on each byz_aggregate call of that thread records one pair
- * around its dominant kernel -- the single-pass kernel (its main launch, not the probe or the
- * finalisation), or the vote kernel for shapes without one -- on the call's stream, until n
- * calls have been recorded.
+ * around its dominant kernel -- the kernel that reads every copy and aggregates in one pass (its
+ * main launch, not the probe or the finalisation), or the vote kernel for calls without one --
+ * on the call's stream, until n calls have been recorded.
  * byz_profile_enable(0) releases the events.  Errors: BYZ_EINVAL (n < 0 or n > 100000),
  * BYZ_ENOMEM, BYZ_EDEVICE.
  * byz_profile_collect waits for the recorded events, writes the kernel durations in
  * milliseconds to host ms_out[0..*n_out-1] (at most `capacity`), and restarts recording at
  * the first pair.
+ * byz_profile_kernel names the kernel the calling thread's last recorded pair stands around
+ * ("fused_kernel", "short_pass_kernel", "fused_halves_kernel" or "vote_pairs_kernel", which reads
+ * the winners a second time afterwards); "" before the first one.  Static storage.
  */
 int byz_profile_enable(int max_calls);
 int byz_profile_collect(float *ms_out, int capacity, int *n_out);
+const char *byz_profile_kernel(void);
 
 /*
  * Reference kernel for hardware HBM counters: copies `bytes` (a multiple of 16) from device

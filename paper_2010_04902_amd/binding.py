@@ -82,6 +82,7 @@ def _load():
         "byz_calibration_read_rows": (c_int, [vp, i64, i64, c_int, vp, c_int, vp]),
         "byz_profile_enable": (c_int, [c_int]),
         "byz_profile_collect": (c_int, [ctypes.POINTER(ctypes.c_float), c_int, ip]),
+        "byz_profile_kernel": (ctypes.c_char_p, []),
         "byz_strerror": (ctypes.c_char_p, [c_int]),
         "byz_last_hip_error": (c_int, []),
     }
@@ -533,6 +534,11 @@ def byz_profile_collect(capacity):
     n = ctypes.c_int()
     _check(_load().byz_profile_collect(buf, int(capacity), ctypes.byref(n)), "byz_profile_collect")
     return [float(buf[i]) for i in range(n.value)]
+
+
+def byz_profile_kernel():
+    """-> name of the kernel the last recorded pair of events stands around, '' before the first."""
+    return _load().byz_profile_kernel().decode()
 
 
 def byz_calibration_read_rows(rows_base, d, n_rows, out, store, stream=None):

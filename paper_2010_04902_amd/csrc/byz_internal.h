@@ -86,6 +86,6 @@ BYZ_DECLARE_TRIMMED_MEAN(256_padded);
 
 // Records the event before (which = 0) or after (1) the dominant kernel of an aggregation, if
 // byz_profile_enable has armed any.  Returns a byz_status.
-int byz_internal_profile_mark(int which, void *stream);
+int byz_internal_profile_mark(int which, void *stream, const char *kernel = nullptr);
 
 #endif

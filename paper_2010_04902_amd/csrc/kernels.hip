@@ -55,6 +55,7 @@ struct ProfileState {
     int count = 0;
     hipEvent_t *start = nullptr;
     hipEvent_t *stop = nullptr;
+    const char *kernel = "";  // the one the last pair stands around
 };
 thread_local ProfileState g_prof;
 #endif
@@ -1924,7 +1925,7 @@ int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
                       uint32_t *out, int trim_b, int32_t *winner_replica, bool *done, hipStream_t s) {
     const int64_t blocks = (d + (int64_t)V * BLOCK - 1) / ((int64_t)V * BLOCK);
     if (blocks > most_slots(F, R)) return BYZ_OK;
-    int rc = byz_internal_profile_mark(0, s);
+    int rc = byz_internal_profile_mark(0, s, "short_pass_kernel");
     if (rc != BYZ_OK) return rc;
     short_pass_kernel<F, R, TRIM, V, BLOCK><<<(unsigned)blocks, BLOCK, 0, s>>>(
         X, d, ld, rows, reinterpret_cast<uint32_t *>(ws->perm_off), trim_b, out);
@@ -1994,7 +1995,7 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     }
     probe_kernel<F, R><<<1, kProbeThreads, 0, s>>>(X, d, ld, rows, ws, probe_opts);
     BYZ_HIP(hipGetLastError());
-    int rc = byz_internal_profile_mark(0, s);
+    int rc = byz_internal_profile_mark(0, s, "fused_kernel");
     if (rc != BYZ_OK) return rc;
     constexpr bool kShortToo = vec_for_pass(F, R, false) > 1;  // or the only width is one word already
     const int64_t one_block = (int64_t)kBlock * vec_for_pass(F, R, trim_b >= 0);
@@ -2323,7 +2324,7 @@ int launch_halves_pass(const uint32_t *X, int64_t d, int64_t ld, const int32_t *
                        uint32_t *out, int trim_b, hipStream_t s) {
     lay_out_rows_kernel<<<1, kWide, 0, s>>>(rows, f, 3, ld, ws);
     BYZ_HIP(hipGetLastError());
-    int rc = byz_internal_profile_mark(0, s);
+    int rc = byz_internal_profile_mark(0, s, "fused_halves_kernel");
     if (rc != BYZ_OK) return rc;
     const unsigned g = (unsigned)((d + 63) / 64);
     const unsigned group = rows_on_lines(X, ld) ? 0 : kHalvesGroup;
@@ -2475,10 +2476,11 @@ int byz_internal_launch_single_pass_7(int f, int r, const void *X, long long d, 
 
 // ---------------------------------------------------------------------------- C-ABI
 
-// which: 0 = before, 1 = after the dominant kernel of an aggregation on `stream`
-int byz_internal_profile_mark(int which, void *stream) {
+// which: 0 = before (kernel: its name), 1 = after the dominant kernel of an aggregation on `stream`
+int byz_internal_profile_mark(int which, void *stream, const char *kernel) {
     if (g_prof.count >= g_prof.capacity) return BYZ_OK;
     if (which == 0) {
+        g_prof.kernel = kernel;
         BYZ_HIP(hipEventRecord(g_prof.start[g_prof.count], (hipStream_t)stream));
     } else {
         BYZ_HIP(hipEventRecord(g_prof.stop[g_prof.count], (hipStream_t)stream));
@@ -2627,7 +2629,7 @@ static int aggregate_on_workspace(const float *copies, int64_t d, int64_t ld,
         reset_workspace_kernel<<<1, kWide, 0, s>>>(ws, (uint32_t)BYZ_PATH_TWO_STEP);
         BYZ_HIP(hipGetLastError());
         if (d > 0) {
-            rc = byz_internal_profile_mark(0, s);
+            rc = byz_internal_profile_mark(0, s, "vote_pairs_kernel");
             if (rc != BYZ_OK) return rc;
             rc = launch_vote_pairs_r(r, X, d, ld, file_rows_dev, f, ws->pair_neq, nullptr, 0, nullptr, s);
             if (rc != BYZ_OK) return rc;
@@ -2808,6 +2810,8 @@ extern "C" int byz_profile_collect(float *ms_out, int capacity, int *n_out) {
     g_prof.count = 0;
     return BYZ_OK;
 }
+
+extern "C" const char *byz_profile_kernel(void) { return g_prof.kernel; }
 
 extern "C" int byz_aggregate_path(const void *workspace, int *path, void *stream) {
     if (workspace == nullptr || path == nullptr) return BYZ_EINVAL;

@@ -53,7 +53,7 @@ CONFIGS = [
            {"kind": "alie", "z": 1.0}, 1, 20101004 + 133),
     # the widest file count the library takes: Ramanujan Case 2 with s = 3, m = 85,
     # (K,f,l,r) = (9,255,85,3), 765 rows (34 GB); q = 2, c_max = 29 from the exhaustive search.
-    # No single pass at this width: vote kernel, then the median over 255 winners
+    # The files are split over two waves at this width; shorter rows: vote kernel, then the median of 255 winners
     Config("cfg14_ram3x85_resnet18_alie", RAMANUJAN, 3, 85, 9, 255, 85, 3, 2, 29, 11173962,
            {"kind": "alie", "z": 1.0}, 1, 20101004 + 385),
 ]

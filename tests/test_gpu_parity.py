@@ -515,6 +515,23 @@ def test_measurement_aids():
     assert B.byz_profile_collect(8) == []
 
 
+def test_profiled_kernel_is_named():
+    # the kernel the events stand around: short rows, rows without room for slots, early-majority mode, files
+    # split over two waves, vote on its own
+    for f, r, d, flags, want in ((25, 3, 5000, 0, "short_pass_kernel"), (25, 3, 1100000, 0, "fused_kernel"),
+                                 (25, 3, 5000, B.BYZ_AGG_EARLY_MAJORITY, "fused_kernel"),
+                                 (171, 3, 1 << 18, 0, "fused_halves_kernel"), (171, 3, 5000, 0, "vote_pairs_kernel"),
+                                 (27, 3, 5000, 0, "vote_pairs_kernel")):
+        X = torch.zeros((f * r, d), device=DEV)
+        rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
+        B.byz_profile_enable(1)
+        assert B.byz_profile_kernel() == ""
+        B.byz_aggregate_opts(X, d, rows, f, r, flags)
+        name, ms = B.byz_profile_kernel(), B.byz_profile_collect(1)
+        B.byz_profile_enable(0)
+        assert name == want and len(ms) == 1, (f, r, d, flags, name)
+
+
 def _assert_trimmed_mean_close(out, Xh, idx_np, d, b, tag):
     """`out` (GPU, fp32) against the fp64 oracle's trimmed mean of the rows idx_np of Xh.
 
