@@ -169,9 +169,9 @@ def test_mols_over_f11_and_f13_full_size(idx, shape):
 
 def test_widest_cluster_full_size():
     # 255 files (Ramanujan Case 2, s = 3, m = 85: (K,f,l,r) = (9,255,85,3)), 765 rows of the
-    # ResNet-18 size: no single pass at this width, so byz_aggregate runs the vote kernel and the
-    # two-wave median over the 255 winners.  The vote is checked in full, the median and the
-    # trimmed mean on the head, the tail and 60,000 random coordinates
+    # ResNet-18 size: byz_aggregate runs the pass that splits the files over two waves.  The vote is
+    # checked in full, the median and the trimmed mean on the head, the tail and 60,000 random
+    # coordinates
     from tests.test_gpu_parity import _assert_trimmed_mean_close
     cfg = synth.CONFIGS[13]
     free_bytes, _ = torch.cuda.mem_get_info()

@@ -1574,6 +1574,31 @@ def test_pass_over_files_split_over_two_waves(f):
                 assert bool((out[d:] == 7.0).all()), tag
 
 
+def _hidden_pattern_case(rng, scheme, a, b, d, tag, seen):
+    """Random equality patterns among the copies of random files, the classes one changed word apart at random
+    coordinates, in both modes against the oracle; the path codes go into seen."""
+    w = W.make(scheme, a, b, 0, d, REVERSED, seed=int(rng.integers(1 << 30)), device=DEV)
+    X = w.X.clone()
+    for j in rng.permutation(w.f)[:int(rng.integers(1, max(2, w.f // 2)))]:
+        n_classes = int(rng.integers(1, w.r + 1))
+        labels = rng.integers(0, n_classes, size=w.r)
+        where = rng.integers(0, d, size=n_classes)
+        for k in range(w.r):
+            if labels[k] or rng.integers(2):
+                X[int(w.file_rows[j, k]), int(where[labels[k]])] += float(1 + labels[k])
+    rows_dev = torch.tensor(w.file_rows.reshape(-1), dtype=torch.int32, device=DEV)
+    Xh = X.cpu().numpy()
+    wrep_o, wrow_o, _ = C.vote(Xh, w.file_rows, d)
+    out_o = C.median(Xh, wrow_o, d)
+    ws = torch.empty(B.byz_aggregate_workspace_bytes(w.f, w.r), dtype=torch.uint8, device=DEV)
+    for flags in (0, B.BYZ_AGG_EARLY_MAJORITY):
+        out, wrep, _ = B.byz_aggregate_opts(X, d, rows_dev, w.f, w.r, flags, workspace=ws)
+        path = B.byz_aggregate_path(ws)
+        seen.add((flags, path))
+        assert np.array_equal(W.bits(out), W.bits(out_o)), (tag, scheme, a, b, d, flags, path)
+        assert np.array_equal(wrep.cpu().numpy(), wrep_o), (tag, scheme, a, b, d, flags, path)
+
+
 def test_hidden_equality_patterns_of_wide_files():
     # r = 3 ... 13: random equality patterns among the copies of random files, the classes one
     # changed word apart at random coordinates (the comparison over all of d is what finds
@@ -1586,39 +1611,33 @@ def test_hidden_equality_patterns_of_wide_files():
     for case in range(90):
         scheme, a, b = shapes[case % len(shapes)]
         d = int(rng.choice([rng.integers(300, 3000), rng.integers(3000, 90000)]))
-        w = W.make(scheme, a, b, 0, d, REVERSED, seed=int(rng.integers(1 << 30)), device=DEV)
-        X = w.X.clone()
-        for j in rng.permutation(w.f)[:int(rng.integers(1, max(2, w.f // 2)))]:
-            n_classes = int(rng.integers(1, w.r + 1))
-            labels = rng.integers(0, n_classes, size=w.r)
-            where = rng.integers(0, d, size=n_classes)
-            for k in range(w.r):
-                if labels[k] or rng.integers(2):
-                    X[int(w.file_rows[j, k]), int(where[labels[k]])] += float(1 + labels[k])
-        rows_dev = torch.tensor(w.file_rows.reshape(-1), dtype=torch.int32, device=DEV)
-        Xh = X.cpu().numpy()
-        wrep_o, wrow_o, _ = C.vote(Xh, w.file_rows, d)
-        out_o = C.median(Xh, wrow_o, d)
-        ws = torch.empty(B.byz_aggregate_workspace_bytes(w.f, w.r), dtype=torch.uint8, device=DEV)
-        for flags in (0, B.BYZ_AGG_EARLY_MAJORITY):
-            out, wrep, _ = B.byz_aggregate_opts(X, d, rows_dev, w.f, w.r, flags, workspace=ws)
-            path = B.byz_aggregate_path(ws)
-            seen.add((flags, path))
-            tag = (case, scheme, a, b, d, flags, path)
-            assert np.array_equal(W.bits(out), W.bits(out_o)), tag
-            assert np.array_equal(wrep.cpu().numpy(), wrep_o), tag
+        _hidden_pattern_case(rng, scheme, a, b, d, case, seen)
     assert {p for fl, p in seen if fl == 0} >= {B.BYZ_PATH_SINGLE_PASS, B.BYZ_PATH_MEDIAN_REDONE,
                                                 B.BYZ_PATH_TWO_STEP}, seen
     assert {p for fl, p in seen if fl} >= {B.BYZ_PATH_SINGLE_PASS, B.BYZ_PATH_REVOTED,
                                            B.BYZ_PATH_REVOTED | B.BYZ_PATH_MEDIAN_REDONE}, seen
 
 
-def test_repeated_calls_on_one_workspace_never_change():
+def test_hidden_equality_patterns_of_rows_past_the_short_form():
+    # the same at lengths where the blocks' findings have no slots left and are merged in shared words: just past
+    # every shape's reach, and (25,3) where it takes four kernels in between
+    rng = np.random.default_rng(6)
+    seen = set()
+    cases = [(MOLS, 5, 3, 524_289), (MOLS, 5, 3, 1_048_577), (RAM, 5, 5, 262_145), (RAM, 5, 7, 208_897), (MOLS, 7, 3, 262_145),
+             (MOLS, 7, 5, 149_505), (RAM, 7, 7, 79_873), (RAM, 7, 9, 32_769), (RAM, 5, 13, 57_857), (MOLS, 9, 3, 87_041),
+             (MOLS, 11, 3, 65_537), (MOLS, 13, 3, 47_617), (RAM, 3, 3, 131_073), (RAM, 3, 5, 131_073)]
+    for case, (scheme, a, b, d) in enumerate(cases + cases):
+        _hidden_pattern_case(rng, scheme, a, b, d + case // len(cases) * 7, case, seen)
+    assert {p for fl, p in seen if fl == 0} == {B.BYZ_PATH_SINGLE_PASS, B.BYZ_PATH_MEDIAN_REDONE}, seen
+
+
+@pytest.mark.parametrize("scheme,a,b,q,d", [(MOLS, 5, 3, 4, 300_007), (MOLS, 5, 3, 4, 1_050_001), (RAM, 7, 7, 5, 80_001)])
+def test_repeated_calls_on_one_workspace_never_change(scheme, a, b, q, d):
     # what the waves publish through atomics (pair bits, which copies were fed) may arrive in
     # any order: the same call forty times on one workspace, on an input that takes the single
-    # pass and on one that sends it past it, has to give the same words, winners and path
-    d = 300_007
-    w = W.make(MOLS, 5, 3, 4, d, ALIE, seed=91, ld=synth.padded_ld(d, 64), device=DEV)
+    # pass and on one that sends it past it, has to give the same words, winners and path.  The
+    # first size writes to slots instead (but in early-majority mode), the others are past them
+    w = W.make(scheme, a, b, q, d, ALIE, seed=91, ld=synth.padded_ld(d, 64), device=DEV)
     rows_dev = torch.tensor(w.file_rows.reshape(-1), dtype=torch.int32, device=DEV)
     split = w.X.clone()
     for j in range(w.f):
