@@ -2117,8 +2117,9 @@ int launch_bulyan_net(const uint32_t *X, int64_t d, int64_t ld, const int32_t *s
     constexpr int BLOCK = F > 49 ? 64 : kBlock;
     constexpr size_t lds = (size_t)F * BLOCK * 4;
     static_assert(lds <= 64 * 1024, "more than a kernel may use without asking");
-    // off the cache lines (1 M coordinates, us: f = 49 44.9 -> 44.1, 65 74.0 -> 69.5, 97 142 -> 138, 127 256 -> 250)
-    const unsigned group = d > kManyBlocks && !rows_on_lines(X, ld) ? (BLOCK == 64 ? kHalvesGroup : 16) : 0;
+    // off the cache lines (us, plain / in groups: f = 15 0.5 M 8.7 / 8.4, 3 M 36.1 / 34.9, 49 0.5 M 26.9 / 26.3, 1 M 47.1 / 46.4,
+    // 65 1 M 77.8 / 73.7, 97 148 / 145, 127 269 / 264; but up to nine wires 3 M 22.4 / 24.3, 1 M 9.2 / 9.9)
+    const unsigned group = F > 9 && d > kManyBlocks && !rows_on_lines(X, ld) ? (BLOCK == 64 ? kHalvesGroup : 16) : 0;
     bulyan_mean_kernel<F, BLOCK><<<(unsigned)((d + BLOCK - 1) / BLOCK), BLOCK, lds, s>>>(
         X, d, ld, selected_rows, theta, beta, group, O);
     BYZ_HIP(hipGetLastError());
