@@ -695,7 +695,7 @@ __global__ __launch_bounds__(kBlock) void selected_mean_kernel(const float *__re
 
 // Both on short rows, where a launch and the chain of loads count and not HBM: every block chooses for itself
 // (block 0 writes the choice) and takes one word per thread, kAheadRows rows in flight; the additions are those
-// of selected_mean_kernel.  Figures at kShortMean.
+// of selected_mean_kernel.  Figures at short_mean.
 constexpr int kAheadRows = 32;
 __global__ __launch_bounds__(kBlock) void choose_and_mean_kernel(const float *__restrict__ X, int64_t d, int64_t ld,
                                                                  const int32_t *__restrict__ row_index,
@@ -786,10 +786,14 @@ void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32
         launch_gram_spans<NT, NG, 1, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
 }
 
+inline bool rows_on_lines(const float *rows_base, int64_t ld) {
+    return ((uintptr_t)rows_base & 127u) == 0 && ld % 32 == 0;
+}
+
 template <int NT, int NG>
 int launch_gram_shape(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
                       int f, float *partial, int *grid, hipStream_t s) {
-    if (((uintptr_t)rows_base & 127u) == 0 && ld % 32 == 0)
+    if (rows_on_lines(rows_base, ld))
         launch_gram_rows<NT, NG, true>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
     else
         launch_gram_rows<NT, NG, false>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
@@ -848,10 +852,15 @@ extern "C" size_t byz_multi_krum_workspace_bytes(int f) {
     return krum_workspace_bytes(f);
 }
 
-// Rows up to which the choice is made in the blocks of the mean.  us a call, two kernels / one: f = 25 d = 1003
-// 21.3 / 18.6, 131072 23.9 / 21.0, 262144 27.8 / 23.8, 400000 31.2 / 28.0, 700000 37.4 / 38.9; f = 127 1003 45.2 / 41.8,
-// 100003 87.2 / 75.0, 262144 118 / 110, 400000 150.3 / 150.1, 1 M 319 / 326.
-constexpr int64_t kShortMean = 3 << 17;
+// Rows up to which the choice is made in the blocks of the mean; its narrow loads cost more where rows are not on cache
+// lines.  us a call, two kernels / one: f = 25 d = 1003 21.3 / 18.6, 131072 23.9 / 21.0, 393216 31.5 / 31.5 off the lines and
+// 35.3 / 31.2 on them, 700000 37.4 / 38.9; f = 31 300001 31.2 / 30.6 and 33.4 / 31.3, 360001 32.5 / 33.3 and 34.9 / 33.5;
+// f = 33 327680 34.5 / 33.3 off; f = 60 262144 47.3 / 48.0 and 50.5 / 47.5, 300001 50.6 / 52.0 and 52.7 / 51.0, 393216 57.1 / 59.3 and 57.8 / 58.0; f = 127 1003
+// 45.2 / 41.8, 100003 87.2 / 75.0, 262144 119 / 121 and 127 / 122, 327680 143 / 146 and 136 / 137, 393216 157 / 162 and 147 / 152.
+constexpr int64_t short_mean(int f, bool lines) {
+    if (lines) return f <= 96 ? 3 << 17 : 5 << 16;
+    return f <= 25 ? 3 << 17 : (f <= 40 ? 5 << 16 : 1 << 18);
+}
 
 extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
                               const int32_t *row_index_dev, int f, int c, int m, float *out,
@@ -871,7 +880,7 @@ extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
     if (rc != BYZ_OK) return rc;
     rc = launch_distance_rows(f, f - c - 2, dist_out, scores_out, ws, s);
     if (rc != BYZ_OK) return rc;
-    if (d > 0 && d <= kShortMean) {
+    if (d > 0 && d <= short_mean(f, rows_on_lines(rows_base, ld))) {
         choose_and_mean_kernel<<<(unsigned)((d + kBlock - 1) / kBlock), kBlock, 0, s>>>(
             rows_base, d, ld, row_index_dev, ws->scores, f, m, selected_out, out);
         BYZ_HIP(hipGetLastError());

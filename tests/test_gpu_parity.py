@@ -1808,16 +1808,17 @@ def test_random_shapes_sizes_and_layouts():
         _tolerant_check(X, w.file_rows, d, w.f, w.r, 1e-6, 1e-5, tag)
 
 
-@pytest.mark.parametrize("f", [3, 31, 32, 33, 64, 65, 128])
+@pytest.mark.parametrize("f", [3, 25, 26, 31, 32, 33, 40, 41, 64, 65, 96, 97, 128])
 def test_multi_krum_mean_of_short_and_long_rows(f):
-    # rows of up to 3 * 2^17 coordinates are averaged in blocks that choose for themselves: one
-    # word more and less than a block and than that limit, more chosen rows than are in flight at once and
-    # fewer, rows off the cache lines.  Choice and mean from the scores the call returned: m lowest, lower index
-    # first; fp32 additions in ascending index order.  NaN compares with nothing: every vector is chosen.
+    # rows of up to 3 * 2^17 coordinates (fewer for many vectors, above all off the cache lines) are averaged in blocks
+    # that choose for themselves: one word more and less than a block and than that limit, more chosen rows than are in
+    # flight at once and fewer, rows off the cache lines.  Choice and mean from the scores the call returned: m lowest,
+    # lower index first; fp32 additions in ascending index order.  NaN compares with nothing: every vector is chosen.
     rng = np.random.default_rng(f)
-    limit = 3 << 17
-    for d, nan in [(1, False), (3, False), (4, False), (255, False), (257, True), (limit, False), (limit + 1, False)]:
-        ld = d + 5
+    off = 3 << 17 if f <= 25 else (5 << 16 if f <= 40 else 1 << 18)
+    on = 3 << 17 if f <= 96 else 5 << 16
+    for d, ld, nan in [(1, 6, False), (3, 8, False), (4, 9, False), (255, 260, False), (257, 262, True), (off, off + 5, False),
+                       (off + 1, off + 6, False), (on, on, False), (on + 1, on + 32, False)]:
         X = torch.empty((f + 2, ld), device=DEV).normal_(generator=torch.Generator(device=DEV).manual_seed(f * 1000 + d % 997))
         idx = rng.permutation(f + 2)[:f].astype(np.int32)
         if nan:
