@@ -1539,11 +1539,15 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const uint64_t *__restrict__ perm_off,
     const uint32_t *__restrict__ slots_per_file, AggWorkspace *ws, int trim_b,
     uint32_t *__restrict__ out) {
-    // wave-uniform choice written by the probe
-    if (*slots_per_file == (R + 1) / 2)
-        fused_body<F, R, (R + 1) / 2, TRIM, V>(X, d, ld, perm_off, ws, trim_b, out);
-    else
-        fused_body<F, R, R, TRIM, V>(X, d, ld, perm_off, ws, trim_b, out);
+    // wave-uniform choice written by the probe (four_words_of_five: no early-majority trimmed mean)
+    constexpr bool kEarly = !(TRIM && R == 5 && V == 4);
+    if constexpr (kEarly) {
+        if (*slots_per_file == (R + 1) / 2) {
+            fused_body<F, R, (R + 1) / 2, TRIM, V>(X, d, ld, perm_off, ws, trim_b, out);
+            return;
+        }
+    }
+    fused_body<F, R, R, TRIM, V>(X, d, ld, perm_off, ws, trim_b, out);
 }
 
 // First kernel of a call on more than 169 files: clears the state the later kernels accumulate into and
