@@ -228,19 +228,24 @@ def _other_stream(stream, device):
     return stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(handle, device=device)
 
 
-def _new(shape, dtype, device, stream):
-    """A tensor a call on `stream` may write at once.  Where that is not the current stream the memory is
-    taken from that stream's share of torch's pool: work still queued on the current one does not use it,
-    and dropped while the call runs (workspaces are, on return) it goes to nobody else.  The current
-    stream, which will read the results, is noted with it."""
+def _empty_on(stream):
+    """torch.empty(shape, dtype=, device=) for tensors a call on `stream` may write at once.  Where that is not
+    the current stream the memory is taken from that stream's share of torch's pool: work still queued on the
+    current one does not use it, and dropped while the call runs (workspaces are, on return) it goes to nobody
+    else.  The current stream, which will read the results, is noted with it.  Callers take torch.empty itself
+    for calls on the current stream: the smallest return in 5.6 us, a function around it added 0.15."""
     torch = _torch()
-    other = _other_stream(stream, device) if stream is not None and device.type == "cuda" else None
-    if other is None:
-        return torch.empty(shape, dtype=dtype, device=device)
-    with torch.cuda.stream(other):
-        t = torch.empty(shape, dtype=dtype, device=device)
-    t.record_stream(torch.cuda.current_stream(device))
-    return t
+
+    def empty(shape, dtype, device):
+        other = _other_stream(stream, device) if device.type == "cuda" else None
+        if other is None:
+            return torch.empty(shape, dtype=dtype, device=device)
+        with torch.cuda.stream(other):
+            t = torch.empty(shape, dtype=dtype, device=device)
+        t.record_stream(torch.cuda.current_stream(device))
+        return t
+
+    return empty
 
 
 _checked_tables = {}
@@ -301,11 +306,12 @@ def _rows_2d(copies):
 def byz_vote(copies, d, file_rows_dev, f, r, stream=None):
     """-> (winner_replica[f] int32, winner_row[f] int32, pair_neq[f] int32 bit masks), on device."""
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(copies)
     _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
-    wrep = _new(max(int(f), 0), torch.int32, copies.device, stream)
-    wrow = _new(max(int(f), 0), torch.int32, copies.device, stream)
-    neq = _new(max(int(f), 0), torch.int32, copies.device, stream)
+    wrep = empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
+    wrow = empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
+    neq = empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
     _check(_load().byz_vote(_dev_ptr(copies, ("float32",), "copies"), int(d), ld,
                             _dev_ptr(file_rows_dev, ("int32",), "file_rows_dev"), int(f), int(r),
                             _dev_ptr(wrep, ("int32",), "winner_replica"),
@@ -318,11 +324,12 @@ def byz_vote(copies, d, file_rows_dev, f, r, stream=None):
 def byz_vote_tolerant(copies, d, file_rows_dev, f, r, atol, rtol, stream=None):
     """-> (winner_replica[f] int32, winner_row[f] int32, pair_far[f] int32 bit masks), on device."""
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(copies)
     _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
-    wrep = _new(max(int(f), 0), torch.int32, copies.device, stream)
-    wrow = _new(max(int(f), 0), torch.int32, copies.device, stream)
-    far = _new(max(int(f), 0), torch.int32, copies.device, stream)
+    wrep = empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
+    wrow = empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
+    far = empty(max(int(f), 0), dtype=torch.int32, device=copies.device)
     _check(_load().byz_vote_tolerant(_dev_ptr(copies, ("float32",), "copies"), int(d), ld,
                                      _dev_ptr(file_rows_dev, ("int32",), "file_rows_dev"),
                                      int(f), int(r), float(atol), float(rtol),
@@ -335,11 +342,12 @@ def byz_vote_tolerant(copies, d, file_rows_dev, f, r, atol, rtol, stream=None):
 
 def byz_median(rows_base, d, row_index_dev, out=None, stream=None):
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = _new(int(d), torch.float32, rows_base.device, stream)
+        out = empty(int(d), dtype=torch.float32, device=rows_base.device)
     _need(out, int(d), "out")
     _check(_load().byz_median(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                               _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f,
@@ -350,11 +358,12 @@ def byz_median(rows_base, d, row_index_dev, out=None, stream=None):
 
 def byz_trimmed_mean(rows_base, d, row_index_dev, b, out=None, stream=None):
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = _new(int(d), torch.float32, rows_base.device, stream)
+        out = empty(int(d), dtype=torch.float32, device=rows_base.device)
     _need(out, int(d), "out")
     _check(_load().byz_trimmed_mean(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                                     _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f,
@@ -370,18 +379,19 @@ def byz_multi_krum_workspace_bytes(f):
 def byz_multi_krum(rows_base, d, row_index_dev, c, m, out=None, workspace=None, stream=None):
     """-> (out[d] float32, selected[f] int32, scores[f] float64, dist[f, f] float64), on device."""
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
     dev = rows_base.device
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = _new(int(d), torch.float32, dev, stream)
+        out = empty(int(d), dtype=torch.float32, device=dev)
     _need(out, int(d), "out")
     if workspace is None:
-        workspace = _new(max(byz_multi_krum_workspace_bytes(f), 256), torch.uint8, dev, stream)
-    selected = _new(f, torch.int32, dev, stream)
-    scores = _new(f, torch.float64, dev, stream)
-    dist = _new((f, f), torch.float64, dev, stream)
+        workspace = empty(max(byz_multi_krum_workspace_bytes(f), 256), dtype=torch.uint8, device=dev)
+    selected = empty(f, dtype=torch.int32, device=dev)
+    scores = empty(f, dtype=torch.float64, device=dev)
+    dist = empty((f, f), dtype=torch.float64, device=dev)
     _check(_load().byz_multi_krum(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                                   _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f, int(c),
                                   int(m), _dev_ptr(out, ("float32",), "out"),
@@ -400,18 +410,19 @@ def byz_bulyan_workspace_bytes(f):
 def byz_bulyan(rows_base, d, row_index_dev, c, out=None, workspace=None, stream=None):
     """-> (out[d] float32, selected[f] int32, order[f-2c] int32, dist[f, f] float64), on device."""
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
     dev = rows_base.device
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = _new(int(d), torch.float32, dev, stream)
+        out = empty(int(d), dtype=torch.float32, device=dev)
     _need(out, int(d), "out")
     if workspace is None:
-        workspace = _new(max(byz_bulyan_workspace_bytes(f), 256), torch.uint8, dev, stream)
-    selected = _new(f, torch.int32, dev, stream)
-    order = _new(max(f - 2 * int(c), 1), torch.int32, dev, stream)
-    dist = _new((f, f), torch.float64, dev, stream)
+        workspace = empty(max(byz_bulyan_workspace_bytes(f), 256), dtype=torch.uint8, device=dev)
+    selected = empty(f, dtype=torch.int32, device=dev)
+    order = empty(max(f - 2 * int(c), 1), dtype=torch.int32, device=dev)
+    dist = empty((f, f), dtype=torch.float64, device=dev)
     _check(_load().byz_bulyan(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                               _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f, int(c),
                               _dev_ptr(out, ("float32",), "out"),
@@ -426,11 +437,12 @@ def byz_bulyan(rows_base, d, row_index_dev, c, out=None, workspace=None, stream=
 def byz_mean_around_median(rows_base, d, row_index_dev, beta, out=None, stream=None):
     """-> out[d] float32 on device: mean of the beta values closest to the median, per coordinate."""
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(rows_base)
     f = int(row_index_dev.numel())
     _need_rows_in_range(row_index_dev, f, int(rows_base.shape[0]), "row_index_dev", stream)
     if out is None:
-        out = _new(int(d), torch.float32, rows_base.device, stream)
+        out = empty(int(d), dtype=torch.float32, device=rows_base.device)
     _need(out, int(d), "out")
     _check(_load().byz_mean_around_median(_dev_ptr(rows_base, ("float32",), "rows_base"), int(d), ld,
                                           _dev_ptr(row_index_dev, ("int32",), "row_index_dev"), f,
@@ -467,16 +479,17 @@ def byz_aggregate(copies, d, file_rows_dev, f, r, out=None, winner_replica=None,
                   stream=None, _flags=None):
     """-> (out[d] float32, winner_replica[f] int32, workspace uint8 tensor), on device."""
     torch = _torch()
+    empty = torch.empty if stream is None else _empty_on(stream)
     ld = _rows_2d(copies)
     if out is None:
-        out = _new(int(d), torch.float32, copies.device, stream)
+        out = empty(int(d), dtype=torch.float32, device=copies.device)
     if winner_replica is None:
-        winner_replica = _new(int(f), torch.int32, copies.device, stream)
+        winner_replica = empty(int(f), dtype=torch.int32, device=copies.device)
     if workspace is None:
         nbytes = byz_aggregate_workspace_bytes(f, r)
         if nbytes == 0:
             raise ByzError(-1, "byz_aggregate_workspace_bytes")
-        workspace = _new(nbytes, torch.uint8, copies.device, stream)
+        workspace = empty(nbytes, dtype=torch.uint8, device=copies.device)
     _need_rows_in_range(file_rows_dev, int(f) * int(r), int(copies.shape[0]), "file_rows_dev", stream)
     _need(out, int(d), "out")
     _need(winner_replica, int(f), "winner_replica")
