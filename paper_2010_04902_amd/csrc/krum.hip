@@ -9,7 +9,8 @@
 // winners: the one dense contraction of the whole path, done with fp32 MFMA tiles
 // (v_mfma_f32_16x16x4f32), only those on and above the diagonal of the symmetric matrix (f = 25
 // costs 3 tiles of 16x16 instead of one padded 32x32), and v_mfma_f32_4x4x1f32 for a few rows behind
-// the last full tile.  The waves walk the coordinates
+// the last full tile.  On long rows the choice is guessed from a sample first and the mean of the guessed vectors is
+// taken in the same pass; the choice from the whole matrix decides whether it stands or is taken again.  The waves walk the coordinates
 // grid-stride.  Per-block partial tiles are added in fp64 in block order, so the result does not
 // depend on scheduling.
 #include <hip/hip_runtime.h>
@@ -62,6 +63,7 @@ __host__ __device__ constexpr int row_tiles(int f) { return row_groups(f) != 0 ?
 __host__ __device__ constexpr int stored_tiles(int nt, int groups) {
     return nt * (nt + 1) / 2 + groups * (nt < 4 ? 1 : 2);
 }
+__host__ __device__ constexpr int stored_tiles(int f) { return stored_tiles(row_tiles(f), row_groups(f)); }
 
 // Tile (ti, tj), ti <= tj < nt, of the upper triangle, numbered row by row.
 __host__ __device__ constexpr int tile_pair(int nt, int ti, int tj) {
@@ -124,6 +126,122 @@ __device__ __forceinline__ void group_products(const f32x4 (&y)[kParts > 0 ? kPa
 #undef BYZ_GROUP
 }
 
+// Sample for a guess at Multi-Krum's choice among up to kMaxGuess vectors: stretches of 32 coordinates, one at a
+// random place of every 1/kSampleSpans of the row (pitch: a whole number of stretches, so that rows on cache lines
+// are sampled in whole lines).
+constexpr int kMaxGuess = 64;
+constexpr int kSampleSpans = 4096;
+__device__ __forceinline__ int64_t sample_start(int64_t at, int64_t pitch) {
+    const uint32_t hash = (uint32_t)at * 2654435761u;
+    return at * pitch + (int64_t)(((uint64_t)hash * (uint64_t)(pitch / kStep)) >> 32) * kStep;
+}
+
+// Multi-Krum's choice, thread i = vector i (the first kMaxKrum threads of a block): the m lowest
+// scores, the lower index first among equal scores.  Returns i's place in that order, chosen if below m;
+// *before = chosen vectors with a lower index, *total = how many there are.  All threads of the block call it.
+__device__ __forceinline__ int choose_vector(const double *__restrict__ scores, int f, int m, double *s_score,
+                                              uint64_t *s_chosen, int *before, int *total) {
+    const int i = threadIdx.x;
+    const double mine = i < f ? scores[i] : 0.0;
+    if (i < kMaxKrum) s_score[i] = mine;
+    __syncthreads();
+    int rank = 0;
+#pragma unroll 8
+    for (int k = 0; k < f; ++k) {
+        const double other = s_score[k];
+        rank += (other < mine || (other == mine && k < i)) ? 1 : 0;
+    }
+    if (i >= f) rank = kMaxKrum;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(rank < m);
+    if (i < kMaxKrum && (i & 63) == 0) s_chosen[i >> 6] = mask;
+    __syncthreads();
+    *before = __builtin_popcountll(mask & ((1ull << (i & 63)) - 1ull));
+    *total = 0;
+#pragma unroll
+    for (int w = 0; w < kMaxKrum / 64; ++w) {
+        const int n = __builtin_popcountll(s_chosen[w]);
+        if (w < (i >> 6)) *before += n;
+        *total += n;
+    }
+    return rank;
+}
+
+// The guess, by every block of the Gram pass for itself from the scores on the sample; all its threads call it.
+// None where it is likely to be wrong (the last chosen score and the next one closer than kMargin: on 131072 Gaussian
+// coordinates scores are off by about 0.3 %), nor where the output overlaps a row, which the guessed mean would
+// overwrite before the row's last reader.
+constexpr double kMargin = 0.002;
+__device__ __forceinline__ uint64_t guess_vectors(const double *__restrict__ scores, int f, int m, const float *rows_base,
+                                                  int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
+                                                  const float *out, double *s_room) {
+    double *s_edge = s_room + kMaxKrum;
+    uint64_t *s_chosen = reinterpret_cast<uint64_t *>(s_edge + 2), *s_overlap = s_chosen + kMaxKrum / 64;
+    const int i = threadIdx.x;
+    if (i < 2) s_edge[i] = 0.0;
+    int before, total;
+    const int rank = choose_vector(scores, f, m, s_room, s_chosen, &before, &total);
+    if (i < f && (rank == m - 1 || rank == m)) s_edge[rank - (m - 1)] = s_room[i];
+    if (i < kMaxGuess) {
+        bool overlap = false;
+        if (i < f) {
+            const uintptr_t row = (uintptr_t)(rows_base + (int64_t)row_index[i] * ld), o = (uintptr_t)out;
+            const uintptr_t bytes = (uintptr_t)d * sizeof(float);
+            overlap = o < row + bytes && row < o + bytes;
+        }
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(overlap);
+        if (i == 0) *s_overlap = mask;
+    }
+    __syncthreads();
+    const bool clear = m == f || s_edge[1] - s_edge[0] > kMargin * s_edge[0];
+    const uint64_t chosen = clear && *s_overlap == 0 ? s_chosen[0] : 0ull;
+    __syncthreads();  // the room is used for other things
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(chosen >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen);
+}
+
+// What a Gram pass that takes a mean on the way is given: scores on the sample, how many vectors to choose, where the
+// mean goes and where the guess is left for chosen_mean_kernel.
+struct GuessedPass {
+    const double *scores;
+    int m;
+    float *out;
+    uint64_t *chosen;
+};
+
+// Mean of the guessed vectors over the stretch a wave has in its stage, lane = coordinate: the additions and the
+// division of chosen_mean_kernel, so that the words are the same.  A vector that is not guessed adds +0, which leaves
+// every partial sum as it is (sums from +0 are never -0).  It adds 25 us to the 176 us of the Gram pass of 25 x 11.2 M
+// (6 of them the output) and saves the 152 us of a second pass; with 49 vectors 80 us.  Eight waves a block, one
+// multiply-add by 1 or 0 for mask and addition, or the place behind the matrix instructions: the same or slower.
+constexpr int kMeanRows = 16;  // a step, whose reads of LDS are under way together
+struct GuessedMean {
+    uint64_t chosen;  // bit i = vector i; none: no mean is taken
+    float count;
+    float *out;
+    template <int ROWS, int SPAN>
+    __device__ __forceinline__ void add(const float *stage, int64_t c0, int64_t d) const {
+        if (count == 0.0f) return;
+        const int lane = threadIdx.x & 63, at = lane % SPAN;
+        float a = 0.0f;
+#pragma unroll
+        for (int r0 = 0; r0 < ROWS; r0 += kMeanRows) {
+            uint32_t bits = (uint32_t)(chosen >> r0) & ((1u << kMeanRows) - 1u);
+            if (bits == 0) continue;
+            asm volatile("" : "+s"(bits));  // or a mask per vector is kept over all stretches, and spilled
+            uint32_t v[kMeanRows];
+#pragma unroll
+            for (int u = 0; u < kMeanRows; ++u)
+                if (r0 + u < ROWS)
+                    v[u] = __float_as_uint(stage[(r0 + u) * SPAN + ((at / 4) ^ (u & 7)) * 4 + at % 4]);
+#pragma unroll
+            for (int u = 0; u < kMeanRows; ++u)
+                if (r0 + u < ROWS) a += __uint_as_float(v[u] & (uint32_t)__builtin_amdgcn_sbfe((int)bits, u, 1));
+        }
+        const float mean = a / count;
+        if (lane < SPAN && c0 + at < d) __builtin_nontemporal_store(mean, out + c0 + at);
+    }
+};
+
 // Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16, NG =
 // groups of four rows behind them (row_groups).
 // A wave takes whole stretches of 32*SF coordinates of every row, so every word is loaded once
@@ -147,15 +265,15 @@ __device__ __forceinline__ void group_products(const f32x4 (&y)[kParts > 0 ? kPa
 // kernel takes 390 us, 344 with its loads left out, 322 with its products left out; more waves, longer
 // stretches or loads two steps ahead changed nothing); the runs cost 3 % there (15 % with eight row
 // tiles, where the sums fill the registers).
-template <int NT, int NG, int SF, bool LINES, bool SHORT>
+template <int NT, int NG, int SF, bool LINES, bool SHORT, bool MEAN>
 __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int64_t d, int64_t ld,
-                                                const int32_t *__restrict__ row_index, int f,
-                                                float *stage, f32x4 (&acc)[stored_tiles(NT, NG)]) {
+                                                const int32_t *__restrict__ row_index, int f, int64_t pitch,
+                                                const GuessedMean &guessed, float *stage, f32x4 (&acc)[stored_tiles(NT, NG)]) {
     constexpr int NP = NT * (NT + 1) / 2, NALL = stored_tiles(NT, NG), kSpan = kStep * SF;
     constexpr int kPieces = kSpan / 4, kRows = 64 / kPieces, kLoads = staged_rows(NT, NG, SF) / kRows;
     constexpr int kParts = NG == 0 ? 0 : (NALL - NP) / NG;  // stretches of 64 rows a group meets
     const int lane = threadIdx.x & 63;
-    const int64_t n_spans = (d + kSpan - 1) / kSpan;
+    const int64_t n_spans = SHORT && pitch != 0 ? kSampleSpans : (d + kSpan - 1) / kSpan;
     constexpr int kWaves = gram_waves(NT, SF);
     const int64_t stride = (int64_t)gridDim.x * kWaves;
     constexpr unsigned kGroup = NT <= 1 ? 1 : (NT == 2 ? 4 : 8);
@@ -176,7 +294,7 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
         if (!used(n)) slots[64 * n + lane] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 raw[kLoads];
     auto fetch = [&](int64_t at) {
-        const int64_t c0 = at * kSpan;
+        const int64_t c0 = SHORT && pitch != 0 ? sample_start(at, pitch) : at * kSpan;
         if (c0 + kSpan <= d) {
 #pragma unroll
             for (int n = 0; n < kLoads; ++n)
@@ -215,6 +333,7 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
                 if (used(n)) slots[64 * n + lane] = raw[n];
             wave_fence();
             if (span + stride < n_spans) fetch(span + stride);
+            if constexpr (MEAN) guessed.template add<16 * NT + 4 * NG, kSpan>(stage, span * kSpan, d);
 #pragma unroll
             for (int h = 0; h < 2 * SF; ++h) {  // 16 coordinates
                 const int piece = 8 * (h / 2) + 2 * (lane >> 4) + h % 2;
@@ -274,14 +393,14 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
 // Partial Gram tiles of the rows row_index[0..f-1] over this block's coordinates.  partial:
 // [gridDim.x][tiles][256] values, position v*64 + lane, tiles = stored_tiles(NT, NG), fp32 or, where a few
 // blocks would leave their last roundings visible, fp64 (d = 2048: 8.9e-9 -> 4.9e-9 at f = 100).
-template <int NT, int NG, int SF, bool LINES, bool SHORT>
+template <int NT, int NG, int SF, bool LINES, bool SHORT, bool MEAN>
 __global__ __launch_bounds__(64 * gram_waves(NT, SF))
 // (2: accumulators in ordinary registers; more row tiles would spill: 96 x 11.2 M 1502 us, 1362 with 1,
 // 80 x 11.2 M 998 and 1060; the same with groups, (5, 1) on long rows 41 registers)
 __attribute__((amdgpu_waves_per_eu(NG > 0 ? (NT <= 4 || (NT == 5 && SHORT) ? 2 : 1) : (NT <= 5 || (NT == 6 && SHORT) ? 2 : 1))))
 void gram_partial_kernel(
     const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
-    float *__restrict__ partial, int in_fp64) {
+    float *__restrict__ partial, int in_fp64, int64_t pitch, GuessedPass guess) {
     constexpr int NP = stored_tiles(NT, NG), kWaves = gram_waves(NT, SF);
     constexpr int kStage = staged_rows(NT, NG, SF) * kStep * SF;  // floats of one wave's stage
     constexpr int kRoom = 16 * 1024 / (kWaves * kTile);  // tiles of every wave that 64 KB hold
@@ -290,7 +409,15 @@ void gram_partial_kernel(
     __shared__ __align__(16) float lds[kRed > kWaves * kStage ? kRed : kWaves * kStage];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     f32x4 acc[NP];
-    gram_accumulate<NT, NG, SF, LINES, SHORT>(X, d, ld, row_index, f, lds + wave * kStage, acc);
+    GuessedMean guessed = {0, 0.0f, nullptr};
+    if constexpr (MEAN) {
+        guessed.chosen = guess_vectors(guess.scores, f, guess.m, X, d, ld, row_index, guess.out,
+                                       reinterpret_cast<double *>(lds));
+        guessed.count = (float)__builtin_popcountll(guessed.chosen);
+        guessed.out = guess.out;
+        if (blockIdx.x == 0 && tid == 0) *guess.chosen = guessed.chosen;
+    }
+    gram_accumulate<NT, NG, SF, LINES, SHORT, MEAN>(X, d, ld, row_index, f, pitch, guessed, lds + wave * kStage, acc);
     // the waves' tiles are added in wave order in fp64, as many tiles at a time as fit
 #pragma unroll
     for (int p0 = 0; p0 < NP; p0 += kAtOnce) {
@@ -362,29 +489,11 @@ __device__ __forceinline__ bool key_before(double a_v, int a_t, double b_v, int 
     return a_spare != b_spare ? b_spare : (a_v < b_v || (a_v == b_v && a_t < b_t));
 }
 
-// Set-up of the selections, one wave per vector i (4 per block), for f <= 64*PER: the lane
-// computes the squared distances d(i,j) = G_ii + G_jj - 2 G_ij (clamped at 0, exactly 0 on the
-// diagonal) for j = lane and, with PER = 2, j = lane + 64, and writes them to dist_out; a
-// bitonic network over the 64*PER keys of the wave then sorts the distances to the other
-// vectors in ascending order (value, then index), the keys of j = i and j >= f sorting behind
-// every distance.  The t-th nearest of vector i goes to sorted_dist[t*kRowStride + i] and
-// sorted_nbr[t*kRowStride + i] (t < f-1; the other entries are not written).  With
-// n_terms >= 0 the wave also adds the n_terms smallest distances one by one in ascending
-// order from +0: the Krum score, into scores and scores_out.
-constexpr int kRowStride = kMaxKrum;
-
+// Distances of vector i, sorted: lane l of the wave ends up with the nearest number l and, with PER = 2, l + 64.
 template <int PER>
-__global__ __launch_bounds__(kBlock) void distance_rows_kernel(const double *__restrict__ gram, int f,
-                                                               int n_terms, double *dist_out,
-                                                               double *__restrict__ sorted_dist,
-                                                               uint8_t *__restrict__ sorted_nbr,
-                                                               double *__restrict__ scores,
-                                                               double *scores_out) {
+__device__ __forceinline__ void sorted_distances(const double *gram, int f, int i, double *dist_out,
+                                                 double (&v)[PER], int (&tag)[PER]) {
     const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    if (i >= f) return;  // whole wave
-    double v[PER];
-    int tag[PER];
     const double g_ii = gram_at(gram, f, i, i);
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
@@ -432,6 +541,42 @@ __global__ __launch_bounds__(kBlock) void distance_rows_kernel(const double *__r
             }
         }
     }
+}
+
+// The n_terms smallest of them, one by one in ascending order from +0: the Krum score.
+template <int PER>
+__device__ __forceinline__ double nearest_sum(const double (&v)[PER], int n_terms) {
+    double score = 0.0;
+    for (int t = 0; t < n_terms && t < 64; ++t) score += lane_value(v[0], t);
+    if constexpr (PER == 2)
+        for (int t = 64; t < n_terms; ++t) score += lane_value(v[1], t - 64);
+    return score;
+}
+
+// Set-up of the selections, one wave per vector i (4 per block), for f <= 64*PER: the lane
+// computes the squared distances d(i,j) = G_ii + G_jj - 2 G_ij (clamped at 0, exactly 0 on the
+// diagonal) for j = lane and, with PER = 2, j = lane + 64, and writes them to dist_out; a
+// bitonic network over the 64*PER keys of the wave then sorts the distances to the other
+// vectors in ascending order (value, then index), the keys of j = i and j >= f sorting behind
+// every distance.  The t-th nearest of vector i goes to sorted_dist[t*kRowStride + i] and
+// sorted_nbr[t*kRowStride + i] (t < f-1; the other entries are not written).  With
+// n_terms >= 0 the wave also adds the n_terms smallest distances one by one in ascending
+// order from +0: the Krum score, into scores and scores_out.
+constexpr int kRowStride = kMaxKrum;
+
+template <int PER>
+__global__ __launch_bounds__(kBlock) void distance_rows_kernel(const double *__restrict__ gram, int f,
+                                                               int n_terms, double *dist_out,
+                                                               double *__restrict__ sorted_dist,
+                                                               uint8_t *__restrict__ sorted_nbr,
+                                                               double *__restrict__ scores,
+                                                               double *scores_out) {
+    const int lane = threadIdx.x & 63;
+    const int i = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (i >= f) return;  // whole wave
+    double v[PER];
+    int tag[PER];
+    sorted_distances<PER>(gram, f, i, dist_out, v, tag);
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         const int t = lane + 64 * e;
@@ -441,59 +586,12 @@ __global__ __launch_bounds__(kBlock) void distance_rows_kernel(const double *__r
         }
     }
     if (n_terms >= 0) {
-        double score = 0.0;
-        for (int t = 0; t < n_terms && t < 64; ++t) score += lane_value(v[0], t);
-        if constexpr (PER == 2)
-            for (int t = 64; t < n_terms; ++t) score += lane_value(v[1], t - 64);
+        const double score = nearest_sum<PER>(v, n_terms);
         if (lane == 0) {
             scores[i] = score;
             if (scores_out != nullptr) scores_out[i] = score;
         }
     }
-}
-
-// Multi-Krum's choice, thread i = vector i (the first kMaxKrum threads of a block): the m lowest
-// scores, the lower index first among equal scores.  Returns whether i is chosen, *before = chosen
-// vectors with a lower index, *total = how many there are.  All threads of the block call it.
-__device__ __forceinline__ bool choose_vector(const double *__restrict__ scores, int f, int m, double *s_score,
-                                              uint64_t *s_chosen, int *before, int *total) {
-    const int i = threadIdx.x;
-    const double mine = i < f ? scores[i] : 0.0;
-    if (i < kMaxKrum) s_score[i] = mine;
-    __syncthreads();
-    int rank = 0;
-#pragma unroll 8
-    for (int k = 0; k < f; ++k) {
-        const double other = s_score[k];
-        rank += (other < mine || (other == mine && k < i)) ? 1 : 0;
-    }
-    const bool chosen = i < f && rank < m;
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(chosen);
-    if (i < kMaxKrum && (i & 63) == 0) s_chosen[i >> 6] = mask;
-    __syncthreads();
-    *before = __builtin_popcountll(mask & ((1ull << (i & 63)) - 1ull));
-    *total = 0;
-#pragma unroll
-    for (int w = 0; w < kMaxKrum / 64; ++w) {
-        const int n = __builtin_popcountll(s_chosen[w]);
-        if (w < (i >> 6)) *before += n;
-        *total += n;
-    }
-    return chosen;
-}
-
-__global__ __launch_bounds__(kMaxKrum) void krum_select_kernel(const double *__restrict__ scores, int f,
-                                                               int m, int32_t *selected_out,
-                                                               int32_t *selected_list,
-                                                               int32_t *n_selected) {
-    __shared__ double s_score[kMaxKrum];
-    __shared__ uint64_t s_chosen[kMaxKrum / 64];
-    const int i = threadIdx.x;
-    int before, total;
-    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &total);
-    if (i < f) selected_out[i] = chosen ? 1 : 0;
-    if (chosen) selected_list[before] = i;
-    if (i == 0) *n_selected = total;
 }
 
 // quad_perm [1,0,3,2]: lane ^ 1; quad_perm [2,3,0,1]: lane ^ 2; row_half_mirror: the other quad of the
@@ -659,43 +757,58 @@ __global__ __launch_bounds__(kSelectThreads) void bulyan_select_kernel(
     if (i == 0) *n_selected = theta;
 }
 
-// out[c] = mean of the selected rows: fp32, added one by one in ascending file index starting
-// from +0, one IEEE division by the count.  Thread t owns the words from min(4t, d-4) (d >= 4).
-__global__ __launch_bounds__(kBlock) void selected_mean_kernel(const float *__restrict__ X, int64_t d,
-                                                               int64_t ld,
-                                                               const int32_t *__restrict__ row_index,
-                                                               const int32_t *__restrict__ selected_list,
-                                                               const int32_t *__restrict__ n_selected,
-                                                               float *__restrict__ out) {
-    const int n = *n_selected;
-    if (d >= 4) {
-        const int64_t n_thr = (d + 3) / 4;
-        const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-        if (gt >= n_thr) return;
+// Choice and mean: every block chooses for itself (block 0 writes the choice; a kernel of its own for the choice
+// took 5 us more: f = 25, 1 M 47.1 -> 45.7), then out[c] = mean of the chosen
+// rows: fp32, added one by one in ascending file index starting from +0, one IEEE division by the count.  Thread t
+// of the grid owns the words from min(4t, d-4) (d >= 4).  With a guess whose mean the Gram pass has written the
+// blocks return when it was right.
+__global__ __launch_bounds__(kBlock) void chosen_mean_kernel(const float *__restrict__ X, int64_t d, int64_t ld,
+                                                             const int32_t *__restrict__ row_index,
+                                                             const double *__restrict__ scores, int f, int m,
+                                                             const uint64_t *__restrict__ guess,
+                                                             int32_t *selected_out, float *__restrict__ out) {
+    static_assert(kBlock >= kMaxKrum, "a thread per vector");
+    __shared__ double s_score[kMaxKrum];
+    __shared__ uint64_t s_chosen[kMaxKrum / 64];
+    __shared__ int32_t s_row[kMaxKrum];
+    const int i = threadIdx.x;
+    int before, n;
+    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &n) < m;
+    n = __builtin_amdgcn_readfirstlane(n);
+    if (blockIdx.x == 0 && i < f) selected_out[i] = chosen ? 1 : 0;
+    if (guess != nullptr) {
+        if (*guess == s_chosen[0]) return;  // at most kMaxGuess vectors
+    }
+    if (chosen) s_row[before] = row_index[i];
+    __syncthreads();
+    const float dn = (float)n;
+    const int64_t n_thr = (d + 3) / 4;
+    for (int64_t gt = (int64_t)blockIdx.x * kBlock + i; gt < n_thr; gt += (int64_t)gridDim.x * kBlock) {
         const int64_t c0 = (gt + 1) * 4 <= d ? gt * 4 : d - 4;
         float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-#pragma unroll 4
-        for (int t = 0; t < n; ++t) {
-            const float *p = X + (int64_t)row_index[selected_list[t]] * ld + c0;
-            const f32x4u v = __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(p));
-            a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3];
+        auto load = [&](int t) {
+            const float *p = X + (int64_t)__builtin_amdgcn_readfirstlane(s_row[t]) * ld + c0;
+            return __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(p));
+        };
+        auto add = [&](const f32x4u &v) { a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3]; };
+        int t = 0;
+        for (; t + 4 <= n; t += 4) {
+            f32x4u v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = load(t + u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(v[u]);
         }
-        const float dn = (float)n;
+        for (; t < n; ++t) add(load(t));
         f32x4u o;
         o[0] = a0 / dn; o[1] = a1 / dn; o[2] = a2 / dn; o[3] = a3 / dn;
         __builtin_nontemporal_store(o, reinterpret_cast<f32x4u *>(out + c0));
-    } else {
-        const int64_t cc = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-        if (cc >= d) return;
-        float a = 0.0f;
-        for (int t = 0; t < n; ++t) a += X[(int64_t)row_index[selected_list[t]] * ld + cc];
-        out[cc] = a / (float)n;
     }
 }
 
 // Both on short rows, where a launch and the chain of loads count and not HBM: every block chooses for itself
 // (block 0 writes the choice) and takes one word per thread, kAheadRows rows in flight; the additions are those
-// of selected_mean_kernel.  Figures at short_mean.
+// of chosen_mean_kernel.  Figures at short_mean.
 constexpr int kAheadRows = 32;
 __global__ __launch_bounds__(kBlock) void choose_and_mean_kernel(const float *__restrict__ X, int64_t d, int64_t ld,
                                                                  const int32_t *__restrict__ row_index,
@@ -707,7 +820,7 @@ __global__ __launch_bounds__(kBlock) void choose_and_mean_kernel(const float *__
     __shared__ int64_t s_first[kMaxKrum];  // first words of the chosen rows
     const int i = threadIdx.x;
     int before, n;
-    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &n);
+    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &n) < m;
     if (blockIdx.x == 0 && i < f) selected_out[i] = chosen ? 1 : 0;
     if (chosen) s_first[before] = (int64_t)row_index[i] * ld;
     __syncthreads();
@@ -732,12 +845,11 @@ struct KrumWorkspace {
     int32_t selected_list[kMaxKrum];
     int32_t selected_rows[kMaxKrum];  // Bulyan: rows of the chosen vectors, spare entries valid
     int32_t n_selected;
-    int32_t pad[63];
+    int32_t pad[61];
+    uint64_t guess;  // Multi-Krum: the vectors the Gram pass has averaged, bit i = vector i
     float partial[1];  // [kGramBlocks][tiles of f][256], sized by krum_workspace_bytes
 };
 static_assert(offsetof(KrumWorkspace, partial) % sizeof(double) == 0, "partial tiles may be fp64");
-
-inline int stored_tiles(int f) { return stored_tiles(row_tiles(f), row_groups(f)); }
 
 // Blocks up to which partial tiles are fp64: a quarter of the grid they have room for in fp32.
 inline bool partials_in_fp64(int grid) { return grid <= kGramBlocks / 4; }
@@ -749,9 +861,16 @@ inline size_t krum_workspace_bytes(int f) {
            sizeof(float) * (size_t)kGramBlocks * (nt * (nt + 1) / 2) * kTile;
 }
 
-template <int NT, int NG, int SF, bool LINES>
+// What a Gram pass is for: the whole matrix, the matrix of a sample, or the whole with a guessed mean (guess.out set).
+struct GramPass {
+    bool sample;
+    GuessedPass guess;
+};
+constexpr GramPass kWholeMatrix = {false, {nullptr, 0, nullptr, nullptr}}, kSampleMatrix = {true, kWholeMatrix.guess};
+
+template <int NT, int NG, int SF, bool LINES, bool MEAN>
 void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
-                       int f, float *partial, int *grid, hipStream_t s) {
+                       int f, float *partial, int *grid, GramPass pass, hipStream_t s) {
     constexpr int kWaves = gram_waves(NT, SF);
     constexpr int64_t kSpan = kStep * SF * kWaves;  // coordinates a block takes at a time
     // up to a block per CU each takes one step, then up to the full grid each takes two: a block more is
@@ -763,27 +882,39 @@ void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int3
     *grid = n < 1 ? 1 : (n < kGramBlocks ? (int)n : kGramBlocks);  // d == 0: one block writes zero tiles
     const int in_fp64 = partials_in_fp64(*grid) ? 1 : 0;
     // up to four steps a wave; two steps of 32 at a time are taken on longer rows only
-    if (SF == 1 && steps <= 4 * (int64_t)*grid)
-        gram_partial_kernel<NT, NG, 1, LINES, SF == 1><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
-            rows_base, d, ld, row_index_dev, f, partial, in_fp64);
+    if (!MEAN && SF == 1 && steps <= 4 * (int64_t)*grid)
+        gram_partial_kernel<NT, NG, 1, LINES, SF == 1, false><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
+            rows_base, d, ld, row_index_dev, f, partial, in_fp64, 0, pass.guess);
     else
-        gram_partial_kernel<NT, NG, SF, LINES, false><<<*grid, 64 * kWaves, 0, s>>>(
-            rows_base, d, ld, row_index_dev, f, partial, in_fp64);
+        gram_partial_kernel<NT, NG, SF, LINES, false, MEAN><<<*grid, 64 * kWaves, 0, s>>>(
+            rows_base, d, ld, row_index_dev, f, partial, in_fp64, 0, pass.guess);
 }
 
 template <int NT, int NG, bool LINES>
 void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
-                      int f, float *partial, int *grid, hipStream_t s) {
+                      int f, float *partial, int *grid, GramPass pass, hipStream_t s) {
+    if (pass.sample) {
+        *grid = kGramBlocks / 2;
+        gram_partial_kernel<NT, NG, 1, LINES, true, false><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
+            rows_base, d, ld, row_index_dev, f, partial, 0, d / kSampleSpans / kStep * kStep, pass.guess);
+        return;
+    }
     // Long rows: two steps at a time up to 32 vectors (four steps per wave or fewer: one at a time
     // spreads them over more waves and partial sums).  Above, more registers and fewer waves cost more
     // than longer pieces of a row give, but for rows off the cache lines that are far larger than the
     // last-level cache (48 x 11.2 M 596 -> 584 us, 64 x 11.2 M 857 -> 804; 64 x 3 M 231 -> 232).
     constexpr int SF = NT <= 2 || (NT + (NG > 0 ? 1 : 0) <= 4 && !LINES) ? 2 : 1;
     const int64_t one_at_a_time = (int64_t)1 << (NT <= 1 ? 20 : (NT <= 2 ? 19 : 22));
+    if constexpr (16 * NT + 4 * NG <= kMaxGuess) {
+        if (pass.guess.out != nullptr) {  // rows long enough for two steps at a time
+            launch_gram_spans<NT, NG, SF, LINES, true>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
+            return;
+        }
+    }
     if (SF > 1 && d > one_at_a_time)
-        launch_gram_spans<NT, NG, SF, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_spans<NT, NG, SF, LINES, false>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
     else
-        launch_gram_spans<NT, NG, 1, LINES>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_spans<NT, NG, 1, LINES, false>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
 }
 
 inline bool rows_on_lines(const float *rows_base, int64_t ld) {
@@ -792,23 +923,23 @@ inline bool rows_on_lines(const float *rows_base, int64_t ld) {
 
 template <int NT, int NG>
 int launch_gram_shape(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
-                      int f, float *partial, int *grid, hipStream_t s) {
+                      int f, float *partial, int *grid, GramPass pass, hipStream_t s) {
     if (rows_on_lines(rows_base, ld))
-        launch_gram_rows<NT, NG, true>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_rows<NT, NG, true>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
     else
-        launch_gram_rows<NT, NG, false>(rows_base, d, ld, row_index_dev, f, partial, grid, s);
+        launch_gram_rows<NT, NG, false>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
 
 // Gram matrix of the f rows into ws->gram (partial tiles, then the fp64 reduction).
 int launch_gram(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev, int f,
-                KrumWorkspace *ws, hipStream_t s) {
+                KrumWorkspace *ws, GramPass pass, hipStream_t s) {
     int rc, grid = 0;
     switch (4 * row_tiles(f) + row_groups(f)) {
-#define BYZ_GRAM_SHAPE(nt, ng)                                                                       \
-    case 4 * (nt) + (ng):                                                                            \
-        rc = launch_gram_shape<nt, ng>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, s);   \
+#define BYZ_GRAM_SHAPE(nt, ng)                                                                           \
+    case 4 * (nt) + (ng):                                                                                \
+        rc = launch_gram_shape<nt, ng>(rows_base, d, ld, row_index_dev, f, ws->partial, &grid, pass, s); \
         break;
         BYZ_GRAM_SHAPE(1, 0) BYZ_GRAM_SHAPE(2, 0) BYZ_GRAM_SHAPE(3, 0) BYZ_GRAM_SHAPE(4, 0)
         BYZ_GRAM_SHAPE(5, 0) BYZ_GRAM_SHAPE(6, 0) BYZ_GRAM_SHAPE(7, 0) BYZ_GRAM_SHAPE(8, 0)
@@ -862,6 +993,21 @@ constexpr int64_t short_mean(int f, bool lines) {
     return f <= 25 ? 3 << 17 : (f <= 40 ? 5 << 16 : 1 << 18);
 }
 
+constexpr int64_t kMeanBlocks = 2048;  // of chosen_mean_kernel: all resident
+
+// Where the mean is taken on the way: m rows fewer to read against the sample with its reduction and scores (20 us up
+// to 32 vectors, 25 above), the additions (about what a quarter of the rows takes to read: vector and matrix
+// instructions share one datapath) and the output written meanwhile.  More than 64 vectors leave no registers.  us a
+// call, in two passes / with a guess: f = 25 m = 20 11.2 M 334 / 254, off the lines 353 / 268, 5.6 M 179 / 140, 4 M 131 / 110, 2.9 M
+// 99 / 105; f = 9 m = 7 23 M 270 / 201; f = 16 m = 14 8.5 M 181 / 141; f = 49 m = 40 11.2 M 711 / 559, 2.6 M 180 / 155, m = 25 6.2 M
+// 348 / 322; f = 64 m = 54 5 M 428 / 338, m = 32 366 / 340.  Scores too close to guess from (rows of one
+// distribution): f = 25 11.2 M 339 / 361, 5.6 M 180 / 197; f = 49 11.2 M 711 / 740; f = 60 m = 50 2.1 M 182 / 207, which is why
+// the line lies higher for more vectors.
+constexpr bool guess_pays(int f, int m, int64_t d) {
+    return f <= kMaxGuess && d >= (int64_t)1 << 20 &&
+           (int64_t)(m - 2 - f / 4) * d >= (f <= 32 ? (int64_t)1 << 26 : (int64_t)3 << 25);
+}
+
 extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
                               const int32_t *row_index_dev, int f, int c, int m, float *out,
                               int32_t *selected_out, double *scores_out, double *dist_out,
@@ -876,25 +1022,29 @@ extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
     if (workspace_bytes < krum_workspace_bytes(f)) return BYZ_ENOMEM;
     hipStream_t s = (hipStream_t)stream;
     KrumWorkspace *ws = reinterpret_cast<KrumWorkspace *>(workspace);
-    int rc = launch_gram(rows_base, d, ld, row_index_dev, f, ws, s);
+    int rc;
+    const bool guess = guess_pays(f, m, d);
+    if (guess) {
+        rc = launch_gram(rows_base, d, ld, row_index_dev, f, ws, kSampleMatrix, s);
+        if (rc != BYZ_OK) return rc;
+        rc = launch_distance_rows(f, f - c - 2, nullptr, nullptr, ws, s);
+        if (rc != BYZ_OK) return rc;
+    }
+    rc = launch_gram(rows_base, d, ld, row_index_dev, f, ws,
+                     guess ? GramPass{false, {ws->scores, m, out, &ws->guess}} : kWholeMatrix, s);
     if (rc != BYZ_OK) return rc;
     rc = launch_distance_rows(f, f - c - 2, dist_out, scores_out, ws, s);
     if (rc != BYZ_OK) return rc;
-    if (d > 0 && d <= short_mean(f, rows_on_lines(rows_base, ld))) {
-        choose_and_mean_kernel<<<(unsigned)((d + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+    if (d <= short_mean(f, rows_on_lines(rows_base, ld))) {
+        const int64_t blocks = d > 0 ? (d + kBlock - 1) / kBlock : 1;  // d == 0: the choice alone
+        choose_and_mean_kernel<<<(unsigned)blocks, kBlock, 0, s>>>(
             rows_base, d, ld, row_index_dev, ws->scores, f, m, selected_out, out);
-        BYZ_HIP(hipGetLastError());
-        return BYZ_OK;
+    } else {
+        const int64_t blocks = ((d + 3) / 4 + kBlock - 1) / kBlock;
+        chosen_mean_kernel<<<(unsigned)(blocks < kMeanBlocks ? blocks : kMeanBlocks), kBlock, 0, s>>>(
+            rows_base, d, ld, row_index_dev, ws->scores, f, m, guess ? &ws->guess : nullptr, selected_out, out);
     }
-    krum_select_kernel<<<1, kMaxKrum, 0, s>>>(ws->scores, f, m, selected_out, ws->selected_list,
-                                              &ws->n_selected);
     BYZ_HIP(hipGetLastError());
-    if (d > 0) {
-        const int64_t n_thr = d >= 4 ? (d + 3) / 4 : d;
-        selected_mean_kernel<<<(unsigned)((n_thr + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-            rows_base, d, ld, row_index_dev, ws->selected_list, &ws->n_selected, out);
-        BYZ_HIP(hipGetLastError());
-    }
     return BYZ_OK;
 }
 
@@ -914,7 +1064,7 @@ extern "C" int byz_bulyan(const float *rows_base, int64_t d, int64_t ld,
     if (workspace_bytes < krum_workspace_bytes(f)) return BYZ_ENOMEM;
     hipStream_t s = (hipStream_t)stream;
     KrumWorkspace *ws = reinterpret_cast<KrumWorkspace *>(workspace);
-    int rc = launch_gram(rows_base, d, ld, row_index_dev, f, ws, s);
+    int rc = launch_gram(rows_base, d, ld, row_index_dev, f, ws, kWholeMatrix, s);
     if (rc != BYZ_OK) return rc;
     rc = launch_distance_rows(f, -1, dist_out, nullptr, ws, s);
     if (rc != BYZ_OK) return rc;

@@ -1841,6 +1841,50 @@ def test_multi_krum_mean_of_short_and_long_rows(f):
             assert bool((out[d:] == 7.0).all()), (f, d, m)
 
 
+@pytest.mark.parametrize("f, c, m, d, ld", [(9, 2, 7, 22400003, 22400003), (16, 2, 14, 8400001, 8400032),
+                                            (25, 5, 20, 5600001, 5600064), (32, 4, 28, 3800035, 3800035),
+                                            (33, 5, 28, 5600002, 5600003), (49, 8, 41, 3900031, 3900064),
+                                            (56, 8, 48, 3200033, 3200064), (64, 10, 54, 2800037, 2800040)])
+def test_multi_krum_mean_taken_with_the_distances(f, c, m, d, ld):
+    # rows long enough that the choice is guessed from a sample and averaged in the pass over all rows: guess right;
+    # wrong, as a chosen row differs from what the sample shows in one word; wrong and infinite; not made, as rows are
+    # alike; not made, as the output is one of the rows.  The words are those of one addition after the other
+    # whichever way they came.
+    gen = torch.Generator(device=DEV).manual_seed(f)
+    X = torch.empty((f + 1, ld), device=DEV)
+    idx = np.random.default_rng(f).permutation(f + 1)[:f].astype(np.int32)
+    idx_dev = torch.tensor(idx, device=DEV)
+    for kind in ("right", "wrong", "infinite", "alike", "in place"):
+        for t, i in enumerate(idx):
+            X[int(i)].normal_(generator=gen)
+            if kind != "alike":
+                X[int(i)].mul_(1.0 + 0.05 * t)
+        first = int(idx[0])  # the smallest row, chosen unless the word is seen
+        if kind == "wrong":
+            X[first, d - 1] = 1e6
+        elif kind == "infinite":
+            X[first, d - 1] = float("inf")
+        out = X[first] if kind == "in place" else torch.full((d + 8,), 7.0, device=DEV)
+        kept = X[:, d - 1].clone()
+        before = X[first].clone()
+        _, sel, scores, _ = B.byz_multi_krum(X, d, idx_dev, c, m, out=out)
+        torch.cuda.synchronize()
+        sc = scores.cpu().numpy()
+        with np.errstate(invalid="ignore"):
+            rank = [sum((sc[k] < sc[i]) or (sc[k] == sc[i] and k < i) for k in range(f)) for i in range(f)]
+        want_sel = np.array([r < m for r in rank])
+        assert np.array_equal(sel.cpu().numpy().astype(bool), want_sel), (f, kind)
+        assert want_sel[0] == (kind not in ("wrong", "infinite")) or kind in ("alike", "infinite"), (f, kind)
+        acc = torch.zeros(d, device=DEV)
+        for i in np.flatnonzero(want_sel):
+            acc += (before if kind == "in place" and int(idx[i]) == first else X[int(idx[i])])[:d]
+        want = acc / torch.tensor(float(want_sel.sum()), device=DEV)
+        n = d - 8 if kind == "in place" else d  # (two threads write the last words of an odd row)
+        assert bool(((out[:n] == want[:n]) | (torch.isnan(out[:n]) & torch.isnan(want[:n]))).all()), (f, kind)
+        if kind != "in place":
+            assert bool((out[d:] == 7.0).all()) and torch.equal(X[:, d - 1], kept), (f, kind)
+
+
 def test_multi_krum_and_bulyan_for_every_f():
     # every f from 3 to 64 and a spread of the wider ones (all tile counts and staging shapes of
     # the Gram kernel, one and two distances per lane in the row sort, Bulyan's rounds in
