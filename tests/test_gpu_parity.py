@@ -1129,6 +1129,42 @@ def test_mean_around_median_alone():
         assert e.value.code == code, (n, beta)
 
 
+@pytest.mark.parametrize("f", [1, 3, 5, 9, 15, 33, 35, 49, 65, 101, 127])
+def test_window_around_the_median_on_special_values(f):
+    # the window's start is found by halving the candidates where the tests are in order, and by counting the failed
+    # ones in the waves that have a NaN or an infinite median: words as of the rule (the window's first position is the
+    # number of failed tests behind the lowest candidate), fp32 additions in ascending order.  Waves of ordinary
+    # values, of ties, of values whose differences overflow, of infinities, of NaNs; every length of a halving.
+    rng = np.random.default_rng(f)
+    d = 64 * 9 + 37
+    Xh = rng.standard_normal((f, d)).astype(np.float32)
+    Xh[:, 64:128] = rng.integers(-2, 3, size=(f, 64))
+    Xh[:, 128:192] = rng.choice(np.float32([3e38, -3e38, 1.0, 2e38]), size=(f, 64))
+    for w, special in ((3, [np.inf, 0.0, 1.0]), (4, [-np.inf, np.inf, 0.5]), (5, [np.nan, 1.0, 2.0, 3.0]),
+                       (6, [np.nan, np.inf, -np.inf, 0.0]), (7, [np.inf, np.inf, 2.0])):
+        Xh[:, 64 * w:64 * w + 64] = rng.choice(np.float32(special), size=(f, 64))
+    Xh[f // 2, 64 * 8 + 5] = -np.float32(np.nan)
+    X = torch.tensor(Xh, device=DEV)
+    idx = torch.arange(f, dtype=torch.int32, device=DEV)
+    order = np.argsort(O.order_key(Xh.view(np.uint32)), axis=0, kind="stable")
+    v = np.take_along_axis(Xh, order, axis=0)
+    h, at = (f - 1) // 2, np.arange(d)
+    for beta in sorted({b for b in (1, 2, 3, 7, 8, h, h + 1, f - 2, f - 1, f) if 1 <= b <= f}):
+        first = max(0, h - beta + 1)
+        start = np.full(d, first)
+        with np.errstate(invalid="ignore", over="ignore"):
+            for s in range(first, h):
+                if s + beta <= f - 1:
+                    start += ~((v[h] - v[s]) <= (v[s + beta] - v[h]))
+            acc = np.zeros(d, dtype=np.float32)
+            for t in range(beta):
+                acc = acc + v[start + t, at]
+            want = acc / np.float32(beta)
+        got = B.byz_mean_around_median(X, d, idx, beta).cpu().numpy()
+        same = (got.view(np.uint32) == want.view(np.uint32)) | (np.isnan(got) & np.isnan(want))
+        assert same.all(), (f, beta, np.flatnonzero(~same)[:5])
+
+
 def _gram_additions(d):
     """Most fp32 additions behind one entry of a partial Gram matrix: a run of at most 128 products, the
     runs of a wave (at least four waves in each of 512 blocks, 96 products or more each), then one
