@@ -17,6 +17,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <type_traits>
 
 #include "byz_internal.h"
 #include "byzshield.h"
@@ -106,16 +107,15 @@ __host__ __device__ constexpr int staged_rows(int nt, int groups, int sf) {
     return (16 * nt + 4 * groups + per_load - 1) / per_load * per_load;
 }
 
-// Element e of the sixteen coordinates in y: run[g * kParts + c] (four rows of group g against the rows
-// 64c + lane) takes the products of the four quarters in ascending order, one rounding each.
+// Element e of the sixteen coordinates in y, quarter q: run[g * kParts + c] (four rows of group g against the rows
+// 64c + lane) takes its product, one rounding; the caller goes through the quarters in ascending order.
 template <int NT, int NG, int kParts, int N>
-__device__ __forceinline__ void group_products(const f32x4 (&y)[kParts > 0 ? kParts : 1][4], int e, bool fresh,
+__device__ __forceinline__ void group_products(const f32x4 (&y)[kParts > 0 ? kParts : 1][4], int q, int e, bool fresh,
                                                f32x4 (&run)[N]) {
     constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     // (cbsz 4 and abid name the block of four lanes that is A for all sixteen blocks; constants)
 #define BYZ_GROUP(g)                                                                                  \
     if constexpr (NG > (g))                                                                           \
-        _Pragma("unroll") for (int q = 0; q < 4; ++q)                                                 \
         _Pragma("unroll") for (int c = 0; c < kParts; ++c)                                            \
             run[(g) * kParts + c] = __builtin_amdgcn_mfma_f32_4x4x1f32(                               \
                 y[kParts - 1][q][e], y[c][q][e], fresh && q == 0 ? zero : run[(g) * kParts + c], 4,   \
@@ -311,76 +311,95 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
         }
     };
     constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    constexpr int kRun = SF == 1 ? 3 : 2;           // stretches of a run
+    constexpr int kRun = SHORT ? 1 : (SF == 1 ? 3 : 2);  // stretches of a run (SHORT: each adds its own)
     constexpr int kRuns = SHORT ? (NP < 6 ? NP : 6) : NP;  // tiles whose runs are open at a time
     constexpr int kGroupRuns = NG > 0 ? NALL - NP : 1;
+    // The first stretch of a run in a body of its own, whose first products take an inline zero instead of cleared
+    // registers; with the groups' chains between the tiles, us a call: Multi-Krum 49 x 3 M 158 -> 155, 81 x 3 M 342 -> 327,
+    // 96 x 2 M 272 -> 262, 101 x 3 M 514 -> 493, 112 x 2 M 339 -> 318, Bulyan 49 x 11.2 M 694 -> 687.  Slower without groups
+    // at 64 and 80 x 3 M (177 / 179, 297 / 307), twice as slow at 128 (spills), the same with the mean.
+    constexpr bool kPeel = SHORT || (NG > 0 && !MEAN) || NT == 6 || NT == 7;
     f32x4 run[kRuns], grun[kGroupRuns];
 #pragma unroll
     for (int p = 0; p < NALL; ++p) acc[p] = zero;
     const int row = lane & 15;
+    // one stretch; `first` of a run: its sums start from zero
+    auto step = [&](auto first) {
+        constexpr bool kFirst = decltype(first)::value;
+        wave_fence();
+#pragma unroll
+        for (int n = 0; n < kLoads; ++n)
+            if (used(n)) slots[64 * n + lane] = raw[n];
+        wave_fence();
+        if (span + stride < n_spans) fetch(span + stride);
+        if constexpr (MEAN) guessed.template add<16 * NT + 4 * NG, kSpan>(stage, span * kSpan, d);
+#pragma unroll
+        for (int h = 0; h < 2 * SF; ++h) {  // 16 coordinates
+            const int piece = 8 * (h / 2) + 2 * (lane >> 4) + h % 2;
+            f32x4 x[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                x[t] = slots[(16 * t + row) * kPieces + (piece ^ (row & 7))];
+            // the groups' operand, both sides of it: lane l holds row l (and 64 + l); the
+            // instruction takes the four lanes of one group as A and all as B.  The order of
+            // the products is that of the 16x16 instruction, which multiplies the four
+            // quarters of the wave one after the other.
+            f32x4 y[NG > 0 ? kParts : 1][4];
+            if constexpr (NG > 0)
+#pragma unroll
+                for (int c = 0; c < kParts; ++c)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int r = 64 * c + lane < 16 * NT + 4 * NG ? 64 * c + lane : 16 * NT;
+                        y[c][q] = slots[r * kPieces + ((8 * (h / 2) + 2 * q + h % 2) ^ (r & 7))];
+                    }
+            // lane l holds A[row = l%16][k = l/16], which is also B[k][col = l%16] of the
+            // transposed operand; tiles p0 .. p0 + kRuns - 1
+#pragma unroll
+            for (int p0 = 0; p0 < NP; p0 += kRuns) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool fresh = e == 0 && (SHORT || (kFirst && h == 0));
+#pragma unroll
+                    for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                        for (int tj = ti; tj < NT; ++tj) {
+                            const int p = tile_pair(NT, ti, tj) - p0;
+                            if (p < 0 || p >= kRuns) continue;
+                            // the groups' chains of four between the tiles, whose instructions they would
+                            // otherwise wait in front of
+                            if constexpr (NG > 0)
+                                if (p0 == 0 && p < 4) group_products<NT, NG, kParts>(y, p, e, fresh, grun);
+                            run[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                x[ti][e], x[tj][e], fresh ? zero : run[p], 0, 0, 0);
+                        }
+                    if constexpr (NG > 0)
+                        if (p0 == 0)
+#pragma unroll
+                            for (int q = kRuns < 4 ? kRuns : 4; q < 4; ++q)
+                                group_products<NT, NG, kParts>(y, q, e, fresh, grun);
+                }
+                if constexpr (SHORT)
+#pragma unroll
+                    for (int p = 0; p < kRuns && p0 + p < NP; ++p) acc[p0 + p] += run[p];
+            }
+            if constexpr (SHORT)
+#pragma unroll
+                for (int p = NP; p < NALL; ++p) acc[p] += grun[p - NP];
+        }
+        span += stride;
+    };
     if (span < n_spans) fetch(span);
     while (span < n_spans) {
-        if constexpr (!SHORT) {
+        if constexpr (kPeel) {
+            step(std::true_type());
+        } else {
 #pragma unroll
             for (int p = 0; p < NP; ++p) run[p] = zero;
 #pragma unroll
             for (int p = 0; p < kGroupRuns; ++p) grun[p] = zero;
         }
-        for (int k = 0; k < kRun && span < n_spans; ++k, span += stride) {
-            wave_fence();
-#pragma unroll
-            for (int n = 0; n < kLoads; ++n)
-                if (used(n)) slots[64 * n + lane] = raw[n];
-            wave_fence();
-            if (span + stride < n_spans) fetch(span + stride);
-            if constexpr (MEAN) guessed.template add<16 * NT + 4 * NG, kSpan>(stage, span * kSpan, d);
-#pragma unroll
-            for (int h = 0; h < 2 * SF; ++h) {  // 16 coordinates
-                const int piece = 8 * (h / 2) + 2 * (lane >> 4) + h % 2;
-                f32x4 x[NT];
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    x[t] = slots[(16 * t + row) * kPieces + (piece ^ (row & 7))];
-                // the groups' operand, both sides of it: lane l holds row l (and 64 + l); the
-                // instruction takes the four lanes of one group as A and all as B.  The order of
-                // the products is that of the 16x16 instruction, which multiplies the four
-                // quarters of the wave one after the other.
-                f32x4 y[NG > 0 ? kParts : 1][4];
-                if constexpr (NG > 0)
-#pragma unroll
-                    for (int c = 0; c < kParts; ++c)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int r = 64 * c + lane < 16 * NT + 4 * NG ? 64 * c + lane : 16 * NT;
-                            y[c][q] = slots[r * kPieces + ((8 * (h / 2) + 2 * q + h % 2) ^ (r & 7))];
-                        }
-                // lane l holds A[row = l%16][k = l/16], which is also B[k][col = l%16] of the
-                // transposed operand; tiles p0 .. p0 + kRuns - 1
-#pragma unroll
-                for (int p0 = 0; p0 < NP; p0 += kRuns) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if constexpr (NG > 0)
-                            if (p0 == 0) group_products<NT, NG, kParts>(y, e, SHORT && e == 0, grun);
-#pragma unroll
-                        for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-                            for (int tj = ti; tj < NT; ++tj) {
-                                const int p = tile_pair(NT, ti, tj) - p0;
-                                if (p < 0 || p >= kRuns) continue;
-                                run[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                    x[ti][e], x[tj][e], SHORT && e == 0 ? zero : run[p], 0, 0, 0);
-                            }
-                    }
-                    if constexpr (SHORT)
-#pragma unroll
-                        for (int p = 0; p < kRuns && p0 + p < NP; ++p) acc[p0 + p] += run[p];
-                }
-                if constexpr (SHORT)
-#pragma unroll
-                    for (int p = NP; p < NALL; ++p) acc[p] += grun[p - NP];
-            }
-        }
+        for (int k = kPeel ? 1 : 0; k < kRun && span < n_spans; ++k) step(std::false_type());
         if constexpr (!SHORT) {
 #pragma unroll
             for (int p = 0; p < NP; ++p) acc[p] += run[p];
