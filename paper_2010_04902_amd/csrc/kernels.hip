@@ -1640,17 +1640,16 @@ constexpr int most_slots(int f, int r) {
     return (int)(sizeof(AggWorkspace::perm_off) / 4) / slot_words(f, r);
 }
 
-// First kernel: fused_body's walk over every copy.
+// fused_body's walk over every copy, by thread gt of the call; the block's findings are in s_bits[slot_words(F, R)]
+// behind the next barrier.
 template <int F, int R, bool TRIM, int V, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void short_pass_kernel(
-    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
-    uint32_t *__restrict__ slots, int trim_b, uint32_t *__restrict__ out) {
+__device__ __forceinline__ void short_pass_body(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows, int64_t gt,
+    int trim_b, uint32_t *__restrict__ out, uint32_t *s_bits) {
     constexpr int NS = R, kBits = slot_bits(R), kWords = slot_words(F, R);
-    __shared__ uint32_t s_bits[kWords];
     for (int t = threadIdx.x; t < kWords; t += BLOCK) s_bits[t] = 0;
     const int lane = threadIdx.x & 63;
     const int64_t n_thr = (d + V - 1) / V;
-    const int64_t gt = (int64_t)tile_of_block<block_group(V)>(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
     const int64_t c0 = (gt + 1) * V <= d ? gt * V : d - V;  // as in fused_body
     const uint32_t voff = (uint32_t)(c0 * 4);
     uint32_t flags[(F + 63) / 64] = {};
@@ -1679,36 +1678,33 @@ __global__ __launch_bounds__(BLOCK) void short_pass_kernel(
         const int bit = (64 * w + lane) * kBits;
         if (64 * w + lane < F && flags[w] != 0) atomicOr(&s_bits[bit / 32], flags[w] << (bit % 32));
     }
+}
+
+// First kernel.
+template <int F, int R, bool TRIM, int V, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void short_pass_kernel(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
+    uint32_t *__restrict__ slots, int trim_b, uint32_t *__restrict__ out) {
+    constexpr int kWords = slot_words(F, R);
+    __shared__ uint32_t s_bits[kWords];
+    const int64_t gt = (int64_t)tile_of_block<block_group(V)>(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
+    short_pass_body<F, R, TRIM, V, BLOCK>(X, d, ld, file_rows, gt, trim_b, out, s_bits);
     __syncthreads();
     for (int t = threadIdx.x; t < kWords; t += BLOCK) slots[(int64_t)blockIdx.x * kWords + t] = s_bits[t];
 }
 
-// Second kernel: the decision of single_pass_decide_kernel in every block, then, where it
-// asks for it, the median or trimmed mean of the winners' rows again.  Block 0 writes what the caller gets.
+// The decision of single_pass_decide_kernel, in every block from the findings of the whole call in s_bits, then, where
+// it asks for it, the median or trimmed mean of the winners' rows again by thread gt.  Block 0 writes what the caller
+// gets.
 template <int F, int R, bool TRIM, int V>
-__global__ __launch_bounds__(kBlock) void short_decide_kernel(
-    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
-    AggWorkspace *ws, int n_slots, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out) {
-    constexpr int kBits = slot_bits(R), kWords = slot_words(F, R), kPieces = kWords / 4;
-    static_assert(R * (R - 1) / 2 + R <= kBits && kPieces <= kBlock && F <= kBlock, "a file's bits, a thread a piece and a file");
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    __shared__ uint32_t s_bits[kWords];
+__device__ __forceinline__ void decide_and_redo(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows, AggWorkspace *ws,
+    int64_t gt, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out, const uint32_t *s_bits) {
+    constexpr int kBits = slot_bits(R);
     __shared__ uint32_t s_redo;
     __shared__ int32_t s_row[F];
-    for (int t = threadIdx.x; t < kWords; t += kBlock) s_bits[t] = 0;
     if (threadIdx.x == 0) s_redo = 0;
-    const u32x4 *pieces = reinterpret_cast<const u32x4 *>(ws->perm_off);
-    constexpr int kStride = kBlock / kPieces * kPieces;  // a thread's pieces are the same files' every time
-    u32x4 mine = {0, 0, 0, 0};
-    if ((int)threadIdx.x < kStride) {
-#pragma unroll 4
-        for (int t = threadIdx.x; t < n_slots * kPieces; t += kStride) mine |= pieces[t];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (mine[e] != 0) atomicOr(&s_bits[(int)threadIdx.x % kPieces * 4 + e], mine[e]);
-    __syncthreads();
+    __syncthreads();  // s_bits is complete, too
     if (const int j = threadIdx.x; j < F) {
         const uint32_t field = s_bits[j * kBits / 32] >> (j * kBits % 32);
         const int w = decide_winner(field, R);
@@ -1724,7 +1720,6 @@ __global__ __launch_bounds__(kBlock) void short_decide_kernel(
     if (blockIdx.x == 0 && threadIdx.x == 0)
         ws->path = redo ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : (uint32_t)BYZ_PATH_SINGLE_PASS;
     if (!redo) return;
-    const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (gt >= (d + V - 1) / V) return;
     const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
     constexpr int NS = 1, kAhead = V == 1 ? 20 : prefetch_depth(F, NS);
@@ -1759,6 +1754,43 @@ __global__ __launch_bounds__(kBlock) void short_decide_kernel(
     }
 #undef BYZ_S_ROW_ADDR
     store_vec<V>(out + c0, o);
+}
+
+// Second kernel.
+template <int F, int R, bool TRIM, int V>
+__global__ __launch_bounds__(kBlock) void short_decide_kernel(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
+    AggWorkspace *ws, int n_slots, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out) {
+    constexpr int kBits = slot_bits(R), kWords = slot_words(F, R), kPieces = kWords / 4;
+    static_assert(R * (R - 1) / 2 + R <= kBits && kPieces <= kBlock && F <= kBlock, "a file's bits, a thread a piece and a file");
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __shared__ uint32_t s_bits[kWords];
+    for (int t = threadIdx.x; t < kWords; t += kBlock) s_bits[t] = 0;
+    const u32x4 *pieces = reinterpret_cast<const u32x4 *>(ws->perm_off);
+    constexpr int kStride = kBlock / kPieces * kPieces;  // a thread's pieces are the same files' every time
+    u32x4 mine = {0, 0, 0, 0};
+    if ((int)threadIdx.x < kStride) {
+#pragma unroll 4
+        for (int t = threadIdx.x; t < n_slots * kPieces; t += kStride) mine |= pieces[t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (mine[e] != 0) atomicOr(&s_bits[(int)threadIdx.x % kPieces * 4 + e], mine[e]);
+    decide_and_redo<F, R, TRIM, V>(X, d, ld, file_rows, ws, (int64_t)blockIdx.x * kBlock + threadIdx.x, trim_b,
+                                   winner_replica, out, s_bits);
+}
+
+// Both in one, for rows that one block holds, a word per thread (64 threads or more: the loops over s_bits and files).
+constexpr int kOneBlock = 1024;
+template <int F, int R, bool TRIM>
+__global__ __launch_bounds__(kOneBlock) void one_block_kernel(
+    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
+    AggWorkspace *ws, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out) {
+    static_assert(F <= 64 && slot_words(F, R) <= 64, "a wave covers the files and the words of their bits");
+    __shared__ uint32_t s_bits[slot_words(F, R)];
+    short_pass_body<F, R, TRIM, 1, kOneBlock>(X, d, ld, file_rows, threadIdx.x, trim_b, out, s_bits);
+    decide_and_redo<F, R, TRIM, 1>(X, d, ld, file_rows, ws, threadIdx.x, trim_b, winner_replica, out, s_bits);
 }
 
 // ---------------------------------------------------------------------------- launchers
@@ -1972,10 +2004,26 @@ int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
 // 35.9 / 37.4), 600000 37.0 / 37.6 (38.0 / 39.6), 700001 39.7 / 39.8 (39.9 / 40.8), 786432 44.5 / 41.5 (44.7 / 42.4); on
 // the far side of 2^20 there are no slots (1048581 63.5, with two kernels' 1048576 53.4).
 constexpr int64_t kOneBlockPerCu = 256;
+// Rows that one block holds take one kernel, where its CU can read them in about the time of a second launch: us a call,
+// two kernels / one, among others: (25,3) d = 64 9.1 / 6.3, 512 8.8 / 6.3, 1024 8.7 to 10.0 / 8.5 (alone 21.6 / 22.3), trimmed mean
+// 1003 8.9 / 9.5; (9,3) 1003 8.9 / 6.3; (21,3) trimmed mean 1000 8.9 / 8.3; (25,5) 500 12.6 / 12.5, 1003 12.3 / 17.0.  Up to 25
+// files: more, a word per thread, take all registers 16 waves have, and are past the line from 300 coordinates on.
+constexpr int64_t one_block_words(int r, bool trim) { return r == 3 && !trim ? 5 << 14 : 3 << 14; }
 template <int F, int R, bool TRIM>
 int launch_short(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
                  uint32_t *out, int trim_b, int32_t *winner_replica, bool *done, hipStream_t s) {
     if (F < 21 && d > kManyBlocks) return BYZ_OK;
+    if constexpr (F <= 25) {
+        if (d <= kOneBlock && d * F * R <= one_block_words(R, TRIM)) {
+            int rc = byz_internal_profile_mark(0, s, "one_block_kernel");
+            if (rc != BYZ_OK) return rc;
+            one_block_kernel<F, R, TRIM><<<1, (unsigned)((d + 63) / 64 * 64), 0, s>>>(X, d, ld, rows, ws, trim_b,
+                                                                                      winner_replica, out);
+            BYZ_HIP(hipGetLastError());
+            *done = true;
+            return byz_internal_profile_mark(1, s);
+        }
+    }
     int rc = launch_short_pair<F, R, TRIM, 1, kBlock, 1>(X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
     if (rc != BYZ_OK || *done) return rc;
     rc = launch_short_pair<F, R, TRIM, 1, 512, 1>(X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);

@@ -1165,6 +1165,43 @@ def test_window_around_the_median_on_special_values(f):
         assert same.all(), (f, beta, np.flatnonzero(~same)[:5])
 
 
+@pytest.mark.parametrize("f, r", [(9, 3), (15, 3), (21, 3), (25, 3), (25, 5)])
+def test_aggregation_in_one_block(f, r):
+    # rows short enough for one block vote, choose and, where the fed copy was not the winner's, redo the output in one
+    # kernel: the smallest row, whole waves and one word more and less, the last length of the rule (five sixteenths or
+    # three sixteenths of 2^18 words in all, 1024 coordinates at most) and the first behind it.
+    rng = np.random.default_rng(f * r)
+    rows = rng.permutation(f * r + 2)[:f * r].reshape(f, r).astype(np.int32)
+    rows_dev = torch.tensor(rows.reshape(-1), device=DEV)
+    for trim in (0, f // 4):
+        most = min(1024, ((3 if trim or r == 5 else 5) << 14) // (f * r))
+        for d in sorted({4, 5, 63, 64, 65, 255, most - 1, most, most + 1}):
+            for split in (False, True):
+                G = rng.standard_normal((f, d)).astype(np.float32)
+                Xh = np.zeros((f * r + 2, d + 3), dtype=np.float32)
+                for j in range(f):
+                    Xh[rows[j], :d] = G[j]
+                    if split and j % 3 == 0:  # no majority; most of the copies are alike but for a word each
+                        for k in range(r // 2 + 1):
+                            Xh[rows[j, r - 1 - k], :d] = -2.0
+                            Xh[rows[j, r - 1 - k], (11 * j + k) % d] = k
+                    elif j % 4 == 1:
+                        Xh[rows[j, int(rng.integers(r))], int(rng.integers(d))] += 1.0
+                X = torch.tensor(Xh, device=DEV)
+                out = torch.full((d + 4,), 7.0, device=DEV)
+                flags = B.BYZ_AGG_TRIM(trim) if trim else 0
+                _, wrep, ws = B.byz_aggregate_opts(X, d, rows_dev, f, r, flags, out=out)
+                out_o, wrep_o, _ = C.aggregate(Xh, rows, d)
+                assert np.array_equal(wrep.cpu().numpy(), wrep_o), (trim, d, split)
+                if trim:
+                    wrow = torch.tensor(rows[np.arange(f), wrep_o], device=DEV)
+                    out_o = B.byz_trimmed_mean(X, d, wrow, trim).cpu().numpy()
+                assert np.array_equal(W.bits(out[:d]), out_o.view(np.uint32)), (trim, d, split)
+                assert bool((out[d:] == 7.0).all()), (trim, d, split)
+                if not split:
+                    assert B.byz_aggregate_path(ws) == B.BYZ_PATH_SINGLE_PASS, (trim, d)
+
+
 def _gram_additions(d):
     """Most fp32 additions behind one entry of a partial Gram matrix: a run of at most 128 products, the
     runs of a wave (at least four waves in each of 512 blocks, 96 products or more each), then one
