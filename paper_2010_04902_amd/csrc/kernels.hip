@@ -1693,20 +1693,20 @@ __global__ __launch_bounds__(BLOCK) void short_pass_kernel(
     for (int t = threadIdx.x; t < kWords; t += BLOCK) slots[(int64_t)blockIdx.x * kWords + t] = s_bits[t];
 }
 
-// The decision of single_pass_decide_kernel, in every block from the findings of the whole call in s_bits, then, where
-// it asks for it, the median or trimmed mean of the winners' rows again by thread gt.  Block 0 writes what the caller
-// gets.
-template <int F, int R, bool TRIM, int V>
+// The decision of single_pass_decide_kernel on a call that read every copy, in every block: findings_of(j) = the bits
+// of file j, complete behind a barrier.  Then, where it asks for it, the median or trimmed mean of the winners' rows
+// again by the threads gt, gt + stride, ...  Block 0 writes what the caller gets.
+template <int F, int R, bool TRIM, int V, typename Findings>
 __device__ __forceinline__ void decide_and_redo(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows, AggWorkspace *ws,
-    int64_t gt, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out, const uint32_t *s_bits) {
-    constexpr int kBits = slot_bits(R);
+    int64_t gt, int64_t stride, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out,
+    Findings findings_of) {
     __shared__ uint32_t s_redo;
     __shared__ int32_t s_row[F];
     if (threadIdx.x == 0) s_redo = 0;
-    __syncthreads();  // s_bits is complete, too
+    __syncthreads();  // the findings are complete, too
     if (const int j = threadIdx.x; j < F) {
-        const uint32_t field = s_bits[j * kBits / 32] >> (j * kBits % 32);
+        const uint32_t field = findings_of(j);
         const int w = decide_winner(field, R);
         if ((field & fed_differs_bit(R, w)) != 0) s_redo = 1;
         s_row[j] = file_rows[j * R + w];
@@ -1720,7 +1720,8 @@ __device__ __forceinline__ void decide_and_redo(
     if (blockIdx.x == 0 && threadIdx.x == 0)
         ws->path = redo ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : (uint32_t)BYZ_PATH_SINGLE_PASS;
     if (!redo) return;
-    if (gt >= (d + V - 1) / V) return;
+    for (const int64_t n_thr = (d + V - 1) / V; gt < n_thr; gt += stride) {
+    asm volatile("" ::: "memory");  // or the rows are read once for all rounds, into more registers than there are
     const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
     constexpr int NS = 1, kAhead = V == 1 ? 20 : prefetch_depth(F, NS);
     uint32_t key[V][F];
@@ -1754,31 +1755,46 @@ __device__ __forceinline__ void decide_and_redo(
     }
 #undef BYZ_S_ROW_ADDR
     store_vec<V>(out + c0, o);
+    }
 }
 
-// Second kernel.
+// The bits of file j in a block's slot.
+template <int R>
+__device__ __forceinline__ uint32_t slot_findings(const uint32_t *s_bits, int j) {
+    constexpr int kBits = slot_bits(R);
+    return s_bits[j * kBits / 32] >> (j * kBits % 32);
+}
+
+// Second kernel, and the last of a long call that reads every copy (n_slots 0: the findings are in ws->pneq).  There a
+// decision in one block and a gated median in a block per tile behind it were two launches and up to 25000 blocks that
+// return at once: us a call, those two / this, (25,3) 11.2 M 524 / 518, (49,3) 25.6 M 2322 / 2308, (25,5) trimmed mean 2 M
+// 165.7 / 163.2, (81,3) 1 M 157.9 / 155.7, (63,7) 200000 66.1 / 61.7, (9,3) 1 M 25.4 / 23.3, (15,3) 500000 21.2 / 19.1; where the
+// output is redone (35,5) 600000 112 / 107, (25,5) trimmed mean 2 M 204 / 202, (65,5) 1 M 271 / 274.
 template <int F, int R, bool TRIM, int V>
-__global__ __launch_bounds__(kBlock) void short_decide_kernel(
+__global__ __launch_bounds__(kBlock) void decide_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
     AggWorkspace *ws, int n_slots, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out) {
     constexpr int kBits = slot_bits(R), kWords = slot_words(F, R), kPieces = kWords / 4;
     static_assert(R * (R - 1) / 2 + R <= kBits && kPieces <= kBlock && F <= kBlock, "a file's bits, a thread a piece and a file");
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     __shared__ uint32_t s_bits[kWords];
-    for (int t = threadIdx.x; t < kWords; t += kBlock) s_bits[t] = 0;
-    const u32x4 *pieces = reinterpret_cast<const u32x4 *>(ws->perm_off);
-    constexpr int kStride = kBlock / kPieces * kPieces;  // a thread's pieces are the same files' every time
-    u32x4 mine = {0, 0, 0, 0};
-    if ((int)threadIdx.x < kStride) {
+    if (n_slots > 0) {
+        for (int t = threadIdx.x; t < kWords; t += kBlock) s_bits[t] = 0;
+        const u32x4 *pieces = reinterpret_cast<const u32x4 *>(ws->perm_off);
+        constexpr int kStride = kBlock / kPieces * kPieces;  // a thread's pieces are the same files' every time
+        u32x4 mine = {0, 0, 0, 0};
+        if ((int)threadIdx.x < kStride) {
 #pragma unroll 4
-        for (int t = threadIdx.x; t < n_slots * kPieces; t += kStride) mine |= pieces[t];
-    }
-    __syncthreads();
+            for (int t = threadIdx.x; t < n_slots * kPieces; t += kStride) mine |= pieces[t];
+        }
+        __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (mine[e] != 0) atomicOr(&s_bits[(int)threadIdx.x % kPieces * 4 + e], mine[e]);
-    decide_and_redo<F, R, TRIM, V>(X, d, ld, file_rows, ws, (int64_t)blockIdx.x * kBlock + threadIdx.x, trim_b,
-                                   winner_replica, out, s_bits);
+        for (int e = 0; e < 4; ++e)
+            if (mine[e] != 0) atomicOr(&s_bits[(int)threadIdx.x % kPieces * 4 + e], mine[e]);
+    }
+    decide_and_redo<F, R, TRIM, V>(
+        X, d, ld, file_rows, ws, (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock, trim_b,
+        winner_replica, out, [&](int j) { return n_slots > 0 ? slot_findings<R>(s_bits, j) : load_shared_word(&ws->pneq[j]); });
 }
 
 // Both in one, for rows that one block holds, a word per thread (64 threads or more: the loops over s_bits and files).
@@ -1790,7 +1806,8 @@ __global__ __launch_bounds__(kOneBlock) void one_block_kernel(
     static_assert(F <= 64 && slot_words(F, R) <= 64, "a wave covers the files and the words of their bits");
     __shared__ uint32_t s_bits[slot_words(F, R)];
     short_pass_body<F, R, TRIM, 1, kOneBlock>(X, d, ld, file_rows, threadIdx.x, trim_b, out, s_bits);
-    decide_and_redo<F, R, TRIM, 1>(X, d, ld, file_rows, ws, threadIdx.x, trim_b, winner_replica, out, s_bits);
+    decide_and_redo<F, R, TRIM, 1>(X, d, ld, file_rows, ws, threadIdx.x, d, trim_b, winner_replica, out,
+                                   [&](int j) { return slot_findings<R>(s_bits, j); });
 }
 
 // ---------------------------------------------------------------------------- launchers
@@ -1964,6 +1981,20 @@ int launch_median(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_i
 
 #endif  // part 5
 
+// Blocks of decide_kernel on long rows: all resident, and few to launch where they nearly always return at once.
+constexpr unsigned kRedoBlocks = 2048;
+
+template <int F, int R, bool TRIM, int V>
+void launch_decide(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws, int n_slots,
+                   unsigned most_blocks, int trim_b, int32_t *winner_replica, uint32_t *out, hipStream_t s) {
+    const bool one_word = V == 1 || d <= kManyBlocks;
+    const unsigned all = blocks_for(one_word ? d : (d + V - 1) / V), grid = all < most_blocks ? all : most_blocks;
+    if (one_word)
+        decide_kernel<F, R, TRIM, 1><<<grid, kBlock, 0, s>>>(X, d, ld, rows, ws, n_slots, trim_b, winner_replica, out);
+    else
+        decide_kernel<F, R, TRIM, V><<<grid, kBlock, 0, s>>>(X, d, ld, rows, ws, n_slots, trim_b, winner_replica, out);
+}
+
 // The two kernels of a short call; *done stays false where the blocks have no room for their slots.
 template <int F, int R, bool TRIM, int V, int BLOCK, int DV>
 int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
@@ -1980,12 +2011,7 @@ int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
     // redone one word per thread up to kManyBlocks coordinates, where the wider form leaves CUs idle (as the gated
     // kernels of long calls).  us a call that redoes its output, four words / one: (49,7) d = 60001 median 50.9 /
     // 46.5, trimmed mean 57.4 / 49.9, (49,5) 100003 38.6 / 34.9 and 44.8 / 38.5, (35,5) 125003 34.6 / 32.8 and 39.4 / 35.7
-    if (DV == 1 || d <= kManyBlocks)
-        short_decide_kernel<F, R, TRIM, 1><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, rows, ws, (int)blocks, trim_b,
-                                                                            winner_replica, out);
-    else
-        short_decide_kernel<F, R, TRIM, DV><<<blocks_for((d + DV - 1) / DV), kBlock, 0, s>>>(
-            X, d, ld, rows, ws, (int)blocks, trim_b, winner_replica, out);
+    launch_decide<F, R, TRIM, DV>(X, d, ld, rows, ws, (int)blocks, blocks_for(d), trim_b, winner_replica, out, s);
     BYZ_HIP(hipGetLastError());
     *done = true;
     return BYZ_OK;
@@ -2038,22 +2064,10 @@ int launch_short(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     return rc;
 }
 
-// WITH_TRIM = false / WITH_MEDIAN = false leave that variant of the kernel out (a shape whose two
-// variants are compiled in different build parts)
-template <int F, int R, bool WITH_TRIM = true, bool WITH_MEDIAN = true>
-int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
-                 uint32_t *out, int probe_opts, int trim_b, int32_t *winner_replica, bool *done,
-                 hipStream_t s) {
-    if ((!WITH_TRIM && trim_b >= 0) || (!WITH_MEDIAN && trim_b < 0)) return BYZ_EINTERNAL;
-    if ((probe_opts & 1) == 0) {
-        int rc = BYZ_EINTERNAL;
-        if (trim_b < 0) {
-            if constexpr (WITH_MEDIAN) rc = launch_short<F, R, false>(X, d, ld, rows, ws, out, 0, winner_replica, done, s);
-        } else if constexpr (WITH_TRIM) {
-            rc = launch_short<F, R, true>(X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
-        }
-        if (rc != BYZ_OK || *done) return rc;
-    }
+// Probe and single pass of a long call (WITH_TRIM, WITH_MEDIAN: see launch_fused).
+template <int F, int R, bool WITH_TRIM, bool WITH_MEDIAN>
+int launch_long_pass(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
+                     uint32_t *out, int probe_opts, int trim_b, hipStream_t s) {
     probe_kernel<F, R><<<1, kProbeThreads, 0, s>>>(X, d, ld, rows, ws, probe_opts);
     BYZ_HIP(hipGetLastError());
     int rc = byz_internal_profile_mark(0, s, "fused_kernel");
@@ -2100,6 +2114,35 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
     }
     BYZ_HIP(hipGetLastError());
     return byz_internal_profile_mark(1, s);
+}
+
+// WITH_TRIM = false / WITH_MEDIAN = false leave that variant of the kernel out (a shape whose two
+// variants are compiled in different build parts)
+template <int F, int R, bool WITH_TRIM = true, bool WITH_MEDIAN = true>
+int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws,
+                 uint32_t *out, int probe_opts, int trim_b, int32_t *winner_replica, bool *done,
+                 hipStream_t s) {
+    if ((!WITH_TRIM && trim_b >= 0) || (!WITH_MEDIAN && trim_b < 0)) return BYZ_EINTERNAL;
+    if ((probe_opts & 1) == 0) {
+        int rc = BYZ_EINTERNAL;
+        if (trim_b < 0) {
+            if constexpr (WITH_MEDIAN) rc = launch_short<F, R, false>(X, d, ld, rows, ws, out, 0, winner_replica, done, s);
+        } else if constexpr (WITH_TRIM) {
+            rc = launch_short<F, R, true>(X, d, ld, rows, ws, out, trim_b, winner_replica, done, s);
+        }
+        if (rc != BYZ_OK || *done) return rc;
+    }
+    int rc = launch_long_pass<F, R, WITH_TRIM, WITH_MEDIAN>(X, d, ld, rows, ws, out, probe_opts, trim_b, s);
+    if (rc != BYZ_OK || (probe_opts & 1) != 0) return rc;  // early-majority mode decides in kernels of its own
+    if (trim_b < 0) {
+        if constexpr (WITH_MEDIAN)
+            launch_decide<F, R, false, gated_vec(F)>(X, d, ld, rows, ws, 0, kRedoBlocks, 0, winner_replica, out, s);
+    } else if constexpr (WITH_TRIM) {
+        launch_decide<F, R, true, gated_vec(F)>(X, d, ld, rows, ws, 0, kRedoBlocks, trim_b, winner_replica, out, s);
+    }
+    BYZ_HIP(hipGetLastError());
+    *done = true;
+    return BYZ_OK;
 }
 
 #if BYZ_IN_PART(6) || BYZ_IN_PART(8) || BYZ_IN_PART(10) || BYZ_IN_PART(14) || BYZ_IN_PART(15) || \

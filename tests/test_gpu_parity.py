@@ -1202,6 +1202,36 @@ def test_aggregation_in_one_block(f, r):
                     assert B.byz_aggregate_path(ws) == B.BYZ_PATH_SINGLE_PASS, (trim, d)
 
 
+@pytest.mark.parametrize("f, r, d, trim", [(9, 3, 4 * 2048 * 256 + 3, 0), (25, 3, 4 * 2048 * 256 + 1029, 5),
+                                           (25, 5, 4 * 2048 * 256 + 1, 0), (49, 3, 4 * 2048 * 256, 0),
+                                           (49, 3, 4 * 2048 * 256 + 5, 8), (81, 3, 2048 * 256 + 1, 0),
+                                           (121, 3, 2048 * 256 + 63, 20), (65, 5, 2048 * 256 - 1, 0)])
+def test_output_redone_in_rounds(f, r, d, trim):
+    # the kernel that decides for a long call redoes the output in rounds of 2048 blocks: one word, one block or nothing
+    # past a round.  In every third file the honest copies win (tie of three, or two alike of five) while the waves
+    # see the false ones alike.
+    gen = torch.Generator(device=DEV).manual_seed(f + d)
+    X = torch.empty((f * r, d), device=DEV)
+    rows = np.arange(f * r, dtype=np.int32).reshape(f, r)
+    for j in range(f):
+        X[j * r].normal_(generator=gen)
+        for k in range(1, r):
+            X[j * r + k] = X[j * r]
+        if j % 3 == 0:
+            for k in range(r // 2 + 1):  # replicas 1, 2 (and 3): alike but for a word each
+                X[j * r + 1 + k] = -2.0
+                X[j * r + 1 + k, (j * 65537 + 31 * k) % d] = k
+    rows_dev = torch.tensor(rows.reshape(-1), device=DEV)
+    out = torch.full((d + 8,), 7.0, device=DEV)
+    _, wrep, ws = B.byz_aggregate_opts(X, d, rows_dev, f, r, B.BYZ_AGG_TRIM(trim) if trim else 0, out=out)
+    assert B.byz_aggregate_path(ws) == B.BYZ_PATH_MEDIAN_REDONE
+    assert not wrep.cpu().numpy().any()
+    winners = torch.tensor(rows[:, 0].copy(), device=DEV)
+    want = B.byz_trimmed_mean(X, d, winners, trim) if trim else B.byz_median(X, d, winners)
+    assert torch.equal(out[:d].view(torch.int32), want.view(torch.int32))
+    assert bool((out[d:] == 7.0).all())
+
+
 def _gram_additions(d):
     """Most fp32 additions behind one entry of a partial Gram matrix: a run of at most 128 products, the
     runs of a wave (at least four waves in each of 512 blocks, 96 products or more each), then one
