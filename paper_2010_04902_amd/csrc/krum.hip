@@ -924,13 +924,19 @@ void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32
     // last-level cache (48 x 11.2 M 596 -> 584 us, 64 x 11.2 M 857 -> 804; 64 x 3 M 231 -> 232).
     constexpr int SF = NT <= 2 || (NT + (NG > 0 ? 1 : 0) <= 4 && !LINES) ? 2 : 1;
     const int64_t one_at_a_time = (int64_t)1 << (NT <= 1 ? 20 : (NT <= 2 ? 19 : 22));
+    const bool two_steps = SF > 1 && d > one_at_a_time;  // whatever the pass is for: the order of the additions
     if constexpr (16 * NT + 4 * NG <= kMaxGuess) {
-        if (pass.guess.out != nullptr) {  // rows long enough for two steps at a time
-            launch_gram_spans<NT, NG, SF, LINES, true>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
+        if (pass.guess.out != nullptr) {
+            if constexpr (NT <= 2)  // such rows are long enough for two steps at a time (guess_pays)
+                launch_gram_spans<NT, NG, SF, LINES, true>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
+            else if (two_steps)
+                launch_gram_spans<NT, NG, SF, LINES, true>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
+            else
+                launch_gram_spans<NT, NG, 1, LINES, true>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
             return;
         }
     }
-    if (SF > 1 && d > one_at_a_time)
+    if (two_steps)
         launch_gram_spans<NT, NG, SF, LINES, false>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
     else
         launch_gram_spans<NT, NG, 1, LINES, false>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);

@@ -1988,6 +1988,22 @@ def test_multi_krum_mean_taken_with_the_distances(f, c, m, d, ld):
             assert bool((out[d:] == 7.0).all()) and torch.equal(X[:, d - 1], kept), (f, kind)
 
 
+@pytest.mark.parametrize("f, d, ld", [(25, 4000003, 4000003), (33, 4400003, 4400003), (40, 3700001, 3700002),
+                                      (49, 3000001, 3000001), (49, 4300001, 4300003), (56, 2600003, 2600064),
+                                      (56, 2600003, 2600005), (64, 2300001, 2300001), (64, 4300001, 4300001)])
+def test_multi_krum_distances_do_not_depend_on_how_many_are_chosen(f, d, ld):
+    # the order of the additions behind a distance follows from f, d, ld and the alignment: the same bits whether the
+    # mean of many rows is taken in the pass over all of them or the mean of one row behind it, one or two stretches
+    # at a time off the cache lines and on them
+    X = torch.empty((f, ld), device=DEV).normal_(generator=torch.Generator(device=DEV).manual_seed(f))
+    X.mul_(torch.linspace(0.5, 2.0, f, device=DEV).view(f, 1))
+    idx = torch.arange(f, dtype=torch.int32, device=DEV)
+    _, _, scores, dist = B.byz_multi_krum(X, d, idx, 0, 1)
+    _, _, scores_m, dist_m = B.byz_multi_krum(X, d, idx, 0, f)
+    assert torch.equal(dist.view(torch.int64), dist_m.view(torch.int64))
+    assert torch.equal(scores.view(torch.int64), scores_m.view(torch.int64))
+
+
 def test_multi_krum_and_bulyan_for_every_f():
     # every f from 3 to 64 and a spread of the wider ones (all tile counts and staging shapes of
     # the Gram kernel, one and two distances per lane in the row sort, Bulyan's rounds in
