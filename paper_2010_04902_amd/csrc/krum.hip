@@ -242,6 +242,11 @@ struct GuessedMean {
     }
 };
 
+// What a Gram kernel reads: long rows, short rows, a sample of long ones, long ones whose mean is taken on the way.  (The
+// sample as a run-time case of the short rows' kernel cost that one up to 16 registers: us a call, with / without, 40 x 250000
+// 31.0 / 30.2, 49 x 100000 27.0 / 26.6, 97 x 250000 83.8 / 82.8.)
+enum class Gram { kLong, kShort, kSample, kMean };
+
 // Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16, NG =
 // groups of four rows behind them (row_groups).
 // A wave takes whole stretches of 32*SF coordinates of every row, so every word is loaded once
@@ -265,15 +270,16 @@ struct GuessedMean {
 // kernel takes 390 us, 344 with its loads left out, 322 with its products left out; more waves, longer
 // stretches or loads two steps ahead changed nothing); the runs cost 3 % there (15 % with eight row
 // tiles, where the sums fill the registers).
-template <int NT, int NG, int SF, bool LINES, bool SHORT, bool MEAN>
+template <int NT, int NG, int SF, bool LINES, Gram KIND>
 __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int64_t d, int64_t ld,
                                                 const int32_t *__restrict__ row_index, int f, int64_t pitch,
                                                 const GuessedMean &guessed, float *stage, f32x4 (&acc)[stored_tiles(NT, NG)]) {
+    constexpr bool SHORT = KIND == Gram::kShort || KIND == Gram::kSample, MEAN = KIND == Gram::kMean;
     constexpr int NP = NT * (NT + 1) / 2, NALL = stored_tiles(NT, NG), kSpan = kStep * SF;
     constexpr int kPieces = kSpan / 4, kRows = 64 / kPieces, kLoads = staged_rows(NT, NG, SF) / kRows;
     constexpr int kParts = NG == 0 ? 0 : (NALL - NP) / NG;  // stretches of 64 rows a group meets
     const int lane = threadIdx.x & 63;
-    const int64_t n_spans = SHORT && pitch != 0 ? kSampleSpans : (d + kSpan - 1) / kSpan;
+    const int64_t n_spans = KIND == Gram::kSample ? kSampleSpans : (d + kSpan - 1) / kSpan;
     constexpr int kWaves = gram_waves(NT, SF);
     const int64_t stride = (int64_t)gridDim.x * kWaves;
     constexpr unsigned kGroup = NT <= 1 ? 1 : (NT == 2 ? 4 : 8);
@@ -294,7 +300,7 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
         if (!used(n)) slots[64 * n + lane] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 raw[kLoads];
     auto fetch = [&](int64_t at) {
-        const int64_t c0 = SHORT && pitch != 0 ? sample_start(at, pitch) : at * kSpan;
+        const int64_t c0 = KIND == Gram::kSample ? sample_start(at, pitch) : at * kSpan;
         if (c0 + kSpan <= d) {
 #pragma unroll
             for (int n = 0; n < kLoads; ++n)
@@ -412,11 +418,11 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
 // Partial Gram tiles of the rows row_index[0..f-1] over this block's coordinates.  partial:
 // [gridDim.x][tiles][256] values, position v*64 + lane, tiles = stored_tiles(NT, NG), fp32 or, where a few
 // blocks would leave their last roundings visible, fp64 (d = 2048: 8.9e-9 -> 4.9e-9 at f = 100).
-template <int NT, int NG, int SF, bool LINES, bool SHORT, bool MEAN>
+template <int NT, int NG, int SF, bool LINES, Gram KIND>
 __global__ __launch_bounds__(64 * gram_waves(NT, SF))
 // (2: accumulators in ordinary registers; more row tiles would spill: 96 x 11.2 M 1502 us, 1362 with 1,
 // 80 x 11.2 M 998 and 1060; the same with groups, (5, 1) on long rows 41 registers)
-__attribute__((amdgpu_waves_per_eu(NG > 0 ? (NT <= 4 || (NT == 5 && SHORT) ? 2 : 1) : (NT <= 5 || (NT == 6 && SHORT) ? 2 : 1))))
+__attribute__((amdgpu_waves_per_eu(NG > 0 ? (NT <= 4 || (NT == 5 && KIND == Gram::kShort) ? 2 : 1) : (NT <= 5 || (NT == 6 && KIND == Gram::kShort) ? 2 : 1))))
 void gram_partial_kernel(
     const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
     float *__restrict__ partial, int in_fp64, int64_t pitch, GuessedPass guess) {
@@ -429,14 +435,14 @@ void gram_partial_kernel(
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     f32x4 acc[NP];
     GuessedMean guessed = {0, 0.0f, nullptr};
-    if constexpr (MEAN) {
+    if constexpr (KIND == Gram::kMean) {
         guessed.chosen = guess_vectors(guess.scores, f, guess.m, X, d, ld, row_index, guess.out,
                                        reinterpret_cast<double *>(lds));
         guessed.count = (float)__builtin_popcountll(guessed.chosen);
         guessed.out = guess.out;
         if (blockIdx.x == 0 && tid == 0) *guess.chosen = guessed.chosen;
     }
-    gram_accumulate<NT, NG, SF, LINES, SHORT, MEAN>(X, d, ld, row_index, f, pitch, guessed, lds + wave * kStage, acc);
+    gram_accumulate<NT, NG, SF, LINES, KIND>(X, d, ld, row_index, f, pitch, guessed, lds + wave * kStage, acc);
     // the waves' tiles are added in wave order in fp64, as many tiles at a time as fit
 #pragma unroll
     for (int p0 = 0; p0 < NP; p0 += kAtOnce) {
@@ -888,22 +894,16 @@ void launch_gram_spans(const float *rows_base, int64_t d, int64_t ld, const int3
     const int in_fp64 = partials_in_fp64(*grid) ? 1 : 0;
     // up to four steps a wave; two steps of 32 at a time are taken on longer rows only
     if (!MEAN && SF == 1 && steps <= 4 * (int64_t)*grid)
-        gram_partial_kernel<NT, NG, 1, LINES, SF == 1, false><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
+        gram_partial_kernel<NT, NG, 1, LINES, SF == 1 ? Gram::kShort : Gram::kLong><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
             rows_base, d, ld, row_index_dev, f, partial, in_fp64, 0, pass.guess);
     else
-        gram_partial_kernel<NT, NG, SF, LINES, false, MEAN><<<*grid, 64 * kWaves, 0, s>>>(
+        gram_partial_kernel<NT, NG, SF, LINES, MEAN ? Gram::kMean : Gram::kLong><<<*grid, 64 * kWaves, 0, s>>>(
             rows_base, d, ld, row_index_dev, f, partial, in_fp64, 0, pass.guess);
 }
 
 template <int NT, int NG, bool LINES>
 void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev,
                       int f, float *partial, int *grid, GramPass pass, hipStream_t s) {
-    if (pass.sample) {
-        *grid = kGramBlocks / 2;
-        gram_partial_kernel<NT, NG, 1, LINES, true, false><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
-            rows_base, d, ld, row_index_dev, f, partial, 0, d / kSampleSpans / kStep * kStep, pass.guess);
-        return;
-    }
     // Long rows: two steps at a time up to 32 vectors (four steps per wave or fewer: one at a time
     // spreads them over more waves and partial sums).  Above, more registers and fewer waves cost more
     // than longer pieces of a row give, but for rows off the cache lines that are far larger than the
@@ -912,6 +912,12 @@ void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32
     const int64_t one_at_a_time = (int64_t)1 << (NT <= 1 ? 20 : (NT <= 2 ? 19 : 22));
     const bool two_steps = SF > 1 && d > one_at_a_time;  // whatever the pass is for: the order of the additions
     if constexpr (16 * NT + 4 * NG <= kMaxGuess) {
+        if (pass.sample) {
+            *grid = kGramBlocks / 2;
+            gram_partial_kernel<NT, NG, 1, LINES, Gram::kSample><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
+                rows_base, d, ld, row_index_dev, f, partial, 0, d / kSampleSpans / kStep * kStep, pass.guess);
+            return;
+        }
         if (pass.guess.out != nullptr) {
             if constexpr (NT <= 2)  // such rows are long enough for two steps at a time (guess_pays)
                 launch_gram_spans<NT, NG, SF, LINES, true>(rows_base, d, ld, row_index_dev, f, partial, grid, pass, s);
