@@ -136,13 +136,12 @@ __device__ __forceinline__ int64_t sample_start(int64_t at, int64_t pitch) {
     return at * pitch + (int64_t)(((uint64_t)hash * (uint64_t)(pitch / kStep)) >> 32) * kStep;
 }
 
-// Multi-Krum's choice, thread i = vector i (the first kMaxKrum threads of a block): the m lowest
+// Multi-Krum's choice, thread i = vector i with the score `mine` (the first kMaxKrum threads of a block): the m lowest
 // scores, the lower index first among equal scores.  Returns i's place in that order, chosen if below m;
 // *before = chosen vectors with a lower index, *total = how many there are.  All threads of the block call it.
-__device__ __forceinline__ int choose_vector(const double *__restrict__ scores, int f, int m, double *s_score,
-                                              uint64_t *s_chosen, int *before, int *total) {
+__device__ __forceinline__ int choose_vector(double mine, int f, int m, double *s_score, uint64_t *s_chosen, int *before,
+                                             int *total) {
     const int i = threadIdx.x;
-    const double mine = i < f ? scores[i] : 0.0;
     if (i < kMaxKrum) s_score[i] = mine;
     __syncthreads();
     int rank = 0;
@@ -179,7 +178,7 @@ __device__ __forceinline__ uint64_t guess_vectors(const double *__restrict__ sco
     const int i = threadIdx.x;
     if (i < 2) s_edge[i] = 0.0;
     int before, total;
-    const int rank = choose_vector(scores, f, m, s_room, s_chosen, &before, &total);
+    const int rank = choose_vector(i < f ? scores[i] : 0.0, f, m, s_room, s_chosen, &before, &total);
     if (i < f && (rank == m - 1 || rank == m)) s_edge[rank - (m - 1)] = s_room[i];
     if (i < kMaxGuess) {
         bool overlap = false;
@@ -768,11 +767,25 @@ __global__ __launch_bounds__(kSelectThreads) void bulyan_select_kernel(
     if (i == 0) *n_selected = theta;
 }
 
+// Whether the m guessed vectors are Multi-Krum's choice, found by every wave for itself (lane = vector) from the upper
+// words of the scores; where those tie or are NaN the answer is no.
+__device__ __forceinline__ bool guess_holds(uint64_t guess, double score, int f, int m) {
+    if (__builtin_popcountll(guess) != m) return false;
+    const int i = threadIdx.x & 63;
+    if (__builtin_amdgcn_ballot_w64(i < f && !(score >= 0.0)) != 0) return false;
+    const uint32_t word = (uint32_t)__double2hiint(score);
+    const bool in = ((guess >> i) & 1ull) != 0;
+    return ~wave_min(in ? ~word : ~0u) < wave_min(in || i >= f ? ~0u : word);
+}
+
 // Choice and mean: every block chooses for itself (block 0 writes the choice; a kernel of its own for the choice
 // took 5 us more: f = 25, 1 M 47.1 -> 45.7), then out[c] = mean of the chosen
 // rows: fp32, added one by one in ascending file index starting from +0, one IEEE division by the count.  Thread t
-// of the grid owns the words from min(4t, d-4) (d >= 4).  With a guess whose mean the Gram pass has written the
-// blocks return when it was right.
+// of the grid owns the words from min(4t, d-4) (d >= 4).  With a guess (f <= kMaxGuess) whose mean the Gram pass has
+// written the blocks return when it was right.  A block per 4 * kBlock words: 2048
+// blocks with a stride are idle for two thirds of the sixth round of 11.2 M coordinates (1819 with even rounds walk in step
+// and are slower still).  us a call that takes its mean here, with a stride / now: 25 x 11.2 M 357.6 / 350.4, 49 x 11.2 M 709 /
+// 692, 9 x 23 M 282 / 269; where the guess held 238.2 / 240.6 (245 with the full choice in front of the return).
 __global__ __launch_bounds__(kBlock) void chosen_mean_kernel(const float *__restrict__ X, int64_t d, int64_t ld,
                                                              const int32_t *__restrict__ row_index,
                                                              const double *__restrict__ scores, int f, int m,
@@ -782,39 +795,46 @@ __global__ __launch_bounds__(kBlock) void chosen_mean_kernel(const float *__rest
     __shared__ double s_score[kMaxKrum];
     __shared__ uint64_t s_chosen[kMaxKrum / 64];
     __shared__ int32_t s_row[kMaxKrum];
-    const int i = threadIdx.x;
+    const int i = threadIdx.x, own = guess != nullptr ? i & 63 : i;
+    const double mine = own < f ? scores[own] : 0.0;
+    if (guess != nullptr) {
+        const uint64_t guessed = *guess;
+        if (guess_holds(guessed, mine, f, m)) {
+            if (blockIdx.x == 0 && i < f) selected_out[i] = (int32_t)((guessed >> i) & 1ull);
+            return;
+        }
+    }
     int before, n;
-    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &n) < m;
+    const bool chosen = choose_vector(mine, f, m, s_score, s_chosen, &before, &n) < m;
     n = __builtin_amdgcn_readfirstlane(n);
     if (blockIdx.x == 0 && i < f) selected_out[i] = chosen ? 1 : 0;
     if (guess != nullptr) {
-        if (*guess == s_chosen[0]) return;  // at most kMaxGuess vectors
+        if (*guess == s_chosen[0]) return;
     }
     if (chosen) s_row[before] = row_index[i];
     __syncthreads();
+    const int64_t gt = (int64_t)blockIdx.x * kBlock + i;
+    if (gt >= (d + 3) / 4) return;
     const float dn = (float)n;
-    const int64_t n_thr = (d + 3) / 4;
-    for (int64_t gt = (int64_t)blockIdx.x * kBlock + i; gt < n_thr; gt += (int64_t)gridDim.x * kBlock) {
-        const int64_t c0 = (gt + 1) * 4 <= d ? gt * 4 : d - 4;
-        float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-        auto load = [&](int t) {
-            const float *p = X + (int64_t)__builtin_amdgcn_readfirstlane(s_row[t]) * ld + c0;
-            return __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(p));
-        };
-        auto add = [&](const f32x4u &v) { a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3]; };
-        int t = 0;
-        for (; t + 4 <= n; t += 4) {
-            f32x4u v[4];
+    const int64_t c0 = (gt + 1) * 4 <= d ? gt * 4 : d - 4;
+    float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
+    auto load = [&](int t) {
+        const float *p = X + (int64_t)__builtin_amdgcn_readfirstlane(s_row[t]) * ld + c0;
+        return __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(p));
+    };
+    auto add = [&](const f32x4u &v) { a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3]; };
+    int t = 0;
+    for (; t + 4 <= n; t += 4) {
+        f32x4u v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = load(t + u);
+        for (int u = 0; u < 4; ++u) v[u] = load(t + u);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) add(v[u]);
-        }
-        for (; t < n; ++t) add(load(t));
-        f32x4u o;
-        o[0] = a0 / dn; o[1] = a1 / dn; o[2] = a2 / dn; o[3] = a3 / dn;
-        __builtin_nontemporal_store(o, reinterpret_cast<f32x4u *>(out + c0));
+        for (int u = 0; u < 4; ++u) add(v[u]);
     }
+    for (; t < n; ++t) add(load(t));
+    f32x4u o;
+    o[0] = a0 / dn; o[1] = a1 / dn; o[2] = a2 / dn; o[3] = a3 / dn;
+    __builtin_nontemporal_store(o, reinterpret_cast<f32x4u *>(out + c0));
 }
 
 // Both on short rows, where a launch and the chain of loads count and not HBM: every block chooses for itself
@@ -831,7 +851,7 @@ __global__ __launch_bounds__(kBlock) void choose_and_mean_kernel(const float *__
     __shared__ int64_t s_first[kMaxKrum];  // first words of the chosen rows
     const int i = threadIdx.x;
     int before, n;
-    const bool chosen = choose_vector(scores, f, m, s_score, s_chosen, &before, &n) < m;
+    const bool chosen = choose_vector(i < f ? scores[i] : 0.0, f, m, s_score, s_chosen, &before, &n) < m;
     if (blockIdx.x == 0 && i < f) selected_out[i] = chosen ? 1 : 0;
     if (chosen) s_first[before] = (int64_t)row_index[i] * ld;
     __syncthreads();
@@ -1010,8 +1030,6 @@ constexpr int64_t short_mean(int f, bool lines) {
     return f <= 25 ? 3 << 17 : (f <= 40 ? 5 << 16 : 1 << 18);
 }
 
-constexpr int64_t kMeanBlocks = 2048;  // of chosen_mean_kernel: all resident
-
 // Where the mean is taken on the way: m rows fewer to read against the sample with its reduction and scores (20 us up
 // to 32 vectors, 25 above), the additions (about what a quarter of the rows takes to read: vector and matrix
 // instructions share one datapath) and the output written meanwhile.  More than 64 vectors leave no registers.  us a
@@ -1057,8 +1075,7 @@ extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
         choose_and_mean_kernel<<<(unsigned)blocks, kBlock, 0, s>>>(
             rows_base, d, ld, row_index_dev, ws->scores, f, m, selected_out, out);
     } else {
-        const int64_t blocks = ((d + 3) / 4 + kBlock - 1) / kBlock;
-        chosen_mean_kernel<<<(unsigned)(blocks < kMeanBlocks ? blocks : kMeanBlocks), kBlock, 0, s>>>(
+        chosen_mean_kernel<<<(unsigned)(((d + 3) / 4 + kBlock - 1) / kBlock), kBlock, 0, s>>>(
             rows_base, d, ld, row_index_dev, ws->scores, f, m, guess ? &ws->guess : nullptr, selected_out, out);
     }
     BYZ_HIP(hipGetLastError());
