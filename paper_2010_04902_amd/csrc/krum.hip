@@ -128,9 +128,11 @@ __device__ __forceinline__ void group_products(const f32x4 (&y)[kParts > 0 ? kPa
 
 // Sample for a guess at Multi-Krum's choice among up to kMaxGuess vectors: stretches of 32 coordinates, one at a
 // random place of every 1/kSampleSpans of the row (pitch: a whole number of stretches, so that rows on cache lines
-// are sampled in whole lines).
+// are sampled in whole lines).  The even blocks' partial matrices are one half of the sample, the odd blocks' the other:
+// what the scores on the halves differ by tells how far the scores on the sample may be off.
 constexpr int kMaxGuess = 64;
 constexpr int kSampleSpans = 4096;
+constexpr int kSampleBlocks = 256, kSampleWaves = 8;  // two stretches a wave: 5 to 8 us, 64 blocks with eight a wave 8 to 17
 __device__ __forceinline__ int64_t sample_start(int64_t at, int64_t pitch) {
     const uint32_t hash = (uint32_t)at * 2654435761u;
     return at * pitch + (int64_t)(((uint64_t)hash * (uint64_t)(pitch / kStep)) >> 32) * kStep;
@@ -165,34 +167,63 @@ __device__ __forceinline__ int choose_vector(double mine, int f, int m, double *
     return rank;
 }
 
+// Scores on the sample: of vector i on all of it, and the first half's less the second's.
+struct SampleScores {
+    double score[kMaxGuess], apart[kMaxGuess];
+};
+
 // The guess, by every block of the Gram pass for itself from the scores on the sample; all its threads call it.
-// None where it is likely to be wrong (the last chosen score and the next one closer than kMargin: on 131072 Gaussian
-// coordinates scores are off by about 0.3 %), nor where the output overlaps a row, which the guessed mean would
-// overwrite before the row's last reader.
-constexpr double kMargin = 0.002;
-__device__ __forceinline__ uint64_t guess_vectors(const double *__restrict__ scores, int f, int m, const float *rows_base,
-                                                  int64_t d, int64_t ld, const int32_t *__restrict__ row_index,
-                                                  const float *out, double *s_room) {
-    double *s_edge = s_room + kMaxKrum;
-    uint64_t *s_chosen = reinterpret_cast<uint64_t *>(s_edge + 2), *s_overlap = s_chosen + kMaxKrum / 64;
+// None where it may be wrong: where the last vector chosen and the first one not are closer than kSure standard deviations
+// of such a distance, taken from what neighbours in the order of the scores, up to kNeighbours on each side of that place,
+// differ by between the halves (relative to their scores: what makes all scores larger or smaller alike does not
+// count).  Right / none / wrong of 40 calls each on 2 M coordinates, a tenth of the vectors reversed, each vector with a
+// scale of its own, by this rule and by a fixed margin of 0.2 % of the score: f = 25 m = 20 37 / 3 / 0 and 37 / 2 / 1, with a
+// log-normal scale (sigma 1) per coordinate besides 23 / 16 / 1 and 28 / 1 / 11, per sixtieth of the row 28 / 10 / 2 and 36 / 1 /
+// 3, sigma 2 per coordinate 0 / 39 / 1 and 1 / 2 / 37; f = 49 m = 40 36 / 4 / 0, 10 / 29 / 1, 22 / 17 / 1, 0 / 40 / 0 and 37 / 3 / 0, 17 / 5 / 18,
+// 32 / 2 / 6, 1 / 2 / 37.  Two deviations halve the right ones of the last three and save no more than one wrong one.
+// Nor where the output overlaps a row, which the guessed mean would overwrite before the row's last reader.
+// (The sample's places are the same in every call on rows of a length, so a sender who knows them can look different
+// there: that makes the guess wrong and the call slower, figures at guess_pays; the words are the same.)
+constexpr double kSure = 1.0;
+constexpr int kNeighbours = 8;
+__device__ __forceinline__ uint64_t guess_vectors(const SampleScores *__restrict__ sample, int f, int m,
+                                                  const float *rows_base, int64_t d, int64_t ld,
+                                                  const int32_t *__restrict__ row_index, const float *out, double *s_room) {
+    double *s_order = s_room + kMaxKrum, *s_off = s_order + kMaxGuess;  // by place: scores, relative differences
+    uint64_t *s_chosen = reinterpret_cast<uint64_t *>(s_off + kMaxGuess), *s_guess = s_chosen + kMaxKrum / 64;
     const int i = threadIdx.x;
-    if (i < 2) s_edge[i] = 0.0;
+    if (i < kMaxGuess) s_order[i] = s_off[i] = 0.0;
+    const double mine = i < f ? sample->score[i] : 0.0, apart = i < f ? sample->apart[i] : 0.0;
+    bool overlap = false;
+    if (i < f) {
+        const uintptr_t row = (uintptr_t)(rows_base + (int64_t)row_index[i] * ld), o = (uintptr_t)out;
+        const uintptr_t bytes = (uintptr_t)d * sizeof(float);
+        overlap = o < row + bytes && row < o + bytes;
+    }
     int before, total;
-    const int rank = choose_vector(i < f ? scores[i] : 0.0, f, m, s_room, s_chosen, &before, &total);
-    if (i < f && (rank == m - 1 || rank == m)) s_edge[rank - (m - 1)] = s_room[i];
-    if (i < kMaxGuess) {
-        bool overlap = false;
-        if (i < f) {
-            const uintptr_t row = (uintptr_t)(rows_base + (int64_t)row_index[i] * ld), o = (uintptr_t)out;
-            const uintptr_t bytes = (uintptr_t)d * sizeof(float);
-            overlap = o < row + bytes && row < o + bytes;
-        }
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(overlap);
-        if (i == 0) *s_overlap = mask;
+    const int rank = choose_vector(mine, f, m, s_room, s_chosen, &before, &total);
+    if (i < f) {
+        s_order[rank] = mine;
+        s_off[rank] = apart / mine;
     }
     __syncthreads();
-    const bool clear = m == f || s_edge[1] - s_edge[0] > kMargin * s_edge[0];
-    const uint64_t chosen = clear && *s_overlap == 0 ? s_chosen[0] : 0ull;
+    if (i < 64) {
+        const int place = m - kNeighbours + i;  // between the vectors of places place - 1 and place
+        const bool used = i < 2 * kNeighbours && place >= 1 && place < f;
+        const double off = used ? s_off[place] - s_off[place - 1] : 0.0;
+        double square = off * off;
+#pragma unroll
+        for (int k = 1; k < 2 * kNeighbours; k <<= 1) square += __shfl_xor(square, k, 64);
+        const int count = __builtin_popcountll(__builtin_amdgcn_ballot_w64(used));
+        const bool clash = __builtin_amdgcn_ballot_w64(overlap) != 0;
+        if (i == 0) {
+            const double last = s_order[m - 1], gap = m < f ? s_order[m] - last : 0.0;
+            const bool sure = m == f || gap * gap * count > kSure * kSure * square * last * last;
+            *s_guess = sure && !clash ? s_chosen[0] : 0ull;
+        }
+    }
+    __syncthreads();
+    const uint64_t chosen = *s_guess;
     __syncthreads();  // the room is used for other things
     return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(chosen >> 32)) << 32 |
            (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen);
@@ -201,7 +232,7 @@ __device__ __forceinline__ uint64_t guess_vectors(const double *__restrict__ sco
 // What a Gram pass that takes a mean on the way is given: scores on the sample, how many vectors to choose, where the
 // mean goes and where the guess is left for chosen_mean_kernel.
 struct GuessedPass {
-    const double *scores;
+    const SampleScores *scores;
     int m;
     float *out;
     uint64_t *chosen;
@@ -245,6 +276,7 @@ struct GuessedMean {
 // sample as a run-time case of the short rows' kernel cost that one up to 16 registers: us a call, with / without, 40 x 250000
 // 31.0 / 30.2, 49 x 100000 27.0 / 26.6, 97 x 250000 83.8 / 82.8.)
 enum class Gram { kLong, kShort, kSample, kMean };
+constexpr int gram_waves(int nt, int sf, Gram kind) { return kind == Gram::kSample ? kSampleWaves : gram_waves(nt, sf); }
 
 // Accumulates the Gram tiles of all f rows over this wave's coordinates, NT = row tiles of 16, NG =
 // groups of four rows behind them (row_groups).
@@ -279,7 +311,7 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
     constexpr int kParts = NG == 0 ? 0 : (NALL - NP) / NG;  // stretches of 64 rows a group meets
     const int lane = threadIdx.x & 63;
     const int64_t n_spans = KIND == Gram::kSample ? kSampleSpans : (d + kSpan - 1) / kSpan;
-    constexpr int kWaves = gram_waves(NT, SF);
+    constexpr int kWaves = gram_waves(NT, SF, KIND);
     const int64_t stride = (int64_t)gridDim.x * kWaves;
     constexpr unsigned kGroup = NT <= 1 ? 1 : (NT == 2 ? 4 : 8);
     const unsigned block = LINES ? blockIdx.x : neighbours_together(blockIdx.x, gridDim.x, kGroup);
@@ -418,14 +450,14 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
 // [gridDim.x][tiles][256] values, position v*64 + lane, tiles = stored_tiles(NT, NG), fp32 or, where a few
 // blocks would leave their last roundings visible, fp64 (d = 2048: 8.9e-9 -> 4.9e-9 at f = 100).
 template <int NT, int NG, int SF, bool LINES, Gram KIND>
-__global__ __launch_bounds__(64 * gram_waves(NT, SF))
+__global__ __launch_bounds__(64 * gram_waves(NT, SF, KIND))
 // (2: accumulators in ordinary registers; more row tiles would spill: 96 x 11.2 M 1502 us, 1362 with 1,
 // 80 x 11.2 M 998 and 1060; the same with groups, (5, 1) on long rows 41 registers)
 __attribute__((amdgpu_waves_per_eu(NG > 0 ? (NT <= 4 || (NT == 5 && KIND == Gram::kShort) ? 2 : 1) : (NT <= 5 || (NT == 6 && KIND == Gram::kShort) ? 2 : 1))))
 void gram_partial_kernel(
     const float *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ row_index, int f,
     float *__restrict__ partial, int in_fp64, int64_t pitch, GuessedPass guess) {
-    constexpr int NP = stored_tiles(NT, NG), kWaves = gram_waves(NT, SF);
+    constexpr int NP = stored_tiles(NT, NG), kWaves = gram_waves(NT, SF, KIND);
     constexpr int kStage = staged_rows(NT, NG, SF) * kStep * SF;  // floats of one wave's stage
     constexpr int kRoom = 16 * 1024 / (kWaves * kTile);  // tiles of every wave that 64 KB hold
     constexpr int kAtOnce = NP < kRoom ? NP : kRoom;
@@ -468,8 +500,9 @@ void gram_partial_kernel(
 
 // gram[t][pos] = sum over blocks of partial[block][t][pos] in fp64, in a fixed order: thread
 // (pos, g) adds the blocks g, g+8, g+16, ... one by one, then the eight group sums are added
-// in order.  Block = 32 positions x 8 groups.
-template <typename T>
+// in order.  Block = 32 positions x 8 groups.  HALVES: the even blocks' sums, and the odd blocks' behind the
+// matrix.
+template <typename T, bool HALVES>
 __global__ __launch_bounds__(kBlock) void gram_reduce_kernel(const T *__restrict__ partial,
                                                              int n_partial, int ntiles,
                                                              double *__restrict__ gram) {
@@ -481,10 +514,10 @@ __global__ __launch_bounds__(kBlock) void gram_reduce_kernel(const T *__restrict
     for (int p = g; p < n_partial; p += 8) acc += (double)partial[(int64_t)p * ntiles * kTile + i];
     s_sum[g][lp] = acc;
     __syncthreads();
-    if (g == 0) {
-        double total = s_sum[0][lp];
-        for (int k = 1; k < 8; ++k) total += s_sum[k][lp];
-        gram[i] = total;
+    if (HALVES ? g < 2 : g == 0) {
+        double total = s_sum[g][lp];
+        for (int k = HALVES ? g + 2 : 1; k < 8; k += HALVES ? 2 : 1) total += s_sum[k][lp];
+        gram[(HALVES ? g * ntiles * kTile : 0) + i] = total;
     }
 }
 
@@ -601,6 +634,36 @@ __global__ __launch_bounds__(kBlock) void distance_rows_kernel(const double *__r
             scores[i] = score;
             if (scores_out != nullptr) scores_out[i] = score;
         }
+    }
+}
+
+// Scores of the f <= kMaxGuess vectors on the sample, a wave per vector, lane = the other one: the n_terms smallest
+// distances on the whole sample, and the same ones on either half.  The n_terms-th smallest is found bit by bit; as many of
+// several equal to it count as are missing.
+__global__ __launch_bounds__(64) void sample_scores_kernel(const double *__restrict__ halves, int f, int n_terms,
+                                                           SampleScores *__restrict__ sample) {
+    const int i = blockIdx.x, lane = threadIdx.x, j = lane < f ? lane : i;
+    auto apart = [&](const double *g) {
+        return fmax(gram_at(g, f, i, i) + gram_at(g, f, j, j) - 2.0 * gram_at(g, f, i, j), 0.0);
+    };
+    const double a = apart(halves), b = apart(halves + stored_tiles(f) * kTile);
+    const uint32_t key = j != i ? __float_as_uint((float)(a + b)) : ~0u;
+    uint32_t nth = 0;
+#pragma unroll
+    for (int bit = 31; bit >= 0; --bit)
+        if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(key < (nth | 1u << bit))) < n_terms) nth |= 1u << bit;
+    const int below = __builtin_popcountll(__builtin_amdgcn_ballot_w64(key < nth));
+    const int equal = __builtin_popcountll(__builtin_amdgcn_ballot_w64(key == nth));
+    const double weight = key < nth ? 1.0 : (key == nth ? (double)(n_terms - below) / (double)equal : 0.0);
+    double sum_a = weight != 0.0 ? weight * a : 0.0, sum_b = weight != 0.0 ? weight * b : 0.0;
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+        sum_a += __shfl_xor(sum_a, k, 64);
+        sum_b += __shfl_xor(sum_b, k, 64);
+    }
+    if (lane == 0) {
+        sample->score[i] = sum_a + sum_b;
+        sample->apart[i] = sum_a - sum_b;
     }
 }
 
@@ -871,7 +934,10 @@ __global__ __launch_bounds__(kBlock) void choose_and_mean_kernel(const float *__
 struct KrumWorkspace {
     double gram[kMaxPairs * kTile];
     double sorted_dist[kMaxKrum * kRowStride];  // [t*kRowStride + i]: i's t-th smallest distance
-    double scores[kMaxKrum];
+    union {
+        double scores[kMaxKrum];
+        SampleScores sample;
+    };
     uint8_t sorted_nbr[kMaxKrum * kRowStride];  // and the vector it leads to
     int32_t selected_list[kMaxKrum];
     int32_t selected_rows[kMaxKrum];  // Bulyan: rows of the chosen vectors, spare entries valid
@@ -881,6 +947,7 @@ struct KrumWorkspace {
     float partial[1];  // [kGramBlocks][tiles of f][256], sized by krum_workspace_bytes
 };
 static_assert(offsetof(KrumWorkspace, partial) % sizeof(double) == 0, "partial tiles may be fp64");
+static_assert(2 * stored_tiles(kMaxGuess) <= kMaxPairs && kSampleBlocks % 8 == 0, "room for both halves' matrices");
 
 // Blocks up to which partial tiles are fp64: a quarter of the grid they have room for in fp32.
 inline bool partials_in_fp64(int grid) { return grid <= kGramBlocks / 4; }
@@ -933,8 +1000,8 @@ void launch_gram_rows(const float *rows_base, int64_t d, int64_t ld, const int32
     const bool two_steps = SF > 1 && d > one_at_a_time;  // whatever the pass is for: the order of the additions
     if constexpr (16 * NT + 4 * NG <= kMaxGuess) {
         if (pass.sample) {
-            *grid = kGramBlocks / 2;
-            gram_partial_kernel<NT, NG, 1, LINES, Gram::kSample><<<*grid, 64 * gram_waves(NT, 1), 0, s>>>(
+            *grid = kSampleBlocks;
+            gram_partial_kernel<NT, NG, 1, LINES, Gram::kSample><<<kSampleBlocks, 64 * kSampleWaves, 0, s>>>(
                 rows_base, d, ld, row_index_dev, f, partial, 0, d / kSampleSpans / kStep * kStep, pass.guess);
             return;
         }
@@ -969,7 +1036,7 @@ int launch_gram_shape(const float *rows_base, int64_t d, int64_t ld, const int32
     return BYZ_OK;
 }
 
-// Gram matrix of the f rows into ws->gram (partial tiles, then the fp64 reduction).
+// Gram matrix of the f rows into ws->gram (partial tiles, then the fp64 reduction; of a sample its two halves').
 int launch_gram(const float *rows_base, int64_t d, int64_t ld, const int32_t *row_index_dev, int f,
                 KrumWorkspace *ws, GramPass pass, hipStream_t s) {
     int rc, grid = 0;
@@ -988,11 +1055,13 @@ int launch_gram(const float *rows_base, int64_t d, int64_t ld, const int32_t *ro
     }
     if (rc != BYZ_OK) return rc;
     const int ntiles = stored_tiles(f);
-    if (partials_in_fp64(grid))
-        gram_reduce_kernel<<<ntiles * kTile / 32, kBlock, 0, s>>>(
+    if (pass.sample)
+        gram_reduce_kernel<float, true><<<ntiles * kTile / 32, kBlock, 0, s>>>(ws->partial, grid, ntiles, ws->gram);
+    else if (partials_in_fp64(grid))
+        gram_reduce_kernel<double, false><<<ntiles * kTile / 32, kBlock, 0, s>>>(
             reinterpret_cast<const double *>(ws->partial), grid, ntiles, ws->gram);
     else
-        gram_reduce_kernel<<<ntiles * kTile / 32, kBlock, 0, s>>>(ws->partial, grid, ntiles, ws->gram);
+        gram_reduce_kernel<float, false><<<ntiles * kTile / 32, kBlock, 0, s>>>(ws->partial, grid, ntiles, ws->gram);
     BYZ_HIP(hipGetLastError());
     return BYZ_OK;
 }
@@ -1030,16 +1099,16 @@ constexpr int64_t short_mean(int f, bool lines) {
     return f <= 25 ? 3 << 17 : (f <= 40 ? 5 << 16 : 1 << 18);
 }
 
-// Where the mean is taken on the way: m rows fewer to read against the sample with its reduction and scores (20 us up
-// to 32 vectors, 25 above), the additions (about what a quarter of the rows takes to read: vector and matrix
-// instructions share one datapath) and the output written meanwhile.  More than 64 vectors leave no registers.  us a
-// call, in two passes / with a guess: f = 25 m = 20 11.2 M 334 / 254, off the lines 353 / 268, 5.6 M 179 / 140, 4 M 131 / 110, 2.9 M
-// 99 / 105; f = 9 m = 7 23 M 270 / 201; f = 16 m = 14 8.5 M 181 / 141; f = 49 m = 40 11.2 M 711 / 559, 2.6 M 180 / 155, m = 25 6.2 M
-// 348 / 322; f = 64 m = 54 5 M 428 / 338, m = 32 366 / 340.  Scores too close to guess from (rows of one
-// distribution): f = 25 11.2 M 339 / 361, 5.6 M 180 / 197; f = 49 11.2 M 711 / 740; f = 60 m = 50 2.1 M 182 / 207, which is why
-// the line lies higher for more vectors.
+// Where the mean is taken on the way: m rows fewer to read against the sample with its reduction and scores (16 us up
+// to 32 vectors, 20 above), the additions (about what a quarter of the rows takes to read: vector and matrix
+// instructions share one datapath) and the output written meanwhile.  More than 64 vectors leave no registers.  Where no
+// guess is made, as on rows of one distribution, the sample is lost, so the two passes have to be 1.4 GB or more.
+// us a call, in two passes / right / none / wrong: f = 25 m = 20 11.2 M 331 / 238 / 347 / 387, off the lines 354 / 257 / 367,
+// 7.9 M 241 / 176 / 255 / 283 (the line; 5.6 M 175 / 131 / 188 / 207); f = 9 m = 7 23 M 267 / 192 / 266 / 304; f = 16 m = 14 11.8 M 242 / 166 /
+// 254 / 280; f = 33 m = 28 5.8 M 244 / 176 / 259 / 278; f = 49 m = 40 11.2 M 698 / 520 / 702 / 797, 4 M 260 / 205 / 274 / 310; f = 64
+// m = 54 3 M 259 / 204 / 277 / 308.
 constexpr bool guess_pays(int f, int m, int64_t d) {
-    return f <= kMaxGuess && d >= (int64_t)1 << 20 &&
+    return f <= kMaxGuess && (int64_t)(f + m) * d >= 350000000 &&
            (int64_t)(m - 2 - f / 4) * d >= (f <= 32 ? (int64_t)1 << 26 : (int64_t)3 << 25);
 }
 
@@ -1062,11 +1131,11 @@ extern "C" int byz_multi_krum(const float *rows_base, int64_t d, int64_t ld,
     if (guess) {
         rc = launch_gram(rows_base, d, ld, row_index_dev, f, ws, kSampleMatrix, s);
         if (rc != BYZ_OK) return rc;
-        rc = launch_distance_rows(f, f - c - 2, nullptr, nullptr, ws, s);
-        if (rc != BYZ_OK) return rc;
+        sample_scores_kernel<<<f, 64, 0, s>>>(ws->gram, f, f - c - 2, &ws->sample);
+        BYZ_HIP(hipGetLastError());
     }
     rc = launch_gram(rows_base, d, ld, row_index_dev, f, ws,
-                     guess ? GramPass{false, {ws->scores, m, out, &ws->guess}} : kWholeMatrix, s);
+                     guess ? GramPass{false, {&ws->sample, m, out, &ws->guess}} : kWholeMatrix, s);
     if (rc != BYZ_OK) return rc;
     rc = launch_distance_rows(f, f - c - 2, dist_out, scores_out, ws, s);
     if (rc != BYZ_OK) return rc;

@@ -2004,6 +2004,79 @@ def test_multi_krum_distances_do_not_depend_on_how_many_are_chosen(f, d, ld):
     assert torch.equal(scores.view(torch.int64), scores_m.view(torch.int64))
 
 
+def _guess_of(workspace, f):
+    """The vectors whose mean Multi-Krum's pass over all rows has taken, one bit each: the word before the partial sums."""
+    nt = (f + 15) // 16
+    at = B.byz_multi_krum_workspace_bytes(f) - 4 * 512 * (nt * (nt + 1) // 2) * 256 - 8
+    return int(workspace[at:at + 8].cpu().numpy().view(np.uint64)[0])
+
+
+@pytest.mark.parametrize("f, c, m, off", [(9, 2, 7, 3), (16, 2, 14, 0), (25, 5, 20, 0), (32, 4, 28, 1), (33, 5, 28, 0),
+                                          (49, 8, 40, 3), (56, 8, 48, 1), (64, 10, 54, 5), (64, 10, 54, 0)])
+def test_multi_krum_guess_is_made_where_it_is_sure(f, c, m, off):
+    # which way a call on long rows goes: the mean taken with the distances (guess right), taken again (wrong), or not
+    # guessed at, and one coordinate below the rule's first length no guess at all; the words are the same, those of
+    # the distances too
+    gen = torch.Generator(device=DEV).manual_seed(f)
+    d = max(-(-350000000 // (f + m)), -(-((1 << 26) if f <= 32 else (3 << 25)) // (m - 2 - f // 4)))
+    X = torch.empty((f, (d + 127) // 64 * 64 + off), device=DEV)
+    idx = torch.arange(f, dtype=torch.int32, device=DEV)
+    ws = torch.empty(B.byz_multi_krum_workspace_bytes(f), dtype=torch.uint8, device=DEV)
+    out = torch.empty(d, device=DEV)
+
+    def call(n):
+        ws.fill_(0xA5)
+        _, sel, scores, dist = B.byz_multi_krum(X, n, idx, c, m, out=out, workspace=ws)
+        chosen = sum(1 << i for i, v in enumerate(sel.cpu().tolist()) if v)
+        guess = _guess_of(ws, f)
+        acc = torch.zeros(n, device=DEV)
+        for i in range(f):
+            if (chosen >> i) & 1:
+                acc += X[i, :n]
+        want = acc / torch.tensor(float(m), device=DEV)
+        assert torch.equal(out[:n].view(torch.int32), want.view(torch.int32)), (f, n)
+        _, _, scores_one, dist_one = B.byz_multi_krum(X, n, idx, c, 1, out=out, workspace=ws)
+        assert torch.equal(scores, scores_one) and torch.equal(dist, dist_one), (f, n)
+        return guess, chosen
+
+    for i in range(f):
+        X[i].normal_(generator=gen).mul_(1.0 + 0.05 * i)
+    guess, chosen = call(d)
+    assert guess == chosen == (1 << m) - 1
+    assert call(d - 1) == (0xA5A5A5A5A5A5A5A5, chosen)
+    X[0, d - 1] = 1e6  # not in the sample
+    guess, chosen = call(d)
+    assert guess == (1 << m) - 1 and chosen == (1 << (m + 1)) - 2
+    X[0].copy_(X[1])  # every vector alike but for their last word
+    for i in range(1, f):
+        X[i].copy_(X[0])
+        X[i, d - 1] = float(i)
+    assert call(d)[0] == 0
+    for i in range(f):  # one distribution, whose scores differ by less than a sample can tell
+        X[i].normal_(generator=gen)
+    assert call(d)[0] == 0
+
+
+def test_multi_krum_guess_knows_uneven_coordinates():
+    # coordinates of very different scale, as the layers of a network have: a few of them make the scores, and a sample tells
+    # little.  A guess by a fixed margin of 0.2 % is made, and wrong, in nine calls of ten.
+    f, c, m, d = 25, 5, 20, 7800000
+    idx = torch.arange(f, dtype=torch.int32, device=DEV)
+    ws = torch.empty(B.byz_multi_krum_workspace_bytes(f), dtype=torch.uint8, device=DEV)
+    X = torch.empty((f, d), device=DEV)
+    wrong = 0
+    for seed in range(8):
+        gen = torch.Generator(device=DEV).manual_seed(seed)
+        scale = torch.rand(f, generator=gen, device=DEV) * 0.2 + 0.9
+        uneven = torch.randn(d, generator=gen, device=DEV).mul_(2.0).exp_()
+        for i in range(f):
+            X[i].normal_(generator=gen).mul_(uneven).mul_(scale[i])
+        _, sel, _, _ = B.byz_multi_krum(X, d, idx, c, m, workspace=ws)
+        chosen = sum(1 << i for i, v in enumerate(sel.cpu().tolist()) if v)
+        wrong += _guess_of(ws, f) not in (0, chosen)
+    assert wrong <= 1  # one in forty is to be expected
+
+
 def test_multi_krum_and_bulyan_for_every_f():
     # every f from 3 to 64 and a spread of the wider ones (all tile counts and staging shapes of
     # the Gram kernel, one and two distances per lane in the row sort, Bulyan's rounds in
