@@ -1695,12 +1695,11 @@ __global__ __launch_bounds__(BLOCK) void short_pass_kernel(
 
 // The decision of single_pass_decide_kernel on a call that read every copy, in every block: findings_of(j) = the bits
 // of file j, complete behind a barrier.  Then, where it asks for it, the median or trimmed mean of the winners' rows
-// again by the threads gt, gt + stride, ...  Block 0 writes what the caller gets.
+// again by thread gt.  Block 0 writes what the caller gets.
 template <int F, int R, bool TRIM, int V, typename Findings>
 __device__ __forceinline__ void decide_and_redo(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows, AggWorkspace *ws,
-    int64_t gt, int64_t stride, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out,
-    Findings findings_of) {
+    int64_t gt, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out, Findings findings_of) {
     __shared__ uint32_t s_redo;
     __shared__ int32_t s_row[F];
     if (threadIdx.x == 0) s_redo = 0;
@@ -1720,8 +1719,7 @@ __device__ __forceinline__ void decide_and_redo(
     if (blockIdx.x == 0 && threadIdx.x == 0)
         ws->path = redo ? (uint32_t)BYZ_PATH_MEDIAN_REDONE : (uint32_t)BYZ_PATH_SINGLE_PASS;
     if (!redo) return;
-    for (const int64_t n_thr = (d + V - 1) / V; gt < n_thr; gt += stride) {
-    asm volatile("" ::: "memory");  // or the rows are read once for all rounds, into more registers than there are
+    if (gt >= (d + V - 1) / V) return;
     const int64_t c0 = gt * V + V <= d ? gt * V : d - V;
     constexpr int NS = 1, kAhead = V == 1 ? 20 : prefetch_depth(F, NS);
     uint32_t key[V][F];
@@ -1755,7 +1753,6 @@ __device__ __forceinline__ void decide_and_redo(
     }
 #undef BYZ_S_ROW_ADDR
     store_vec<V>(out + c0, o);
-    }
 }
 
 // The bits of file j in a block's slot.
@@ -1765,12 +1762,9 @@ __device__ __forceinline__ uint32_t slot_findings(const uint32_t *s_bits, int j)
     return s_bits[j * kBits / 32] >> (j * kBits % 32);
 }
 
-// Second kernel, and the last of a long call that reads every copy (n_slots 0: the findings are in ws->pneq).  There a
-// decision in one block and a gated median in a block per tile behind it were two launches and up to 25000 blocks that
-// return at once: us a call, those two / this, (25,3) 11.2 M 524 / 518, (49,3) 25.6 M 2322 / 2308, (25,5) trimmed mean 2 M
-// 165.7 / 163.2, (81,3) 1 M 157.9 / 155.7, (63,7) 200000 66.1 / 61.7, (9,3) 1 M 25.4 / 23.3, (15,3) 500000 21.2 / 19.1; where the
-// output is redone (35,5) 600000 112 / 107, (25,5) trimmed mean 2 M 204 / 202, (65,5) 1 M 271 / 274.
-template <int F, int R, bool TRIM, int V>
+// Second kernel, and the last one of a call that reads every copy and has no slots (SLOTS false: the findings are in
+// ws->pneq; decides_in_median).
+template <int F, int R, bool TRIM, int V, bool SLOTS>
 __global__ __launch_bounds__(kBlock) void decide_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
     AggWorkspace *ws, int n_slots, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out) {
@@ -1778,7 +1772,7 @@ __global__ __launch_bounds__(kBlock) void decide_kernel(
     static_assert(R * (R - 1) / 2 + R <= kBits && kPieces <= kBlock && F <= kBlock, "a file's bits, a thread a piece and a file");
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     __shared__ uint32_t s_bits[kWords];
-    if (n_slots > 0) {
+    if constexpr (SLOTS) {
         for (int t = threadIdx.x; t < kWords; t += kBlock) s_bits[t] = 0;
         const u32x4 *pieces = reinterpret_cast<const u32x4 *>(ws->perm_off);
         constexpr int kStride = kBlock / kPieces * kPieces;  // a thread's pieces are the same files' every time
@@ -1792,9 +1786,11 @@ __global__ __launch_bounds__(kBlock) void decide_kernel(
         for (int e = 0; e < 4; ++e)
             if (mine[e] != 0) atomicOr(&s_bits[(int)threadIdx.x % kPieces * 4 + e], mine[e]);
     }
-    decide_and_redo<F, R, TRIM, V>(
-        X, d, ld, file_rows, ws, (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock, trim_b,
-        winner_replica, out, [&](int j) { return n_slots > 0 ? slot_findings<R>(s_bits, j) : load_shared_word(&ws->pneq[j]); });
+    decide_and_redo<F, R, TRIM, V>(X, d, ld, file_rows, ws, (int64_t)blockIdx.x * kBlock + threadIdx.x, trim_b,
+                                   winner_replica, out, [&](int j) {
+                                       if constexpr (SLOTS) return slot_findings<R>(s_bits, j);
+                                       else return load_shared_word(&ws->pneq[j]);
+                                   });
 }
 
 // Both in one, for rows that one block holds, a word per thread (64 threads or more: the loops over s_bits and files).
@@ -1806,7 +1802,7 @@ __global__ __launch_bounds__(kOneBlock) void one_block_kernel(
     static_assert(F <= 64 && slot_words(F, R) <= 64, "a wave covers the files and the words of their bits");
     __shared__ uint32_t s_bits[slot_words(F, R)];
     short_pass_body<F, R, TRIM, 1, kOneBlock>(X, d, ld, file_rows, threadIdx.x, trim_b, out, s_bits);
-    decide_and_redo<F, R, TRIM, 1>(X, d, ld, file_rows, ws, threadIdx.x, d, trim_b, winner_replica, out,
+    decide_and_redo<F, R, TRIM, 1>(X, d, ld, file_rows, ws, threadIdx.x, trim_b, winner_replica, out,
                                    [&](int j) { return slot_findings<R>(s_bits, j); });
 }
 
@@ -1820,7 +1816,7 @@ inline unsigned blocks_for(int64_t n_vec) {
     return (unsigned)(b > 0 ? b : 1);
 }
 
-// Behind the single pass the median or trimmed-mean kernel nearly always returns at once, and its
+// Behind the single pass and its decision the median or trimmed-mean kernel nearly always returns at once, and its
 // cost is that of launching its blocks (1800 a microsecond: 24 us of a 540 us call with one word
 // per thread at d = 11.2 M).  There, on rows longer than this, the networks of up to 49 wires run
 // four words per thread.
@@ -1981,18 +1977,30 @@ int launch_median(const uint32_t *X, int64_t d, int64_t ld, const int32_t *row_i
 
 #endif  // part 5
 
-// Blocks of decide_kernel on long rows: all resident, and few to launch where they nearly always return at once.
-constexpr unsigned kRedoBlocks = 2048;
-
-template <int F, int R, bool TRIM, int V>
+// Redone one word per thread up to kManyBlocks coordinates.
+template <int F, int R, bool TRIM, int V, bool SLOTS>
 void launch_decide(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, AggWorkspace *ws, int n_slots,
-                   unsigned most_blocks, int trim_b, int32_t *winner_replica, uint32_t *out, hipStream_t s) {
-    const bool one_word = V == 1 || d <= kManyBlocks;
-    const unsigned all = blocks_for(one_word ? d : (d + V - 1) / V), grid = all < most_blocks ? all : most_blocks;
-    if (one_word)
-        decide_kernel<F, R, TRIM, 1><<<grid, kBlock, 0, s>>>(X, d, ld, rows, ws, n_slots, trim_b, winner_replica, out);
+                   int trim_b, int32_t *winner_replica, uint32_t *out, hipStream_t s) {
+    if (V == 1 || d <= kManyBlocks)
+        decide_kernel<F, R, TRIM, 1, SLOTS><<<blocks_for(d), kBlock, 0, s>>>(X, d, ld, rows, ws, n_slots, trim_b,
+                                                                             winner_replica, out);
     else
-        decide_kernel<F, R, TRIM, V><<<grid, kBlock, 0, s>>>(X, d, ld, rows, ws, n_slots, trim_b, winner_replica, out);
+        decide_kernel<F, R, TRIM, V, SLOTS><<<blocks_for((d + V - 1) / V), kBlock, 0, s>>>(
+            X, d, ld, rows, ws, n_slots, trim_b, winner_replica, out);
+}
+
+// Calls without slots that decide in the blocks of the median, one launch for two; beyond, their many blocks would each
+// decide for themselves in turn, and a fixed number of blocks that redo the output in rounds is slower at it than a block
+// per tile ((25,3) 11.2 M 722 us a call that redoes its output, 702 in kernels of their own; (49,3) trimmed mean 4 M
+// 576 and 515; 1 to 4 us less for calls that don't).  us a call, kernels of their own / this, in brackets redone: (9,3) 1 M 23.5 / 21.0
+// (32.4 / 30.6), (25,3) 2 M 97.7 / 95.3 (133 / 131), (25,5) 0.6 M 56.0 / 52.7 (90.5 / 88.8), (49,7) 0.2 M 52.1 / 47.0 (65.5 / 59.0), (81,3)
+// 0.5 M 85.0 / 81.4 (113 / 110); (121,3) 150000 57.5 / 54.5 (75.3 / 73.1), (169,3) 101.3 / 99.1 (129.5 / 130.7), but 300000 86.2 / 92.1
+// and (121,3) 0.5 M 127 / 131 (172 / 179).  The trimmed mean of 49 files takes all registers with four words a thread ((49,3)
+// 2 M redone 277 and 313), and decides here with one.
+constexpr int decide_vec(int f, bool trim) { return f == 49 && trim ? 1 : gated_vec(f); }
+constexpr bool decides_in_median(int f, bool trim, int64_t d) {
+    if (decide_vec(f, trim) != gated_vec(f)) return d <= kManyBlocks;
+    return d <= (int64_t)(f <= 81 ? 2048 : 768) * kBlock * gated_vec(f);
 }
 
 // The two kernels of a short call; *done stays false where the blocks have no room for their slots.
@@ -2011,7 +2019,7 @@ int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
     // redone one word per thread up to kManyBlocks coordinates, where the wider form leaves CUs idle (as the gated
     // kernels of long calls).  us a call that redoes its output, four words / one: (49,7) d = 60001 median 50.9 /
     // 46.5, trimmed mean 57.4 / 49.9, (49,5) 100003 38.6 / 34.9 and 44.8 / 38.5, (35,5) 125003 34.6 / 32.8 and 39.4 / 35.7
-    launch_decide<F, R, TRIM, DV>(X, d, ld, rows, ws, (int)blocks, blocks_for(d), trim_b, winner_replica, out, s);
+    launch_decide<F, R, TRIM, DV, true>(X, d, ld, rows, ws, (int)blocks, trim_b, winner_replica, out, s);
     BYZ_HIP(hipGetLastError());
     *done = true;
     return BYZ_OK;
@@ -2032,7 +2040,7 @@ int launch_short_pair(const uint32_t *X, int64_t d, int64_t ld, const int32_t *r
 constexpr int64_t kOneBlockPerCu = 256;
 // Rows that one block holds take one kernel, where its CU can read them in about the time of a second launch: us a call,
 // two kernels / one, among others: (25,3) d = 64 9.1 / 6.3, 512 8.8 / 6.3, 1024 8.7 to 10.0 / 8.5 (alone 21.6 / 22.3), trimmed mean
-// 1003 8.9 / 9.5; (9,3) 1003 8.9 / 6.3; (21,3) trimmed mean 1000 8.9 / 8.3; (25,5) 500 12.6 / 12.5, 1003 12.3 / 17.0.  Up to 25
+// 1003 8.9 / 9.5; (25,3) where the output is redone 500 9.6 / 7.6, 1003 9.8 / 10.6; (9,3) 1003 8.9 / 6.3; (21,3) trimmed mean 1000 8.9 / 8.3; (25,5) 500 12.6 / 12.5, 1003 12.3 / 17.0.  Up to 25
 // files: more, a word per thread, take all registers 16 waves have, and are past the line from 300 coordinates on.
 constexpr int64_t one_block_words(int r, bool trim) { return r == 3 && !trim ? 5 << 14 : 3 << 14; }
 template <int F, int R, bool TRIM>
@@ -2133,12 +2141,13 @@ int launch_fused(const uint32_t *X, int64_t d, int64_t ld, const int32_t *rows, 
         if (rc != BYZ_OK || *done) return rc;
     }
     int rc = launch_long_pass<F, R, WITH_TRIM, WITH_MEDIAN>(X, d, ld, rows, ws, out, probe_opts, trim_b, s);
-    if (rc != BYZ_OK || (probe_opts & 1) != 0) return rc;  // early-majority mode decides in kernels of its own
+    // early-majority mode and longer rows decide in kernels of their own
+    if (rc != BYZ_OK || (probe_opts & 1) != 0 || !decides_in_median(F, trim_b >= 0, d)) return rc;
     if (trim_b < 0) {
-        if constexpr (WITH_MEDIAN)
-            launch_decide<F, R, false, gated_vec(F)>(X, d, ld, rows, ws, 0, kRedoBlocks, 0, winner_replica, out, s);
-    } else if constexpr (WITH_TRIM) {
-        launch_decide<F, R, true, gated_vec(F)>(X, d, ld, rows, ws, 0, kRedoBlocks, trim_b, winner_replica, out, s);
+        if constexpr (WITH_MEDIAN && decides_in_median(F, false, 0))
+            launch_decide<F, R, false, decide_vec(F, false), false>(X, d, ld, rows, ws, 0, 0, winner_replica, out, s);
+    } else if constexpr (WITH_TRIM && decides_in_median(F, true, 0)) {
+        launch_decide<F, R, true, decide_vec(F, true), false>(X, d, ld, rows, ws, 0, trim_b, winner_replica, out, s);
     }
     BYZ_HIP(hipGetLastError());
     *done = true;
@@ -2751,9 +2760,10 @@ static int aggregate_on_workspace(const float *copies, int64_t d, int64_t ld,
     }
 
     // probe -> single pass -> decision (one block) -> median, which returns at once unless the
-    // decision found a file whose slot 0 did not hold its winner.  Early-majority mode adds the
+    // decision found a file of which some wave fed a copy that is not the winner's.  Early-majority mode adds the
     // gated vote kernel and its decision between the two, for the files whose r' copies differ.
-    // Short rows take two kernels instead of all that.
+    // Where the blocks of the median are few they decide for themselves (decides_in_median); short rows
+    // take two kernels instead of all that, rows that one block holds one.
     bool done = false;
     if (f == 169 && trim_b >= 0)
         rc = byz_internal_launch_single_pass_8(f, r, X, d, ld, file_rows_dev, ws, O, probe_opts, trim_b,

@@ -1205,11 +1205,15 @@ def test_aggregation_in_one_block(f, r):
 @pytest.mark.parametrize("f, r, d, trim", [(9, 3, 4 * 2048 * 256 + 3, 0), (25, 3, 4 * 2048 * 256 + 1029, 5),
                                            (25, 5, 4 * 2048 * 256 + 1, 0), (49, 3, 4 * 2048 * 256, 0),
                                            (49, 3, 4 * 2048 * 256 + 5, 8), (81, 3, 2048 * 256 + 1, 0),
-                                           (121, 3, 2048 * 256 + 63, 20), (65, 5, 2048 * 256 - 1, 0)])
+                                           (121, 3, 2048 * 256 + 63, 20), (65, 5, 2048 * 256 - 1, 0),
+                                           (9, 3, 4 * 2048 * 256, 2), (25, 5, 4 * 2048 * 256 - 3, 5),
+                                           (49, 7, 131072, 8), (49, 7, 131073, 8), (121, 3, 768 * 256, 0),
+                                           (121, 3, 768 * 256 + 1, 0), (169, 3, 768 * 256, 20), (169, 3, 768 * 256 + 1, 0)])
 def test_output_redone_in_rounds(f, r, d, trim):
-    # the kernel that decides for a long call redoes the output in rounds of 2048 blocks: one word, one block or nothing
-    # past a round.  In every third file the honest copies win (tie of three, or two alike of five) while the waves
-    # see the false ones alike.
+    # longer calls decide in the blocks that redo the output up to 2048 of them (768 for more than 81 files, 131072
+    # coordinates for the trimmed mean of 49), and in a kernel of their own beyond: one word or one block past the line, or on
+    # it.  In every third file the honest copies win (tie of three, or two alike of five) while the waves see the false
+    # ones alike.
     gen = torch.Generator(device=DEV).manual_seed(f + d)
     X = torch.empty((f * r, d), device=DEV)
     rows = np.arange(f * r, dtype=np.int32).reshape(f, r)
