@@ -405,7 +405,8 @@ def main():
                 "ms": ms_mk, "c": cmax, "m": mk_m, "algorithmic_bytes": kb,
                 "gbps": kb / ms_mk / 1e6, "frac": kb / ms_mk / 1e6 / HBM_PEAK_GBPS,
                 "gram_tflops": 2.0 * asg.f * asg.f * d / ms_mk / 1e9,
-                "note": "Gram (fp32 MFMA) + reduce + select + mean of m rows"},
+                "note": "Gram (fp32 MFMA) + reduce + select + mean of m rows; the bytes are those of two passes, "
+                        "of which a call on long rows takes one where it can guess the choice"},
             "byz_bulyan": None if ms_bu is None else {
                 "ms": ms_bu, "c": bu_c, "theta": asg.f - 2 * bu_c, "beta": asg.f - 4 * bu_c,
                 "algorithmic_bytes": bb, "gbps": bb / ms_bu / 1e6,
