@@ -354,8 +354,10 @@ __device__ __forceinline__ void gram_accumulate(const float *__restrict__ X, int
     // The first stretch of a run in a body of its own, whose first products take an inline zero instead of cleared
     // registers; with the groups' chains between the tiles, us a call: Multi-Krum 49 x 3 M 158 -> 155, 81 x 3 M 342 -> 327,
     // 96 x 2 M 272 -> 262, 101 x 3 M 514 -> 493, 112 x 2 M 339 -> 318, Bulyan 49 x 11.2 M 694 -> 687.  Slower without groups
-    // at 64 and 80 x 3 M (177 / 179, 297 / 307), twice as slow at 128 (spills), the same with the mean.
-    constexpr bool kPeel = SHORT || (NG > 0 && !MEAN) || NT == 6 || NT == 7;
+    // at 64 and 80 x 3 M (177 / 179, 297 / 307), twice as slow at 128 (spills), the same with the mean; and with four tiles and a
+    // group (65 x 11 M off the cache lines 723 / 751) and seven and three (spills: 121 x 11 M 1915 / 2816, 0.3 M 103 / 124).
+    constexpr bool kPeel =
+        SHORT || (NG > 0 ? !MEAN && NT != 4 && !(NT == 7 && NG == 3) : NT == 6 || NT == 7);
     f32x4 run[kRuns], grun[kGroupRuns];
 #pragma unroll
     for (int p = 0; p < NALL; ++p) acc[p] = zero;
