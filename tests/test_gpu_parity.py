@@ -516,20 +516,31 @@ def test_measurement_aids():
 
 
 def test_profiled_kernel_is_named():
-    # the kernel the events stand around: rows that one block holds and the first that it doesn't (by its threads, by
-    # the words in all), short rows, rows without room for slots, early-majority mode, files split over two waves, vote
-    # on its own
+    # the kernel the events stand around: short rows, rows without room for slots, early-majority mode, files
+    # split over two waves, vote on its own
+    for f, r, d, flags, want in ((25, 3, 5000, 0, "short_pass_kernel"), (25, 3, 1100000, 0, "fused_kernel"),
+                                 (25, 3, 5000, B.BYZ_AGG_EARLY_MAJORITY, "fused_kernel"),
+                                 (171, 3, 1 << 18, 0, "fused_halves_kernel"), (171, 3, 5000, 0, "vote_pairs_kernel"),
+                                 (27, 3, 5000, 0, "vote_pairs_kernel")):
+        X = torch.zeros((f * r, d), device=DEV)
+        rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
+        B.byz_profile_enable(1)
+        assert B.byz_profile_kernel() == ""
+        B.byz_aggregate_opts(X, d, rows, f, r, flags)
+        name, ms = B.byz_profile_kernel(), B.byz_profile_collect(1)
+        B.byz_profile_enable(0)
+        assert name == want and len(ms) == 1, (f, r, d, flags, name)
+
+
+def test_profiled_kernel_of_rows_that_one_block_holds():
+    # the longest such row and the first that isn't one, by its threads and by the words in all
     for f, r, d, flags, want in ((25, 3, 1003, 0, "one_block_kernel"), (25, 3, 1024, 0, "one_block_kernel"),
                                  (25, 3, 1025, 0, "short_pass_kernel"), (25, 5, 393, 0, "one_block_kernel"),
                                  (25, 5, 394, 0, "short_pass_kernel"),
                                  (25, 3, 655, B.BYZ_AGG_TRIM(2), "one_block_kernel"),
                                  (25, 3, 656, B.BYZ_AGG_TRIM(2), "short_pass_kernel"),
                                  (25, 3, 1003, B.BYZ_AGG_EARLY_MAJORITY, "fused_kernel"),
-                                 (35, 5, 64, 0, "short_pass_kernel"),
-                                 (25, 3, 5000, 0, "short_pass_kernel"), (25, 3, 1100000, 0, "fused_kernel"),
-                                 (25, 3, 5000, B.BYZ_AGG_EARLY_MAJORITY, "fused_kernel"),
-                                 (171, 3, 1 << 18, 0, "fused_halves_kernel"), (171, 3, 5000, 0, "vote_pairs_kernel"),
-                                 (27, 3, 5000, 0, "vote_pairs_kernel")):
+                                 (35, 5, 64, 0, "short_pass_kernel")):
         X = torch.zeros((f * r, d), device=DEV)
         rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
         B.byz_profile_enable(1)
@@ -1206,10 +1217,30 @@ def test_aggregation_in_one_block(f, r):
                     out_o = B.byz_trimmed_mean(X, d, wrow, trim).cpu().numpy()
                 assert np.array_equal(W.bits(out[:d]), out_o.view(np.uint32)), (trim, d, split)
                 assert bool((out[d:] == 7.0).all()), (trim, d, split)
-                # (the differing words lie in two waves at most; rows of a wave or two may show them all)
-                if not split or d >= 255:
-                    want = B.BYZ_PATH_MEDIAN_REDONE if split else B.BYZ_PATH_SINGLE_PASS
-                    assert B.byz_aggregate_path(ws) == want, (trim, d, split)
+                if not split:
+                    assert B.byz_aggregate_path(ws) == B.BYZ_PATH_SINGLE_PASS, (trim, d)
+
+
+@pytest.mark.parametrize("f, r, trim", [(9, 3, 0), (9, 3, 2), (15, 3, 0), (21, 3, 0), (25, 3, 0), (25, 3, 6), (25, 5, 0),
+                                        (25, 5, 6)])
+def test_output_redone_in_one_block(f, r, trim):
+    # false copies that differ in a word each: the waves without such a word feed one of them, the vote goes to an honest
+    # one, and the path says so (the differing words lie in two waves at most, so rows of four waves and more are redone)
+    gen = torch.Generator(device=DEV).manual_seed(f * r)
+    rows = torch.arange(f * r, dtype=torch.int32, device=DEV)
+    most = min(1024, ((3 if trim or r == 5 else 5) << 14) // (f * r))
+    for d in (255, most - 1, most):
+        X = torch.empty((f, d), device=DEV).normal_(generator=gen).repeat_interleave(r, dim=0)
+        for j in range(0, f, 3):
+            for k in range(r // 2 + 1):
+                X[j * r + r - 1 - k] = -2.0
+                X[j * r + r - 1 - k, (11 * j + k) % d] = float(k)
+        out, wrep, ws = B.byz_aggregate_opts(X, d, rows, f, r, B.BYZ_AGG_TRIM(trim) if trim else 0)
+        assert B.byz_aggregate_path(ws) == B.BYZ_PATH_MEDIAN_REDONE, d
+        assert int(wrep.max()) == 0, d  # a tie of three, or two alike of five
+        won = rows[::r].contiguous()
+        want = B.byz_trimmed_mean(X, d, won, trim) if trim else B.byz_median(X, d, won)
+        assert torch.equal(out.view(torch.int32), want.view(torch.int32)), d
 
 
 @pytest.mark.parametrize("f, r, d, trim", [(9, 3, 4 * 2048 * 256 + 3, 0), (25, 3, 4 * 2048 * 256 + 1029, 5),
