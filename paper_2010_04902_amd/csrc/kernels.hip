@@ -1641,55 +1641,13 @@ constexpr int most_slots(int f, int r) {
     return (int)(sizeof(AggWorkspace::perm_off) / 4) / slot_words(f, r);
 }
 
-// fused_body's walk over every copy, by thread gt of the call; the block's findings are in s_bits[slot_words(F, R)]
-// behind the next barrier.
-template <int F, int R, bool TRIM, int V, int BLOCK>
-__device__ __forceinline__ void short_pass_body(
-    const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows, int64_t gt,
-    int trim_b, uint32_t *__restrict__ out, uint32_t *s_bits) {
-    constexpr int NS = R, kBits = slot_bits(R), kWords = slot_words(F, R);
-    for (int t = threadIdx.x; t < kWords; t += BLOCK) s_bits[t] = 0;
-    const int lane = threadIdx.x & 63;
-    const int64_t n_thr = (d + V - 1) / V;
-    const int64_t c0 = (gt + 1) * V <= d ? gt * V : d - V;  // as in fused_body
-    const uint32_t voff = (uint32_t)(c0 * 4);
-    uint32_t flags[(F + 63) / 64] = {};
-    const char *Xb = reinterpret_cast<const char *>(X);
-    uint32_t key[V][F];
-    constexpr int kAhead = V == 1 ? short_pass_ahead(F, R) : prefetch_depth(F, NS);
-    uint32_t stage[kAhead + 1][NS][V];
-    uint32_t o[V];
-#define BYZ_S_ROW_ADDR(j, k) \
-    (Xb + (uint64_t)(uint32_t)file_rows[(j) * R + (k)] * (uint64_t)ld * 4u + voff)
-    if constexpr (!TRIM) {
-#include "selnet_pin_on.inc"
-#include "generated/selnet_stream_dispatch.inc"
-#include "selnet_pin_off.inc"
-    } else {
-#include "selnet_pin_on.inc"
-#include "generated/selnet_sort_stream_dispatch.inc"
-#include "selnet_pin_off.inc"
-        trimmed_mean_of_sorted<F, V, true>(key, F, trim_b, o);
-    }
-#undef BYZ_S_ROW_ADDR
-    if (gt < n_thr) store_vec<V>(out + c0, o);
-    __syncthreads();  // s_bits is clear
-#pragma unroll
-    for (int w = 0; w < (F + 63) / 64; ++w) {
-        const int bit = (64 * w + lane) * kBits;
-        if (64 * w + lane < F && flags[w] != 0) atomicOr(&s_bits[bit / 32], flags[w] << (bit % 32));
-    }
-}
-
 // First kernel.
 template <int F, int R, bool TRIM, int V, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void short_pass_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
     uint32_t *__restrict__ slots, int trim_b, uint32_t *__restrict__ out) {
-    constexpr int kWords = slot_words(F, R);
-    __shared__ uint32_t s_bits[kWords];
     const int64_t gt = (int64_t)tile_of_block<block_group(V)>(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
-    short_pass_body<F, R, TRIM, V, BLOCK>(X, d, ld, file_rows, gt, trim_b, out, s_bits);
+#include "short_pass.inc"
     __syncthreads();
     for (int t = threadIdx.x; t < kWords; t += BLOCK) slots[(int64_t)blockIdx.x * kWords + t] = s_bits[t];
 }
@@ -1801,8 +1759,9 @@ __global__ __launch_bounds__(kOneBlock) void one_block_kernel(
     const uint32_t *__restrict__ X, int64_t d, int64_t ld, const int32_t *__restrict__ file_rows,
     AggWorkspace *ws, int trim_b, int32_t *winner_replica, uint32_t *__restrict__ out) {
     static_assert(F <= 64 && slot_words(F, R) <= 64, "a wave covers the files and the words of their bits");
-    __shared__ uint32_t s_bits[slot_words(F, R)];
-    short_pass_body<F, R, TRIM, 1, kOneBlock>(X, d, ld, file_rows, threadIdx.x, trim_b, out, s_bits);
+    constexpr int V = 1, BLOCK = kOneBlock;
+    const int64_t gt = threadIdx.x;
+#include "short_pass.inc"
     decide_and_redo<F, R, TRIM, 1>(X, d, ld, file_rows, ws, threadIdx.x, trim_b, winner_replica, out,
                                    [&](int j) { return slot_findings<R>(s_bits, j); });
 }
